@@ -1,5 +1,6 @@
 // C ABI of libsti: argument validation, shard-table staging, kernel sequencing.
 // Every check runs before the first launch; device work goes to the caller's stream.
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <string.h>
@@ -306,6 +307,7 @@ inline bool few_token_path(const sti_dims &d, int64_t T)
 {
     return T <= 128 || (T <= 192 && d.d_model <= 768);
 }
+constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
 static_assert(kSkinnyMaxTokens >= 192, "the partial-sum planes are sized with kSkinnyMaxTokens");
 
 
@@ -394,17 +396,32 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     void *qkv = ws + wl.qkv, *ctx = ws + wl.ctx, *h = ws + wl.h, *u = ws + wl.u;
     float *pre = (float *)(ws + wl.pre);
     const sti_dtype act_dtype = f32 ? STI_F32 : STI_F16;
-    // (a layer with every shard absent has nothing to multiply: on the matrix-core path its two
-    //  LayerNorms run alone, over bias + residual, like those behind the few-token kernels)
+    // (a layer with every shard absent has nothing to multiply: its two LayerNorms run alone, over
+    //  bias + residual, like those behind the few-token kernels)
     const bool skinny = !f32 && (few_token_path(d, T) || m == 0);
-    const bool no_products = !f32 && m == 0;
+    const bool no_products = m == 0;
     const int64_t partial_stride = (int64_t)T * dm;
     int pre_partials = 1;   // partial sums the last K-split GEMM left in `pre`
+    // float32: the O and FFN2 products leave partial sums in buffers that are free by then (O: Q/K/V;
+    // FFN2: Q/K/V, context and `pre`, which lie behind each other)
+    int f32_planes = 1;
+    auto f32_sums = [&](size_t end) {
+        f32_planes = (int)std::min<size_t>(kF32MaxSplits, (end - wl.qkv) / ((size_t)partial_stride * 4));
+        pre = (float *)(ws + (f32_planes >= 1 ? wl.qkv : wl.pre));
+        if (f32_planes < 1) f32_planes = 1;
+    };
     auto gemm = [&](const GemmProblem &p, const GemmBlocks &blk) {
         static const int cls[5] = {STI_K_GEMM_QKV, STI_K_GEMM_FFN_UP, STI_K_GEMM_OUT,
                                    STI_K_GEMM_FFN_DOWN, STI_K_GEMM_QKV};
         return timed(cls[p.kind], stream, [&] {
-            if (f32) return launch_gemm_f32(p, blk, stream);
+            if (f32) {
+                GemmProblem q = p;
+                q.partial_stride = partial_stride;
+                int splits = 1;
+                const hipError_t e = launch_gemm_f32(q, blk, f32_planes, &splits, stream);
+                if (p.kind == GEMM_OUT || p.kind == GEMM_FFN_DOWN) pre_partials = splits;
+                return e;
+            }
             if (!skinny) {
                 GemmProblem q = p;
                 if (p.kind == GEMM_OUT || p.kind == GEMM_FFN_DOWN) {
@@ -419,14 +436,14 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             return launch_gemm_skinny(p, blk, splits, partial_stride, stream);
         });
     };
-    // the MFMA GEMMs leave bias and residual to the LayerNorm kernel
+    // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM
     auto layernorm = [&](void *dst, sti_dtype dt, const float *g, const float *b,
                          const float *bias, const void *resid) {
         return timed(STI_K_LAYERNORM, stream, [&] {
             if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
-            return launch_layernorm(pre, pre_partials, partial_stride, f32 ? nullptr : bias,
-                                    f32 ? nullptr : resid, dst, dt, g, b, T, dm, d.ln_eps, stream);
+            return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32, dst, dt, g, b, T, dm,
+                                    d.ln_eps, stream);
         });
     };
 
@@ -459,6 +476,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         }
     }
     memset(&p, 0, sizeof(p));
+    if (f32) f32_sums(wl.ctx);
     p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
     p.A = ctx; p.lda = m * dh; p.C = pre; p.ldc = dm; p.bias0 = prm.bo; p.resid = in; p.ldr = dm;
     if (no_products) pre_partials = 0;
@@ -471,6 +489,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         STI_TRY(gemm(p, b1));
     }
     memset(&p, 0, sizeof(p));
+    if (f32) f32_sums(wl.h);
     p.kind = GEMM_FFN_DOWN; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = f;
     p.d_head = dh; p.A = u; p.lda = m * f; p.C = pre; p.ldc = dm; p.bias0 = prm.b2; p.resid = h;
     p.ldr = dm;

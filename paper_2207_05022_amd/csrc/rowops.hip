@@ -44,10 +44,10 @@ template <> struct Elem<STI_BF16> {
 
 // v[t][:] = pre[t][:] (+ bias[:]) (+ resid[t][:]);  y[t][:] = LayerNorm(v) * g + b.
 // One wave per row; two-pass mean / variance in float32.  General sizes.
-template <int DT>
+template <int DT, typename RT>   // RT: type of the residual rows
 __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_partials,
                                                         int64_t partial_stride, const float *bias,
-                                                        const _Float16 *resid,
+                                                        const RT *resid,
                                                         typename Elem<DT>::type *y, const float *g,
                                                         const float *b, int T, int d, float eps)
 {
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_
     const int lane = threadIdx.x % 64;
     if (row >= T) return;
     const float *r = pre + (int64_t)row * d;
-    const _Float16 *rs = resid ? resid + (int64_t)row * d : nullptr;
+    const RT *rs = resid ? resid + (int64_t)row * d : nullptr;
     auto value = [&](int c) {
         float v = n_partials > 0 ? r[c] : 0.f;
         for (int s = 1; s < n_partials; ++s) v += r[(int64_t)s * partial_stride + c];
@@ -92,10 +92,10 @@ __device__ inline float row_sum(float v)
     return v;
 }
 
-template <int DT, int LPR, int MAXC>   // MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC
+template <int DT, typename RT, int LPR, int MAXC>   // MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC
 __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, int n_partials,
                                                             int64_t partial_stride,
-                                                            const float *bias, const _Float16 *resid,
+                                                            const float *bias, const RT *resid,
                                                             typename Elem<DT>::type *y,
                                                             const float *g, const float *b, int T,
                                                             int d, float eps)
@@ -114,14 +114,15 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, in
     int cj[MAXC];
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) cj[j] = min(sub + LPR * j, last);
+    typedef RT resid4 __attribute__((ext_vector_type(4)));
     f32x4 bs[MAXC];
-    half4 rs4[MAXC];
+    resid4 rs4[MAXC];
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
         bs[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        rs4[j] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+        rs4[j] = resid4{(RT)0.f, (RT)0.f, (RT)0.f, (RT)0.f};
         if (bias) bs[j] = ((const f32x4 *)bias)[cj[j]];
-        if (resid) rs4[j] = ((const half4 *)(resid + (int64_t)row * d))[cj[j]];
+        if (resid) rs4[j] = ((const resid4 *)(resid + (int64_t)row * d))[cj[j]];
     }
     f32x4 gg[MAXC], bb[MAXC];
 #pragma unroll
@@ -322,7 +323,7 @@ hipError_t convert_from(const void *src, void *dst, sti_dtype dst_dtype, uint64_
 
 }  // namespace
 
-template <int DT>
+template <int DT, typename RT>
 void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, const float *bias,
                      const void *resid, void *y, const float *g, const float *b, int T, int d, float eps,
                      bool vec, hipStream_t stream)
@@ -330,8 +331,8 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
     typedef typename Elem<DT>::type O;
     dim3 grid((T + 3) / 4);
 #define STI_LN_VEC(LPR, MAXC, GRID) \
-    launch((layernorm_vec_kernel<DT, LPR, MAXC>), GRID, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, \
-           (const _Float16 *)resid, (O *)y, g, b, T, d, eps)
+    launch((layernorm_vec_kernel<DT, RT, LPR, MAXC>), GRID, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, \
+           (const RT *)resid, (O *)y, g, b, T, d, eps)
     // many rows: 32 lanes per row (8 rows per workgroup); few rows: a whole wave per row; chunks
     // per lane sized to the row, so that the registers hold no more loads in flight than it has
     if (vec && T >= 2048 && d <= 1024) {
@@ -342,13 +343,13 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
         else if (d <= 1024) STI_LN_VEC(64, 4, grid);
         else STI_LN_VEC(64, 8, grid);
     } else {
-        launch((layernorm_kernel<DT>), grid, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const _Float16 *)resid, (O *)y, g, b, T, d, eps);
+        launch((layernorm_kernel<DT, RT>), grid, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (O *)y, g, b, T, d, eps);
     }
 #undef STI_LN_VEC
 }
 
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
-                            const float *bias, const void *resid_f16, void *y, sti_dtype out_dtype,
+                            const float *bias, const void *resid, bool resid_f32, void *y, sti_dtype out_dtype,
                             const float *g, const float *b, int T, int d, float eps,
                             hipStream_t stream)
 {
@@ -356,12 +357,17 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
     if (n_partials < 0 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
     const bool vec = d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) &&
-                     (!bias || al16(bias)) && (!resid_f16 || al16(resid_f16));
-    switch (out_dtype) {
-        case STI_F32: launch_ln_typed<STI_F32>(pre, n_partials, partial_stride, bias, resid_f16, y, g, b, T, d, eps, vec, stream); break;
-        case STI_F16: launch_ln_typed<STI_F16>(pre, n_partials, partial_stride, bias, resid_f16, y, g, b, T, d, eps, vec, stream); break;
-        case STI_BF16: launch_ln_typed<STI_BF16>(pre, n_partials, partial_stride, bias, resid_f16, y, g, b, T, d, eps, vec, stream); break;
-    }
+                     (!bias || al16(bias)) && (!resid || al16(resid));
+    auto go = [&](auto resid_type) {
+        typedef decltype(resid_type) RT;
+        switch (out_dtype) {
+            case STI_F32: launch_ln_typed<STI_F32, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
+            case STI_F16: launch_ln_typed<STI_F16, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
+            case STI_BF16: launch_ln_typed<STI_BF16, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
+        }
+    };
+    if (resid_f32) go(float{});
+    else go(_Float16{});
     return hipGetLastError();
 }
 

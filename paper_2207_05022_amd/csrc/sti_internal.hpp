@@ -104,8 +104,11 @@ struct GemmProblem {
     int32_t next_shards, next_workgroups, next_ffn_per_shard;
 };
 
-// float32 path (layer_f32.hip): A, C, resid are float32; weights are float32 blocks.
-hipError_t launch_gemm_f32(const GemmProblem &p, const GemmBlocks &blocks, hipStream_t stream);
+// float32 path (layer_f32.hip): A and C are float32; weights are float32 blocks at a constant distance.
+// QKV / FFN_UP apply bias (and GELU); OUT / FFN_DOWN leave raw sums for launch_layernorm, those of
+// K split s at C + s * partial_stride, with at most max_splits of them (the number comes back in splits_used).
+hipError_t launch_gemm_f32(const GemmProblem &p, const GemmBlocks &blocks, int max_splits, int *splits_used,
+                           hipStream_t stream);
 // qkv [T x m*3*dh] float32 (per shard: q, k, v each dh wide) -> ctx [T x m*dh] float32.
 // key_lengths (device, [B], may be null): keys of sequence b beyond key_lengths[b] take no part.
 hipError_t launch_attention_f32(const float *qkv, float *ctx, int B, int L, int m, int dh,
@@ -142,10 +145,10 @@ hipError_t launch_gemm_skinny(const GemmProblem &p, const GemmBlocks &blocks, in
 
 // rowops.hip
 // v = sum_{s < n_partials} pre[s * partial_stride + t*d + :] + bias[:] + resid[t][:]  (n_partials may be 0);
-// y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid_f16 (binary16
-// [T x d]) may be NULL; y of out_dtype.
+// y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid (binary16, or float32
+// with resid_f32, [T x d]) may be NULL; y of out_dtype.
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
-                            const float *bias, const void *resid_f16, void *y, sti_dtype out_dtype,
+                            const float *bias, const void *resid, bool resid_f32, void *y, sti_dtype out_dtype,
                             const float *g, const float *b, int T, int d, float eps,
                             hipStream_t stream);
 // y[t][:] = LayerNorm(pre_f16[t][:]) * g + b for rows that already hold sum + bias + residual.

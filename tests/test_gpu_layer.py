@@ -178,6 +178,25 @@ def test_f32_random_shapes(gpu, oracle_mod):
         assert_parity(got, want, tol, (case, d, M, dh, f, B, L, n_abs, n_layers, io))
 
 
+@pytest.mark.parametrize("d,M,dh,f,B,L", [
+    (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
+    (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows
+    (132, 2, 64, 96, 1, 65),      # one column past two tiles
+    (97, 3, 33, 51, 2, 67),       # odd everywhere: scalar loads, odd row ends
+    (192, 4, 16, 32, 7, 129),     # narrow heads and blocks, one key past two blocks
+    (96, 2, 100, 64, 2, 70),      # padded features
+    (64, 2, 128, 32, 1, 64), (64, 2, 130, 32, 2, 40),   # widest head on the matrix cores, one beyond
+    (256, 4, 64, 128, 16, 130),   # several workgroups per compute unit
+])
+def test_f32_tile_edges(gpu, oracle_mod, d, M, dh, f, B, L):
+    """Edges of the float32 products' tiles, K splits and attention blocks."""
+    dims = S.Dims(d, M, dh, f, 1e-12)
+    wl = S.small_workload(13000 + d + L, dims, 2, B, L, n_absent=1)
+    S.make_every_term_matter(wl, d, amp=2.0)
+    want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x)
+    assert_parity(run_gpu(gpu, wl, "f32"), want, TOL["f32"])
+
+
 def test_empty_batch_and_zero_layers(gpu):
     torch, P, D = gpu
     wl = S.small_workload(3, SMALL, 1, 1, 4)
