@@ -174,3 +174,25 @@ def test_quantizer_reports_a_layer_without_inliers():
     for s in range(4):
         assert np.array_equal(g["pos"][s].cpu().numpy(), np.arange(512))
         assert np.array_equal(g["val"][s].cpu().numpy().view(np.uint32), w[s, :512].view(np.uint32))
+
+
+@pytest.mark.parametrize("k,kind", [(2, "zeros"), (6, "zeros"), (4, "one_bin"), (6, "one_bin"), (5, "few_values"), (3, "shifted")])
+def test_quantizer_crowded_bins(k, kind):
+    """Distributions that put many weights, or many cluster boundaries, into one bin of the value histogram: mostly
+    exact zeros of both signs (more weights of a boundary bin than a workgroup keeps), a few huge weights that
+    stretch the range, a handful of distinct values, a mean far from zero."""
+    dims = S.Dims(768, 4, 64, 256, 1e-12) if kind == "zeros" else MID
+    rng = np.random.default_rng([k, len(kind)])
+    w = rng.normal(0.0, 0.03, size=(dims.n_heads, dims.weights_per_shard)).astype(np.float32)
+    if kind == "zeros":
+        w[rng.random(w.shape) < 0.8] = 0.0
+        w[rng.random(w.shape) < 0.1] *= np.float32(-1.0)
+    elif kind == "one_bin":
+        w *= np.float32(1e-3)
+        w.ravel()[rng.choice(w.size, 9, replace=False)] = 200.0
+    elif kind == "few_values":
+        w = rng.choice(np.array([-0.07, -0.02, -0.0, 0.0, 0.01, 0.05], dtype=np.float32), size=w.shape)
+    else:
+        w += np.float32(3.0)
+    g = run_gpu(dims, w, k, max_out=dims.weights_per_shard)
+    check_against_reference(dims, w, k, g)
