@@ -8,7 +8,11 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from operator import attrgetter
 from typing import Optional, Sequence
+
+import numpy as np
+import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # STI_LIBRARY names another build of the same sources to load instead (the build with phase time
@@ -91,12 +95,12 @@ def _load():
     L.sti_model_forward_masked.restype = C.c_int
     L.sti_model_forward_masked.argtypes = [
         C.POINTER(StiDims), C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams),
-        C.POINTER(C.c_int8), C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_int,
+        C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_int,
         C.c_void_p, C.c_size_t, C.c_void_p]
     L.sti_model_forward.restype = C.c_int
     L.sti_model_forward.argtypes = [
         C.POINTER(StiDims), C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams),
-        C.POINTER(C.c_int8), C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int,
+        C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int,
         C.c_void_p, C.c_size_t, C.c_void_p]
     L.sti_static_scratch_bytes.restype = C.c_size_t
     L.sti_static_scratch_bytes.argtypes = []
@@ -120,8 +124,8 @@ def _load():
     L.sti_plan_submodel.restype = C.c_int
     L.sti_plan_submodel.argtypes = [C.POINTER(StiPlanTables), C.c_double, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
     L.sti_plan_bitwidths.restype = C.c_int
-    L.sti_plan_bitwidths.argtypes = [C.POINTER(StiPlanTables), C.c_int32, C.c_int32, C.POINTER(C.c_int8),
-                                     C.POINTER(C.c_int32), C.POINTER(C.c_int8), C.POINTER(C.c_double)]
+    L.sti_plan_bitwidths.argtypes = [C.POINTER(StiPlanTables), C.c_int32, C.c_int32, C.c_void_p,
+                                     C.POINTER(C.c_int32), C.c_void_p, C.POINTER(C.c_double)]
     L.sti_model_workspace_bytes.restype = C.c_size_t
     L.sti_model_workspace_bytes.argtypes = [C.POINTER(StiDims), C.c_int, C.c_int, C.c_int, C.c_int]
     L.sti_pipeline_staging_bytes.restype = C.c_size_t
@@ -131,12 +135,12 @@ def _load():
                                       C.c_size_t, C.POINTER(C.c_void_p)]
     L.sti_pipeline_forward_masked.restype = C.c_int
     L.sti_pipeline_forward_masked.argtypes = [
-        C.c_void_p, C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams), C.POINTER(C.c_int8),
+        C.c_void_p, C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams), C.c_void_p,
         C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_void_p, C.c_size_t,
         C.c_void_p, C.POINTER(StiPipelineStats)]
     L.sti_pipeline_forward.restype = C.c_int
     L.sti_pipeline_forward.argtypes = [
-        C.c_void_p, C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams), C.POINTER(C.c_int8),
+        C.c_void_p, C.c_int, C.POINTER(StiShard), C.POINTER(StiLayerParams), C.c_void_p,
         C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_size_t,
         C.c_void_p, C.POINTER(StiPipelineStats)]
     L.sti_pipeline_destroy.restype = C.c_int
@@ -155,20 +159,26 @@ def status_string(status: int) -> str:
     return lib.sti_status_string(int(status)).decode()
 
 
+_DTYPE_CODES = {torch.float32: STI_F32, torch.float16: STI_F16, torch.bfloat16: STI_BF16}
+
+
 def _dtype_code(t) -> int:
-    import torch
-    return {torch.float32: STI_F32, torch.float16: STI_F16, torch.bfloat16: STI_BF16}[t.dtype]
+    return _DTYPE_CODES[t.dtype]
 
 
-def _stream_handle(stream) -> Optional[int]:
-    import torch
+def _stream_handle(stream) -> int:
+    """Raw handle of `stream`, or of the current stream of the current device (without a Stream object)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
+
+
+def _nbytes(t) -> int:
+    return 0 if t is None else t.nbytes
 
 
 def make_dims(dims) -> StiDims:
@@ -190,7 +200,34 @@ def make_params(p) -> StiLayerParams:
     """p: object with CUDA float32 tensors bq, bk, bv, bo, b1, b2, ln1_g, ln1_b, ln2_g, ln2_b."""
     if isinstance(p, StiLayerParams):
         return p
-    return StiLayerParams(*[_ptr(getattr(p, n)) for n, _ in StiLayerParams._fields_])
+    return StiLayerParams(*_param_pointers(p))
+
+
+_PARAM_NAMES = tuple(n for n, _ in StiLayerParams._fields_)
+_param_tensors = attrgetter(*_PARAM_NAMES)
+
+
+def _param_pointers(p) -> list:
+    tensors = _param_tensors(p)
+    try:
+        return [t.data_ptr() for t in tensors]
+    except AttributeError:   # (a missing tensor is a null pointer)
+        return [_ptr(t) for t in tensors]
+
+
+def params_array(params: Sequence, n_layers: int) -> "C.Array":
+    """HOST array of sti_layer_params from `n_layers` parameter objects (see make_params)."""
+    pointers = []
+    for p in params[:n_layers]:
+        if isinstance(p, StiLayerParams):
+            pointers.extend(getattr(p, n) for n in _PARAM_NAMES)
+        else:
+            pointers.extend(_param_pointers(p))
+    if len(pointers) != n_layers * len(_PARAM_NAMES):
+        raise ValueError("one parameter object per layer is needed")
+    if not pointers:
+        return (StiLayerParams * 1)()
+    return (StiLayerParams * n_layers).from_buffer((C.c_void_p * len(pointers))(*pointers))
 
 
 def shard_array(shards: Sequence) -> "C.Array":
@@ -219,7 +256,7 @@ def sti_decode_shards(shards: Sequence, weights_per_shard: int, out, workspace=N
     """Decode ``shards`` into ``out`` (CUDA tensor of float32/float16/bfloat16 with
     len(shards) * weights_per_shard elements)."""
     arr = shard_array(shards)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     st = lib.sti_decode_shards(arr, len(shards), int(weights_per_shard), _ptr(out),
                                _dtype_code(out), _ptr(workspace), ws_bytes, _stream_handle(stream))
     if st != 0:
@@ -260,7 +297,6 @@ def _key_lengths_ptr(key_lengths, batch: int):
     """key_lengths: CUDA int32 tensor [batch] (None passes a null pointer through)."""
     if key_lengths is None:
         return None
-    import torch
     if key_lengths.dtype != torch.int32 or tuple(key_lengths.shape) != (batch,):
         raise ValueError("key_lengths must be an int32 tensor with one entry per sequence")
     return _ptr(key_lengths)
@@ -273,7 +309,7 @@ def sti_layer_forward(dims, shards: Sequence, params, x, y, precision: int, work
     arr = shard_array(shards)
     p = make_params(params)
     batch, seq = int(x.shape[0]), int(x.shape[1])
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     st = lib.sti_layer_forward(C.byref(d), arr, C.byref(p), _ptr(x), _ptr(y), _dtype_code(x),
                                batch, seq, int(precision), _ptr(workspace), ws_bytes,
                                _stream_handle(stream))
@@ -299,7 +335,7 @@ def sti_layer_forward_masked(dims, shards: Sequence, params, x, y, key_lengths, 
     arr = shard_array(shards)
     p = make_params(params)
     batch, seq = int(x.shape[0]), int(x.shape[1])
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     st = lib.sti_layer_forward_masked(C.byref(d), arr, C.byref(p), _ptr(x), _ptr(y), _dtype_code(x),
                                       batch, seq, _key_lengths_ptr(key_lengths, batch), int(precision),
                                       _ptr(workspace), ws_bytes, _stream_handle(stream))
@@ -327,19 +363,16 @@ def sti_model_forward(dims, store, params: Sequence, plan, x, y, precision: int,
                       stream=None) -> None:
     """store: result of make_store (or a ctypes StiShard array [n_layers][M][6]);
     plan: int8 numpy array [n_layers][M]."""
-    import numpy as np
     d = make_dims(dims)
     plan = np.ascontiguousarray(plan, dtype=np.int8)
     n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
     if not isinstance(store, C.Array):
         store = make_store(store)
-    ps = (StiLayerParams * max(1, n_layers))()
-    for l in range(n_layers):
-        ps[l] = make_params(params[l])
+    ps = params_array(params, n_layers)
     batch, seq = int(x.shape[0]), int(x.shape[1])
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     st = lib.sti_model_forward(C.byref(d), n_layers, store, ps,
-                               plan.ctypes.data_as(C.POINTER(C.c_int8)), _ptr(x), _ptr(y),
+                               plan.ctypes.data, _ptr(x), _ptr(y),
                                _dtype_code(x), batch, seq, int(precision), _ptr(workspace),
                                ws_bytes, _stream_handle(stream))
     if st != 0:
@@ -349,19 +382,16 @@ def sti_model_forward(dims, store, params: Sequence, plan, x, y, precision: int,
 def sti_model_forward_masked(dims, store, params: Sequence, plan, x, y, key_lengths, precision: int,
                              workspace, stream=None) -> None:
     """As sti_model_forward; key_lengths: CUDA int32 tensor [batch], the same in every layer."""
-    import numpy as np
     d = make_dims(dims)
     plan = np.ascontiguousarray(plan, dtype=np.int8)
     n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
     if not isinstance(store, C.Array):
         store = make_store(store)
-    ps = (StiLayerParams * max(1, n_layers))()
-    for l in range(n_layers):
-        ps[l] = make_params(params[l])
+    ps = params_array(params, n_layers)
     batch, seq = int(x.shape[0]), int(x.shape[1])
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     st = lib.sti_model_forward_masked(C.byref(d), n_layers, store, ps,
-                                      plan.ctypes.data_as(C.POINTER(C.c_int8)), _ptr(x), _ptr(y),
+                                      plan.ctypes.data, _ptr(x), _ptr(y),
                                       _dtype_code(x), batch, seq, _key_lengths_ptr(key_lengths, batch),
                                       int(precision), _ptr(workspace), ws_bytes, _stream_handle(stream))
     if st != 0:
@@ -407,19 +437,16 @@ class StiPipeline:
                 key_lengths=None) -> dict:
         """store: make_store(...) of versions whose ``data`` are pinned host tensors.
         With key_lengths (CUDA int32 tensor [batch]) the call goes to sti_pipeline_forward_masked."""
-        import numpy as np
         plan = np.ascontiguousarray(plan, dtype=np.int8)
         n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
         if not isinstance(store, C.Array):
             store = make_store(store)
-        ps = (StiLayerParams * max(1, n_layers))()
-        for l in range(n_layers):
-            ps[l] = make_params(params[l])
+        ps = params_array(params, n_layers)
         stats = StiPipelineStats()
-        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        ws_bytes = _nbytes(workspace)
         if key_lengths is not None:
             st = lib.sti_pipeline_forward_masked(
-                self._h, n_layers, store, ps, plan.ctypes.data_as(C.POINTER(C.c_int8)), _ptr(x), _ptr(y),
+                self._h, n_layers, store, ps, plan.ctypes.data, _ptr(x), _ptr(y),
                 _dtype_code(x), int(x.shape[0]), int(x.shape[1]),
                 _key_lengths_ptr(key_lengths, int(x.shape[0])), int(precision), _ptr(workspace), ws_bytes,
                 _stream_handle(stream), C.byref(stats))
@@ -427,7 +454,7 @@ class StiPipeline:
                 raise StiError(st, "sti_pipeline_forward_masked")
             return {n: int(getattr(stats, n)) for n, _ in StiPipelineStats._fields_}
         st = lib.sti_pipeline_forward(self._h, n_layers, store, ps,
-                                      plan.ctypes.data_as(C.POINTER(C.c_int8)), _ptr(x), _ptr(y),
+                                      plan.ctypes.data, _ptr(x), _ptr(y),
                                       _dtype_code(x), int(x.shape[0]), int(x.shape[1]), int(precision),
                                       _ptr(workspace), ws_bytes, _stream_handle(stream), C.byref(stats))
         if st != 0:
@@ -466,7 +493,6 @@ def sti_plan_submodel(t_io, t_comp, n_layers: int, deadline_s: float):
 
 def sti_plan_bitwidths(t_io, t_comp, n_layers: int, n: int, m: int, preloaded, importance):
     """Returns (plan int8 [n_layers][M], aib float64 [n])."""
-    import numpy as np
     tab, _keep = _plan_tables(t_io, t_comp, n_layers)
     M = len(t_comp)
     pre = None if preloaded is None else np.ascontiguousarray(preloaded, dtype=np.int8).ravel()
@@ -474,9 +500,9 @@ def sti_plan_bitwidths(t_io, t_comp, n_layers: int, n: int, m: int, preloaded, i
     plan = np.zeros(n_layers * M, dtype=np.int8)
     aib = np.zeros(max(n, 1), dtype=np.float64)
     st = lib.sti_plan_bitwidths(C.byref(tab), int(n), int(m),
-                                None if pre is None else pre.ctypes.data_as(C.POINTER(C.c_int8)),
+                                None if pre is None else pre.ctypes.data,
                                 imp.ctypes.data_as(C.POINTER(C.c_int32)),
-                                plan.ctypes.data_as(C.POINTER(C.c_int8)),
+                                plan.ctypes.data,
                                 aib.ctypes.data_as(C.POINTER(C.c_double)))
     if st != 0:
         raise StiError(st, "sti_plan_bitwidths")
@@ -498,7 +524,7 @@ def sti_quantize_layer(dims, weights, bitwidth: int, packed, codebook, outlier_p
     st = lib.sti_quantize_layer(C.byref(d), _ptr(weights), int(bitwidth), float(loglik_threshold), float(reg_covar),
                                 _ptr(packed), _ptr(codebook), _ptr(outlier_pos), _ptr(outlier_val), max_out,
                                 _ptr(outlier_count), _ptr(stats), _ptr(workspace),
-                                0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                _nbytes(workspace),
                                 _stream_handle(stream))
     if st != 0:
         raise StiError(st, "sti_quantize_layer")
