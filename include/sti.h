@@ -74,11 +74,11 @@ typedef enum { STI_F32 = 0, STI_F16 = 1, STI_BF16 = 2 } sti_dtype;
 /* STI_PREC_F32: float32 storage and arithmetic end to end (decode to a float32
  *   working buffer, then float32 kernels); any dimensions.
  * STI_PREC_F16_MFMA: binary16 operands on the matrix cores with float32
- *   accumulation.  Up to 128 tokens per call (192 when d_model <= 768) the
- *   projections decode the packed streams inside their weight loader; with
- *   more tokens, and for shards that carry an outlier dictionary, a layer's
- *   shards are decompressed once into a binary16 working buffer in the
- *   workspace that the projections then read (every weight would otherwise be
+ *   accumulation.  With few tokens per call (up to 128; up to a few hundred at d_model
+ *   256 .. 1024, depending on the layer's size) the projections decode the packed streams
+ *   inside their weight loader; with more tokens, and for shards that carry an outlier
+ *   dictionary, a layer's shards are decompressed once into a binary16 working buffer in
+ *   the workspace that the projections then read (every weight would otherwise be
  *   decoded once per 64 or 128 token rows).  Needs d_head == 64, d_model and
  *   ffn_per_shard multiples of 64 and seq <= 512 (STI_ERR_DIMS otherwise). */
 typedef enum { STI_PREC_F32 = 0, STI_PREC_F16_MFMA = 1 } sti_precision;
@@ -293,8 +293,8 @@ sti_status sti_model_forward_masked(const sti_dims *dims, int n_layers, const st
  * computes - by the workgroups that the Q/K/V launch of that layer has to spare, when it has at
  * least 32 of them - and otherwise a few layers are decompressed by one launch right before the
  * first of them runs).  Applies to STI_PREC_F16_MFMA whenever
- * the layer goes through the working buffer (more than 128 tokens, more than 192 when
- * d_model <= 768); otherwise, and for n_layers <= 1, it equals sti_workspace_bytes.
+ * the layer goes through the working buffer (many tokens, see sti_precision); otherwise, and for
+ * n_layers <= 1, it equals sti_workspace_bytes.
  * sti_model_forward takes this whole-model route whenever workspace_bytes is at least this value
  * and the per-layer route otherwise: same results either way.  The whole-model route uploads
  * a shard table through a pinned host buffer that later calls reuse and is therefore

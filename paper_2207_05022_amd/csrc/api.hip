@@ -200,6 +200,24 @@ sti_status check_decode_shard(const sti_shard &s)
 // ---------------------------------------------------------------------------
 
 
+// Which GEMM family a matrix-core layer takes.  The few-token kernels decode every weight once per
+// 64-row block and take partial sums through LayerNorm; from some row blocks on it is cheaper to
+// decompress the layer once into the working buffer and run the wide-tile kernels.  Measured per layer (us,
+// few-token against working buffer, 6-bit mix, full shard set): BERT-base 128 tokens 34 / 51, 256 41 / 54,
+// 512 46 / 56, 640 53 / 59, 768 61 / 60; d_model 1024 x 16 shards 256 49 / 66, 512 68 / 85, 640 79 / 77; 512 x 8
+// shards of 128 neurons 1024 41 / 45, 1536 48 / 48; 256 x 4 of 64 1024 32 / 36.  In workgroups of the FFN1 product (32
+// columns x 64 tokens) the lines lie at about 1024.  Outside d_model 256 .. 1024 the line is the older
+// one, 128 tokens, or 192 when d_model <= 768.
+inline bool few_token_path(const sti_dims &d, int64_t T)
+{
+    if (T <= 128 || (T <= 192 && d.d_model <= 768)) return true;
+    const int64_t workgroups = (T + 63) / 64 * d.n_heads * (d.ffn_per_shard / 32);
+    return T <= kFewMaxTokens && d.d_model >= 256 && d.d_model <= 1024 && workgroups <= 1024;
+}
+
+constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
+
+
 // Offsets of the scratch regions of one layer call (sized for all M shards present).
 WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers)
 {
@@ -227,21 +245,28 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     };
     if (prec == STI_PREC_F32) L.w32 = take(M * dm * (4 * dh + 2 * f) * 4);
     else L.w16 = take((size_t)L.w16_layers * M * dm * (4 * dh + 2 * f) * 2);
-    L.act[0] = take((size_t)T * dm * es);
-    L.act[1] = take((size_t)T * dm * es);
-    L.qkv = take((size_t)T * M * 3 * dh * es);
-    L.ctx = take((size_t)T * M * dh * es);
+    // (tiled activations: whole blocks of 32 rows)
+    const size_t Tb = inner_layout(d, T, prec) == LAYOUT_TILED ? ((size_t)T + 31) / 32 * 32 : (size_t)T;
+    L.act[0] = take(Tb * dm * es);
+    L.act[1] = take(Tb * dm * es);
+    L.qkv = take(Tb * M * 3 * dh * es);
+    L.ctx = take(Tb * M * dh * es);
     {   // float32 sums before LayerNorm; the few-token GEMM may leave several partial sums
         size_t rows = (size_t)T;
-        if (prec != STI_PREC_F32 && T <= kSkinnyMaxTokens) rows *= kSkinnyMaxSplits;
+        if (prec != STI_PREC_F32 && few_token_path(d, T)) {
+            GemmProblem p;
+            memset(&p, 0, sizeof(p));
+            p.kind = GEMM_FFN_DOWN; p.n_blocks = d.n_heads; p.block_cols = f > dh ? f : dh;   // (FFN2's splits, or O's)
+            rows *= few_k_splits(p);
+        }
         if (prec != STI_PREC_F32) {   // ... and so may the wide-tile GEMM when it has few tiles
             const size_t wide_rows = (size_t)T * gemm_wide_max_k_splits(T, (int)dm);
             if (wide_rows > rows) rows = wide_rows;
         }
         L.pre = take(rows * dm * 4);
     }
-    L.h = take((size_t)T * dm * es);
-    L.u = take((size_t)T * M * f * es);
+    L.h = take(Tb * dm * es);
+    L.u = take(Tb * M * f * es);
     if (L.w16_layers > 1) L.table = take((size_t)model_layers * M * sizeof(ShardDesc));
     L.total = off;
     return L;
@@ -293,23 +318,27 @@ inline const void *block_start(const sti_shard &s, size_t elem_off)
     return (const uint8_t *)s.data + elem_off * (size_t)s.bitwidth / 8;
 }
 
-// From this many tokens on, a layer's shards are decompressed once into the binary16
-// working buffer; below it, the GEMMs decode the streams themselves (every weight is then
-// used by at most a few row tiles).
-// Which GEMM family a matrix-core layer takes.  The few-token kernels decode every weight
-// once per 64-row block and take partial sums through LayerNorm; from a couple of row blocks
-// on it is cheaper to decompress the layer once into the working buffer and run the
-// wide-tile kernels (measured per layer, BERT-base with 9 of 12 shards: 128 tokens 57 against
-// 69 us, 192 tokens 60 against 63, 256 tokens 68 against 65, 384 tokens 164 -- with the
-// decode fused into a tiled GEMM, as used before -- against 70; d_model 1024, 12 of 16 shards:
-// 192 tokens 82 against 76, 256 tokens 92 against 77).
-inline bool few_token_path(const sti_dims &d, int64_t T)
+ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec)
 {
-    return T <= 128 || (T <= 192 && d.d_model <= 768);
+    return prec == STI_PREC_F16_MFMA && few_token_path(d, T) ? LAYOUT_TILED : LAYOUT_ROWS;
 }
-constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
-static_assert(kSkinnyMaxTokens >= 192, "the partial-sum planes are sized with kSkinnyMaxTokens");
 
+sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+                    const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer)
+{
+    const sti_dtype act = (prec == STI_PREC_F32) ? STI_F32 : STI_F16;
+    *in = x;
+    *in_layout = LAYOUT_ROWS;
+    *in_buffer = io_dtype != act;
+    if (io_dtype == act) return STI_OK;
+    *in = ws + wl.act[0];
+    *in_layout = inner_layout(d, T, prec);
+    STI_TRY(timed(STI_K_CONVERT, stream, [&] {
+        return *in_layout == LAYOUT_TILED ? launch_tile_rows(x, io_dtype, ws + wl.act[0], (int)T, d.d_model, stream)
+                                          : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
+    }));
+    return STI_OK;
+}
 
 // One layer, arguments already validated.  `in` is float32 (F32 precision) or
 // binary16 (MFMA precision); `out` is written as out_dtype.
@@ -326,7 +355,8 @@ int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, sti_preci
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
-                     const void *predecoded, const int32_t *key_lengths, const NextLayerDecode *next)
+                     const void *predecoded, const int32_t *key_lengths, const NextLayerDecode *next,
+                     ActLayout in_layout, ActLayout out_layout)
 {
     const int dm = d.d_model, M = d.n_heads, dh = d.d_head, f = d.ffn_per_shard;
     const int T = B * Lseq;
@@ -431,25 +461,29 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                 }
                 return launch_gemm_wide(q, blk, stream);
             }
-            const int splits = skinny_k_splits(p);
+            const int splits = few_k_splits(p);
             if (p.kind == GEMM_OUT || p.kind == GEMM_FFN_DOWN) pre_partials = splits;
-            return launch_gemm_skinny(p, blk, splits, partial_stride, stream);
+            return launch_gemm_few(p, blk, splits, partial_stride, stream);
         });
     };
     // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM
-    auto layernorm = [&](void *dst, sti_dtype dt, const float *g, const float *b,
-                         const float *bias, const void *resid) {
+    auto layernorm = [&](void *dst, sti_dtype dt, ActLayout dst_layout, const float *g, const float *b,
+                         const float *bias, const void *resid, ActLayout resid_layout) {
         return timed(STI_K_LAYERNORM, stream, [&] {
             if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
-            return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32, dst, dt, g, b, T, dm,
-                                    d.ln_eps, stream);
+            return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32, resid_layout, dst, dt, dst_layout,
+                                    g, b, T, dm, d.ln_eps, stream);
         });
     };
 
+    // few tokens: activations inside the layer are tiled, Q/K/V too where the few-token attention takes them
+    const ActLayout inner = inner_layout(d, T, prec);
+    const bool few_attention = inner == LAYOUT_TILED && attention_few_supported(B, Lseq);
     GemmProblem p;
     if (m > 0) {
         memset(&p, 0, sizeof(p));
+        p.a_layout = in_layout; p.c_layout = few_attention ? LAYOUT_TILED : LAYOUT_ROWS;
         p.kind = GEMM_QKV; p.T = T; p.n_blocks = m; p.block_rows = 3 * dh; p.block_cols = dm;
         p.d_head = dh; p.A = in; p.lda = dm; p.C = qkv; p.ldc = m * 3 * dh;
         p.bias0 = prm.bq; p.bias1 = prm.bk; p.bias2 = prm.bv;
@@ -470,32 +504,36 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             }
             STI_TRY(gemm(p, bq));
             STI_TRY(timed(STI_K_ATTENTION, stream, [&] {
-                return f32 ? launch_attention_f32((const float *)qkv, (float *)ctx, B, Lseq, m, dh, key_lengths, stream)
-                           : launch_attention_mfma(qkv, ctx, B, Lseq, m, dh, key_lengths, stream);
+                if (f32) return launch_attention_f32((const float *)qkv, (float *)ctx, B, Lseq, m, dh, key_lengths, stream);
+                if (few_attention) return launch_attention_few(qkv, ctx, B, Lseq, m, dh, key_lengths, stream);
+                return launch_attention_mfma(qkv, ctx, inner, B, Lseq, m, dh, key_lengths, stream);
             }));
         }
     }
     memset(&p, 0, sizeof(p));
     if (f32) f32_sums(wl.ctx);
+    p.a_layout = inner;
     p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
     p.A = ctx; p.lda = m * dh; p.C = pre; p.ldc = dm; p.bias0 = prm.bo; p.resid = in; p.ldr = dm;
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, bo));
-    STI_TRY(layernorm(h, act_dtype, prm.ln1_g, prm.ln1_b, prm.bo, in));
+    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout));
     if (m > 0) {
         memset(&p, 0, sizeof(p));
+        p.a_layout = inner; p.c_layout = inner;
         p.kind = GEMM_FFN_UP; p.T = T; p.n_blocks = m; p.block_rows = f; p.block_cols = dm;
         p.d_head = dh; p.A = h; p.lda = dm; p.C = u; p.ldc = m * f; p.bias0 = prm.b1;
         STI_TRY(gemm(p, b1));
     }
     memset(&p, 0, sizeof(p));
     if (f32) f32_sums(wl.h);
+    p.a_layout = inner;
     p.kind = GEMM_FFN_DOWN; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = f;
     p.d_head = dh; p.A = u; p.lda = m * f; p.C = pre; p.ldc = dm; p.bias0 = prm.b2; p.resid = h;
     p.ldr = dm;
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
-    STI_TRY(layernorm(out, out_dtype, prm.ln2_g, prm.ln2_b, prm.b2, h));
+    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner));
     return STI_OK;
 }
 
@@ -581,14 +619,13 @@ sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
 
     hipStream_t stream = (hipStream_t)hip_stream;
     uint8_t *ws = (uint8_t *)workspace;
-    const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
-    const void *in = x;
-    if (io_dtype != act) {
-        STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * dims->d_model, stream); }));
-        in = ws + wl.act[0];
-    }
+    const void *in;
+    ActLayout in_layout;
+    bool in_buffer;
+    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &in, &in_layout, &in_buffer);
+    if (st != STI_OK) return st;
     return run_layer(*dims, shards, *params, in, y, io_dtype, batch, seq, precision, ws, wl, stream,
-                     nullptr, masked ? key_lengths : nullptr);
+                     nullptr, masked ? key_lengths : nullptr, nullptr, in_layout, LAYOUT_ROWS);
 }
 
 sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *store,
@@ -952,13 +989,13 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         return spare_decode_workgroups(*dims, batch, seq, (int)(last_shard(l) - first_shard[l]), precision);
     };
     const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
-    const void *cur = x;
-    int next_buf = 0;
-    if (io_dtype != act) {
-        STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * dims->d_model, stream); }));
-        cur = ws + wl.act[0];
-        next_buf = 1;
-    }
+    const ActLayout inner = inner_layout(*dims, T, precision);
+    const void *cur;
+    ActLayout cur_layout;
+    bool in_buffer;
+    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    if (st != STI_OK) return st;
+    int next_buf = in_buffer ? 1 : 0;
     int decoded_upto = 0;   // layers [0, decoded_upto) have their working buffers (as far as the stream is concerned)
     for (int l = 0; l < n_layers; ++l) {
         const bool last = (l == n_layers - 1);
@@ -984,13 +1021,14 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         const void *predecoded = whole_model_fits ? (const void *)w16_of(l) : nullptr;
         st = run_layer(*dims, &chosen[(size_t)l * M], params[l], cur, out, last ? io_dtype : act,
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
-                       next_decode.workgroups > 0 ? &next_decode : nullptr);
+                       next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner);
         if (st != STI_OK) return st;
         if (next_decode.workgroups > 0) {
             st = patch_layer(l + 1);
             if (st != STI_OK) return st;
         }
         cur = out;
+        cur_layout = inner;
         next_buf ^= 1;
     }
     return STI_OK;

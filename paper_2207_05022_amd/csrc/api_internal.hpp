@@ -48,11 +48,19 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded = nullptr, const int32_t *key_lengths = nullptr,
-                     const NextLayerDecode *next = nullptr);
+                     const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
+                     ActLayout out_layout = LAYOUT_ROWS);
+// Layers of few tokens keep their activations tiled between them: how a call's layers hand activations on.
+ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec);
+// The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
+// otherwise converted into the first activation buffer (in_buffer: whether it is there).
+sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+                    const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer);
 // `predecoded`: the layer's present shards already sit there in fragment-tiled binary16 order
 // (outliers applied); run_layer then decompresses nothing.
 // `key_lengths` (device, [B]): real positions per padded sequence; null = every position is real.
 // `next` (only with `predecoded`, and only when spare_decode_workgroups says so for this layer).
+// Layouts of `in` and `out`: tiled only where inner_layout() says so.
 sti_status check_key_lengths(const int32_t *key_lengths);   // non-null, 4-byte aligned
 
 }  // namespace sti

@@ -37,7 +37,7 @@ __device__ inline int vt_stride(int Lp) { return Lp + 8; }
 // known before the first exponential, and the output accumulators are never rescaled.
 template <int NW, int SHORT>
 __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float16 *qkv, _Float16 *ctx,
-                                                                 int L, int Lp, int m,
+                                                                 int L, int Lp, int m, int ctx_tiled,
                                                                  const int32_t *key_lengths)
 {
     constexpr int QB = NW * 32;
@@ -187,7 +187,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float
     if constexpr (SHORT == 0) run_sum += __shfl_xor(run_sum, 32, 64);   // (the register-resident variant returns the pair's sum)
     if (q >= L) return;
     const float inv = 1.0f / run_sum;
+    // (a tiled context: chunk v4 of half e of the head's cell; the strides of e and v4 in elements)
     _Float16 *out = ctx + ((int64_t)b * L + q) * ((int64_t)m * DH) + (int64_t)p * DH;
+    int e_step = 32, v4_step = 8;
+    if (ctx_tiled) {
+        out = ctx + tiled_offset(b * L + q, p * DH, m);
+        e_step = 256;
+        v4_step = 512;
+    }
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -195,13 +202,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float
             half4 h;
 #pragma unroll
             for (int i = 0; i < 4; ++i) h[i] = (_Float16)(o[e][v4 * 4 + i] * inv);
-            *(half4 *)(out + e * 32 + v4 * 8 + g * 4) = h;
+            *(half4 *)(out + e * e_step + v4 * v4_step + g * 4) = h;
         }
 }
 
 }  // namespace
 
-hipError_t launch_attention_mfma(const void *qkv, void *ctx, int B, int L, int m, int dh,
+hipError_t launch_attention_mfma(const void *qkv, void *ctx, ActLayout ctx_layout, int B, int L, int m, int dh,
                                  const int32_t *key_lengths, hipStream_t stream)
 {
     if (B <= 0 || L <= 0 || m <= 0) return hipSuccess;
@@ -224,24 +231,24 @@ hipError_t launch_attention_mfma(const void *qkv, void *ctx, int B, int L, int m
         dim3 grid((L + 63) / 64, m, B);
         if (Lp <= 128)
             launch((attention_mfma_kernel<2, 4>), grid, dim3(128), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
         else if (Lp <= 256)
             launch((attention_mfma_kernel<2, 8>), grid, dim3(128), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
         else
             launch((attention_mfma_kernel<2, 0>), grid, dim3(128), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
     } else {
         dim3 grid((L + 127) / 128, m, B);
         if (Lp <= 128)
             launch((attention_mfma_kernel<4, 4>), grid, dim3(256), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
         else if (Lp <= 256)
             launch((attention_mfma_kernel<4, 8>), grid, dim3(256), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
         else
             launch((attention_mfma_kernel<4, 0>), grid, dim3(256), lds, stream, (const _Float16 *)qkv,
-                                                                          (_Float16 *)ctx, L, Lp, m, key_lengths);
+                                                                          (_Float16 *)ctx, L, Lp, m, (int)ctx_layout, key_lengths);
     }
     return hipGetLastError();
 }

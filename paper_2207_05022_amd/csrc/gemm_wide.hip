@@ -204,6 +204,11 @@ __device__ inline void decode_next_layer(const GemmProblem &p, int d, unsigned c
     }
 }
 
+struct ShardIds {   // original shard id of every weight block (selects the bias slice), four to a scalar-loadable dword
+    uint32_t id4[kMaxShardsPerLayer / 4];
+    __device__ inline int id(int block) const { return (id4[block >> 2] >> (8 * (block & 3))) & 0xFF; }
+};
+
 // KS = 2 (outputs as narrow as d_model, long K): the workgroup has two groups of NW waves that
 // each take one half of K for the same tile, with A stages of their own; the second group
 // hands its accumulators over through LDS at the end.  Twice the waves per compute unit for
@@ -216,7 +221,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // (14 dwords fit: block_shape = block_rows | block_cols << 16, blocks_splits = n_blocks | k_splits << 16)
     const void *hot_A, const void *hot_w0, const void *hot_resid, const float *hot_bias0, int32_t hot_w_stride,
     int32_t hot_T, int32_t hot_lda, int32_t hot_ldr, uint32_t hot_block_shape, uint32_t hot_blocks_splits,
-    GemmProblem p, GemmBlocks blocks)   // (of p, only the fields that are not among the leading arguments are read)
+    GemmProblem p, ShardIds shard_of)   // (of p, only the fields that are not among the leading arguments are read)
 {
     const int hot_block_rows = hot_block_shape & 0xffff, hot_block_cols = hot_block_shape >> 16;
     const int hot_n_blocks = hot_blocks_splits & 0xffff, hot_k_splits = hot_blocks_splits >> 16;
@@ -373,9 +378,9 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             if constexpr (qkv) {
                 const int nrow = nrow0 + c;
                 const int which = nrow / p.d_head, e0 = nrow - which * p.d_head;
-                bp = (which == 0 ? hot_bias0 : (which == 1 ? p.bias1 : p.bias2)) + blocks.b[nblk].shard * p.d_head + e0;
+                bp = (which == 0 ? hot_bias0 : (which == 1 ? p.bias1 : p.bias2)) + shard_of.id(nblk) * p.d_head + e0;
             } else if constexpr (KIND == GEMM_FFN_UP) {
-                bp = hot_bias0 + blocks.b[nblk].shard * hot_block_rows + nrow0 + c;
+                bp = hot_bias0 + shard_of.id(nblk) * hot_block_rows + nrow0 + c;
             } else {
                 bp = hot_bias0 + nw + c;
             }
@@ -668,9 +673,13 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
         grid.x += p.next_workgroups;
     }
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
+    ShardIds shard_of;   // (the kernel takes these instead of the block table: a shorter argument list is a cheaper launch)
+    for (int b = 0; b < kMaxShardsPerLayer; b += 4)
+        shard_of.id4[b / 4] = (uint32_t)blocks.b[b].shard | (uint32_t)blocks.b[b + 1].shard << 8 |
+                              (uint32_t)blocks.b[b + 2].shard << 16 | (uint32_t)blocks.b[b + 3].shard << 24;
     launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
            p.resid, p.bias0, (int32_t)w_stride, p.T, p.lda, p.ldr, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
-           (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, p, blocks);
+           (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, p, shard_of);
     return hipGetLastError();
 }
 

@@ -290,13 +290,13 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
     if (pl->has_last) STI_TRY(hipStreamWaitEvent(pl->copy_stream, pl->last_done, 0));
 
     const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
-    const void *cur = x;
-    int next_buf = 0;
-    if (io_dtype != act) {
-        STI_TRY(launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * dims->d_model, stream));
-        cur = ws + wl.act[0];
-        next_buf = 1;
-    }
+    const ActLayout inner = inner_layout(*dims, T, precision);
+    const void *cur;
+    ActLayout cur_layout;
+    bool in_buffer;
+    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    if (st != STI_OK) return st;
+    int next_buf = in_buffer ? 1 : 0;
     size_t want_pos = 0;   // next entry of `want` (entries are in layer, shard order)
     for (int s = 0; s < kMaxSlots; ++s) pl->slot_used[s] = false;
     for (int l = 0; l < n_layers; ++l) {
@@ -352,13 +352,15 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
         const bool last = (l == n_layers - 1);
         void *out = last ? y : (void *)(ws + wl.act[next_buf]);
         st = run_layer(*dims, row, params[l], cur, out, last ? io_dtype : act, batch, seq, precision,
-                       ws, wl, stream, nullptr, masked ? key_lengths : nullptr);
+                       ws, wl, stream, nullptr, masked ? key_lengths : nullptr, nullptr, cur_layout,
+                       last ? LAYOUT_ROWS : inner);
         if (st != STI_OK) return st;
         if (slot_off > 0) {
             STI_TRY(hipEventRecord(pl->computed[slot], stream));
             pl->slot_used[slot] = true;
         }
         cur = out;
+        cur_layout = inner;
         next_buf ^= 1;
     }
     STI_TRY(hipEventRecord(pl->last_done, stream));

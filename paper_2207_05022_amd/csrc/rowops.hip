@@ -42,12 +42,18 @@ template <> struct Elem<STI_BF16> {
     static __device__ inline void store(uint16_t *p, float v) { *p = f32_to_bf16_bits(v); }
 };
 
+// element offset of columns c .. of a row (runs of 8 columns are contiguous in both layouts)
+__device__ inline int64_t act_offset(int layout, int row, int c, int d)
+{
+    return layout == LAYOUT_TILED ? tiled_offset(row, c, d >> 6) : (int64_t)row * d + c;
+}
+
 // v[t][:] = pre[t][:] (+ bias[:]) (+ resid[t][:]);  y[t][:] = LayerNorm(v) * g + b.
 // One wave per row; two-pass mean / variance in float32.  General sizes.
 template <int DT, typename RT>   // RT: type of the residual rows
 __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_partials,
                                                         int64_t partial_stride, const float *bias,
-                                                        const RT *resid,
+                                                        const RT *resid, int resid_layout, int y_layout,
                                                         typename Elem<DT>::type *y, const float *g,
                                                         const float *b, int T, int d, float eps)
 {
@@ -55,12 +61,11 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_
     const int lane = threadIdx.x % 64;
     if (row >= T) return;
     const float *r = pre + (int64_t)row * d;
-    const RT *rs = resid ? resid + (int64_t)row * d : nullptr;
     auto value = [&](int c) {
         float v = n_partials > 0 ? r[c] : 0.f;
         for (int s = 1; s < n_partials; ++s) v += r[(int64_t)s * partial_stride + c];
         if (bias) v += bias[c];
-        if (rs) v += (float)rs[c];
+        if (resid) v += (float)resid[act_offset(resid_layout, row, c, d)];
         return v;
     };
     float s = 0.f;
@@ -73,8 +78,8 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_
     }
     const float var = wave_sum(q) / (float)d;
     const float inv = 1.0f / sqrtf(var + eps);
-    typename Elem<DT>::type *o = y + (int64_t)row * d;
-    for (int c = lane; c < d; c += 64) Elem<DT>::store(o + c, (value(c) - mean) * inv * g[c] + b[c]);
+    for (int c = lane; c < d; c += 64)
+        Elem<DT>::store(y + act_offset(y_layout, row, c, d), (value(c) - mean) * inv * g[c] + b[c]);
 }
 
 // Same, for d a multiple of 4 and at most 2048: the row is read once with 16-byte loads
@@ -92,10 +97,11 @@ __device__ inline float row_sum(float v)
     return v;
 }
 
-template <int DT, typename RT, int LPR, int MAXC>   // MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC
+template <int DT, typename RT, bool TILED, int LPR, int MAXC>   // TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC
 __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, int n_partials,
                                                             int64_t partial_stride,
                                                             const float *bias, const RT *resid,
+                                                            int resid_layout, int y_layout,
                                                             typename Elem<DT>::type *y,
                                                             const float *g, const float *b, int T,
                                                             int d, float eps)
@@ -122,7 +128,7 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, in
         bs[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         rs4[j] = resid4{(RT)0.f, (RT)0.f, (RT)0.f, (RT)0.f};
         if (bias) bs[j] = ((const f32x4 *)bias)[cj[j]];
-        if (resid) rs4[j] = ((const resid4 *)(resid + (int64_t)row * d))[cj[j]];
+        if (resid) rs4[j] = *(const resid4 *)(resid + act_offset(TILED ? resid_layout : LAYOUT_ROWS, row, 4 * cj[j], d));
     }
     f32x4 gg[MAXC], bb[MAXC];
 #pragma unroll
@@ -170,19 +176,19 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, in
     }
     const float var = row_sum<LPR>(q) / (float)d;
     const float inv = 1.0f / sqrtf(var + eps);
-    typename Elem<DT>::type *o = y + (int64_t)row * d;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
         const int c = sub + LPR * j;
+        typename Elem<DT>::type *o = y + act_offset(TILED ? y_layout : LAYOUT_ROWS, row, 4 * c, d);
         if (c < nchunk) {
             const f32x4 t = (v[j] - mean) * inv * gg[j] + bb[j];
             if constexpr (DT == STI_F32) {
-                ((f32x4 *)o)[c] = t;
+                *(f32x4 *)o = t;
             } else if constexpr (DT == STI_F16) {
-                ((half4 *)o)[c] = half4{(_Float16)t.x, (_Float16)t.y, (_Float16)t.z, (_Float16)t.w};
+                *(half4 *)o = half4{(_Float16)t.x, (_Float16)t.y, (_Float16)t.z, (_Float16)t.w};
             } else {
-                Elem<DT>::store(o + 4 * c, t.x); Elem<DT>::store(o + 4 * c + 1, t.y);
-                Elem<DT>::store(o + 4 * c + 2, t.z); Elem<DT>::store(o + 4 * c + 3, t.w);
+                Elem<DT>::store(o, t.x); Elem<DT>::store(o + 1, t.y);
+                Elem<DT>::store(o + 2, t.z); Elem<DT>::store(o + 3, t.w);
             }
         }
     }
@@ -323,16 +329,16 @@ hipError_t convert_from(const void *src, void *dst, sti_dtype dst_dtype, uint64_
 
 }  // namespace
 
-template <int DT, typename RT>
+template <int DT, typename RT, bool TILED>
 void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, const float *bias,
-                     const void *resid, void *y, const float *g, const float *b, int T, int d, float eps,
-                     bool vec, hipStream_t stream)
+                     const void *resid, ActLayout resid_layout, ActLayout y_layout, void *y, const float *g, const float *b,
+                     int T, int d, float eps, bool vec, hipStream_t stream)
 {
     typedef typename Elem<DT>::type O;
     dim3 grid((T + 3) / 4);
 #define STI_LN_VEC(LPR, MAXC, GRID) \
-    launch((layernorm_vec_kernel<DT, RT, LPR, MAXC>), GRID, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, \
-           (const RT *)resid, (O *)y, g, b, T, d, eps)
+    launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC>), GRID, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, \
+           (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps)
     // many rows: 32 lanes per row (8 rows per workgroup); few rows: a whole wave per row; chunks
     // per lane sized to the row, so that the registers hold no more loads in flight than it has
     if (vec && T >= 2048 && d <= 1024) {
@@ -343,31 +349,35 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
         else if (d <= 1024) STI_LN_VEC(64, 4, grid);
         else STI_LN_VEC(64, 8, grid);
     } else {
-        launch((layernorm_kernel<DT, RT>), grid, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (O *)y, g, b, T, d, eps);
+        launch((layernorm_kernel<DT, RT>), grid, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps);
     }
 #undef STI_LN_VEC
 }
 
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
-                            const float *bias, const void *resid, bool resid_f32, void *y, sti_dtype out_dtype,
+                            const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
+                            sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
                             hipStream_t stream)
 {
     if (T <= 0 || d <= 0) return hipSuccess;
     if (n_partials < 0 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
+    if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || resid_f32)) return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
     const bool vec = d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) &&
                      (!bias || al16(bias)) && (!resid || al16(resid));
-    auto go = [&](auto resid_type) {
+    auto go = [&](auto resid_type, auto tiled) {
         typedef decltype(resid_type) RT;
+        constexpr bool TL = decltype(tiled)::value;
         switch (out_dtype) {
-            case STI_F32: launch_ln_typed<STI_F32, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
-            case STI_F16: launch_ln_typed<STI_F16, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
-            case STI_BF16: launch_ln_typed<STI_BF16, RT>(pre, n_partials, partial_stride, bias, resid, y, g, b, T, d, eps, vec, stream); break;
+            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
+            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
+            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
         }
     };
-    if (resid_f32) go(float{});
-    else go(_Float16{});
+    if (resid_f32) go(float{}, std::false_type{});
+    else if (resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) go(_Float16{}, std::true_type{});
+    else go(_Float16{}, std::false_type{});
     return hipGetLastError();
 }
 
@@ -402,6 +412,41 @@ hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dt
         case STI_F32: go(std::integral_constant<int, STI_F32>{}); break;
         case STI_F16: go(std::integral_constant<int, STI_F16>{}); break;
         case STI_BF16: go(std::integral_constant<int, STI_BF16>{}); break;
+    }
+    return hipGetLastError();
+}
+
+// Rows to tiled binary16: a thread takes 8 consecutive columns, consecutive threads the rows of a
+// 32-row block first, so that a wave's store is one contiguous fragment.
+namespace {
+
+template <int SRC>
+__global__ __launch_bounds__(256) void tile_rows_kernel(const typename Elem<SRC>::type *src, _Float16 *dst, int T, int d)
+{
+    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+    const int chunks = d >> 3, i = blockIdx.x * 256 + threadIdx.x;
+    const int row = i / (32 * chunks) * 32 + i % 32, c = i / 32 % chunks * 8;
+    if (row >= T) return;
+    const typename Elem<SRC>::type *p = src + (int64_t)row * d + c;
+    half8 h;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = (_Float16)Elem<SRC>::load(p + e);
+    *(half8 *)(dst + tiled_offset(row, c, d >> 6)) = h;
+}
+
+}  // namespace
+
+hipError_t launch_tile_rows(const void *src, sti_dtype src_dtype, void *dst, int T, int d, hipStream_t stream)
+{
+    if (T <= 0 || d <= 0) return hipSuccess;
+    if (d % 64) return hipErrorInvalidValue;
+    const int64_t threads = (int64_t)((T + 31) / 32) * 32 * (d / 8);
+    if (threads > 0x7FFFFF00) return hipErrorInvalidValue;
+    const dim3 grid((uint32_t)((threads + 255) / 256));
+    switch (src_dtype) {
+        case STI_F32: launch((tile_rows_kernel<STI_F32>), grid, dim3(256), 0, stream, (const float *)src, (_Float16 *)dst, T, d); break;
+        case STI_F16: launch((tile_rows_kernel<STI_F16>), grid, dim3(256), 0, stream, (const _Float16 *)src, (_Float16 *)dst, T, d); break;
+        case STI_BF16: launch((tile_rows_kernel<STI_BF16>), grid, dim3(256), 0, stream, (const uint16_t *)src, (_Float16 *)dst, T, d); break;
     }
     return hipGetLastError();
 }

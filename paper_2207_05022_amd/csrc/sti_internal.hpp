@@ -65,6 +65,19 @@ enum GemmKind : int32_t {
     GEMM_QKV_ATTN = 4
 };
 
+// How an activation matrix lies in memory: row by row, or (few tokens) in the cells of the weights' working
+// buffer: 32 rows x 64 columns = 4 KiB, [row block][column cell][fragment q][lane][8 values], lane l of
+// fragment q owning row l % 32, columns (l / 32) * 32 + q * 8 .. + 8 - a matrix-core operand of a wave is one contiguous
+// 1 KiB load.  Buffers of tiled matrices hold whole row blocks; what lies in rows past the last token is arbitrary.
+enum ActLayout : int32_t { LAYOUT_ROWS = 0, LAYOUT_TILED = 1 };
+
+// element offset of (row, col) in a tiled matrix of `cells` 64-column cells per row block
+__host__ __device__ inline int64_t tiled_offset(int row, int col, int cells)
+{
+    return ((int64_t)(row >> 5) * cells + (col >> 6)) * 2048 + ((col & 31) >> 3) * 512 + (((col >> 5) & 1) * 32 + (row & 31)) * 8 +
+           (col & 7);
+}
+
 struct GemmBlock {
     const void *w;          // start of the block's weights: float32 values, or a k-bit stream
     const float *codebook;  // centroids when bits <= 6
@@ -90,6 +103,7 @@ struct GemmProblem {
     const float *bias0, *bias1, *bias2;  // QKV: bq,bk,bv; FFN_UP: b1; OUT/FFN_DOWN: bias[N]
     const void *resid;  // OUT/FFN_DOWN: [T x N] residual, row stride ldr
     int32_t ldr;
+    ActLayout a_layout, c_layout;   // few-token kernel; tiled: lda / ldc are the matrices' widths
     // wide-tile kernel, OUT/FFN_DOWN only: with k_splits > 1 the K range is also split over
     // that many workgroups per tile, C is float32 and takes the raw partial sums of split s
     // at C + s * partial_stride (bias and residual are left to launch_layernorm)
@@ -131,29 +145,38 @@ int gemm_wide_spare_workgroups(const GemmProblem &p);
 // largest value it can return for T tokens and N output columns (workspace sizing)
 int gemm_wide_k_splits(const GemmProblem &p);
 int gemm_wide_max_k_splits(int64_t T, int N);
-hipError_t launch_attention_mfma(const void *qkv, void *ctx, int B, int L, int m, int dh,
+// ctx_layout: how the context is left behind (the Q/K/V matrix is row-major)
+hipError_t launch_attention_mfma(const void *qkv, void *ctx, ActLayout ctx_layout, int B, int L, int m, int dh,
                                  const int32_t *key_lengths, hipStream_t stream);
+// Few tokens: Q/K/V and context tiled, the V cells transposed as the few-token GEMM leaves them
+// (attention_few.hip; one sequence, or sequences of a multiple of 32 tokens).
+bool attention_few_supported(int B, int L);
+hipError_t launch_attention_few(const void *qkv, void *ctx, int B, int L, int m, int dh, const int32_t *key_lengths,
+                                hipStream_t stream);
 
-// Few-token variant of the MFMA GEMM (gemm_skinny.hip): T <= kSkinnyMaxTokens, split-K inside the
+// Few-token variant of the MFMA GEMM (gemm_few.hip): T <= kFewMaxTokens, split-K inside the
 // workgroup and, for the K-split kinds, across `k_splits` workgroups that write float32
 // partial sums at C + s * partial_stride (to be added by launch_layernorm).
-constexpr int kSkinnyMaxTokens = 256;
-constexpr int kSkinnyMaxSplits = 8;
-int skinny_k_splits(const GemmProblem &p);
-hipError_t launch_gemm_skinny(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
+constexpr int kFewMaxTokens = 1024;
+constexpr int kFewMaxSplits = 8;
+int few_k_splits(const GemmProblem &p);
+hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                               int64_t partial_stride, hipStream_t stream);
 
 // rowops.hip
 // v = sum_{s < n_partials} pre[s * partial_stride + t*d + :] + bias[:] + resid[t][:]  (n_partials may be 0);
 // y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid (binary16, or float32
-// with resid_f32, [T x d]) may be NULL; y of out_dtype.
+// with resid_f32, [T x d]) may be NULL; y of out_dtype.  A residual or a binary16 y may be tiled.
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
-                            const float *bias, const void *resid, bool resid_f32, void *y, sti_dtype out_dtype,
+                            const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
+                            sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
                             hipStream_t stream);
 // y[t][:] = LayerNorm(pre_f16[t][:]) * g + b for rows that already hold sum + bias + residual.
 hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dtype, const float *g,
                                   const float *b, int T, int d, float eps, hipStream_t stream);
+// rows of src -> binary16, tiled (d a multiple of 64)
+hipError_t launch_tile_rows(const void *src, sti_dtype src_dtype, void *dst, int T, int d, hipStream_t stream);
 // elementwise conversion between activation types
 hipError_t launch_convert(const void *src, sti_dtype src_dtype, void *dst, sti_dtype dst_dtype,
                           uint64_t n, hipStream_t stream);

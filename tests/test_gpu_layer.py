@@ -312,6 +312,34 @@ def test_mfma_full_size_every_term_matters(gpu, oracle_mod):
     assert_parity(got, want, TOL["mfma"])
 
 
+@pytest.mark.parametrize("d,M,f,B,L,masked,outliers", [
+    (256, 4, 64, 1, 1, False, False),      # one token: a row block with one row
+    (256, 3, 64, 1, 33, True, False),      # a second row block with one row; two attention waves
+    (320, 5, 128, 1, 95, True, True),      # ragged end, weights from the working buffer
+    (768, 12, 256, 3, 64, True, False),    # several sequences of whole row blocks
+    (768, 12, 256, 5, 40, True, False),    # sequences that straddle row blocks: row-major Q/K/V
+    (1024, 16, 256, 1, 300, True, False),  # more workgroups than compute units; ten key blocks for four waves
+    (256, 4, 64, 2, 512, False, False),    # the longest sequence
+    (512, 20, 64, 1, 130, False, False),   # more than 16 weight blocks
+])
+def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, outliers):
+    """Edges of the few-token route: part row blocks, K splits, both attention kernels, float32 and binary16
+    inputs (tiled by a launch of its own, or read row by row), two layers (tiled activations in between)."""
+    torch, P, D = gpu
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    for io in ("f32", "f16"):
+        wl = S.small_workload(41000 + d + L, dims, 2, B, L, n_absent=1, io_dtype=io)
+        if outliers:
+            wl = _with_outliers(wl, 5, fraction=0.005)
+        S.make_every_term_matter(wl, L, amp=2.0)
+        lens = _key_lengths(L, B, L) if masked else None
+        if B == 1 and masked:
+            lens[0] = max(1, L - 1)
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x, key_lengths=lens)
+        got = _run_masked(gpu, wl, "mfma", lens, "model").float().cpu().numpy()
+        assert_parity(got, want, TOL["mfma"], io)
+
+
 def test_mfma_rejects_unsupported_dims(gpu):
     torch, P, D = gpu
     assert P.sti_workspace_bytes(SMALL, 1, 8, P.STI_PREC_F16_MFMA) == 0
