@@ -73,8 +73,7 @@ __device__ inline float attention_scores_in_registers(const att_half8 (&qf)[4], 
             const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], scale, shift));
             const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v + 1], scale, shift));
             run_sum += p0 + p1;
-            pk[v / 2] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)p0) |
-                        ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)p1) << 16);
+            pk[v / 2] = f16_pair_bits(p0, p1);
         }
         // O^T += V^T P^T over the two k16 steps of key block kb
 #pragma unroll

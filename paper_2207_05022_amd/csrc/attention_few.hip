@@ -85,7 +85,7 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
             const float p0 = __builtin_amdgcn_exp2f(s_acc[v] - new_max);
             const float p1 = __builtin_amdgcn_exp2f(s_acc[v + 1] - new_max);
             psum += p0 + p1;
-            pk[v / 2] = f16_bits(p0) | (f16_bits(p1) << 16);
+            pk[v / 2] = f16_pair_bits(p0, p1);
         }
         run_sum = run_sum * alpha + psum;
 #pragma unroll

@@ -78,6 +78,14 @@ __host__ __device__ inline int64_t tiled_offset(int row, int col, int cells)
            (col & 7);
 }
 
+// two values rounded to binary16 (nearest even) in one dword: one conversion instruction
+__device__ inline uint32_t f16_pair_bits(float lo, float hi)
+{
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    const half2v h = {(_Float16)lo, (_Float16)hi};
+    return __builtin_bit_cast(uint32_t, h);
+}
+
 struct GemmBlock {
     const void *w;          // start of the block's weights: float32 values, or a k-bit stream
     const float *codebook;  // centroids when bits <= 6
