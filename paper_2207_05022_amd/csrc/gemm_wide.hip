@@ -7,7 +7,8 @@
 //
 // One workgroup of NW waves owns a (RA*32) x (NW*32) tile and is sized so that a compute
 // unit holds all its waves at once (12 wave slots at this register budget): all waves of a
-// unit then move through the K loop in step, share one copy of the A tile and finish together.
+// unit then move through the K loop in step, share one copy of the A tile and finish together - or, with
+// many tiles, so that two workgroups share a unit (RB = 2 below).
 //   - the A tile [BM x 64] goes global -> LDS directly (global_load_lds_dwordx4, no
 //     registers, no LDS store instructions), three stages; its 16-byte chunks are XOR-swizzled
 //     by row pair so that the unpadded rows read without bank conflicts;
@@ -110,11 +111,11 @@ constexpr int ATT_L = 128, ATT_DH = 64, ATT_KPAD = ATT_DH + 8, ATT_VTS = ATT_L +
 constexpr int ATT_HEAD_HALVES = 2 * ATT_L * ATT_KPAD + ATT_DH * ATT_VTS;
 constexpr size_t kAttentionLdsBytes = (size_t)2 * ATT_HEAD_HALVES * 2;
 
-template <int RA, int NW, int KS>
+template <int RA, int NW, int KS, int RB>
 constexpr size_t wide_lds_bytes()
 {
-    constexpr size_t stages = (size_t)KS * 3 * (RA * 32) * BK * 2;
-    constexpr size_t tile = (size_t)(RA * 32) * (NW * 32 + 8) * 2;
+    constexpr size_t stages = (size_t)KS * (RB == 2 ? 2 : 3) * (RA * 32) * BK * 2;
+    constexpr size_t tile = (size_t)(RA * 32) * (NW * RB * 32 + 8) * 2;
     constexpr size_t partial = (size_t)(KS - 1) * (RA * 32) * (NW * 32) * 4;
     constexpr size_t m = stages > tile ? stages : tile;
     return m > partial ? m : partial;
@@ -213,8 +214,14 @@ struct ShardIds {   // original shard id of every weight block (selects the bias
 // each take one half of K for the same tile, with A stages of their own; the second group
 // hands its accumulators over through LDS at the end.  Twice the waves per compute unit for
 // a tile count that is fixed by the output size.
-template <int KIND, int RA, int NW, int KS, bool EARLY>
-__global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
+//
+// RB = 2 (many tiles): a wave owns two 32-column strips, 128 x 64 outputs, so that an A fragment out of LDS serves two
+// products; four waves are a workgroup and two workgroups share a compute unit without waiting for
+// each other: one multiplies while the other is in its start-up or epilogue.  128 accumulators leave room for
+// one K tile of weights in flight instead of two.  9216 tokens, d_model 1024: FFN1 89 us (121 with the best of the other
+// shapes), Q/K/V 69 (85).
+template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
+__global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kernel(
     // what the first loads of a workgroup depend on, as leading scalar arguments: these arrive
     // preloaded in scalar registers (the build asks for kernel-argument preloading), so that the
     // first A fetches and weight loads are not behind a round trip to the argument buffer
@@ -230,10 +237,10 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     const unsigned long long wall0 = wall_clock64();
     STI_STAMP(0);
 #endif
-    constexpr int BM = RA * 32, BN = NW * 32, NT = NW * KS * 64, NTH = NW * 64;
+    constexpr int BM = RA * 32, BN = NW * RB * 32, NT = NW * KS * 64, NTH = NW * 64, STAGES = RB == 2 ? 2 : 3;
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
     constexpr bool qkv = (KIND == GEMM_QKV || KIND == GEMM_QKV_ATTN);
-    static_assert(KIND != GEMM_QKV_ATTN || (RA == 4 && NW == 12 && KS == 1), "two heads of one 128-token sequence per tile");
+    static_assert(KIND != GEMM_QKV_ATTN || (RA == 4 && NW == 12 && KS == 1 && RB == 1), "two heads of one 128-token sequence per tile");
     constexpr int STAGE = BM * BK;              // halves per A stage
     constexpr int FETCHES = BM / 8;             // fetch instructions per A stage: 8 rows (1 KiB) each
     constexpr int FPW = (FETCHES + NW - 1) / NW;   // per wave: wave w issues fetches w, w + NW, ...
@@ -276,10 +283,10 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     const int tile_n = in_band / band_rows;
     const int tile_m = band * group + (in_band - tile_n * band_rows);
     const int m0 = tile_m * BM;
-    // N and the block widths are multiples of 32, so a wave's columns are all inside or all
-    // outside the matrix; a wave outside recomputes the first columns and its results are
+    // N and the block widths are multiples of 64, so a wave's columns are all inside or all
+    // outside the matrix and inside one block; a wave outside recomputes the first columns and its results are
     // dropped by the column mask of the stores
-    const int nw_real = tile_n * BN + wave * 32;
+    const int nw_real = tile_n * BN + wave * (RB * 32);
     const int nw = nw_real < N ? nw_real : 0;
     int nblk = 0, nrow0 = nw;
     if (n_split) {
@@ -288,11 +295,13 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     }
     const int tiles_per_kblock = n_split ? nkt * KS : hot_block_cols / BK;
 
-    float16v acc[RA];
+    float16v acc[RA][RB];
 #pragma unroll
     for (int i = 0; i < RA; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][r][v] = 0.f;
 
     // ---- A tile: lane l of a fetch instruction fills LDS slot (row l/8, chunk l%8) of its 8
     //      rows with the chunk (l%8) ^ ((row/2)%8) of that row, so that the 16 rows that one
@@ -315,7 +324,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         for (int j = 0; j < FPW; ++j) {
             if (wave + NW * j < FETCHES) {
                 const _Float16 *gp = A + (kt0 + kt) * BK;   // scalar base, per-lane 32-bit offset
-                const uint32_t dst = lds_base + (uint32_t)(((half * 3 + buf) * STAGE + (wave + NW * j) * 8 * BK) * 2);
+                const uint32_t dst = lds_base + (uint32_t)(((half * STAGES + buf) * STAGE + (wave + NW * j) * 8 * BK) * 2);
                 asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                              :: "v"(src[j]), "s"(gp), "s"(dst) : "memory", "m0");
             }
@@ -327,13 +336,13 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     for (int s = 0; s < 4; ++s) frag_off[s] = lr * (BK * 2) + (((g * 4 + s) ^ ((lr >> 1) & 7)) * 16);
 
     const uint32_t lane16 = lane * 16;
-    auto frag_ptr = [&](int kt) -> const uint8_t * {
+    auto frag_ptr = [&](int kt, int r) -> const uint8_t * {
         int blk, ktb, row;
         kt += kt0;
         if (n_split) {
-            blk = nblk; ktb = kt; row = nrow0;
+            blk = nblk; ktb = kt; row = nrow0 + r * 32;
         } else {
-            blk = kt / tiles_per_kblock; ktb = kt - blk * tiles_per_kblock; row = nw;
+            blk = kt / tiles_per_kblock; ktb = kt - blk * tiles_per_kblock; row = nw + r * 32;
         }
         // (the blocks of a working buffer lie at a constant distance: no look-up in the block table)
         const uint8_t *base = (const uint8_t *)hot_w0 + (int64_t)blk * hot_w_stride;   // (stride < 2^31)
@@ -346,18 +355,21 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // barrier: measured 2 % faster end to end than issuing at the top, while the split-K
     // shapes are faster with the issue at the top).  The wait in front of the barrier is
     // written by hand: it lets the loads of tile t+1, the last ones issued, stay in flight.
-    u32x4 bw[3][4];
+    u32x4 bw[STAGES][RB][4];
     int n_fetch = 0;   // A fetches this wave issues per stage
 #pragma unroll
     for (int j = 0; j < FPW; ++j) n_fetch += (wave + NW * j < FETCHES) ? 1 : 0;
-    auto issue = [&](int kt, u32x4 (&dst)[4]) {
-        fetch_a(kt, kt % 3);
-        const uint8_t *q = frag_ptr(kt);
-        asm volatile("global_load_dwordx4 %0, %4, %5\n\t"
-                     "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
-                     "global_load_dwordx4 %2, %4, %5 offset:2048\n\t"
-                     "global_load_dwordx4 %3, %4, %5 offset:3072"
-                     : "=&v"(dst[0]), "=&v"(dst[1]), "=&v"(dst[2]), "=&v"(dst[3]) : "v"(lane16), "s"(q) : "memory");
+    auto issue = [&](int kt, u32x4 (&dst)[RB][4]) {
+        fetch_a(kt, kt % STAGES);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const uint8_t *q = frag_ptr(kt, r);
+            asm volatile("global_load_dwordx4 %0, %4, %5\n\t"
+                         "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
+                         "global_load_dwordx4 %2, %4, %5 offset:2048\n\t"
+                         "global_load_dwordx4 %3, %4, %5 offset:3072"
+                         : "=&v"(dst[r][0]), "=&v"(dst[r][1]), "=&v"(dst[r][2]), "=&v"(dst[r][3]) : "v"(lane16), "s"(q) : "memory");
+        }
     };
 #define STI_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
     // EARLY (64-row tiles of the d_model-wide projections, K not split over workgroups): what
@@ -366,14 +378,14 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // clock kernel).  They are the oldest loads in flight, so the first wait of the K loop
     // covers them.  (A variant of its own: with K split over workgroups nothing is added here.)
     constexpr bool PRE = EARLY;
-    static_assert(!EARLY || (!n_split && RA <= 2), "early operands: 64-row tiles of OUT / FFN_DOWN");
+    static_assert(!EARLY || (!n_split && RA <= 2 && RB == 1), "early operands: 64-row tiles of OUT / FFN_DOWN");
     const _Float16 *R = (const _Float16 *)hot_resid;
-    f32x4 bias[2][2];
+    f32x4 bias[RB][2][2];
     u32x4 resv[PRE ? RA : 1][2];
     auto load_epilogue_operands = [&]() {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int c = 16 * q + 8 * g;     // first column of the piece inside the wave's strip
+        for (int rq = 0; rq < 2 * RB; ++rq) {
+            const int c = 16 * rq + 8 * g;    // first column of the piece inside the wave's columns
             const float *bp;
             if constexpr (qkv) {
                 const int nrow = nrow0 + c;
@@ -384,8 +396,8 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             } else {
                 bp = hot_bias0 + nw + c;
             }
-            bias[q][0] = *(const f32x4 *)bp;
-            bias[q][1] = *(const f32x4 *)(bp + 4);
+            bias[rq >> 1][rq & 1][0] = *(const f32x4 *)bp;
+            bias[rq >> 1][rq & 1][1] = *(const f32x4 *)(bp + 4);
         }
         if constexpr (PRE) {
 #pragma unroll
@@ -396,10 +408,11 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             }
         }
     };
-    auto step = [&](int kt, u32x4 (&bcur)[4], u32x4 (&bnew)[4]) {
+    auto step = [&](int kt, u32x4 (&bcur)[RB][4], u32x4 (&bnew)[RB][4]) {
+        constexpr int AHEAD = STAGES - 1;   // K tiles in flight
         // the weight fragments and the A stage of tile kt have landed (the barrier below is a
         // scheduling boundary: no MFMA of this step is placed above the wait) ...
-        if (kt + 1 < nkt) {
+        if (AHEAD > 1 && kt + 1 < nkt) {
             if (n_fetch == 2) STI_WAIT_LOADS(6);
             else if (n_fetch == 1) STI_WAIT_LOADS(5);
             else STI_WAIT_LOADS(4);
@@ -413,8 +426,8 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #ifdef STI_PHASE_STAMPS
         if (kt == 0) STI_STAMP(2);
 #endif
-        if (KS == 2 && kt + 2 < nkt) issue(kt + 2, bnew);
-        const unsigned char *stage = smem_raw + (half * 3 + kt % 3) * (STAGE * 2);
+        if (KS == 2 && kt + AHEAD < nkt) issue(kt + AHEAD, bnew);
+        const unsigned char *stage = smem_raw + (half * STAGES + kt % STAGES) * (STAGE * 2);
         half8 a_cur[RA], a_nxt[RA];
 #pragma unroll
         for (int i = 0; i < RA; ++i) a_cur[i] = *(const half8 *)(stage + i * (32 * BK * 2) + frag_off[0]);
@@ -428,10 +441,12 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < RA; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[s]), a_cur[i],
-                                                              acc[i], 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    acc[i][r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[r][s]), a_cur[i],
+                                                                     acc[i][r], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if (KS == 1 && s == 0 && kt + 2 < nkt) issue(kt + 2, bnew);
+            if (KS == 1 && s == 0 && kt + AHEAD < nkt) issue(kt + AHEAD, bnew);
             __builtin_amdgcn_sched_barrier(0);
             if (s < 3) {
 #pragma unroll
@@ -439,15 +454,22 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             }
         }
     };
-    static_assert(FPW <= 2, "the hand-written waits cover up to two A fetches per wave");
+    static_assert(FPW <= 2 || RB == 2, "the hand-written waits cover up to two A fetches per wave");
     if (PRE && half == 0) load_epilogue_operands();
     if (nkt > 0) issue(0, bw[0]);
-    if (nkt > 1) issue(1, bw[1]);
+    if (STAGES > 2 && nkt > 1) issue(1, bw[1]);
     STI_STAMP(1);
-    for (int kt = 0; kt < nkt; kt += 3) {
-        step(kt, bw[0], bw[2]);
-        if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
-        if (kt + 2 < nkt) step(kt + 2, bw[2], bw[1]);
+    if constexpr (RB == 2) {
+        for (int kt = 0; kt < nkt; kt += 2) {
+            step(kt, bw[0], bw[1]);
+            if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
+        }
+    } else {
+        for (int kt = 0; kt < nkt; kt += 3) {
+            step(kt, bw[0], bw[2]);
+            if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
+            if (kt + 2 < nkt) step(kt + 2, bw[2], bw[1]);
+        }
     }
 #undef STI_WAIT_LOADS
     STI_STAMP(3);
@@ -478,12 +500,12 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                 half8 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
+                    const float lo = acc[i][0][(2 * q) * 4 + e], hi = acc[i][0][(2 * q + 1) * 4 + e];
                     const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                      __builtin_bit_cast(uint32_t, hi), false, false);
                     const uint32_t s0 = sw[0], s1 = sw[1];
-                    o[e] = (_Float16)(__builtin_bit_cast(float, s0) + bias[q][0][e]);
-                    o[4 + e] = (_Float16)(__builtin_bit_cast(float, s1) + bias[q][1][e]);
+                    o[e] = (_Float16)(__builtin_bit_cast(float, s0) + bias[0][q][0][e]);
+                    o[4 + e] = (_Float16)(__builtin_bit_cast(float, s1) + bias[0][q][1][e]);
                 }
                 const int c = ch + 16 * q + 8 * g;
                 if (part < 2) {
@@ -531,14 +553,14 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) part[(i * 16 + v) * NTH + th] = acc[i][v];
+                for (int v = 0; v < 16; ++v) part[(i * 16 + v) * NTH + th] = acc[i][0][v];
         }
         __syncthreads();
         if (half == 0) {
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][v] += part[(i * 16 + v) * NTH + th];
+                for (int v = 0; v < 16; ++v) acc[i][0][v] += part[(i * 16 + v) * NTH + th];
         }
         __syncthreads();   // the sums are in registers: the buffer can take the staged tile
     }
@@ -554,7 +576,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                     float x[8];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
+                        const float lo = acc[i][0][(2 * q) * 4 + e], hi = acc[i][0][(2 * q + 1) * 4 + e];
                         const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                          __builtin_bit_cast(uint32_t, hi), false, false);
                         const uint32_t s0 = sw[0], s1 = sw[1];
@@ -577,26 +599,27 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
         const int row = i * 32 + lr;          // row inside the tile
-        half8 res[2];
+        half8 res[2 * RB];
         if constexpr (PRE) {
             res[0] = __builtin_bit_cast(half8, resv[i][0]);
             res[1] = __builtin_bit_cast(half8, resv[i][1]);
         } else if constexpr (!n_split) {
             const int m = m0 + row;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
+            for (int q = 0; q < 2 * RB; ++q) {
                 u32x4 v = {0, 0, 0, 0};
                 if (m < hot_T) v = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
                 res[q] = __builtin_bit_cast(half8, v);
             }
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int rq = 0; rq < 2 * RB; ++rq) {
+            const int r = rq >> 1, q = rq & 1;
             float x[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // (element values first: a bit cast applied to a vector element itself reads element 0)
-                const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
+                const float lo = acc[i][r][(2 * q) * 4 + e], hi = acc[i][r][(2 * q + 1) * 4 + e];
                 const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                  __builtin_bit_cast(uint32_t, hi), false, false);
                 const uint32_t s0 = sw[0], s1 = sw[1];
@@ -606,12 +629,12 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             half8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float y = x[e] + bias[q][e >> 2][e & 3];
+                float y = x[e] + bias[r][q][e >> 2][e & 3];
                 if constexpr (KIND == GEMM_FFN_UP) y = gelu_erf(y);
-                if constexpr (!n_split) y += (float)res[q][e];
+                if constexpr (!n_split) y += (float)res[rq][e];
                 o[e] = (_Float16)y;
             }
-            *(half8 *)(tile_out + row * LDT + wave * 32 + 16 * q + 8 * g) = o;
+            *(half8 *)(tile_out + row * LDT + wave * (RB * 32) + 16 * rq + 8 * g) = o;
         }
     }
     }
@@ -637,28 +660,28 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     STI_STAMPS_OUT();
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY>
+template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream);
 
-template <int KIND, int RA, int NW, int KS>
+template <int KIND, int RA, int NW, int KS, int RB = 1>
 hipError_t launch_shape(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
     if constexpr (!n_split && RA <= 2) {
-        if (p.k_splits <= 1) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
+        if (p.k_splits <= 1) return launch_variant<KIND, RA, NW, KS, true, RB>(p, blocks, N, stream);
     }
-    return launch_variant<KIND, RA, NW, KS, false>(p, blocks, N, stream);
+    return launch_variant<KIND, RA, NW, KS, false, RB>(p, blocks, N, stream);
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY>
+template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
-    constexpr int BM = RA * 32, BN = NW * 32;
-    constexpr size_t lds = (KIND == GEMM_QKV_ATTN && kAttentionLdsBytes > wide_lds_bytes<RA, NW, KS>())
-                               ? kAttentionLdsBytes : wide_lds_bytes<RA, NW, KS>();
+    constexpr int BM = RA * 32, BN = NW * RB * 32;
+    constexpr size_t lds = (KIND == GEMM_QKV_ATTN && kAttentionLdsBytes > wide_lds_bytes<RA, NW, KS, RB>())
+                               ? kAttentionLdsBytes : wide_lds_bytes<RA, NW, KS, RB>();
     // once per instantiation, and safe when several host threads make their first call together
     static const hipError_t attr_status =
-        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, EARLY>,
+        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, EARLY, RB>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_status != hipSuccess) return attr_status;
     const int total = ((N + BN - 1) / BN) * ((p.T + BM - 1) / BM);
@@ -677,37 +700,41 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
     for (int b = 0; b < kMaxShardsPerLayer; b += 4)
         shard_of.id4[b / 4] = (uint32_t)blocks.b[b].shard | (uint32_t)blocks.b[b + 1].shard << 8 |
                               (uint32_t)blocks.b[b + 2].shard << 16 | (uint32_t)blocks.b[b + 3].shard << 24;
-    launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
+    launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY, RB>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
            p.resid, p.bias0, (int32_t)w_stride, p.T, p.lda, p.ldr, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
            (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, p, shard_of);
     return hipGetLastError();
 }
 
-template <int RA, int NW>
+template <int RA, int NW, int RB>
 hipError_t launch_kind(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     switch (p.kind) {
-    case GEMM_QKV: return launch_shape<GEMM_QKV, RA, NW, 1>(p, blocks, N, stream);
-    case GEMM_FFN_UP: return launch_shape<GEMM_FFN_UP, RA, NW, 1>(p, blocks, N, stream);
-    case GEMM_OUT: return launch_shape<GEMM_OUT, RA, NW, 1>(p, blocks, N, stream);
-    case GEMM_FFN_DOWN: return launch_shape<GEMM_FFN_DOWN, RA, NW, 1>(p, blocks, N, stream);
+    case GEMM_QKV: return launch_shape<GEMM_QKV, RA, NW, 1, RB>(p, blocks, N, stream);
+    case GEMM_FFN_UP: return launch_shape<GEMM_FFN_UP, RA, NW, 1, RB>(p, blocks, N, stream);
+    case GEMM_OUT: return launch_shape<GEMM_OUT, RA, NW, 1, RB>(p, blocks, N, stream);
+    case GEMM_FFN_DOWN: return launch_shape<GEMM_FFN_DOWN, RA, NW, 1, RB>(p, blocks, N, stream);
     case GEMM_QKV_ATTN: break;   // one shape only, launched by launch_gemm_wide itself
     }
     return hipErrorInvalidValue;
 }
 
+// Tile shapes: (32 ra) x (32 nw rb).  Time of a workgroup, fitted to launches of all four projections at 8 token
+// counts from 1056 to 9216 and d_model 768 and 1024: block_us per 32 x 32 outputs and 1024 of K, start_us
+// for start-up and epilogue (GELU: 3.5 us more).  shared: two workgroups on a compute unit also share
+// out its last round.
 struct Shape {
-    int ra, nw;
+    int ra, nw, rb;
+    float block_us, start_us;
+    bool shared;
 };
-constexpr Shape kShapes[] = {{4, 12}, {4, 9}, {2, 12}, {2, 6}};
-constexpr int kWaveSlots = 12;   // waves a compute unit holds at this kernel's register budget
+constexpr Shape kShapes[] = {{4, 12, 1, 0.37f, 6.5f, false}, {4, 9, 1, 0.38f, 8.f, false}, {2, 12, 1, 0.48f, 6.f, false},
+                             {2, 6, 1, 0.72f, 3.f, false},   {4, 4, 2, 0.54f, 4.f, true}};
+constexpr float kSplitBlockUs = 0.45f, kSplitStartUs = 5.5f;   // {2, 6} with K split over two wave groups (one workgroup per unit)
+constexpr float kGeluUs = 3.5f;
 
 }  // namespace
 
-// Tile shape for a [T x N] output: the one whose busiest compute unit has the least MFMA
-// work (workgroups are spread evenly over the units, floor(12 / NW) of them fit on one at a
-// time); ties go to fewer rounds of workgroups on that unit, then to more rows per weight
-// fragment, then to more waves per unit.
 bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks)
 {
     if (p.n_blocks <= 0 || p.T <= 0) return false;
@@ -733,38 +760,38 @@ struct Choice {
     int nkt_total;
 };
 
+// The shape with the least estimated time.
 Choice choose(const GemmProblem &p, int N)
 {
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN);
-    int best = -1;
-    long best_key[4] = {0, 0, 0, 0}, best_tiles = 0;
+    const int nkt = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
+    const float k = nkt * BK / 1024.f;
+    Choice best = {};
+    float best_us = 0.f;
     for (int c = 0; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
-        const int bm = kShapes[c].ra * 32, bn = kShapes[c].nw * 32;
+        const Shape &sh = kShapes[c];
+        const int bm = sh.ra * 32, bn = sh.nw * sh.rb * 32, blocks = sh.ra * sh.nw * sh.rb;
         const long tiles = (long)((N + bn - 1) / bn) * ((p.T + bm - 1) / bm);
-        const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;        // workgroups on the busiest unit
-        const long resident = kWaveSlots / kShapes[c].nw;
-        const long key[4] = {per_cu * kShapes[c].nw * kShapes[c].ra,            // its MFMA work
-                             (per_cu + resident - 1) / resident,                // rounds
-                             -kShapes[c].ra,
-                             -(per_cu < resident ? per_cu : resident) * kShapes[c].nw};
-        bool better = best < 0;
-        for (int i = 0; i < 4 && !better; ++i) {
-            if (key[i] != best_key[i]) { better = key[i] < best_key[i]; break; }
-        }
-        if (better) {
-            best = c;
-            best_tiles = tiles;
-            for (int i = 0; i < 4; ++i) best_key[i] = key[i];
+        const float avg = (float)tiles / kComputeUnits;
+        const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
+        // one 6-wave workgroup per unit: K is split inside the workgroup to fill the unit
+        const bool ks2 = !n_split && sh.ra == 2 && sh.nw == 6 && per_cu == 1 && nkt % 2 == 0 && nkt >= 4;
+        const float start = (ks2 ? kSplitStartUs : sh.start_us) + (p.kind == GEMM_FFN_UP ? kGeluUs : 0.f);
+        const float products = blocks * k * (ks2 ? kSplitBlockUs : sh.block_us);
+        // (workgroups that share a unit: half way between average and busiest, start-up and epilogue hidden but for one;
+        //  two 6-wave workgroups share a unit too, but a unit with one more than its neighbours holds all up)
+        float us = per_cu * (products + start);
+        if (sh.shared) us = (avg < 1.f ? 1.f : (avg + per_cu) / 2) * products + start;
+        else if (sh.nw == 6) us = per_cu * products + start;
+        if (c == 0 || us < best_us) {
+            best_us = us;
+            best.shape = c;
+            best.ks2 = ks2;
+            best.tiles = tiles;
+            best.nkt_total = nkt;
         }
     }
-    Choice ch;
-    ch.shape = best;
-    ch.tiles = best_tiles;
-    ch.nkt_total = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
-    // one 6-wave workgroup per unit: split K inside the workgroup to fill the unit
-    ch.ks2 = !n_split && kShapes[best].ra == 2 && kShapes[best].nw == 6 && best_key[1] == 1 &&
-             best_key[0] == 12 && ch.nkt_total % 2 == 0 && ch.nkt_total >= 4;
-    return ch;
+    return best;
 }
 
 }  // namespace
@@ -832,10 +859,11 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
                                   : launch_shape<GEMM_FFN_DOWN, 2, 6, 2>(p, blocks, N, stream);
     }
     switch (ch.shape) {
-    case 0: return launch_kind<4, 12>(p, blocks, N, stream);
-    case 1: return launch_kind<4, 9>(p, blocks, N, stream);
-    case 2: return launch_kind<2, 12>(p, blocks, N, stream);
-    default: return launch_kind<2, 6>(p, blocks, N, stream);
+    case 0: return launch_kind<4, 12, 1>(p, blocks, N, stream);
+    case 1: return launch_kind<4, 9, 1>(p, blocks, N, stream);
+    case 2: return launch_kind<2, 12, 1>(p, blocks, N, stream);
+    case 3: return launch_kind<2, 6, 1>(p, blocks, N, stream);
+    default: return launch_kind<4, 4, 2>(p, blocks, N, stream);
     }
 }
 

@@ -603,6 +603,16 @@ def test_mfma_many_column_tiles_take_the_band_order(gpu, oracle_mod):
     assert_parity(got, want, TOL["mfma"])
 
 
+@pytest.mark.parametrize("B,L,n_absent", [(40, 150, 0), (37, 161, 1)])
+def test_mfma_many_tiles_shared_compute_units(gpu, oracle_mod, B, L, n_absent):
+    """Enough tiles for two 128 x 256 workgroups per compute unit (Q/K/V and FFN1): part tiles in both directions."""
+    dims = S.Dims(256, 12, 64, 256, 1e-12)
+    wl = S.small_workload(52000 + B, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
+    S.make_every_term_matter(wl, B, amp=2.0)
+    want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x)
+    assert_parity(run_gpu(gpu, wl, "mfma"), want, TOL["mfma"])
+
+
 @pytest.mark.parametrize("B,L", [(1, 64), (3, 100)])   # few-token route / working-buffer route
 def test_mfma_widest_supported_model(gpu, oracle_mod, B, L):
     """d_model 2048 (rows of 2048 features in LayerNorm, K = 2048 in the projections, 22-26 column
