@@ -13,7 +13,7 @@ namespace sti {
 
 
 // Pinned host ring through which shard tables larger than the inline limit are
-// uploaded.  A slot is reused only after the copy that read it has completed.
+// uploaded.  A slot is reused only after the kernel that read it has completed.
 class StagingRing {
 public:
     static constexpr int kSlots = 4;
@@ -45,9 +45,7 @@ public:
             s.capacity = cap;
         }
         memcpy(s.ptr, src, bytes);
-        e = hipMemcpyAsync(dst, s.ptr, bytes, hipMemcpyHostToDevice, stream);
-        if (e != hipSuccess) return e;
-        return hipEventRecord(s.event, stream);
+        return launch_fetch_table((const ShardDesc *)s.ptr, (ShardDesc *)dst, count, stream, s.event);
     }
 
 private:
@@ -399,8 +397,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             const sti_shard &s = shards[present[p]];
             t.d[p] = make_desc(s, present[p]);
         }
-        STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode(nullptr, &t, m, wsh, ws + wl.w32, STI_F32, stream); }));
-        STI_TRY(launch_patch_outliers(nullptr, &t, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream));
+        STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode(nullptr, &t, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream); }));
     }
     for (int p = 0; p < m; ++p) {
         const sti_shard &s = shards[present[p]];
@@ -704,23 +701,17 @@ sti_status sti_decode_shards(const sti_shard *shards, int n_shards, uint64_t wei
         e = staging().upload(table.data(), table.size(), workspace, stream);
         if (e != hipSuccess) return STI_ERR_HIP;
         e = timed(STI_K_DECODE, stream, [&] {
-            return launch_decode((const ShardDesc *)workspace, nullptr, n_shards, weights_per_shard,
-                                 out, out_dtype, stream);
+            return launch_decode((const ShardDesc *)workspace, nullptr, n_shards, max_outliers,
+                                 weights_per_shard, out, out_dtype, stream);
         });
-        if (e == hipSuccess)
-            e = launch_patch_outliers((const ShardDesc *)workspace, nullptr, n_shards, max_outliers,
-                                      weights_per_shard, out, out_dtype, stream);
     } else {
         InlineShardTable t;
         memset(&t, 0, sizeof(t));
         for (int s = 0; s < n_shards; ++s)
             t.d[s] = make_desc(shards[s], s);
         e = timed(STI_K_DECODE, stream, [&] {
-            return launch_decode(nullptr, &t, n_shards, weights_per_shard, out, out_dtype, stream);
+            return launch_decode(nullptr, &t, n_shards, max_outliers, weights_per_shard, out, out_dtype, stream);
         });
-        if (e == hipSuccess)
-            e = launch_patch_outliers(nullptr, &t, n_shards, max_outliers, weights_per_shard, out,
-                                      out_dtype, stream);
     }
     return e == hipSuccess ? STI_OK : STI_ERR_HIP;
 }

@@ -1,27 +1,39 @@
 // Shard decompression: k-bit dictionary indexes -> centroids (Section
 // "quantization per shard"; the substitution loop of Section "Implementation").
 //
-// HBM-bound streaming kernel.  One workgroup decodes one chunk of one shard:
-//  - the shard's codebook is rounded to the output type once and kept in LDS;
-//  - work is cut into units of 8 indexes, which occupy exactly k bytes for
-//    every k, so a unit is two aligned dword loads and a funnel shift;
-//  - consecutive lanes take consecutive units, so each store instruction of a
-//    wave writes one contiguous 1 KiB (f16/bf16) or 2 KiB (f32) span.
+// Bound by memory: 1 byte read per 2.7 to 16 bytes written.  Every wave decodes a stretch of one shard by itself:
+//  - its codes come in as 16-byte loads and pass through a piece of LDS that is the wave's own, so that a lane can
+//    pick up the codes of its outputs wherever they begin (loading them from memory lane by lane takes two 4-byte
+//    loads per lane and 8 weights);
+//  - the codebook is rounded to the output type once and kept in LDS, a copy per wave: no barrier;
+//  - a lane decodes runs of 16 output bytes that lie on 16-byte boundaries of the output, whatever a shard's
+//    length is, and consecutive lanes take consecutive runs: a store instruction writes one contiguous KiB.
+// 2 runs per lane, stored nontemporal, loads temporal (streams that the 256 MB cache holds stay there).  Measured
+// against two unaligned 4-byte nontemporal loads per 8 weights and one lane per 8 weights in every output type:
+// 12 x 589824 weights float32 12.4 -> 6.1 us, binary16 5.3 -> 4.8; 1500 x 589824 (2 to 6 bits) binary16 451 -> 346
+// (6.4 TB/s), float32 with raw shards 1530 -> 746; 60 x 300001 float32 48 -> 15.  4 runs per lane: 376 and 835 us,
+// 1 run: 527 and 1003; a workgroup's codes staged together behind one barrier: 391 for binary16.
+#include <type_traits>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
 
 namespace sti {
 namespace {
 
-// 4 units per thread and nontemporal stores measured best on the 1 GiB stream (5.2 TB/s, the
-// rate a plain kernel with the same 1 : 4.6 read : write ratio reaches on this chip).
+// pointers that come out of a shard table: without the address space they would be loaded through flat
+// instructions, whose waits also cover the LDS
+#define STI_GLOBAL __attribute__((address_space(1)))
 #define STI_STORE(v, p) __builtin_nontemporal_store((v), (p))
-constexpr int kThreads = 256;
-constexpr int kUnitsPerThread = 4;                          // units of 8 weights
-constexpr int kChunkUnits = kThreads * kUnitsPerThread;     // 1024 units = 8192 weights
+constexpr int kThreads = 512;
+// Dictionaries of outliers: up to this many workgroups and entries per shard, each workgroup looks through its
+// shard's whole list for the entries that fall into its stretch; beyond that the searching costs more than the launch
+// it saves (binary16, 885 entries in 589824 weights: 864 workgroups 7.5 -> 5.5 us, 2304 10.8 -> 9.9, 10800 41.8 ->
+// 43.7) and a kernel of its own goes over the lists.
+constexpr uint32_t kScannedOutliers = 4096, kScanningWorkgroups = 4096;
+// workgroups per launch: a grid holds fewer than 2^32 work items
+constexpr uint32_t kLaunchWorkgroups = 1u << 22;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // ---- output element traits: LUT entries are stored as raw bit patterns ----
 __device__ inline uint32_t f32_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -56,99 +68,138 @@ struct OutBF16 {
     static __device__ inline bits_t cvt(float v) { return to_bf16_bits(v); }
 };
 
-// Store 8 consecutive outputs starting at element e (16-byte aligned address).
-__device__ inline void store8(uint16_t *out, uint64_t e, const uint32_t v[8])
+template <typename Out> constexpr int kRun = 16 / (int)sizeof(typename Out::bits_t);   // weights per run
+constexpr int kItems = 2;                                                              // runs per lane
+template <typename Out> constexpr int kWaveWeights = 64 * kItems * kRun<Out>;
+template <typename Out> constexpr int kChunkWeights = kWaveWeights<Out> * (kThreads / 64);   // per workgroup
+
+template <typename Out>
+__device__ __forceinline__ void store_run(typename Out::bits_t *p, const uint32_t *v)
 {
-    u32x4 p;
-    p.x = v[0] | (v[1] << 16);
-    p.y = v[2] | (v[3] << 16);
-    p.z = v[4] | (v[5] << 16);
-    p.w = v[6] | (v[7] << 16);
-    STI_STORE(p, (u32x4 *)(out + e));
-}
-__device__ inline void store8(uint32_t *out, uint64_t e, const uint32_t v[8])
-{
-    u32x4 a = {v[0], v[1], v[2], v[3]};
-    u32x4 b = {v[4], v[5], v[6], v[7]};
-    STI_STORE(a, (u32x4 *)(out + e));
-    STI_STORE(b, (u32x4 *)(out + e + 4));
+    u32x4 q;
+    if constexpr (sizeof(typename Out::bits_t) == 4) q = u32x4{v[0], v[1], v[2], v[3]};
+    else q = u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+    STI_STORE(q, (STI_GLOBAL u32x4 *)p);
 }
 
-// 64-bit window holding the k bytes of unit u (bits beyond the stream read as 0).
-template <int K>
-__device__ inline uint64_t load_window(const uint8_t *data, uint64_t nbytes, uint64_t u)
-{
-    uint64_t b = u * (uint64_t)K;            // first byte of the unit
-    uint64_t i0 = b >> 2;                    // dword holding it
-    uint64_t ndw = nbytes >> 2;              // dwords lying fully inside the stream
-    const uint32_t *dw = (const uint32_t *)data;
-    if (i0 + 1 < ndw) {
-        uint32_t lo = __builtin_nontemporal_load(dw + i0);
-        uint32_t hi = __builtin_nontemporal_load(dw + i0 + 1);
-        uint64_t w = ((uint64_t)hi << 32) | lo;
-        return w >> ((uint32_t)(b & 3) * 8);
-    }
-    uint64_t w = 0;
-    for (int t = 0; t < K; ++t)
-        if (b + t < nbytes) w |= (uint64_t)data[b + t] << (8 * t);
-    return w;
-}
-
+// K-bit shards: first is the wave's first weight (negative where a shard's first run begins before it).
 template <int K, typename Out>
-__device__ inline void decode_packed_chunk(const uint8_t *data, uint64_t n, uint64_t unit0,
-                                           const typename Out::bits_t *lut,
-                                           typename Out::bits_t *out, bool vec_ok)
+__device__ __forceinline__ void decode_packed(const ShardDesc &sd, int64_t n, int64_t first, uint32_t *codes,
+                                              typename Out::bits_t *lut, typename Out::bits_t *out, int lane)
 {
-    const uint64_t nbytes = (n * K + 7) >> 3;
-    const uint64_t n_units = (n + 7) >> 3;
-    uint64_t w[kUnitsPerThread];
+    constexpr int RUN = kRun<Out>, ITEMS = kItems, WEIGHTS = kWaveWeights<Out>;
+    constexpr int PIECES = (WEIGHTS * K / 128 + 1 + 63) / 64;   // 16-byte pieces per lane
+    const STI_GLOBAL uint8_t *data = (const STI_GLOBAL uint8_t *)sd.data;
+    const int64_t nbytes = (n * K + 7) >> 3;
+    const int64_t begin = (first < 0 ? 0 : first * K >> 3) & ~(int64_t)15;
+    const int64_t last = first + WEIGHTS < n ? first + WEIGHTS : n;
+    const int pieces = (int)(((last * K + 7) >> 3) - begin + 15) >> 4;
+    const STI_GLOBAL u32x4 *from = (const STI_GLOBAL u32x4 *)(data + begin);
+    float centroid = 0.f;
+    if (lane < (1 << K)) centroid = ((const STI_GLOBAL float *)sd.codebook)[lane];
+    u32x4 w[PIECES];
+    if (begin + (int64_t)pieces * 16 <= nbytes) {
 #pragma unroll
-    for (int r = 0; r < kUnitsPerThread; ++r) {
-        uint64_t u = unit0 + (uint64_t)r * kThreads + threadIdx.x;
-        w[r] = (u < n_units) ? load_window<K>(data, nbytes, u) : 0;
+        for (int i = 0; i < PIECES; ++i)
+            if (i * 64 < pieces) w[i] = from[min(lane + i * 64, pieces - 1)];
+    } else {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+            const int at = min(lane + i * 64, pieces - 1);
+            w[i] = u32x4{0, 0, 0, 0};
+            if (begin + (at + 1) * 16 <= nbytes) {
+                w[i] = from[at];
+            } else {
+                // the stream ends inside the piece: its bytes one by one, all on their way at once
+                const int left = (int)(nbytes - begin) - at * 16;
+                uint32_t byte[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) byte[t] = data[begin + at * 16 + min(t, left - 1)];
+#pragma unroll
+                for (int t = 0; t < 16; ++t)
+                    if (t < left) w[i][t / 4] |= byte[t] << (8 * (t & 3));
+            }
+        }
     }
+    if (lane < (1 << K)) lut[lane] = Out::cvt(centroid);
 #pragma unroll
-    for (int r = 0; r < kUnitsPerThread; ++r) {
-        uint64_t u = unit0 + (uint64_t)r * kThreads + threadIdx.x;
-        if (u >= n_units) continue;
-        uint32_t v[8];
+    for (int i = 0; i < PIECES; ++i)
+        if (i * 64 < pieces) ((u32x4 *)codes)[min(lane + i * 64, pieces - 1)] = w[i];
+    // (a wave's LDS accesses are served in order; the fence keeps the compiler from moving reads up)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int bit0 = (int)(first * K - begin * 8);
+    auto run = [&](int item, auto two, typename Out::bits_t *o) {
+        const int bit = bit0 + item * (RUN * K);
+        const uint32_t *q = codes + (bit >> 5);
+        uint64_t x = (((uint64_t)q[1] << 32) | q[0]) >> (bit & 31);
+        if (!decltype(two)::value && (bit & 31)) x |= (uint64_t)q[2] << (64 - (bit & 31));
+        uint32_t v[RUN];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = lut[(uint32_t)(w[r] >> (j * K)) & ((1u << K) - 1u)];
-        uint64_t e = u * 8;
-        if (vec_ok && e + 8 <= n) {
-            store8(out, e, v);
+        for (int j = 0; j < RUN; ++j) v[j] = lut[(uint32_t)(x >> (j * K)) & ((1u << K) - 1u)];
+        store_run<Out>(o, v);
+    };
+    if (first >= 0 && first + WEIGHTS <= n) {
+        typename Out::bits_t *o = out + first + lane * RUN;
+        auto all = [&](auto two) {
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) run(r * 64 + lane, two, o + r * (64 * RUN));
+        };
+        // runs of up to 33 bits span two dwords wherever they begin; those of 40 and 48 bits, if the first
+        // begins with a byte and a 16-bit word
+        if (RUN * K <= 33 || (bit0 & (RUN * K > 40 ? 15 : 7)) == 0) all(std::true_type{});
+        else all(std::false_type{});
+        return;
+    }
+#pragma unroll 1
+    for (int r = 0; r < ITEMS; ++r) {
+        const int item = r * 64 + lane;
+        const int64_t e = first + item * RUN;
+        if (e >= 0 && e + RUN <= n) {
+            run(item, std::false_type{}, out + e);
         } else {
-            for (int j = 0; j < 8; ++j)
-                if (e + j < n) out[e + j] = (typename Out::bits_t)v[j];
+#pragma unroll 1
+            for (int j = 0; j < RUN; ++j) {
+                if (e + j < 0 || e + j >= n) continue;
+                const int bit = bit0 + (item * RUN + j) * K;
+                const uint64_t x = (((uint64_t)codes[(bit >> 5) + 1] << 32) | codes[bit >> 5]) >> (bit & 31);
+                out[e + j] = (typename Out::bits_t)lut[(uint32_t)x & ((1u << K) - 1u)];
+            }
         }
     }
 }
 
 template <typename Out>
-__device__ inline void decode_raw_chunk(const float *data, uint64_t n, uint64_t unit0,
-                                        typename Out::bits_t *out, bool vec_ok)
+__device__ __forceinline__ void decode_raw(const float *data, int64_t n, int64_t first, typename Out::bits_t *out, int lane)
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const uint64_t n_units = (n + 7) >> 3;
-#pragma unroll 4
-    for (int r = 0; r < kUnitsPerThread; ++r) {
-        uint64_t u = unit0 + (uint64_t)r * kThreads + threadIdx.x;
-        if (u >= n_units) continue;
-        uint64_t e = u * 8;
-        uint32_t v[8];
-        if (e + 8 <= n) {
-            f32x4 a = __builtin_nontemporal_load((const f32x4 *)(data + e));
-            f32x4 b = __builtin_nontemporal_load((const f32x4 *)(data + e + 4));
-            v[0] = Out::cvt(a.x); v[1] = Out::cvt(a.y); v[2] = Out::cvt(a.z); v[3] = Out::cvt(a.w);
-            v[4] = Out::cvt(b.x); v[5] = Out::cvt(b.y); v[6] = Out::cvt(b.z); v[7] = Out::cvt(b.w);
-            if (vec_ok) {
-                store8(out, e, v);
-                continue;
-            }
-            for (int j = 0; j < 8; ++j) out[e + j] = (typename Out::bits_t)v[j];
+    constexpr int RUN = kRun<Out>, ITEMS = kItems, WEIGHTS = kWaveWeights<Out>;
+    typedef float f32x4_v __attribute__((ext_vector_type(4)));
+    typedef STI_GLOBAL f32x4_v f32x4_any __attribute__((aligned(4)));
+    auto run = [&](int64_t e) {
+        f32x4_v x[RUN / 4];
+#pragma unroll
+        for (int h = 0; h < RUN / 4; ++h) x[h] = *((const f32x4_any *)(data + e) + h);
+        uint32_t v[RUN];
+#pragma unroll
+        for (int j = 0; j < RUN; ++j) v[j] = Out::cvt(x[j / 4][j % 4]);
+        store_run<Out>(out + e, v);
+    };
+    if (first >= 0 && first + WEIGHTS <= n) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) run(first + (r * 64 + lane) * RUN);
+        return;
+    }
+#pragma unroll 1
+    for (int r = 0; r < ITEMS; ++r) {
+        const int64_t e = first + (int64_t)(r * 64 + lane) * RUN;
+        if (e + RUN <= 0 || e >= n) continue;
+        if (e >= 0 && e + RUN <= n) {
+            run(e);
         } else {
-            for (int j = 0; j < 8; ++j)
-                if (e + j < n) out[e + j] = Out::cvt(data[e + j]);
+#pragma unroll 1
+            for (int j = 0; j < RUN; ++j)
+                if (e + j >= 0 && e + j < n) out[e + j] = (typename Out::bits_t)Out::cvt(data[e + j]);
         }
     }
 }
@@ -160,69 +211,44 @@ struct TableInline {
 
 template <typename Out, typename Table>
 __global__ __launch_bounds__(kThreads) void decode_kernel(Table table, uint64_t n,
-                                                          uint32_t chunks_per_shard,
-                                                          typename Out::bits_t *out, int vec_ok)
+                                                          uint32_t chunks_per_shard, uint32_t first_chunk,
+                                                          typename Out::bits_t *out, int patch)
 {
-    __shared__ typename Out::bits_t lut[64];
-    const uint32_t s = blockIdx.x / chunks_per_shard;
-    const uint32_t c = blockIdx.x - s * chunks_per_shard;
+    __shared__ alignas(16) uint32_t wave_codes[kThreads / 64][kWaveWeights<Out> * 6 / 32 + 12];
+    __shared__ typename Out::bits_t wave_lut[kThreads / 64][64];
+    const uint32_t block = first_chunk + blockIdx.x;
+    const uint32_t s = block / chunks_per_shard;
+    const uint32_t c = block - s * chunks_per_shard;
     const ShardDesc sd = table.get(s);
-    const int bits = sd.bits;
-    if (bits != 32) {
-        if (threadIdx.x < (1u << bits)) lut[threadIdx.x] = Out::cvt(sd.codebook[threadIdx.x]);
-        __syncthreads();
+    const uint64_t at = (uint64_t)s * n;
+    typename Out::bits_t *o = out + at;
+    // runs lie on 16-byte boundaries of the output
+    const int64_t chunk = (int64_t)c * kChunkWeights<Out> - (int64_t)(at % kRun<Out>);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t first = chunk + wave * kWaveWeights<Out>;
+    uint32_t *codes = wave_codes[wave];
+    typename Out::bits_t *lut = wave_lut[wave];
+    if (first < (int64_t)n) {
+        switch (sd.bits) {
+            case 2: decode_packed<2, Out>(sd, n, first, codes, lut, o, lane); break;
+            case 3: decode_packed<3, Out>(sd, n, first, codes, lut, o, lane); break;
+            case 4: decode_packed<4, Out>(sd, n, first, codes, lut, o, lane); break;
+            case 5: decode_packed<5, Out>(sd, n, first, codes, lut, o, lane); break;
+            case 6: decode_packed<6, Out>(sd, n, first, codes, lut, o, lane); break;
+            case 32: decode_raw<Out>((const float *)sd.data, n, first, o, lane); break;
+            default: break;
+        }
     }
-    typename Out::bits_t *o = out + (uint64_t)s * n;
-    const uint64_t unit0 = (uint64_t)c * kChunkUnits;
-    const uint8_t *data = (const uint8_t *)sd.data;
-    switch (bits) {
-        case 2: decode_packed_chunk<2, Out>(data, n, unit0, lut, o, vec_ok); break;
-        case 3: decode_packed_chunk<3, Out>(data, n, unit0, lut, o, vec_ok); break;
-        case 4: decode_packed_chunk<4, Out>(data, n, unit0, lut, o, vec_ok); break;
-        case 5: decode_packed_chunk<5, Out>(data, n, unit0, lut, o, vec_ok); break;
-        case 6: decode_packed_chunk<6, Out>(data, n, unit0, lut, o, vec_ok); break;
-        case 32: decode_raw_chunk<Out>((const float *)sd.data, n, unit0, o, vec_ok); break;
-        default: break;
+    if (sd.n_outliers == 0 || !patch) return;
+    __syncthreads();   // the workgroup's outputs are written
+    for (uint32_t t = threadIdx.x; t < sd.n_outliers; t += kThreads) {
+        const uint32_t pos = ((const STI_GLOBAL uint32_t *)sd.outlier_pos)[t];
+        const int64_t rel = (int64_t)pos - chunk;
+        if (rel >= 0 && rel < kChunkWeights<Out> && pos < n) o[pos] = Out::cvt(sd.outlier_val[t]);
     }
-}
-
-template <typename Out>
-hipError_t launch_typed(const ShardDesc *table, const InlineShardTable *inline_table, int n_shards,
-                        uint64_t n, void *out, hipStream_t stream)
-{
-    const uint64_t n_units = (n + 7) / 8;
-    const uint64_t chunks = (n_units + kChunkUnits - 1) / kChunkUnits;
-    const uint64_t blocks = chunks * (uint64_t)n_shards;
-    if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFFull || chunks > 0xFFFFFFFFull) return hipErrorInvalidValue;
-    // vector stores need every shard's output to start on a 16-byte boundary
-    const int vec_ok = (n % 8 == 0) ? 1 : 0;
-    typedef typename Out::bits_t bits_t;
-    if (table) {
-        TablePtr t{table};
-        launch((decode_kernel<Out, TablePtr>), dim3((uint32_t)blocks), dim3(kThreads), 0, stream, 
-            t, n, (uint32_t)chunks, (bits_t *)out, vec_ok);
-    } else {
-        TableInline t;
-        t.t = *inline_table;
-        launch((decode_kernel<Out, TableInline>), dim3((uint32_t)blocks), dim3(kThreads), 0, stream, 
-            t, n, (uint32_t)chunks, (bits_t *)out, vec_ok);
-    }
-    return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t launch_decode(const ShardDesc *table, const InlineShardTable *inline_table, int n_shards,
-                         uint64_t n, void *out, sti_dtype out_dtype, hipStream_t stream)
-{
-    switch (out_dtype) {
-        case STI_F32: return launch_typed<OutF32>(table, inline_table, n_shards, n, out, stream);
-        case STI_F16: return launch_typed<OutF16>(table, inline_table, n_shards, n, out, stream);
-        case STI_BF16: return launch_typed<OutBF16>(table, inline_table, n_shards, n, out, stream);
-    }
-    return hipErrorInvalidValue;
-}
 
 // ---------------------------------------------------------------------------
 // Working buffer for the matrix-core path (Section "Submodel execution": a buffer
@@ -289,6 +315,31 @@ hipError_t patch_typed(const ShardDesc *table, const InlineShardTable *inline_ta
     return hipGetLastError();
 }
 
+template <typename Out>
+hipError_t launch_typed(const ShardDesc *table, const InlineShardTable *inline_table, int n_shards,
+                        uint32_t max_outliers, uint64_t n, void *out, hipStream_t stream)
+{
+    const uint64_t reach = n + (n % kRun<Out> ? kRun<Out> - 1 : 0);   // first run of a shard may begin before it
+    const uint64_t chunks = (reach + kChunkWeights<Out> - 1) / kChunkWeights<Out>;
+    const uint64_t blocks = chunks * (uint64_t)n_shards;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull || chunks > 0xFFFFFFFFull) return hipErrorInvalidValue;
+    const bool patch = max_outliers > 0 && max_outliers <= kScannedOutliers && blocks <= kScanningWorkgroups;
+    typedef typename Out::bits_t bits_t;
+    for (uint64_t b = 0; b < blocks; b += kLaunchWorkgroups) {
+        const dim3 grid((uint32_t)(blocks - b < kLaunchWorkgroups ? blocks - b : kLaunchWorkgroups));
+        if (table)
+            launch((decode_kernel<Out, TablePtr>), grid, dim3(kThreads), 0, stream, TablePtr{table}, n, (uint32_t)chunks,
+                   (uint32_t)b, (bits_t *)out, (int)patch);
+        else
+            launch((decode_kernel<Out, TableInline>), grid, dim3(kThreads), 0, stream, TableInline{*inline_table}, n,
+                   (uint32_t)chunks, (uint32_t)b, (bits_t *)out, (int)patch);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || patch || max_outliers == 0) return e;
+    return patch_typed<Out>(table, inline_table, n_shards, max_outliers, n, out, stream);
+}
+
 // offset inside a shard -> byte offset inside its fragment-tiled image
 __device__ inline int64_t tiled_byte_offset(uint32_t pos, int d, int dh, int f)
 {
@@ -319,15 +370,32 @@ __global__ __launch_bounds__(256) void patch_outliers_tiled_kernel(InlineShardTa
 
 }  // namespace
 
-hipError_t launch_patch_outliers(const ShardDesc *table, const InlineShardTable *inline_table,
-                                 int n_shards, uint32_t max_outliers, uint64_t n, void *out,
-                                 sti_dtype out_dtype, hipStream_t stream)
+// A shard table on its way to the device: tens of KiB, so what counts is the latency.  A kernel that reads the
+// pinned slot, with the slot's event as the completion signal of that one dispatch, takes 2.3 us where a
+// copy command and a recorded event behind it took 4 us more for 100 descriptors and 20 us more for 1500.
+__global__ __launch_bounds__(256) void fetch_table_kernel(const u32x4 *from, u32x4 *to, uint32_t n)
 {
-    if (n_shards <= 0 || max_outliers == 0 || n == 0) return hipSuccess;
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
+hipError_t launch_fetch_table(const ShardDesc *pinned, ShardDesc *table, size_t count, hipStream_t stream, hipEvent_t done)
+{
+    static_assert(sizeof(ShardDesc) % 16 == 0, "descriptors travel as 16-byte pieces");
+    const uint64_t n = count * (sizeof(ShardDesc) / 16);
+    if (n == 0 || n > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipExtLaunchKernelGGL(fetch_table_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, stream, nullptr, done, 0,
+                          (const u32x4 *)pinned, (u32x4 *)table, (uint32_t)n);
+    return hipGetLastError();
+}
+
+hipError_t launch_decode(const ShardDesc *table, const InlineShardTable *inline_table, int n_shards,
+                         uint32_t max_outliers, uint64_t n, void *out, sti_dtype out_dtype, hipStream_t stream)
+{
     switch (out_dtype) {
-        case STI_F32: return patch_typed<OutF32>(table, inline_table, n_shards, max_outliers, n, out, stream);
-        case STI_F16: return patch_typed<OutF16>(table, inline_table, n_shards, max_outliers, n, out, stream);
-        case STI_BF16: return patch_typed<OutBF16>(table, inline_table, n_shards, max_outliers, n, out, stream);
+        case STI_F32: return launch_typed<OutF32>(table, inline_table, n_shards, max_outliers, n, out, stream);
+        case STI_F16: return launch_typed<OutF16>(table, inline_table, n_shards, max_outliers, n, out, stream);
+        case STI_BF16: return launch_typed<OutBF16>(table, inline_table, n_shards, max_outliers, n, out, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -27,17 +27,17 @@ struct InlineShardTable {
 };
 
 // ---- decode.hip -----------------------------------------------------------
-// Decode n_shards shards of n weights each into out[s*n + j].  `table` is a
-// device pointer to n_shards descriptors, or NULL to use `inline_table`.
+// Decode n_shards shards of n weights each into out[s*n + j] and put the bookkept outliers back:
+// out[s*n + pos] = round_to(out_dtype, val) for every entry of every shard's outlier dictionary
+// (offsets >= n are ignored).  `table` is a device pointer to n_shards descriptors, or NULL to use
+// `inline_table`; max_outliers: the largest dictionary.
 hipError_t launch_decode(const ShardDesc *table, const InlineShardTable *inline_table, int n_shards,
-                         uint64_t n, void *out, sti_dtype out_dtype, hipStream_t stream);
+                         uint32_t max_outliers, uint64_t n, void *out, sti_dtype out_dtype, hipStream_t stream);
 
-// Put the bookkept outliers back: out[s*n + pos] = round_to(out_dtype, val) for every entry of
-// every shard's outlier dictionary (offsets >= n are ignored).  Runs after launch_decode.
-hipError_t launch_patch_outliers(const ShardDesc *table, const InlineShardTable *inline_table,
-                                 int n_shards, uint32_t max_outliers, uint64_t n, void *out,
-                                 sti_dtype out_dtype, hipStream_t stream);
-// Same for the fragment-tiled binary16 working buffer written by launch_decode_tiled.
+// Copy `count` descriptors from pinned host memory to the device; `done` is recorded by the launch itself.
+hipError_t launch_fetch_table(const ShardDesc *pinned, ShardDesc *table, size_t count, hipStream_t stream, hipEvent_t done);
+
+// Put outliers back into the fragment-tiled binary16 working buffer written by launch_decode_tiled.
 hipError_t launch_patch_outliers_tiled(const InlineShardTable &table, int n_shards,
                                        uint32_t max_outliers, int d, int dh, int f, void *out,
                                        hipStream_t stream);

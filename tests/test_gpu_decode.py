@@ -122,6 +122,24 @@ def test_outlier_dictionary(gpu, oracle_mod, dtype):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "f32", "bf16"])
+@pytest.mark.parametrize("n,count", [(8192, 40), (8193, 41), (4096 * 3 - 1, 4096), (4096 * 3 + 5, 4097), (1024 * 9 + 3, 300)])
+def test_stretches_and_dictionaries_end_anywhere(gpu, oracle_mod, dtype, n, count):
+    """Shards that begin off the 16-byte boundaries of the output, dictionaries on both sides of the size up to which
+    the decoding workgroups look their entries up themselves, entries at the edges of a wave's and a workgroup's stretch."""
+    rng = np.random.default_rng(n + count)
+    edges = [e for b in (0, 512, 1024, 4096, 8192, n) for e in (b - 1, b, b + 1) if 0 <= e < n]
+    shards = []
+    for k in (5, 2, 6, 3, 4):
+        s = S.make_shard(rng, n, k)
+        pos = np.unique(np.concatenate([edges, rng.choice(n, size=count - len(set(edges)), replace=False)]))
+        while pos.size < count:
+            pos = np.unique(np.concatenate([pos, rng.integers(0, n, count - pos.size)]))
+        s.outlier_pos, s.outlier_val = pos.astype(np.uint32), rng.standard_normal(pos.size).astype(np.float32)
+        shards += [s, S.make_shard(rng, n, 32)]
+    assert np.array_equal(run_decode(gpu, shards, n, dtype), oracle_bits(oracle_mod, shards, n, dtype))
+
+
 def test_outliers_with_device_table(gpu, oracle_mod):
     n = 4096
     rng = np.random.default_rng(92)
