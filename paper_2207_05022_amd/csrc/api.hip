@@ -213,6 +213,7 @@ inline bool few_token_path(const sti_dims &d, int64_t T)
     return T <= kFewMaxTokens && d.d_model >= 256 && d.d_model <= 1024 && workgroups <= 1024;
 }
 
+constexpr uint64_t kRidingEntries = 65536;
 constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
 
 
@@ -512,6 +513,10 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.a_layout = inner;
     p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
     p.A = ctx; p.lda = m * dh; p.C = pre; p.ldc = dm; p.bias0 = prm.bo; p.resid = in; p.ldr = dm;
+    if (next && next->workgroups > 0) {
+        p.next_table = next->table; p.next_shards = next->n_shards; p.next_out = next->out;
+        p.next_outliers = next->max_outliers; p.next_ffn_per_shard = f;
+    }
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, bo));
     STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout));
@@ -952,6 +957,14 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
                                                 dims->ffn_per_shard, w16_of(l), stream));
         return STI_OK;
     };
+    // ... or, for a layer decompressed beside its predecessor's Q/K/V projection, beside the predecessor's output
+    // projection: the most entries a shard has, 0 if there are none or too many.  (kRidingEntries: no more than
+    // 256 workgroups of 256 threads and one more per shard; larger dictionaries spread over the chip by themselves.)
+    auto riding_outliers = [&](size_t a, size_t b) -> int {
+        uint32_t max_outliers = 0;
+        for (size_t e = a; e < b; ++e) max_outliers = std::max(max_outliers, table[e].n_outliers);
+        return (uint64_t)max_outliers * (b - a) <= kRidingEntries ? (int)max_outliers : 0;
+    };
     // decompress layers [l0, l1) into their working buffers and apply their outlier dictionaries
     auto decode_layers = [&](int l0, int l1) -> sti_status {
         // (the caller keeps a group inside the ring: slots l0 % w16_layers ... are consecutive)
@@ -991,7 +1004,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
     for (int l = 0; l < n_layers; ++l) {
         const bool last = (l == n_layers - 1);
         void *out = last ? y : (void *)(ws + wl.act[next_buf]);
-        NextLayerDecode next_decode = {nullptr, 0, nullptr, 0};
+        NextLayerDecode next_decode = {nullptr, 0, nullptr, 0, 0};
         if (whole_model_fits && !table.empty()) {
             const int spare_here = spare(l);
             if (l >= decoded_upto) {
@@ -1005,7 +1018,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
             }
             if (spare_here > 0 && l + 1 == decoded_upto && l + 1 < n_layers) {
                 const size_t a = first_shard[l + 1], b = last_shard(l + 1);
-                if (b > a) next_decode = {dev_table + a, (int)(b - a), w16_of(l + 1), spare_here};
+                if (b > a) next_decode = {dev_table + a, (int)(b - a), w16_of(l + 1), spare_here, riding_outliers(a, b)};
                 decoded_upto = l + 2;
             }
         }
@@ -1014,7 +1027,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
                        next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner);
         if (st != STI_OK) return st;
-        if (next_decode.workgroups > 0) {
+        if (next_decode.workgroups > 0 && next_decode.max_outliers == 0) {
             st = patch_layer(l + 1);
             if (st != STI_OK) return st;
         }

@@ -39,6 +39,7 @@ struct NextLayerDecode {
     int n_shards;
     void *out;
     int workgroups;
+    int max_outliers;   // > 0: the layer's output projection puts the outlier dictionaries in
 };
 // Workgroups such a launch has to spare for a layer of m present shards (0: the layer does not go
 // through the many-token route, or its projection fills the chip).

@@ -205,6 +205,25 @@ __device__ inline void decode_next_layer(const GemmProblem &p, int d, unsigned c
     }
 }
 
+// Workgroups of an output projection beyond those of its tiles: the outlier dictionaries of the layer that this
+// layer's Q/K/V launch has decompressed.  One entry per thread, chunks workgroups per shard: three round trips
+// (descriptor, entry, store) beside the projection, where a launch of its own is on the chain of launches.
+// 1023 tokens, 10 shards of BERT-base with about 900 entries each: 61.8 -> 58.6 us per layer.
+template <int NT>
+__device__ inline void patch_next_layer(const GemmProblem &p, int d, int dh, int worker)
+{
+    const int chunks = (p.next_outliers + NT - 1) / NT, f = p.next_ffn_per_shard;
+    const int s = worker / chunks;
+    const uint32_t t = (uint32_t)(worker - s * chunks) * NT + threadIdx.x;
+    const ShardDesc sd = p.next_table[s];
+    const int64_t wsh = (int64_t)d * (4 * dh + 2 * f);
+    if (t < sd.n_outliers) {
+        const uint32_t pos = ((const uint32_t *)(global_cptr *)sd.outlier_pos)[t];
+        const float val = ((const float *)(global_cptr *)sd.outlier_val)[t];
+        if (pos < wsh) *(uint16_t *)((uint8_t *)p.next_out + s * wsh * 2 + tiled_byte_offset(pos, d, dh, f)) = to_f16_bits(val);
+    }
+}
+
 struct ShardIds {   // original shard id of every weight block (selects the bias slice), four to a scalar-loadable dword
     uint32_t id4[kMaxShardsPerLayer / 4];
     __device__ inline int id(int block) const { return (id4[block >> 2] >> (8 * (block & 3))) & 0xFF; }
@@ -272,6 +291,13 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     if constexpr (qkv) {
         if ((int)(blockIdx.x >> 3) >= per_xcd) {   // behind the tiles' workgroups: the next layer's decompression
             if (p.next_workgroups > 0) decode_next_layer<NW * KS>(p, hot_block_cols, smem_raw, (int)blockIdx.x - 8 * per_xcd);
+            return;
+        }
+    }
+    if constexpr (KIND == GEMM_OUT) {
+        if ((int)(blockIdx.x >> 3) >= per_xcd) {   // behind the tiles' workgroups: the next layer's outlier dictionaries
+            if (p.next_outliers > 0 && blockIdx.y == 0)
+                patch_next_layer<NT>(p, hot_block_rows, hot_block_cols, (int)blockIdx.x - 8 * per_xcd);
             return;
         }
     }
@@ -694,6 +720,11 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
             (int)grid.x + p.next_workgroups > kComputeUnits)
             return hipErrorInvalidValue;
         grid.x += p.next_workgroups;
+    }
+    if (KIND == GEMM_OUT && p.next_outliers > 0) {
+        constexpr int NT = NW * KS * 64;
+        if (!p.next_table || !p.next_out || p.next_shards <= 0 || p.next_ffn_per_shard <= 0) return hipErrorInvalidValue;
+        grid.x += p.next_shards * ((p.next_outliers + NT - 1) / NT);
     }
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
     ShardIds shard_of;   // (the kernel takes these instead of the block table: a shorter argument list is a cheaper launch)

@@ -124,6 +124,9 @@ struct GemmProblem {
     const ShardDesc *next_table;
     void *next_out;
     int32_t next_shards, next_workgroups, next_ffn_per_shard;
+    // wide-tile kernel, GEMM_OUT: with next_outliers > 0 workgroups beyond those of the tiles put the outlier dictionaries
+    // of the next_shards shards of next_table (at most next_outliers entries each) into next_out
+    int32_t next_outliers;
 };
 
 // float32 path (layer_f32.hip): A and C are float32; weights are float32 blocks at a constant distance.

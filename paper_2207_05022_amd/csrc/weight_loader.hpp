@@ -20,6 +20,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLutEntries = 64;  // per block
 
+__device__ inline uint16_t to_f16_bits(float v)
+{
+    uint32_t u = __builtin_bit_cast(uint32_t, v);
+    if ((u & 0x7FFFFFFFu) > 0x7F800000u)  // NaN: keep sign and top payload bits, set quiet bit
+        return (uint16_t)(((u >> 16) & 0x8000u) | 0x7E00u | ((u & 0x7FFFFFu) >> 13));
+    _Float16 h = (_Float16)v;  // v_cvt_f16_f32: round to nearest even, subnormals kept
+    return __builtin_bit_cast(uint16_t, h);
+}
 __device__ inline uint32_t f16_bits(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
 __device__ inline float gelu_erf(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f)); }
 
@@ -134,6 +142,22 @@ constexpr int kTiledBits = 17;   // GemmBlock::bits value marking a fragment-til
 __device__ inline int64_t tiled_cell_offset(int strip, int kt, int cols)
 {
     return ((int64_t)strip * (cols >> 6) + kt) * 4096;
+}
+
+// offset inside a shard -> byte offset inside its fragment-tiled image
+__device__ inline int64_t tiled_byte_offset(uint32_t pos, int d, int dh, int f)
+{
+    const int64_t o_o = (int64_t)3 * dh * d, o_1 = (int64_t)4 * dh * d, o_2 = o_1 + (int64_t)f * d;
+    int64_t sub_off;
+    int cols;
+    if (pos < o_o) { sub_off = 0; cols = d; }
+    else if (pos < o_1) { sub_off = o_o; cols = dh; }
+    else if (pos < o_2) { sub_off = o_1; cols = d; }
+    else { sub_off = o_2; cols = f; }
+    const int64_t rel = pos - sub_off;
+    const int row = (int)(rel / cols), col = (int)(rel - (int64_t)row * cols);
+    const int lane = ((col & 63) >> 5) * 32 + (row & 31), q = (col & 31) >> 3, e = col & 7;
+    return sub_off * 2 + tiled_cell_offset(row >> 5, col >> 6, cols) + q * 1024 + lane * 16 + e * 2;
 }
 
 // Cells of the fragment-tiled binary16 working buffer (Section "Submodel execution": the working buffer a

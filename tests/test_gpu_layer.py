@@ -498,6 +498,34 @@ def test_next_layer_decompressed_beside_the_projection_with_outlier_dictionaries
         assert_parity(got[b], want[b], TOL["mfma"], b)
 
 
+@pytest.mark.parametrize("B,L,entries", [
+    (11, 93, 1),        # one entry per dictionary; K of the output projection split over workgroups
+    (11, 93, 769),      # one more than a workgroup takes
+    (9, 113, 5461),     # 12 shards: the most entries that go in beside the projection ...
+    (9, 113, 5462),     # ... and one more, by a launch of their own
+    (32, 128, 885),     # the projection's tiles fill the chip
+    (26, 61, 256),
+])
+def test_outlier_dictionaries_beside_the_output_projection(gpu, B, L, entries):
+    """The dictionaries of a layer that was decompressed beside its predecessor's Q/K/V projection: the bits of
+    the per-layer route, where a launch of their own puts them in."""
+    torch, P, D = gpu
+    dims = S.BERT_BASE
+    plan = np.full((3, 12), 3, dtype=np.int8)
+    plan[1, ::3] = 32          # shards without a dictionary among those with one
+    plan[2] = 5
+    wl = S.small_workload(700 + entries, dims, 3, B, L, plan=plan, io_dtype="f16")
+    wl = _with_outliers(wl, entries, fraction=entries / dims.weights_per_shard)
+    assert all(len(s.outlier_pos) == entries for s in wl.shards[2])
+    prec = P.STI_PREC_F16_MFMA
+    big = P.sti_model_workspace_bytes(dims, 3, B, L, prec)
+    small = P.sti_workspace_bytes(dims, B, L, prec)
+    assert big > small
+    whole = _run_model_route(gpu, wl, big)
+    assert torch.equal(whole, _run_model_route(gpu, wl, small))
+    assert torch.isfinite(whole.float()).all()
+
+
 def test_layers_that_can_and_cannot_take_the_next_layer_along(gpu, oracle_mod):
     """38 sequences: a full layer has 228 tiles and no compute unit to spare, a layer with 9 or 10 shards
     190 tiles and 64; with an all-absent layer in between.  Layers 0 to 3 are decompressed as a group,
