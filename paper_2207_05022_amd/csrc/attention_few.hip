@@ -66,6 +66,17 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
 #pragma unroll
         for (int s = 0; s < 4; ++s) v_now[s] = vf[s];
         if (kb + W < nkb) request(kb + W);
+        if (kb * 32 + 32 > Lk) {
+            // keys past the last one (padding, rows past the last token): their probabilities are zero, and their values
+            // have to be, since 0 times an infinity or NaN would reach every query.  Dword w of a fragment: two keys.
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int key = kb * 32 + (s & 1) * 16 + (w >> 1) * 8 + g * 4 + (w & 1) * 2;
+                    v_now[s][w] = key + 1 < Lk ? v_now[s][w] : key < Lk ? v_now[s][w] & 0xFFFFu : 0u;
+                }
+        }
         float bmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {

@@ -221,8 +221,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
         } else if ((rb0 + i) * 32 >= hot_T) {
             continue;                           // (a row block past the last one)
         } else if (hot_kind == GEMM_QKV && part == 2) {
-            // V transposed for the attention's second product (attention_few.hip): tokens past the end are zero
-            if (t >= hot_T) h = half4{};
+            // V transposed for the attention's second product (attention_few.hip)
             _Float16 *cell = C + ((int64_t)(rb0 + i) * (p.ldc >> 6) + (n >> 6)) * 2048;
             const int half = (n >> 5) & 1, s2 = lr >> 4, gk = (lr >> 2) & 1, pos = ((lr >> 3) & 1) * 4 + (lr & 3);
 #pragma unroll

@@ -1015,6 +1015,33 @@ def test_padded_sequences_ignore_what_the_padding_holds(gpu):
     assert torch.equal(_run_masked(gpu, wl, "mfma", wild, "model"), bb)
 
 
+@pytest.mark.parametrize("prec,dims,B,L,route", [
+    ("mfma", MID, 1, 95, "model"), ("mfma", MID, 3, 64, "model"),     # few tokens: values in tiles, one and several sequences
+    ("mfma", MID, 6, 32, "layer"), ("mfma", MID, 2, 96, "model"),
+    ("mfma", MID, 3, 50, "model"),                                    # few tokens, sequences that straddle row blocks
+    ("mfma", MID, 7, 93, "model"), ("mfma", MID, 4, 200, "whole"),    # keys staged in LDS: all of them, block by block
+    ("f32", MID, 3, 70, "model"),
+])
+def test_no_value_in_the_padding_reaches_a_real_row(gpu, prec, dims, B, L, route):
+    """Real rows have the bits they have over zero padding when the padding holds values beyond binary16's range,
+    infinities or NaN: a masked key has weight zero, and nothing multiplies that by its value."""
+    torch, P, D = gpu
+    lens = _key_lengths(L, B, 1)
+    if B == 1:
+        lens[0] = L - 20
+    for io, fills in (("f32", (1e6, float("inf"), float("nan"))), ("f16", (6e4, float("-inf")))):
+        wl = S.small_workload(8150 + L, dims, 1 if route == "layer" else 2, B, L, n_absent=1, io_dtype=io)
+        S.make_every_term_matter(wl, 4)
+        outs = []
+        for fill in (0.0,) + fills:
+            for b, n in enumerate(lens):
+                wl.x[b, n:] = fill
+            outs.append(_run_masked(gpu, wl, prec, lens, route))
+        for fill, y in zip(fills, outs[1:]):
+            for b, n in enumerate(lens):
+                assert torch.equal(y[b, :n], outs[0][b, :n]), (io, fill, b, int(n))
+
+
 def test_captured_masked_forward_follows_the_lengths_in_device_memory(gpu):
     """The key lengths are read by the kernels, not by the host: a graph captured once serves
     other lengths by rewriting the device array between replays."""
