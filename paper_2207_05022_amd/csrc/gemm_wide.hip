@@ -518,6 +518,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
         _Float16 *hb = (_Float16 *)smem_raw + (wave / 6) * ATT_HEAD_HALVES;   // this wave's head
         const int part = (wave % 6) >> 1;      // 0 Q, 1 K, 2 V (wave-uniform)
         const int ch = (wave & 1) * 32;        // first feature of the wave's 32 columns
+        int Lk = ATT_L;                        // keys that take part
+        if (p.key_lengths) Lk = min(max(p.key_lengths[tile_m], 1), ATT_L);
 #pragma unroll
         for (int i = 0; i < RA; ++i) {
             const int row = i * 32 + lr;
@@ -537,6 +539,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
                 if (part < 2) {
                     *(half8 *)(hb + part * (ATT_L * ATT_KPAD) + row * ATT_KPAD + c) = o;
                 } else {
+                    // (a masked key has weight zero, but 0 times an infinity or NaN in its value would not be)
+                    if (row >= Lk) o = half8{};
                     _Float16 *vt = hb + 2 * (ATT_L * ATT_KPAD);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) vt[(c + e) * ATT_VTS + row] = o[e];
@@ -549,8 +553,6 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
         if (wave >= 8 || head >= hot_n_blocks) return;
         hb = (_Float16 *)smem_raw + (wave >> 2) * ATT_HEAD_HALVES;
         const _Float16 *Qs = hb, *Ks = hb + ATT_L * ATT_KPAD, *Vt = hb + 2 * (ATT_L * ATT_KPAD);
-        int Lk = ATT_L;
-        if (p.key_lengths) Lk = min(max(p.key_lengths[tile_m], 1), ATT_L);
         const int qrow = (wave & 3) * 32 + lr;
         half8 qf[4];
 #pragma unroll

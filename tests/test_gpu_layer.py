@@ -1020,6 +1020,7 @@ def test_padded_sequences_ignore_what_the_padding_holds(gpu):
     ("mfma", MID, 6, 32, "layer"), ("mfma", MID, 2, 96, "model"),
     ("mfma", MID, 3, 50, "model"),                                    # few tokens, sequences that straddle row blocks
     ("mfma", MID, 7, 93, "model"), ("mfma", MID, 4, 200, "whole"),    # keys staged in LDS: all of them, block by block
+    ("mfma", MID, 64, 128, "model"),                                  # attention inside the Q/K/V projection
     ("f32", MID, 3, 70, "model"),
 ])
 def test_no_value_in_the_padding_reaches_a_real_row(gpu, prec, dims, B, L, route):
