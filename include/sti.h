@@ -190,10 +190,11 @@ sti_status sti_layer_forward(const sti_dims *dims, const sti_shard *shards,
  *
  * The array holds sti_static_scratch_bytes() = 64 MiB on every GPU the library runs on,
  * from the first use of the library on that GPU until the process ends.  A call whose
- * sti_workspace_bytes(dims, batch, seq, precision) exceeds it returns STI_ERR_WORKSPACE
- * before anything is enqueued (BERT-base dimensions fit 20 x 128 tokens with
+ * sti_workspace_bytes(dims, batch, seq, precision) is at most that fits, and so do some that would
+ * have more, whose buffers then lie more closely; any other call returns STI_ERR_WORKSPACE
+ * before anything is enqueued (BERT-base dimensions fit 24 x 128 tokens with
  * STI_PREC_F16_MFMA and 8 x 128 with STI_PREC_F32; d_model 1024 with 16 shards fits
- * 12 x 128 and 2 x 128).  All calls on one GPU share the one array:
+ * 14 x 128 and 2 x 128).  All calls on one GPU share the one array:
  * calls whose kernels may overlap on that GPU (different streams, or several host
  * threads) race; calls on one stream are ordered and safe.  The array keeps the last
  * call's contents; no kernel of the layer reads scratch memory it has not written in

@@ -213,14 +213,21 @@ inline bool few_token_path(const sti_dims &d, int64_t T)
     return T <= kFewMaxTokens && d.d_model >= 256 && d.d_model <= 1024 && workgroups <= 1024;
 }
 
+// Layers of few tokens keep their activations tiled.
+inline ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec)
+{
+    return prec == STI_PREC_F16_MFMA && few_token_path(d, T) ? LAYOUT_TILED : LAYOUT_ROWS;
+}
+
 constexpr uint64_t kRidingEntries = 65536;
 constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
 
 
 // Offsets of the scratch regions of one layer call (sized for all M shards present).
-WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers)
+WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers, bool compact)
 {
     WorkspaceLayout L;
+    L.inner = compact ? LAYOUT_ROWS : inner_layout(d, T, prec);
     const size_t es = (prec == STI_PREC_F32) ? 4 : 2;
     const size_t M = d.n_heads, dm = d.d_model, dh = d.d_head, f = d.ffn_per_shard;
     if (prec != STI_PREC_F32 && model_layers > 1) {
@@ -245,24 +252,37 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     if (prec == STI_PREC_F32) L.w32 = take(M * dm * (4 * dh + 2 * f) * 4);
     else L.w16 = take((size_t)L.w16_layers * M * dm * (4 * dh + 2 * f) * 2);
     // (tiled activations: whole blocks of 32 rows)
-    const size_t Tb = inner_layout(d, T, prec) == LAYOUT_TILED ? ((size_t)T + 31) / 32 * 32 : (size_t)T;
+    const size_t Tb = L.inner == LAYOUT_TILED ? ((size_t)T + 31) / 32 * 32 : (size_t)T;
     L.act[0] = take(Tb * dm * es);
     L.act[1] = take(Tb * dm * es);
-    L.qkv = take(Tb * M * 3 * dh * es);
-    L.ctx = take(Tb * M * dh * es);
-    {   // float32 sums before LayerNorm; the few-token GEMM may leave several partial sums
-        size_t rows = (size_t)T;
-        if (prec != STI_PREC_F32 && few_token_path(d, T)) {
+    // float32 sums before LayerNorm, several partial sums per row where the GEMM splits K
+    const size_t plane = (size_t)T * dm * 4;
+    size_t out_planes = 1, down_planes = 1;
+    if (prec != STI_PREC_F32) {
+        out_planes = down_planes = gemm_wide_max_k_splits(T, (int)dm);
+        if (few_token_path(d, T)) {
             GemmProblem p;
             memset(&p, 0, sizeof(p));
-            p.kind = GEMM_FFN_DOWN; p.n_blocks = d.n_heads; p.block_cols = f > dh ? f : dh;   // (FFN2's splits, or O's)
-            rows *= few_k_splits(p);
+            p.n_blocks = d.n_heads;
+            p.kind = GEMM_OUT; p.block_cols = d.d_head;
+            out_planes = few_k_splits(p);
+            p.kind = GEMM_FFN_DOWN; p.block_cols = d.ffn_per_shard;
+            down_planes = few_k_splits(p);
         }
-        if (prec != STI_PREC_F32) {   // ... and so may the wide-tile GEMM when it has few tiles
-            const size_t wide_rows = (size_t)T * gemm_wide_max_k_splits(T, (int)dm);
-            if (wide_rows > rows) rows = wide_rows;
-        }
-        L.pre = take(rows * dm * 4);
+    }
+    if (!compact) {
+        L.qkv = take(Tb * M * 3 * dh * es);
+        L.ctx = take(Tb * M * dh * es);
+        L.pre_out = L.pre_down = take(plane * std::max(out_planes, down_planes));
+    } else {
+        // those of the O product over Q/K/V, which is read by then, those of FFN2 over context and Q/K/V (measured
+        // slower where there is room for buffers of their own: 24 layers of d_model 1024, 256 tokens 1163 -> 1206 us)
+        L.ctx = take(Tb * M * dh * es);
+        L.qkv = take(Tb * M * 3 * dh * es);
+        L.pre_out = L.qkv;
+        L.pre_down = L.ctx;
+        const size_t end = std::max(L.pre_out + plane * out_planes, L.pre_down + plane * down_planes);
+        if (end > off) off = align_up(end, 256);
     }
     L.h = take(Tb * dm * es);
     L.u = take(Tb * M * f * es);
@@ -317,11 +337,6 @@ inline const void *block_start(const sti_shard &s, size_t elem_off)
     return (const uint8_t *)s.data + elem_off * (size_t)s.bitwidth / 8;
 }
 
-ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec)
-{
-    return prec == STI_PREC_F16_MFMA && few_token_path(d, T) ? LAYOUT_TILED : LAYOUT_ROWS;
-}
-
 sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
                     const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer)
 {
@@ -331,7 +346,7 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
     *in_buffer = io_dtype != act;
     if (io_dtype == act) return STI_OK;
     *in = ws + wl.act[0];
-    *in_layout = inner_layout(d, T, prec);
+    *in_layout = wl.inner;
     STI_TRY(timed(STI_K_CONVERT, stream, [&] {
         return *in_layout == LAYOUT_TILED ? launch_tile_rows(x, io_dtype, ws + wl.act[0], (int)T, d.d_model, stream)
                                           : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
@@ -422,7 +437,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         }
     }
     void *qkv = ws + wl.qkv, *ctx = ws + wl.ctx, *h = ws + wl.h, *u = ws + wl.u;
-    float *pre = (float *)(ws + wl.pre);
+    float *pre = (float *)(ws + wl.pre_out);
     const sti_dtype act_dtype = f32 ? STI_F32 : STI_F16;
     // (a layer with every shard absent has nothing to multiply: its two LayerNorms run alone, over
     //  bias + residual, like those behind the few-token kernels)
@@ -435,7 +450,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     int f32_planes = 1;
     auto f32_sums = [&](size_t end) {
         f32_planes = (int)std::min<size_t>(kF32MaxSplits, (end - wl.qkv) / ((size_t)partial_stride * 4));
-        pre = (float *)(ws + (f32_planes >= 1 ? wl.qkv : wl.pre));
+        pre = (float *)(ws + (f32_planes >= 1 ? wl.qkv : wl.pre_out));
         if (f32_planes < 1) f32_planes = 1;
     };
     auto gemm = [&](const GemmProblem &p, const GemmBlocks &blk) {
@@ -476,7 +491,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     };
 
     // few tokens: activations inside the layer are tiled, Q/K/V too where the few-token attention takes them
-    const ActLayout inner = inner_layout(d, T, prec);
+    const ActLayout inner = wl.inner;
     const bool few_attention = inner == LAYOUT_TILED && attention_few_supported(B, Lseq);
     GemmProblem p;
     if (m > 0) {
@@ -529,6 +544,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     }
     memset(&p, 0, sizeof(p));
     if (f32) f32_sums(wl.h);
+    else pre = (float *)(ws + wl.pre_down);
     p.a_layout = inner;
     p.kind = GEMM_FFN_DOWN; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = f;
     p.d_head = dh; p.A = u; p.lda = m * f; p.C = pre; p.ldc = dm; p.bias0 = prm.b2; p.resid = h;
@@ -592,11 +608,20 @@ hipError_t static_scratch(uint8_t **out)
     return hipSuccess;
 }
 
+// The usual buffers if they fit `bytes`, else as few bytes as the layer can do with.
+WorkspaceLayout fitting_layout(const sti_dims &d, int64_t T, sti_precision prec, size_t bytes)
+{
+    const WorkspaceLayout wl = workspace_layout(d, T, prec);
+    return wl.total <= bytes || prec == STI_PREC_F32 ? wl : workspace_layout(d, T, prec, 1, true);
+}
+
 // masked: the call came through a *_masked entry point and key_lengths must be usable
+// fixed_workspace: the caller has this much and cannot ask for more
 sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
                          const sti_layer_params *params, const void *x, void *y,
                          sti_dtype io_dtype, int batch, int seq, bool masked, const int32_t *key_lengths,
-                         sti_precision precision, void *workspace, size_t workspace_bytes, void *hip_stream)
+                         sti_precision precision, void *workspace, size_t workspace_bytes, void *hip_stream,
+                         bool fixed_workspace = false)
 {
     sti_status st = check_dims(dims, batch, seq, precision);
     if (st != STI_OK) return st;
@@ -614,7 +639,8 @@ sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
         st = check_layer_shard(shards[i]);
         if (st != STI_OK) return st;
     }
-    const WorkspaceLayout wl = workspace_layout(*dims, T, precision);
+    const WorkspaceLayout wl = fixed_workspace ? fitting_layout(*dims, T, precision, workspace_bytes)
+                                               : workspace_layout(*dims, T, precision);
     if (!workspace || workspace_bytes < wl.total) return STI_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return STI_ERR_ALIGN;
     if (T == 0) return STI_OK;
@@ -800,12 +826,12 @@ sti_status sti_layer_forward_static(const sti_dims *dims, const sti_shard *shard
     // everything that can be refused is refused before the scratch array is looked at
     sti_status st = check_dims(dims, batch, seq, precision);
     if (st != STI_OK) return st;
-    const size_t need = workspace_layout(*dims, (int64_t)batch * seq, precision).total;
-    if (need > kStaticScratchBytes) return STI_ERR_WORKSPACE;
+    if (fitting_layout(*dims, (int64_t)batch * seq, precision, kStaticScratchBytes).total > kStaticScratchBytes)
+        return STI_ERR_WORKSPACE;
     uint8_t *scratch_ptr = nullptr;
     if (static_scratch(&scratch_ptr) != hipSuccess) return STI_ERR_HIP;
     return layer_forward(dims, shards, params, x, y, io_dtype, batch, seq, false, nullptr, precision,
-                         scratch_ptr, kStaticScratchBytes, hip_stream);
+                         scratch_ptr, kStaticScratchBytes, hip_stream, true);
 }
 
 size_t sti_static_scratch_bytes(void) { return kStaticScratchBytes; }
@@ -993,7 +1019,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         return spare_decode_workgroups(*dims, batch, seq, (int)(last_shard(l) - first_shard[l]), precision);
     };
     const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
-    const ActLayout inner = inner_layout(*dims, T, precision);
+    const ActLayout inner = wl.inner;
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;

@@ -15,14 +15,17 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Offsets of the scratch regions of one layer call inside the caller's workspace.
 struct WorkspaceLayout {
-    size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, pre = 0, h = 0, u = 0, table = 0, total = 0;
+    size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
+    size_t pre_out = 0, pre_down = 0;   // sums before LayerNorm of the O and of the FFN2 product (compact: over other buffers)
+    ActLayout inner = LAYOUT_ROWS;      // how the layers of the call hand activations on
     int w16_layers = 1;   // layers the binary16 working buffer holds at once (a ring: layer l in slot l % w16_layers)
     int decode_group = 1; // layers that one decompression launch of sti_model_forward takes (<= w16_layers)
 };
 // model_layers > 1 (sti_model_forward with room for it): a ring of binary16 working buffers - as many
 // layers as one decompression launch takes (64 MiB worth), at least two, so that a layer can be
 // decompressed while the one before it computes - and the device copy of the whole model's shard table.
-WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers = 1);
+// compact (binary16 only): activations row by row without padding, sums before LayerNorm over buffers that are read by then.
+WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers = 1, bool compact = false);
 
 sti_status check_dims(const sti_dims *dims, int batch, int seq, sti_precision prec);
 sti_status check_decode_shard(const sti_shard &s);   // bitwidth 2..6 or 32, pointers, alignment
@@ -51,8 +54,6 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const void *predecoded = nullptr, const int32_t *key_lengths = nullptr,
                      const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
                      ActLayout out_layout = LAYOUT_ROWS);
-// Layers of few tokens keep their activations tiled between them: how a call's layers hand activations on.
-ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec);
 // The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
 // otherwise converted into the first activation buffer (in_buffer: whether it is there).
 sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
@@ -61,7 +62,7 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
 // (outliers applied); run_layer then decompresses nothing.
 // `key_lengths` (device, [B]): real positions per padded sequence; null = every position is real.
 // `next` (only with `predecoded`, and only when spare_decode_workgroups says so for this layer).
-// Layouts of `in` and `out`: tiled only where inner_layout() says so.
+// Layouts of `in` and `out`: tiled only where wl.inner is.
 sti_status check_key_lengths(const int32_t *key_lengths);   // non-null, 4-byte aligned
 
 }  // namespace sti

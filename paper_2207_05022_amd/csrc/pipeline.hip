@@ -290,7 +290,7 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
     if (pl->has_last) STI_TRY(hipStreamWaitEvent(pl->copy_stream, pl->last_done, 0));
 
     const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
-    const ActLayout inner = inner_layout(*dims, T, precision);
+    const ActLayout inner = wl.inner;
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;

@@ -125,6 +125,18 @@ def test_workspace_query(P):
     assert P.sti_workspace_bytes(Dims(d=100, dh=10, f=7), 2, 9, P.STI_PREC_F32) > 0
 
 
+@pytest.mark.parametrize("d,M,f,B,L", [(896, 48, 256, 1, 1), (1024, 48, 64, 2, 320), (960, 24, 512, 1, 100), (64, 48, 4096, 1, 33)])
+def test_fixed_workspace_takes_layers_near_its_size(P, d, M, f, B, L):
+    """Layers whose buffers, at their exact number of tokens, come to nearly the 64 MiB of
+    sti_layer_forward_static are not refused for their size: the call goes on to the next check (no shards)
+    or, without a GPU, to the array's address."""
+    dims = P.binding.make_dims(Dims(d=d, M=M, f=f))
+    status = P.lib.sti_layer_forward_static(C.byref(dims), None, None, None, None, 0, B, L, P.STI_PREC_F16_MFMA, None)
+    assert status in (1, 8)
+    too_long = P.lib.sti_layer_forward_static(C.byref(dims), None, None, None, None, 0, 32, 512, P.STI_PREC_F16_MFMA, None)
+    assert too_long == 6
+
+
 def layer(P, dims=None, shards=None, params="ok", x=FAKE, y=FAKE + 0x100000, io=0, batch=1, seq=8,
           prec=0, ws=FAKE + 0x200000, ws_bytes=1 << 40):
     d = P.binding.make_dims(dims or Dims(d=64, M=2, dh=64, f=64))

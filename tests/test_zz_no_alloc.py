@@ -70,6 +70,22 @@ def test_two_calls_in_a_row_the_second_smaller(gpu, oracle_mod, prec):
         assert_parity(y_static.float().cpu().numpy(), want, TOL[prec])
 
 
+@pytest.mark.parametrize("d,M,f,B,L,outliers", [(896, 48, 256, 1, 1, True), (64, 48, 4096, 1, 33, False), (1024, 48, 64, 2, 320, True)])
+def test_layers_that_fit_only_row_by_row(gpu, oracle_mod, d, M, f, B, L, outliers):
+    """Few-token layers that nearly fill the array keep their activations row by row (the kernels' other layout)."""
+    torch, P, D = gpu
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    wl = S.small_workload(53, dims, 1, B, L, n_absent=1, io_dtype="f16")
+    if outliers:
+        rng = np.random.default_rng(9)
+        for s in wl.shards[0]:
+            if s is not None and s.bitwidth != 32:
+                S.add_outliers(rng, s, dims.weights_per_shard, 0.002)
+    y_static, _ = _call_both(gpu, wl, 1)
+    want = oracle_mod.layer_forward(dims, wl.shards[0], wl.params[0], wl.x)
+    assert_parity(y_static.float().cpu().numpy(), want, TOL[1])
+
+
 def test_sizes_beyond_the_array_are_refused_and_nothing_is_written(gpu):
     torch, P, D = gpu
     assert P.lib.sti_static_scratch_bytes() == 64 << 20
