@@ -172,7 +172,9 @@ sti_status sti_decode_shards(const sti_shard *shards, int n_shards, uint64_t wei
  *  x, y     DEVICE [batch][seq][d_model] of io_dtype, 16-byte aligned, not aliased.
  *  workspace DEVICE, >= sti_workspace_bytes(dims, batch, seq, precision), 256-byte aligned.
  *
- * sti_workspace_bytes returns 0 for invalid arguments.
+ * sti_workspace_bytes returns 0 for invalid arguments.  With the other arguments equal it does not
+ * shrink as batch * seq grows, and neither does sti_model_workspace_bytes: a workspace sized for the
+ * largest call serves the smaller ones.
  * ------------------------------------------------------------------------- */
 size_t sti_workspace_bytes(const sti_dims *dims, int batch, int seq, sti_precision precision);
 

@@ -206,12 +206,14 @@ sti_status check_decode_shard(const sti_shard &s)
 // shards of 128 neurons 1024 41 / 45, 1536 48 / 48; 256 x 4 of 64 1024 32 / 36.  In workgroups of the FFN1 product (32
 // columns x 64 tokens) the lines lie at about 1024.  Outside d_model 256 .. 1024 the line is the older
 // one, 128 tokens, or 192 when d_model <= 768.
-inline bool few_token_path(const sti_dims &d, int64_t T)
+inline int64_t few_token_limit(const sti_dims &d)
 {
-    if (T <= 128 || (T <= 192 && d.d_model <= 768)) return true;
-    const int64_t workgroups = (T + 63) / 64 * d.n_heads * (d.ffn_per_shard / 32);
-    return T <= kFewMaxTokens && d.d_model >= 256 && d.d_model <= 1024 && workgroups <= 1024;
+    const int64_t small = d.d_model <= 768 ? 192 : 128;
+    if (d.d_model < 256 || d.d_model > 1024) return small;
+    const int64_t row_blocks = 1024 / ((int64_t)d.n_heads * (d.ffn_per_shard / 32));
+    return std::max(small, std::min<int64_t>(kFewMaxTokens, row_blocks * 64));
 }
+inline bool few_token_path(const sti_dims &d, int64_t T) { return T <= few_token_limit(d); }
 
 // Layers of few tokens keep their activations tiled.
 inline ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec)
@@ -289,6 +291,22 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     if (L.w16_layers > 1) L.table = take((size_t)model_layers * M * sizeof(ShardDesc));
     L.total = off;
     return L;
+}
+
+// What a caller has to provide for up to T tokens: a smaller call can need more than a larger one where
+// the larger one takes another route or fewer partial sums, so the numbers of tokens at which that happens
+// are looked at, too.
+size_t workspace_query(const sti_dims &d, int64_t T, sti_precision prec, int n_layers)
+{
+    auto bytes = [&](int64_t t) {
+        const bool whole_model = prec == STI_PREC_F16_MFMA && !few_token_path(d, t) && n_layers > 1;
+        return workspace_layout(d, t, prec, whole_model ? n_layers : 1).total;
+    };
+    size_t most = bytes(T);
+    if (prec == STI_PREC_F16_MFMA)
+        for (int64_t t : {few_token_limit(d), gemm_wide_most_tokens(4, d.d_model), gemm_wide_most_tokens(2, d.d_model)})
+            if (t < T) most = std::max(most, bytes(t));
+    return most ? most : 256;
 }
 
 sti_status check_dims(const sti_dims *dims, int batch, int seq, sti_precision prec)
@@ -805,8 +823,7 @@ sti_status sti_decode_working_buffer(const sti_dims *dims, const sti_shard *shar
 size_t sti_workspace_bytes(const sti_dims *dims, int batch, int seq, sti_precision precision)
 {
     if (check_dims(dims, batch, seq, precision) != STI_OK) return 0;
-    size_t t = workspace_layout(*dims, (int64_t)batch * seq, precision).total;
-    return t ? t : 256;
+    return workspace_query(*dims, (int64_t)batch * seq, precision, 1);
 }
 
 sti_status sti_layer_forward(const sti_dims *dims, const sti_shard *shards,
@@ -1071,9 +1088,7 @@ extern "C" {
 size_t sti_model_workspace_bytes(const sti_dims *dims, int n_layers, int batch, int seq, sti_precision precision)
 {
     if (check_dims(dims, batch, seq, precision) != STI_OK || n_layers < 0) return 0;
-    const int64_t T = (int64_t)batch * seq;
-    const bool whole_model = precision == STI_PREC_F16_MFMA && !few_token_path(*dims, T) && n_layers > 1;
-    return workspace_layout(*dims, T, precision, whole_model ? n_layers : 1).total;
+    return workspace_query(*dims, (int64_t)batch * seq, precision, n_layers);
 }
 
 sti_status sti_profile_begin(void)

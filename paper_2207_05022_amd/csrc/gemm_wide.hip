@@ -847,10 +847,14 @@ int gemm_wide_k_splits(const GemmProblem &p)
 
 int gemm_wide_max_k_splits(int64_t T, int N)
 {
-    const int64_t tiles = ((T + 63) / 64) * ((N + 191) / 192);
     for (int s = 4; s >= 2; s >>= 1)
-        if (tiles * s <= kComputeUnits / 2) return s;
+        if (T <= gemm_wide_most_tokens(s, N)) return s;
     return 1;
+}
+
+int64_t gemm_wide_most_tokens(int splits, int N)   // (64 x 192 tiles)
+{
+    return (int64_t)64 * (kComputeUnits / 2 / splits / ((N + 191) / 192));
 }
 
 // The fused form pays once its 128 x 384 tiles (one per sequence and pair of heads) fill at least

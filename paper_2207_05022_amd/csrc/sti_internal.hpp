@@ -156,6 +156,8 @@ int gemm_wide_spare_workgroups(const GemmProblem &p);
 // largest value it can return for T tokens and N output columns (workspace sizing)
 int gemm_wide_k_splits(const GemmProblem &p);
 int gemm_wide_max_k_splits(int64_t T, int N);
+// the most tokens for which it can be `splits` (2 or 4)
+int64_t gemm_wide_most_tokens(int splits, int N);
 // ctx_layout: how the context is left behind (the Q/K/V matrix is row-major)
 hipError_t launch_attention_mfma(const void *qkv, void *ctx, ActLayout ctx_layout, int B, int L, int m, int dh,
                                  const int32_t *key_lengths, hipStream_t stream);

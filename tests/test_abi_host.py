@@ -125,6 +125,18 @@ def test_workspace_query(P):
     assert P.sti_workspace_bytes(Dims(d=100, dh=10, f=7), 2, 9, P.STI_PREC_F32) > 0
 
 
+@pytest.mark.parametrize("d,M,f", [(768, 12, 256), (1024, 16, 256), (512, 8, 128), (256, 4, 64), (2048, 32, 256), (64, 1, 64)])
+def test_workspace_of_a_larger_call_serves_the_smaller_ones(P, d, M, f):
+    """Neither query shrinks with the number of tokens, across the lines between the routes and between numbers of K splits."""
+    dims = Dims(d=d, M=M, f=f)
+    for prec in (P.STI_PREC_F16_MFMA, P.STI_PREC_F32):
+        layer = [P.sti_workspace_bytes(dims, n, 1, prec) for n in range(4200)]
+        model = [P.sti_model_workspace_bytes(dims, 12, n, 1, prec) for n in range(4200)]
+        assert all(a <= b for a, b in zip(layer, layer[1:]))
+        assert all(a <= b for a, b in zip(model, model[1:]))
+        assert all(a <= b for a, b in zip(layer, model))
+
+
 @pytest.mark.parametrize("d,M,f,B,L", [(896, 48, 256, 1, 1), (1024, 48, 64, 2, 320), (960, 24, 512, 1, 100), (64, 48, 4096, 1, 33)])
 def test_fixed_workspace_takes_layers_near_its_size(P, d, M, f, B, L):
     """Layers whose buffers, at their exact number of tokens, come to nearly the 64 MiB of
