@@ -13,7 +13,10 @@
 //   dictionaries and sums per cluster -> (centroids).
 // The steps in brackets are small kernels in between.  Every result is independent of the order in
 // which workgroups and lanes run: counts are integers, the moments are added in a fixed order in float64, and the
-// sums of a workgroup are 64-bit integers (weights scaled by a power of two).
+// sums of a workgroup are 64-bit integers (weights scaled by a power of two) that hold every weight exactly.
+//
+// Infinite and NaN weights (the moments are NaN then, so that nothing is an outlier) take the general ways through
+// the same kernels: one bin for all weights, clusters by comparison of keys, sums beside the integers.
 //
 // What bounds it: 28 MB read four times (one BERT-base layer; the last three out of the memory-side
 // cache) and eight dependent launches.  BERT-base at 4 bits: 54 us, against 149 us of the version with
@@ -40,7 +43,8 @@ struct QuantState {
     double mu, var;
     float xlo, xhi;                 // inliers are the weights in [xlo, xhi]
     float bin_scale, bin_shift;     // bin of x: (int)(x * scale + shift), clamped to 0 .. kBins - 1
-    double sum_scale;               // power of two: |inlier| * sum_scale <= 2^46
+    int sum_exp;                    // |inlier| < 2^sum_exp
+    uint32_t non_finite;            // some weight is infinite or NaN
     unsigned long long n_inliers;
     uint32_t error;                 // 1: no inliers
     uint32_t n_slots;               // bins that hold a boundary
@@ -151,9 +155,14 @@ __global__ __launch_bounds__(256) void moments_kernel(const float *w, uint64_t n
 
 // What every workgroup of the histogram pass works out for itself from the partial moments (all get the same).
 struct Fit {
-    double mu, var, sum_scale;
+    double mu, var;
     float xlo, xhi, bin_scale, bin_shift;
+    int sum_exp;
+    uint32_t non_finite;
 };
+
+// (NaN weights, whose Gaussian has a NaN mean and no bounds, are inliers)
+__device__ inline bool is_inlier(float x, float xlo, float xhi) { return !(x < xlo || x > xhi); }
 
 __device__ inline Fit fit_gaussian(double ts, double tss, float largest, uint64_t n, double threshold, double reg_covar)
 {
@@ -181,15 +190,16 @@ __device__ inline Fit fit_gaussian(double ts, double tss, float largest, uint64_
         if (outlier(f.xhi) || outlier(f.xlo)) { f.xlo = INFINITY; f.xhi = -INFINITY; }   // (no float lies inside)
     }
     const float lo = fmaxf(f.xlo, -largest), hi = fminf(f.xhi, largest);
-    f.bin_scale = 0.0f;
+    f.bin_scale = 0.0f;   // (every weight in bin 0)
     f.bin_shift = 0.0f;
-    if (hi > lo) {
+    f.non_finite = !(fabs(ts) < INFINITY);
+    if (hi > lo && !f.non_finite) {
         const float scale = (float)kBins / (hi - lo);
         if (scale < 1.0e30f && fabsf(lo * scale) < 1.0e30f) { f.bin_scale = scale; f.bin_shift = -lo * scale; }
     }
     int e = 0;
     (void)frexp((double)fmaxf(fabsf(lo), fabsf(hi)), &e);      // largest inlier magnitude < 2^e
-    f.sum_scale = (hi >= lo) ? ldexp(1.0, min(46 - e, 1000)) : 1.0;
+    f.sum_exp = f.non_finite ? 128 : hi >= lo ? e : 0;
     return f;
 }
 
@@ -229,7 +239,8 @@ __global__ __launch_bounds__(kThreads) void histogram_kernel(const float *w, uin
         fit = fit_gaussian(ts, tq, (float)tm, n, threshold, reg_covar);
         if (blockIdx.x == 0) {
             st->mu = fit.mu; st->var = fit.var; st->xlo = fit.xlo; st->xhi = fit.xhi;
-            st->bin_scale = fit.bin_scale; st->bin_shift = fit.bin_shift; st->sum_scale = fit.sum_scale;
+            st->bin_scale = fit.bin_scale; st->bin_shift = fit.bin_shift;
+            st->sum_exp = fit.sum_exp; st->non_finite = fit.non_finite;
         }
     }
     __syncthreads();
@@ -245,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void histogram_kernel(const float *w, uin
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float x = v[h][e];
-                const bool in = x >= xlo && x <= xhi;
+                const bool in = is_inlier(x, xlo, xhi);
                 outliers += __popcll(__ballot(!in));
                 atomicAdd(&hist[in ? bin_of(x, scale, shift) : kBins], 1u);
             }
@@ -448,7 +459,7 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
     if (tid == 0) { n_found = 0; table[kBins] = 0; }
     __syncthreads();
     auto slot_of = [&](float x) -> uint32_t {   // slot + 1, or 0
-        return (table[(x >= xlo && x <= xhi) ? bin_of(x, scale, shift) : kBins] & ~kSeveral) >> 8;
+        return (table[is_inlier(x, xlo, xhi) ? bin_of(x, scale, shift) : kBins] & ~kSeveral) >> 8;
     };
     while (u < n_units) {
         const f32x4 v[2] = {next[0], next[1]};
@@ -573,8 +584,14 @@ __global__ __launch_bounds__(1024) void boundary_values_kernel(QuantState *st, c
 // Cluster of every weight -> packed streams and outlier dictionaries (in offset order), and the
 // sum of every cluster's inliers in this workgroup.  A wave takes 512 weights, 8 per lane = k bytes.
 // The cluster is looked up by bin and settled by one comparison with the next boundary value (more where a
-// bin holds several); nothing in the common path branches.  Sums: 64-bit integers (weight * power of two, at least 46 bits below the largest) in LDS, 32
-// copies by lane so that the atomics of one instruction never meet.
+// bin holds several); nothing in the common path branches.
+// Sums: 64-bit integers in LDS, weight * 2^(46 - sum_exp), 32 copies by lane so that the atomics of one instruction never
+// meet.  A weight down to 2^(sum_exp - 22) is an integer at that scale; the rare smaller ones go to further sums whose
+// scales are 22 powers of two apart, so that every weight is held exactly (a float32 has 24 bits, a sum of a workgroup's
+// 57344 weights below 2^46 fits 62).
+constexpr int kSumBits = 46, kSumStep = 22;
+constexpr int kSumScales = (128 + 149 + kSumStep - 1) / kSumStep;   // from 2^128 down to the last subnormal, 2^-149
+
 template <int K>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t n, const QuantState *st, const uint16_t *table_in,
                                                         const uint32_t *unit_off, uint32_t units_per_shard, uint8_t *packed,
@@ -585,7 +602,10 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t
     constexpr int COPIES = 32;
     __shared__ uint16_t table[kBins];
     __shared__ unsigned long long sums[C][COPIES];
-    __shared__ float edges[kMaxClusters];            // boundary values; infinity behind the last
+    __shared__ unsigned long long small_sums[C][kSumScales];
+    __shared__ float non_finite_sums[C];
+    __shared__ float edges[kMaxClusters];            // boundary values; NaN behind the last: no weight reaches it
+    __shared__ uint32_t edge_keys[kMaxClusters];
     __shared__ uint32_t bytes[kWaves][16 * K];      // a wave's 64 k bytes of stream
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t n_units = n / kUnit, stride = (uint64_t)gridDim.x * kWaves;
@@ -600,10 +620,17 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t
     };
     if (u < n_units) request(u);
     ((uint2 *)table)[tid] = ((const uint2 *)table_in)[tid];
-    if (tid < kMaxClusters) edges[tid] = (tid < C - 1 && !st->error) ? key_value(st->edge_key[tid]) : INFINITY;
+    if (tid < kMaxClusters) {
+        edge_keys[tid] = (tid < C - 1 && !st->error) ? st->edge_key[tid] : 0xFFFFFFFFu;
+        edges[tid] = key_value(edge_keys[tid]);
+    }
     for (int i = tid; i < C * COPIES; i += kThreads) (&sums[0][0])[i] = 0;
+    for (int i = tid; i < C * kSumScales; i += kThreads) (&small_sums[0][0])[i] = 0;
+    if (tid < C) non_finite_sums[tid] = 0.0f;
     const float xlo = st->xlo, xhi = st->xhi, scale = st->bin_scale, shift = st->bin_shift;
-    const double sum_scale = st->sum_scale;
+    const int sum_exp = st->sum_exp;
+    const double sum_scale = ldexp(1.0, kSumBits - sum_exp);
+    const float least = st->non_finite ? __builtin_nanf("") : ldexpf(1.0f, sum_exp - kSumStep);
     const double magic = 6755399441055744.0;        // 1.5 * 2^52: x + magic holds round(x) in its low bits
     __syncthreads();
     while (u < n_units) {
@@ -627,17 +654,34 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t
         if (__ballot(several & kSeveral)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                while (cluster[e] < C - 1 && edges[cluster[e]] <= x[e]) ++cluster[e];
+                for (cluster[e] = entry[e] & 0xFFu; cluster[e] < C - 1 && edge_keys[cluster[e]] <= order_key(x[e]);) ++cluster[e];
         }
         uint64_t bits = 0;
+        uint32_t small = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             bits |= (uint64_t)cluster[e] << (e * K);
-            const bool in = x[e] >= xlo && x[e] <= xhi;
+            const bool in = is_inlier(x[e], xlo, xhi), regular = fabsf(x[e]) >= least;
             if (!in) flags |= 1u << e;
-            const double y = fma((double)(in ? x[e] : 0.0f), sum_scale, magic);
+            if (in && !regular && x[e] != 0.0f) small |= 1u << e;
+            const double y = fma((double)(in && regular ? x[e] : 0.0f), sum_scale, magic);
             atomicAdd(&sums[cluster[e]][lane & (COPIES - 1)],
                       __builtin_bit_cast(unsigned long long, y) - __builtin_bit_cast(unsigned long long, magic));
+        }
+        if (__ballot(small != 0)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (!(small & (1u << e))) continue;
+                if (!(fabsf(x[e]) < INFINITY)) {
+                    unsafeAtomicAdd(&non_finite_sums[cluster[e]], x[e]);
+                    continue;
+                }
+                int exp;
+                (void)frexpf(x[e], &exp);               // |x| < 2^exp
+                const int scale = (sum_exp - exp) / kSumStep;
+                const double whole = ldexp((double)x[e], kSumBits - sum_exp + scale * kSumStep);
+                atomicAdd(&small_sums[cluster[e]][scale], (unsigned long long)(long long)whole);
+            }
         }
         uint8_t *dst = packed + here * (kUnit / 8 * K);
         if constexpr (K == 4) {
@@ -682,9 +726,11 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t
     }
     __syncthreads();
     if (tid < C) {
-        unsigned long long s = 0;
-        for (int i = 0; i < COPIES; ++i) s += sums[tid][(i + tid) & (COPIES - 1)];
-        csum[(size_t)blockIdx.x * kMaxClusters + tid] = (double)(long long)s / sum_scale;
+        unsigned long long first = small_sums[tid][0];
+        for (int i = 0; i < COPIES; ++i) first += sums[tid][(i + tid) & (COPIES - 1)];
+        double s = 0.0;
+        for (int i = kSumScales - 1; i > 0; --i) s += ldexp((double)(long long)small_sums[tid][i], sum_exp - kSumBits - i * kSumStep);
+        csum[(size_t)blockIdx.x * kMaxClusters + tid] = s + ldexp((double)(long long)first, sum_exp - kSumBits) + non_finite_sums[tid];
     }
 }
 

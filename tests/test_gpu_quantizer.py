@@ -3,6 +3,7 @@ against the reference quantizer: codebook, packed index streams and outlier dict
 be identical bit for bit; the fitted moments agree to float64 rounding; and the library's own
 decoder turns the quantizer's output back into the reference's dequantized weights."""
 import ctypes as C
+import math
 
 import numpy as np
 import pytest
@@ -196,3 +197,60 @@ def test_quantizer_crowded_bins(k, kind):
         w += np.float32(3.0)
     g = run_gpu(dims, w, k, max_out=dims.weights_per_shard)
     check_against_reference(dims, w, k, g)
+
+
+@pytest.mark.parametrize("k,lowest", [(2, -8), (6, -20), (4, -44)])
+def test_quantizer_centroids_of_weights_of_any_magnitude(k, lowest):
+    """Weights from 10^lowest to 1, equally many per decade: a cluster's mean is as exact for weights far below
+    the layer's largest as for those next to it (correctly rounded from the exact sum of its members)."""
+    from fractions import Fraction
+    from oracle import sti_quantizer_oracle as Q
+    rng = np.random.default_rng(100 + k)
+    w = (10.0 ** rng.uniform(lowest, 0.0, size=(MID.n_heads, MID.weights_per_shard))).astype(np.float32)
+    w[:, ::7] = 0.0
+    g = run_gpu(MID, w, k, max_out=MID.weights_per_shard)
+    q = Q.quantize_layer(w, k)
+    outlier = np.zeros(w.shape, dtype=bool)
+    for s, p in enumerate(q["outlier_pos"]):
+        outlier[s, p] = True
+    for s in range(MID.n_heads):
+        assert np.array_equal(g["packed"][s].cpu().numpy(), Q.pack_indexes(q["indexes"][s], k))
+    got = g["codebook"].cpu().numpy()
+    for c in range(1 << k):
+        members = w[(q["indexes"] == c) & ~outlier]
+        if members.size:
+            mean = float(Fraction(math.fsum(members.astype(np.float64))) / members.size)
+            assert got[c] == np.float32(mean), (c, got[c], mean)
+
+
+@pytest.mark.parametrize("k", [2, 5, 6])
+@pytest.mark.parametrize("kind", ["inf", "both", "nan", "mixed"])
+def test_quantizer_infinite_and_nan_weights(k, kind):
+    """The moments are NaN, nothing is an outlier; clusters by sorted order, -NaN below -infinity and NaN above
+    infinity; a cluster that holds an infinity or NaN has the mean that follows from it, the others their own."""
+    rng = np.random.default_rng(200 + k)
+    w = rng.normal(0.0, 0.03, size=(MID.n_heads, MID.weights_per_shard)).astype(np.float32)
+    flat = w.ravel()
+    at = rng.choice(flat.size, 9, replace=False)
+    neg_nan = np.array([0xFFC00000], dtype=np.uint32).view(np.float32)[0]
+    if kind in ("inf", "both", "mixed"):
+        flat[at[:3]] = np.inf
+    if kind in ("both", "mixed"):
+        flat[at[3:5]] = -np.inf
+    if kind in ("nan", "mixed"):
+        flat[at[5:7]] = np.nan
+        flat[at[7]] = neg_nan
+    g = run_gpu(MID, w, k, max_out=64)
+    u = (flat + np.float32(0.0)).view(np.uint32)
+    key = np.where(u & 0x80000000, ~u, u | 0x80000000)
+    C, n = 1 << k, key.size
+    edges = np.sort(key)[[(c * n) // C for c in range(1, C)]]
+    idx = np.searchsorted(edges, key, side="right").astype(np.uint8).reshape(w.shape)
+    assert g["stats"].status == 0 and g["stats"].n_outliers == 0 and math.isnan(g["stats"].variance)
+    assert not g["cnt"].cpu().numpy().any()
+    from oracle import sti_quantizer_oracle as Q
+    for s in range(MID.n_heads):
+        assert np.array_equal(g["packed"][s].cpu().numpy(), Q.pack_indexes(idx[s], k))
+    with np.errstate(invalid="ignore"):
+        want = np.array([w[idx == c].astype(np.float64).mean() for c in range(C)]).astype(np.float32)
+    assert np.array_equal(g["codebook"].cpu().numpy(), want, equal_nan=True)
