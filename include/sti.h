@@ -293,8 +293,8 @@ sti_status sti_model_forward_masked(const sti_dims *dims, int n_layers, const st
  * layers' worth (64 MiB), never fewer than two - and the model's shard table in device memory
  * (Section "Submodel execution" keeps one layer's working buffer and decompresses a layer right
  * before it computes; with a second buffer a layer is decompressed while the layer before it
- * computes - by the workgroups that the Q/K/V launch of that layer has to spare, when it has at
- * least 32 of them - and otherwise a few layers are decompressed by one launch right before the
+ * computes - by the workgroups that the Q/K/V launch of that layer has to spare, when it has
+ * enough of them - and otherwise a few layers are decompressed by one launch right before the
  * first of them runs).  Applies to STI_PREC_F16_MFMA whenever
  * the layer goes through the working buffer (many tokens, see sti_precision); otherwise, and for
  * n_layers <= 1, it equals sti_workspace_bytes.

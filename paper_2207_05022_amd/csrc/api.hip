@@ -374,14 +374,15 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
 
 // One layer, arguments already validated.  `in` is float32 (F32 precision) or
 // binary16 (MFMA precision); `out` is written as out_dtype.
-int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, sti_precision prec)
+int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_next, bool grouped, sti_precision prec)
 {
     if (prec != STI_PREC_F16_MFMA || m <= 0 || few_token_path(d, (int64_t)B * Lseq)) return 0;
     GemmProblem p;
     memset(&p, 0, sizeof(p));
     p.kind = gemm_wide_fuses_attention(B, Lseq, m, d.d_head) ? GEMM_QKV_ATTN : GEMM_QKV;
     p.T = B * Lseq; p.n_blocks = m; p.block_rows = 3 * d.d_head; p.block_cols = d.d_model;
-    return gemm_wide_spare_workgroups(p);
+    p.next_shards = m_next; p.next_ffn_per_shard = d.ffn_per_shard;
+    return gemm_wide_spare_workgroups(p, grouped);
 }
 
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
@@ -1029,11 +1030,13 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         }
         return STI_OK;
     };
-    // A layer whose Q/K/V projection leaves compute units idle (spare_decode_workgroups) decompresses
+    // A layer whose Q/K/V projection leaves enough compute units idle (spare_decode_workgroups) decompresses
     // the layer behind it on those units: then only the first layer (and whatever follows a layer that
     // cannot) is decompressed by a launch of its own.
     auto spare = [&](int l) {
-        return spare_decode_workgroups(*dims, batch, seq, (int)(last_shard(l) - first_shard[l]), precision);
+        const int m_next = l + 1 < n_layers ? (int)(last_shard(l + 1) - first_shard[l + 1]) : 0;
+        return spare_decode_workgroups(*dims, batch, seq, (int)(last_shard(l) - first_shard[l]), m_next,
+                                       m_next == M && decode_group > 1, precision);
     };
     const sti_dtype act = (precision == STI_PREC_F32) ? STI_F32 : STI_F16;
     const ActLayout inner = wl.inner;

@@ -44,9 +44,10 @@ struct NextLayerDecode {
     int workgroups;
     int max_outliers;   // > 0: the layer's output projection puts the outlier dictionaries in
 };
-// Workgroups such a launch has to spare for a layer of m present shards (0: the layer does not go
-// through the many-token route, or its projection fills the chip).
-int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, sti_precision prec);
+// Workgroups such a launch of a layer of m present shards gives to the m_next of the next layer (0: the layer does not go
+// through the many-token route, its projection fills the chip, or a decompression launch in the chain - for several
+// layers if `grouped` - costs less).
+int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_next, bool grouped, sti_precision prec);
 
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,

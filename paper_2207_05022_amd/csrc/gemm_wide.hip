@@ -26,6 +26,8 @@
 // one whole sequence, so the Q/K/V projection is cut into 128 x 384 tiles = Q | K | V of two
 // heads, and the workgroup that has multiplied such a tile keeps it in LDS and computes those
 // heads' attention itself (kind GEMM_QKV_ATTN): no Q/K/V buffer in memory and no attention launch.
+#include <algorithm>
+#include <math.h>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
 #include "attention_core.hpp"
@@ -766,6 +768,29 @@ constexpr Shape kShapes[] = {{4, 12, 1, 0.37f, 6.5f, false}, {4, 9, 1, 0.38f, 8.
 constexpr float kSplitBlockUs = 0.45f, kSplitStartUs = 5.5f;   // {2, 6} with K split over two wave groups (one workgroup per unit)
 constexpr float kGeluUs = 3.5f;
 
+// Workgroups beside `tiles` that still find a compute unit of their own in the first round; fewer than an eighth of the
+// chip are not used.
+inline int spare_units(long tiles)
+{
+    const long spare = kComputeUnits - (tiles + 7) / 8 * 8;
+    return spare >= kComputeUnits / 8 ? (int)spare : 0;
+}
+
+// Time of a layer's decompression beside the tiles of a Q/K/V launch, by `spare` workgroups of nw waves, and of one that
+// stands in the chain by itself (grouped: several full layers in one launch).  Fitted to 98 layer shapes (512 x 8, 768 x 6
+// to 12, 1024 x 12 and 16 shards, 704 to 6144 tokens) with every tile shape, each with and without the decompression beside
+// it.  What a Q/K/V shape costs is therefore not its own time alone: 768 x 10 shards at 3584 tokens took
+// 789 us per 8 layers where 32 workgroups of four waves were left to the decompression (now 706), 768 at 4096 tokens where
+// none were (now 741).
+inline float beside_us(float cells, int spare, int nw) { return (1.0f + 0.035f * nw) * cells / (spare * nw) + 4.f + 0.5f * nw; }
+inline float in_chain_us(float cells, bool grouped) { return cells * 2048.f * 0.4e-6f + (grouped ? -0.7f : 2.7f); }
+
+// 2048-weight cells of the layer that p.next_shards and p.next_ffn_per_shard describe
+inline float next_cells(const GemmProblem &p)
+{
+    return (float)p.next_shards * p.block_cols * (4 * (p.block_rows / 3) + 2 * p.next_ffn_per_shard) / 2048.f;
+}
+
 }  // namespace
 
 bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks)
@@ -791,16 +816,18 @@ struct Choice {
     bool ks2;        // K split over two wave groups inside the workgroup
     long tiles;
     int nkt_total;
+    float us;        // estimated; infinite: no shape has workgroups to spare
 };
 
-// The shape with the least estimated time.
+// The shape with the least estimated time; with next_workgroups, of those that have workgroups to spare.
 Choice choose(const GemmProblem &p, int N)
 {
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN);
     const int nkt = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
     const float k = nkt * BK / 1024.f;
+    const bool beside = p.kind == GEMM_QKV && p.next_workgroups > 0;
     Choice best = {};
-    float best_us = 0.f;
+    best.us = INFINITY;
     for (int c = 0; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
         const Shape &sh = kShapes[c];
         const int bm = sh.ra * 32, bn = sh.nw * sh.rb * 32, blocks = sh.ra * sh.nw * sh.rb;
@@ -816,8 +843,13 @@ Choice choose(const GemmProblem &p, int N)
         float us = per_cu * (products + start);
         if (sh.shared) us = (avg < 1.f ? 1.f : (avg + per_cu) / 2) * products + start;
         else if (sh.nw == 6) us = per_cu * products + start;
-        if (c == 0 || us < best_us) {
-            best_us = us;
+        if (beside) {
+            const int spare = spare_units(tiles);
+            if (spare == 0) continue;
+            us = std::max(us, beside_us(next_cells(p), spare, sh.nw));
+        }
+        if (us < best.us) {
+            best.us = us;
             best.shape = c;
             best.ks2 = ks2;
             best.tiles = tiles;
@@ -864,17 +896,20 @@ bool gemm_wide_fuses_attention(int B, int L, int m, int dh)
     return L == ATT_L && dh == ATT_DH && m > 0 && (int64_t)B * ((m + 1) / 2) >= kComputeUnits / 2;
 }
 
-// Every workgroup of the launch, tiles and decompression, finds a compute unit in the first round;
-// below an eighth of the chip the decompression would outlast the projection.
-int gemm_wide_spare_workgroups(const GemmProblem &p)
+// Every workgroup of the launch, tiles and decompression, finds a compute unit in the first round.
+int gemm_wide_spare_workgroups(const GemmProblem &p, bool grouped)
 {
     if (p.n_blocks <= 0 || p.T <= 0) return 0;
-    int64_t tiles;
-    if (p.kind == GEMM_QKV_ATTN) tiles = (int64_t)(p.T / ATT_L) * ((p.n_blocks + 1) / 2);
-    else if (p.kind == GEMM_QKV) tiles = choose(p, p.n_blocks * p.block_rows).tiles;
-    else return 0;
-    const int64_t spare = kComputeUnits - (tiles + 7) / 8 * 8;
-    return spare >= kComputeUnits / 8 ? (int)spare : 0;
+    if (p.kind == GEMM_QKV_ATTN) return spare_units((long)(p.T / ATT_L) * ((p.n_blocks + 1) / 2));
+    if (p.kind != GEMM_QKV) return 0;
+    const int N = p.n_blocks * p.block_rows;
+    GemmProblem q = p;
+    q.next_workgroups = 0;
+    const Choice alone = choose(q, N);
+    if (p.next_shards <= 0) return spare_units(alone.tiles);
+    q.next_workgroups = 1;
+    const Choice beside = choose(q, N);
+    return beside.us <= alone.us + in_chain_us(next_cells(p), grouped) ? spare_units(beside.tiles) : 0;
 }
 
 hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipStream_t stream)
@@ -890,6 +925,7 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
         return launch_shape<GEMM_QKV_ATTN, 4, 12, 1>(p, blocks, N, stream);
     }
     const Choice ch = choose(p, N);
+    if (!(ch.us < INFINITY)) return hipErrorInvalidValue;
     if (p.k_splits > 1 && (!ch.ks2 || p.k_splits != gemm_wide_k_splits(p))) return hipErrorInvalidValue;
     if (ch.ks2) {
         return p.kind == GEMM_OUT ? launch_shape<GEMM_OUT, 2, 6, 2>(p, blocks, N, stream)

@@ -148,10 +148,10 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
 bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks);
 // whether the Q/K/V projection of B sequences of L tokens over m heads should go out as GEMM_QKV_ATTN
 bool gemm_wide_fuses_attention(int B, int L, int m, int dh);
-// workgroups a Q/K/V launch (GEMM_QKV or GEMM_QKV_ATTN; kind, T, n_blocks, block_rows, block_cols set)
-// can give to the next layer's decompression: one per compute unit that its tiles leave idle (0: none to
-// spare, decompress with a launch of its own)
-int gemm_wide_spare_workgroups(const GemmProblem &p);
+// workgroups a Q/K/V launch (GEMM_QKV or GEMM_QKV_ATTN; kind, T, n_blocks, block_rows, block_cols, next_shards,
+// next_ffn_per_shard set) should give to the next layer's decompression: one per compute unit that its tiles leave idle
+// (0: none to spare, or a launch of its own costs less; grouped: that launch takes several layers)
+int gemm_wide_spare_workgroups(const GemmProblem &p, bool grouped);
 // K splits across workgroups the wide-tile kernel wants for this problem (1 = none), and the
 // largest value it can return for T tokens and N output columns (workspace sizing)
 int gemm_wide_k_splits(const GemmProblem &p);

@@ -526,6 +526,36 @@ def test_outlier_dictionaries_beside_the_output_projection(gpu, B, L, entries):
     assert torch.isfinite(whole.float()).all()
 
 
+@pytest.mark.parametrize("d,M,f,absent,B,L,entries", [
+    (768, 12, 256, (0, 1, 1), 11, 93, 1),       # K of the output projection split over workgroups
+    (768, 12, 256, (0, 1, 1), 11, 93, 769),
+    (768, 12, 256, (0, 1, 1), 9, 113, 5957),    # 11 shards: the most entries beside the output projection ...
+    (768, 12, 256, (0, 1, 1), 9, 113, 5958),    # ... and one more
+    (768, 12, 256, (2, 2, 2), 60, 64, 3),       # the fastest tiles of Q/K/V alone would leave no compute unit ...
+    (1024, 16, 256, (0, 0, 0), 40, 64, 2),
+    (768, 12, 256, (2, 2, 2), 56, 64, 0),       # ... or too few
+    (1024, 4, 64, (0, 1, 1), 28, 100, 300),     # output projection in 128 x 256 tiles of four waves
+    (1024, 8, 64, (0, 1, 1), 55, 100, 257),
+])
+def test_a_layer_rides_where_that_is_faster_than_a_launch_of_its_own(gpu, d, M, f, absent, B, L, entries):
+    """Layers behind the first are decompressed beside the Q/K/V projection in front of them (one decompression
+    launch in all), their dictionaries beside its output projection: the bits of the per-layer route."""
+    torch, P, D = gpu
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    plan = np.full((3, M), 4, dtype=np.int8)
+    for l, n in enumerate(absent):
+        plan[l, 1:1 + n] = 0
+    wl = S.small_workload(810 + entries, dims, 3, B, L, plan=plan, io_dtype="f16")
+    if entries:
+        wl = _with_outliers(wl, entries, fraction=entries / dims.weights_per_shard)
+    prec = P.STI_PREC_F16_MFMA
+    P.sti_profile_begin()
+    whole = _run_model_route(gpu, wl, P.sti_model_workspace_bytes(dims, 3, B, L, prec))
+    assert P.sti_profile_end()["decode"][0] == 1
+    assert torch.equal(whole, _run_model_route(gpu, wl, P.sti_workspace_bytes(dims, B, L, prec)))
+    assert torch.isfinite(whole.float()).all()
+
+
 def test_layers_that_can_and_cannot_take_the_next_layer_along(gpu, oracle_mod):
     """38 sequences: a full layer has 228 tiles and no compute unit to spare, a layer with 9 or 10 shards
     190 tiles and 64; with an all-absent layer in between.  Layers 0 to 3 are decompressed as a group,
