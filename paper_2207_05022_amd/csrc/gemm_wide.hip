@@ -767,6 +767,9 @@ constexpr Shape kShapes[] = {{4, 12, 1, 0.37f, 6.5f, false}, {4, 9, 1, 0.38f, 8.
                              {2, 6, 1, 0.72f, 3.f, false},   {4, 4, 2, 0.54f, 4.f, true}};
 constexpr float kSplitBlockUs = 0.45f, kSplitStartUs = 5.5f;   // {2, 6} with K split over two wave groups (one workgroup per unit)
 constexpr float kGeluUs = 3.5f;
+// two {2, 6} workgroups on a unit: the second one's residual is not hidden.  768 x 6 shards, 4608 tokens, O: 3 us a launch slower than
+// {2, 12}, estimated 1 us faster without this
+constexpr float kSecondResidualUs = 3.f;
 
 // Workgroups beside `tiles` that still find a compute unit of their own in the first round; fewer than an eighth of the
 // chip are not used.
@@ -842,7 +845,7 @@ Choice choose(const GemmProblem &p, int N)
         //  two 6-wave workgroups share a unit too, but a unit with one more than its neighbours holds all up)
         float us = per_cu * (products + start);
         if (sh.shared) us = (avg < 1.f ? 1.f : (avg + per_cu) / 2) * products + start;
-        else if (sh.nw == 6) us = per_cu * products + start;
+        else if (sh.nw == 6) us = per_cu * products + start + (!n_split && per_cu == 2 ? kSecondResidualUs : 0.f);
         if (beside) {
             const int spare = spare_units(tiles);
             if (spare == 0) continue;

@@ -671,6 +671,20 @@ def test_mfma_many_tiles_shared_compute_units(gpu, oracle_mod, B, L, n_absent):
     assert_parity(run_gpu(gpu, wl, "mfma"), want, TOL["mfma"])
 
 
+@pytest.mark.parametrize("n_absent", [0, 1])
+def test_mfma_output_projections_with_shared_compute_units(gpu, oracle_mod, n_absent):
+    """O and FFN2 in 128 x 256 workgroups, two per compute unit, residual and a ragged last row tile: sampled
+    sequences, the last tile's among them."""
+    dims = S.Dims(1024, 16, 64, 64, 1e-12)
+    wl = S.small_workload(53000, dims, 1, 55, 100, n_absent=n_absent, io_dtype="f16")
+    S.make_every_term_matter(wl, 6, amp=2.0)
+    got = run_gpu(gpu, wl, "mfma")
+    assert np.all(np.isfinite(got))
+    for b in (0, 21, 53, 54):
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
+        assert_parity(got[b:b + 1], want, TOL["mfma"], b)
+
+
 @pytest.mark.parametrize("B,L", [(1, 64), (3, 100)])   # few-token route / working-buffer route
 def test_mfma_widest_supported_model(gpu, oracle_mod, B, L):
     """d_model 2048 (rows of 2048 features in LayerNorm, K = 2048 in the projections, 22-26 column
