@@ -9,6 +9,7 @@
 //
 // Bound by latency: one round trip for all operands, two short products, one barrier.  One sequence of 128
 // tokens, 12 heads: 3.5 us, against 5.7 us of the kernel that stages K and V of a whole head in LDS per workgroup.
+#include <float.h>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
 
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
     int kb = wave;
     if (kb < nkb) request(kb);
     const float scale = 0.125f * 1.44269504088896340736f;   // 1/sqrt(64) * log2(e)
-    float run_max = -INFINITY, run_sum = 0.f;               // (of the scaled scores)
+    float run_max = -FLT_MAX, run_sum = 0.f;                // (of the scaled scores; finite: a block may hold none but -infinity)
     float16v o[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e)
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
             bmax = fmaxf(bmax, x);
         }
         bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        const float new_max = fmaxf(run_max, bmax);         // (finite: block kb < nkb holds a key)
+        const float new_max = fmaxf(run_max, bmax);
         const float alpha = __builtin_amdgcn_exp2f(run_max - new_max);
         run_max = new_max;
         float psum = 0.f;

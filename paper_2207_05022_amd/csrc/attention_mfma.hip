@@ -15,6 +15,7 @@
 // Padded sequences (the input length is fixed after padding, Section "Prerequisite: Offline
 // Profiling"): with key_lengths, sequence b attends to its first key_lengths[b] positions only
 // (clamped to 1..L); rows of padded positions are still computed, from those keys.
+#include <float.h>
 #include "sti_internal.hpp"
 #include "attention_core.hpp"
 
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
         }
     };
     const float scale = 0.125f * 1.44269504088896340736f;   // 1/sqrt(64) * log2(e)
-    float run_max = -INFINITY, run_sum = 0.f;               // (of the unscaled scores; this lane's keys only)
+    float run_max = -FLT_MAX, run_sum = 0.f;                // (of the unscaled scores, finite: a block may hold none but -infinity; sum: this lane's keys only)
     float16v o[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e)

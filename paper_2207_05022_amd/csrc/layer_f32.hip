@@ -5,6 +5,7 @@
 //
 // Products run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32: 256 flops per clock and
 // compute unit, float32 multiply and accumulate), in the projections as well as in the attention.
+#include <float.h>
 #include <type_traits>
 #include "sti_internal.hpp"
 
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qk
         }
     }
     const float scale = 1.0f / sqrtf((float)dh);
-    float run_max = -INFINITY, run_sum = 0.f;
+    float run_max = -FLT_MAX, run_sum = 0.f;   // (finite: a block may hold no score but -infinity)
     f32x4 o[DB];
 #pragma unroll
     for (int c = 0; c < DB; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -1087,6 +1087,32 @@ def test_no_value_in_the_padding_reaches_a_real_row(gpu, prec, dims, B, L, route
                 assert torch.equal(y[b, :n], outs[0][b, :n]), (io, fill, b, int(n))
 
 
+@pytest.mark.parametrize("prec,dims,B,L", [
+    ("f32", SMALL, 2, 150), ("f32", MID, 1, 130),
+    ("mfma", MID, 1, 95), ("mfma", MID, 1, 160), ("mfma", MID, 2, 128),   # few tokens: a wave's blocks of 32 keys
+    ("mfma", MID, 3, 50), ("mfma", MID, 3, 200), ("mfma", WIDE, 9, 130),  # all scores at once; blocks of 64 keys
+])
+def test_keys_with_scores_of_minus_infinity_have_weight_zero(gpu, oracle_mod, prec, dims, B, L):
+    """The first keys' scores overflow to -infinity (K in binary16, the product in float32), whole key blocks of
+    them, and the others are finite: the softmax is that of the finite ones, as over all scores at once."""
+    d, dh = dims.d_model, dims.d_head
+    n_overflow = min(96, L - 10)
+    wl = S.small_workload(8400 + L, dims, 1, B, L, bit_choices=(32,), io_dtype="f32")
+    for s in wl.shards[0]:
+        rows = s.data.reshape(-1)
+        rows[:d] = 0.0                        # Q feature 0: its bias
+        rows[dh * d:(dh + 1) * d] = 0.0       # K feature 0: -2000 or -1e30 times x feature 0
+        rows[dh * d] = -2000.0 if prec == "mfma" else -1e30
+    wl.params[0].bq.reshape(-1, dh)[:, 0] = 1.0 if prec == "mfma" else 1e10
+    wl.params[0].bk.reshape(-1, dh)[:, 0] = 0.0
+    wl.x[:, :, 0] = 0.0
+    wl.x[:, :n_overflow, 0] = 60.0
+    with np.errstate(over="ignore"):
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x)
+    assert np.all(np.isfinite(want))
+    assert_parity(run_gpu(gpu, wl, prec), want, TOL[prec])
+
+
 def test_captured_masked_forward_follows_the_lengths_in_device_memory(gpu):
     """The key lengths are read by the kernels, not by the host: a graph captured once serves
     other lengths by rewriting the device array between replays."""
