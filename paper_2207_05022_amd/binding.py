@@ -11,9 +11,6 @@ import os
 from operator import attrgetter
 from typing import Optional, Sequence
 
-import numpy as np
-import torch
-
 HERE = os.path.dirname(os.path.abspath(__file__))
 # STI_LIBRARY names another build of the same sources to load instead (the build with phase time
 # stamps that bench.py --phase-budget measures with); unset, the product library beside this file
@@ -159,16 +156,22 @@ def status_string(status: int) -> str:
     return lib.sti_status_string(int(status)).decode()
 
 
-_DTYPE_CODES = {torch.float32: STI_F32, torch.float16: STI_F16, torch.bfloat16: STI_BF16}
+# torch and numpy are imported by the calls that take their objects only: sizes and the planner's submodel
+# search need neither
+_DTYPE_CODES = {}
 
 
 def _dtype_code(t) -> int:
+    if not _DTYPE_CODES:
+        import torch
+        _DTYPE_CODES.update({torch.float32: STI_F32, torch.float16: STI_F16, torch.bfloat16: STI_BF16})
     return _DTYPE_CODES[t.dtype]
 
 
 def _stream_handle(stream) -> int:
     """Raw handle of `stream`, or of the current stream of the current device (without a Stream object)."""
     if stream is None:
+        import torch
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream
 
@@ -218,13 +221,12 @@ def _param_pointers(p) -> list:
 def params_array(params: Sequence, n_layers: int) -> "C.Array":
     """HOST array of sti_layer_params from `n_layers` parameter objects (see make_params)."""
     pointers = []
-    for p in params[:n_layers]:
+    for l in range(n_layers):
+        p = params[l]
         if isinstance(p, StiLayerParams):
             pointers.extend(getattr(p, n) for n in _PARAM_NAMES)
         else:
             pointers.extend(_param_pointers(p))
-    if len(pointers) != n_layers * len(_PARAM_NAMES):
-        raise ValueError("one parameter object per layer is needed")
     if not pointers:
         return (StiLayerParams * 1)()
     return (StiLayerParams * n_layers).from_buffer((C.c_void_p * len(pointers))(*pointers))
@@ -297,6 +299,7 @@ def _key_lengths_ptr(key_lengths, batch: int):
     """key_lengths: CUDA int32 tensor [batch] (None passes a null pointer through)."""
     if key_lengths is None:
         return None
+    import torch
     if key_lengths.dtype != torch.int32 or tuple(key_lengths.shape) != (batch,):
         raise ValueError("key_lengths must be an int32 tensor with one entry per sequence")
     return _ptr(key_lengths)
@@ -363,6 +366,7 @@ def sti_model_forward(dims, store, params: Sequence, plan, x, y, precision: int,
                       stream=None) -> None:
     """store: result of make_store (or a ctypes StiShard array [n_layers][M][6]);
     plan: int8 numpy array [n_layers][M]."""
+    import numpy as np
     d = make_dims(dims)
     plan = np.ascontiguousarray(plan, dtype=np.int8)
     n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
@@ -382,6 +386,7 @@ def sti_model_forward(dims, store, params: Sequence, plan, x, y, precision: int,
 def sti_model_forward_masked(dims, store, params: Sequence, plan, x, y, key_lengths, precision: int,
                              workspace, stream=None) -> None:
     """As sti_model_forward; key_lengths: CUDA int32 tensor [batch], the same in every layer."""
+    import numpy as np
     d = make_dims(dims)
     plan = np.ascontiguousarray(plan, dtype=np.int8)
     n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
@@ -437,6 +442,7 @@ class StiPipeline:
                 key_lengths=None) -> dict:
         """store: make_store(...) of versions whose ``data`` are pinned host tensors.
         With key_lengths (CUDA int32 tensor [batch]) the call goes to sti_pipeline_forward_masked."""
+        import numpy as np
         plan = np.ascontiguousarray(plan, dtype=np.int8)
         n_layers = int(plan.shape[0]) if plan.ndim == 2 else 0
         if not isinstance(store, C.Array):
@@ -493,6 +499,7 @@ def sti_plan_submodel(t_io, t_comp, n_layers: int, deadline_s: float):
 
 def sti_plan_bitwidths(t_io, t_comp, n_layers: int, n: int, m: int, preloaded, importance):
     """Returns (plan int8 [n_layers][M], aib float64 [n])."""
+    import numpy as np
     tab, _keep = _plan_tables(t_io, t_comp, n_layers)
     M = len(t_comp)
     pre = None if preloaded is None else np.ascontiguousarray(preloaded, dtype=np.int8).ravel()

@@ -3,6 +3,8 @@ include/sti.h declares, and rejects bad arguments before touching the device.  N
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -109,6 +111,30 @@ def test_model_workspace_query(P):
     assert P.sti_model_workspace_bytes(Dims(), 1, 32, 128, P.STI_PREC_F16_MFMA) == one
     assert P.sti_model_workspace_bytes(Dims(), 12, 32, 128, P.STI_PREC_F32) == P.sti_workspace_bytes(Dims(), 32, 128, P.STI_PREC_F32)
     assert P.sti_model_workspace_bytes(Dims(), -1, 32, 128, P.STI_PREC_F16_MFMA) == 0
+
+
+def test_sizes_and_submodel_search_need_neither_torch_nor_numpy(P):
+    """Programs that only plan (sizes, the submodel that meets a deadline) import the package without them."""
+    code = ("import sys; sys.modules['torch'] = sys.modules['numpy'] = None\n"
+            "import paper_2207_05022_amd as P\n"
+            "d = P.StiDims(768, 12, 64, 256, 1e-12)\n"
+            "assert P.sti_workspace_bytes(d, 1, 128, P.STI_PREC_F16_MFMA) > 0 and P.sti_quantize_workspace_bytes(d) > 0\n"
+            "assert P.sti_plan_submodel([1e-4] * 6, [1e-3 * (m + 1) for m in range(12)], 12, 1.0)[0] > 0\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
+
+
+def test_parameter_objects_are_taken_one_by_one(P):
+    """Any container that is indexed by layer serves, longer ones too; a shorter one is an IndexError."""
+    from collections import deque
+    from types import SimpleNamespace
+    names = [n for n, _ in P.StiLayerParams._fields_]
+    layers = [SimpleNamespace(**{n: None for n in names}) for _ in range(3)]
+    layers[1] = P.StiLayerParams(*range(16, 26))
+    for box in (layers, tuple(layers), deque(layers), dict(enumerate(layers))):
+        arr = P.binding.params_array(box, 2)
+        assert len(arr) == 2 and arr[0].bq is None and arr[1].bq == 16 and getattr(arr[1], names[-1]) == 25
+    with pytest.raises(IndexError):
+        P.binding.params_array(layers, 4)
 
 
 def test_workspace_query(P):
