@@ -184,9 +184,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
         if (hot_kind == GEMM_QKV) {
             part = nrow0 / p.d_head;
             const float *bp = part == 0 ? p.bias0 : (part == 1 ? p.bias1 : p.bias2);
-            bias = *(const f32x4 *)(bp + shard * p.d_head + nrow - part * p.d_head);
+            bias = *(const f32x4_any *)(bp + shard * p.d_head + nrow - part * p.d_head);
         } else {
-            bias = *(const f32x4 *)(p.bias0 + shard * hot_block_rows + nrow);
+            bias = *(const f32x4_any *)(p.bias0 + shard * hot_block_rows + nrow);
         }
     }
 #pragma unroll

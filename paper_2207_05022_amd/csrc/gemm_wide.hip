@@ -424,8 +424,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             } else {
                 bp = hot_bias0 + nw + c;
             }
-            bias[rq >> 1][rq & 1][0] = *(const f32x4 *)bp;
-            bias[rq >> 1][rq & 1][1] = *(const f32x4 *)(bp + 4);
+            bias[rq >> 1][rq & 1][0] = *(const f32x4_any *)bp;
+            bias[rq >> 1][rq & 1][1] = *(const f32x4_any *)(bp + 4);
         }
         if constexpr (PRE) {
 #pragma unroll

@@ -17,6 +17,7 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));   // four floats wherever they begin (parameters promise no more than 4 bytes)
 
 constexpr int kLutEntries = 64;  // per block
 

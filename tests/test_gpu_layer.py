@@ -340,6 +340,37 @@ def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, o
         assert_parity(got, want, TOL["mfma"], io)
 
 
+@pytest.mark.parametrize("prec,dims,B,L", [("f32", SMALL, 2, 19), ("mfma", MID, 1, 66), ("mfma", MID, 12, 100), ("mfma", MID, 64, 128)])
+def test_parameters_begin_at_any_float(gpu, prec, dims, B, L):
+    """Biases and LayerNorm parameters 4, 8 and 12 bytes past a 16-byte boundary."""
+    import types
+    torch, P, D = gpu
+    wl = S.small_workload(8600 + L, dims, 1, B, L, io_dtype="f32")
+    S.make_every_term_matter(wl, 3)
+    shards, params, x = D.upload_workload(wl)
+    precision = P.STI_PREC_F32 if prec == "f32" else P.STI_PREC_F16_MFMA
+    ws = torch.empty(P.sti_workspace_bytes(dims, B, L, precision), dtype=torch.uint8, device="cuda")
+    outs = []
+    for shift in range(4):
+        moved = types.SimpleNamespace()
+        for n, _ in P.StiLayerParams._fields_:
+            t = getattr(params[0], n).reshape(-1)
+            room = torch.empty(t.numel() + 4, device="cuda")
+            room[shift:shift + t.numel()] = t
+            setattr(moved, n, room[shift:shift + t.numel()])
+            assert getattr(moved, n).data_ptr() % 16 == 4 * shift
+        y = torch.full_like(x, float("nan"))
+        P.sti_layer_forward(dims, shards[0], moved, x, y, precision, ws)
+        torch.cuda.synchronize()
+        outs.append(y)
+    assert torch.isfinite(outs[0]).all()
+    # LayerNorm takes rows with unaligned parameters by single features: other order of its sums.  In binary16 that
+    # can move a row's value between the two LayerNorms to its neighbour, 2^-11 of it, which the residual hands on.
+    for y in outs[1:]:
+        assert torch.equal(y, outs[1])
+        assert rel_err(y.cpu().numpy(), outs[0].cpu().numpy().astype(np.float64)) <= (1e-6 if prec == "f32" else 2.0 ** -11)
+
+
 def test_mfma_rejects_unsupported_dims(gpu):
     torch, P, D = gpu
     assert P.sti_workspace_bytes(SMALL, 1, 8, P.STI_PREC_F16_MFMA) == 0
