@@ -203,14 +203,21 @@ sti_status check_decode_shard(const sti_shard &s)
 // decompress the layer once into the working buffer and run the wide-tile kernels.  Measured per layer (us,
 // few-token against working buffer, 6-bit mix, full shard set): BERT-base 128 tokens 34 / 51, 256 41 / 54,
 // 512 46 / 56, 640 53 / 59, 768 61 / 60; d_model 1024 x 16 shards 256 49 / 66, 512 68 / 85, 640 79 / 77; 512 x 8
-// shards of 128 neurons 1024 41 / 45, 1536 48 / 48; 256 x 4 of 64 1024 32 / 36.  In workgroups of the FFN1 product (32
-// columns x 64 tokens) the lines lie at about 1024.  Outside d_model 256 .. 1024 the line is the older
-// one, 128 tokens, or 192 when d_model <= 768.
+// shards of 128 neurons 1024 41 / 45, 1536 48 / 48; 256 x 4 of 64 1024 32 / 36; 1024 x 16 of 64 768 62 / 59, 1024 72 / 60;
+// 1024 x 8 of 256 768 57 / 61, 1024 68 / 62.  The work of a row block is its workgroups: columns of Q/K/V and FFN1, and
+// those of O and FFN2, which also split K and cost LayerNorm a plane per split.  Over 84 shapes (d_model 256 .. 1024, 64
+// to 256 neurons) at 256 .. 1024 tokens a line on n_heads (192 + ffn) + 4 d_model, counted per row block, is within 0.1 %
+// of the faster route on average; one on the workgroups of FFN1 alone had cost up to 27 %.  Dictionaries and
+// float32 shards, which this route decompresses to the working buffer or reads once per row block, leave the
+// line where it is (BERT-base 640 tokens 676 / 723 and 731 / 758 us per 12 layers).  Outside d_model 256 .. 1024 the line is
+// the older one, 128 tokens, or 192 when d_model <= 768.
 inline int64_t few_token_limit(const sti_dims &d)
 {
     const int64_t small = d.d_model <= 768 ? 192 : 128;
     if (d.d_model < 256 || d.d_model > 1024) return small;
-    const int64_t row_blocks = 1024 / ((int64_t)d.n_heads * (d.ffn_per_shard / 32));
+    const int64_t columns = (int64_t)d.n_heads * (3 * d.d_head + d.ffn_per_shard) + 4 * (int64_t)d.d_model;
+    const int64_t row_blocks = std::min(688 * 8448 / 64 / columns,                                      // (8448: BERT-base's)
+                                        1024 / ((int64_t)d.n_heads * (d.ffn_per_shard / 32)));   // more than 256 neurons: FFN1 alone
     return std::max(small, std::min<int64_t>(kFewMaxTokens, row_blocks * 64));
 }
 inline bool few_token_path(const sti_dims &d, int64_t T) { return T <= few_token_limit(d); }

@@ -163,6 +163,17 @@ def test_workspace_of_a_larger_call_serves_the_smaller_ones(P, d, M, f):
         assert all(a <= b for a, b in zip(layer, model))
 
 
+@pytest.mark.parametrize("d,M,f,last", [(768, 12, 256, 640), (1024, 16, 256, 512), (512, 8, 128, 1024), (256, 4, 64, 1024),
+                                        (1024, 16, 64, 704), (1024, 16, 128, 576), (896, 14, 128, 704), (1024, 8, 256, 704),
+                                        (768, 12, 192, 704), (896, 10, 192, 768), (128, 2, 64, 192), (1088, 4, 64, 128)])
+def test_line_between_the_routes(P, d, M, f, last):
+    """Few-token kernels up to `last` tokens: the whole-model route's buffers are only asked for beyond."""
+    dims = Dims(d=d, M=M, f=f)
+    few = [P.sti_model_workspace_bytes(dims, 4, n, 1, P.STI_PREC_F16_MFMA) == P.sti_workspace_bytes(dims, n, 1, P.STI_PREC_F16_MFMA)
+           for n in (1, last, last + 1)]
+    assert few == [True, True, False]
+
+
 @pytest.mark.parametrize("d,M,f,B,L", [(896, 48, 256, 1, 1), (1024, 48, 64, 2, 320), (960, 24, 512, 1, 100), (64, 48, 4096, 1, 33)])
 def test_fixed_workspace_takes_layers_near_its_size(P, d, M, f, B, L):
     """Layers whose buffers, at their exact number of tokens, come to nearly the 64 MiB of
