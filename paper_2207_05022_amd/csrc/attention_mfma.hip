@@ -142,8 +142,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float
 // compute unit whatever the length.  Online softmax; the output accumulators are only rescaled when some
 // query's maximum moves.
 // Bound by the softmax's vector instructions (about 1200 clocks per wave and block, 512 of matrix
-// work).  24 sequences of 384 tokens, 16 heads (14.5 GFLOP): 34 us, against 71 us of the kernel that kept all keys of
-// a head in LDS (105 KB: one workgroup of four waves per compute unit).
+// work).  24 sequences of 384 tokens, 16 heads (14.5 GFLOP): 32 us, against 71 us of the kernel that kept all keys of
+// a head in LDS (105 KB: one workgroup of four waves per compute unit).  The block that the last key cuts is
+// behind the loop, 32 keys at a time: inside it, masked as a whole, it cost the loop 8 spilled registers and the half
+// without keys its time (8 sequences of 160 tokens, 12 heads: 8.1 us, now 6.7; the kernel with all keys in LDS 7.5).
 constexpr int SB = 64;            // keys per block
 constexpr int SV = SB + 8;        // padded V^T row (halves)
 
@@ -207,33 +209,16 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
     request(0);
     put(0);
     __syncthreads();
-    for (int kb = 0, buf = 0; kb < Lk; kb += SB, buf ^= 1) {
-        if (kb + SB < Lk) request(kb + SB);
-        __builtin_amdgcn_sched_barrier(0);
-        float16v sc[2];
-        float bmax = -INFINITY;
+    auto scores = [&](int buf, int t) {   // of 32 keys
+        float16v s;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sc[t][v] = 0.f;
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(*(const half8 *)(Ks[buf] + (t * 32 + lr) * KPAD + s * 16 + g * 8),
-                                                              qf[s], sc[t], 0, 0, 0);
-        }
-        if (kb + SB > Lk) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int key = kb + t * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
-                    sc[t][v] = key < Lk ? sc[t][v] : -INFINITY;
-                }
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) bmax = fmaxf(bmax, sc[t][v]);
+        for (int f = 0; f < 4; ++f)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_f16(*(const half8 *)(Ks[buf] + (t * 32 + lr) * KPAD + f * 16 + g * 8), qf[f], s, 0, 0, 0);
+        return s;
+    };
+    auto rescale = [&](float bmax) {
         bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
         if (__ballot(bmax > run_max)) {
             const float new_max = fmaxf(run_max, bmax);
@@ -245,32 +230,59 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[e][v] *= alpha;
         }
-        const float shift = -run_max * scale;
+    };
+    auto weigh = [&](const float16v &s, int buf, int t, float shift) {
+        uint32_t pk[8];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            uint32_t pk[8];
+        for (int v = 0; v < 16; v += 2) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(s[v], scale, shift));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(s[v + 1], scale, shift));
+            run_sum += p0 + p1;
+            pk[v / 2] = f16_pair_bits(p0, p1);
+        }
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) {
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][v], scale, shift));
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][v + 1], scale, shift));
-                run_sum += p0 + p1;
-                pk[v / 2] = f16_pair_bits(p0, p1);
-            }
+        for (int s2 = 0; s2 < 2; ++s2) {
+            const u32x4 pv = {pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]};
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-                const u32x4 pv = {pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]};
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const _Float16 *vrow = Vt[buf] + (e * 32 + lr) * SV + t * 32 + s2 * 16 + g * 4;
-                    const u32x2 lo = *(const u32x2 *)vrow, hi = *(const u32x2 *)(vrow + 8);
-                    const u32x4 vv = {lo.x, lo.y, hi.x, hi.y};
-                    o[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, vv), __builtin_bit_cast(half8, pv), o[e], 0, 0, 0);
-                }
+            for (int e = 0; e < 2; ++e) {
+                const _Float16 *vrow = Vt[buf] + (e * 32 + lr) * SV + t * 32 + s2 * 16 + g * 4;
+                const u32x2 lo = *(const u32x2 *)vrow, hi = *(const u32x2 *)(vrow + 8);
+                const u32x4 vv = {lo.x, lo.y, hi.x, hi.y};
+                o[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, vv), __builtin_bit_cast(half8, pv), o[e], 0, 0, 0);
             }
         }
+    };
+    int kb = 0, buf = 0;
+    for (; kb + SB <= Lk; kb += SB, buf ^= 1) {
+        if (kb + SB < Lk) request(kb + SB);
+        __builtin_amdgcn_sched_barrier(0);
+        const float16v sc[2] = {scores(buf, 0), scores(buf, 1)};
+        float bmax = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bmax = fmaxf(bmax, sc[t][v]);
+        rescale(bmax);
+        const float shift = -run_max * scale;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) weigh(sc[t], buf, t, shift);
         __builtin_amdgcn_sched_barrier(0);
         if (kb + SB < Lk) put(buf ^ 1);
         __syncthreads();
+    }
+    // the block that the last key cuts: 32 keys at a time, as far as there are any
+#pragma unroll 1
+    for (int t = 0; kb + t * 32 < Lk; ++t) {
+        float16v s = scores(buf, t);
+        float bmax = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int key = kb + t * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
+            s[v] = key < Lk ? s[v] : -INFINITY;
+            bmax = fmaxf(bmax, s[v]);
+        }
+        rescale(bmax);
+        weigh(s, buf, t, -run_max * scale);
     }
     run_sum += __shfl_xor(run_sum, 32, 64);
     // (worked out again instead of kept: the loop uses all 128 registers of four waves per SIMD)

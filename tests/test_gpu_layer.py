@@ -671,8 +671,8 @@ def test_every_term_of_the_layer_matters(gpu, oracle_mod, prec, dims, B, L):
     LayerNorm gain, and stay inside the binary16 tolerance (tests/test_oracle_layer.py measures
     that on the reference).  Here weights are six times as large and gains, shifts and biases
     are random, on every route: float32; few-token, partial-sum and wide-tile matrix-core
-    GEMMs; attention with the scores in registers (up to 128 and up to 256 keys) and with the
-    running maximum (300 keys)."""
+    GEMMs; attention with all scores in registers (up to 128 keys) and with the running maximum
+    (more keys)."""
     wl = S.small_workload(31000 + B * L, dims, 2, B, L, n_absent=1, io_dtype="f32" if prec == "f32" else "f16")
     S.make_every_term_matter(wl, 77 + B)
     want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x)
@@ -1023,11 +1023,11 @@ def _run_masked(gpu, wl, prec, lens, route):
     ("mfma", MID, 3, 40, "layer"),      # two-wave workgroups, scores in registers
     ("mfma", MID, 2, 64, "model"),      # few-token route
     ("mfma", MID, 9, 128, "model"),
-    ("mfma", MID, 8, 200, "whole"),     # eight key blocks in registers, every layer's working buffer
+    ("mfma", MID, 8, 200, "whole"),     # keys in blocks of 64, every layer's working buffer
     ("mfma", MID, 48, 128, "model"),    # four-wave workgroups
     ("mfma", MID, 64, 128, "model"),    # attention inside the Q/K/V projection; 3 present heads: a tile with one head
     ("mfma", WIDE, 24, 128, "whole"),   # the same with 11 present heads, every layer's working buffer
-    ("mfma", MID, 7, 300, "whole"),     # online softmax
+    ("mfma", MID, 7, 300, "whole"),
     ("mfma", MID, 2, 512, "model"),
 ])
 def test_padded_sequences_match_the_reference(gpu, oracle_mod, prec, dims, B, L, route):
@@ -1045,6 +1045,16 @@ def test_padded_sequences_match_the_reference(gpu, oracle_mod, prec, dims, B, L,
     assert rel_err(plain.float().cpu().numpy(), want) > 3 * TOL[prec]
     full = _run_masked(gpu, wl, prec, np.full(B, L, dtype=np.int32), route)
     assert torch.equal(full, plain)
+
+
+@pytest.mark.parametrize("L", [129, 160, 161, 192, 224, 255])
+def test_attention_over_any_part_of_a_key_block(gpu, oracle_mod, L):
+    """Keys in blocks of 64: sequences whose last block holds 1, 31, 32, 33, 63 and 64 keys, or is the first."""
+    wl = S.small_workload(8700 + L, MID, 1, 12, L)
+    S.make_every_term_matter(wl, 5)
+    lens = np.array([L, 128, 127, 97, 96, 95, 65, 64, 63, 33, 32, 1], dtype=np.int32)
+    want = oracle_mod.model_forward(MID, wl.shards, wl.params, wl.x, key_lengths=lens)
+    assert_parity(_run_masked(gpu, wl, "mfma", lens, "layer").float().cpu().numpy(), want, TOL["mfma"])
 
 
 @pytest.mark.parametrize("dims,n_absent", [(MID, 1), (MID, 0), (WIDE, 3)])
