@@ -74,8 +74,9 @@ typedef enum { STI_F32 = 0, STI_F16 = 1, STI_BF16 = 2 } sti_dtype;
 /* STI_PREC_F32: float32 storage and arithmetic end to end (decode to a float32
  *   working buffer, then float32 kernels); any dimensions.
  * STI_PREC_F16_MFMA: binary16 operands on the matrix cores with float32
- *   accumulation.  With few tokens per call (up to 128; up to a few hundred at d_model
- *   256 .. 1024, depending on the layer's size) the projections decode the packed streams
+ *   accumulation.  With few tokens per call (up to 128; up to 192 when d_model <= 768; up to
+ *   between 128 and 1024, fewer for larger layers, at d_model 256 .. 1024: BERT-base 640,
+ *   d_model 1024 with 16 shards 512) the projections decode the packed streams
  *   inside their weight loader; with more tokens, and for shards that carry an outlier
  *   dictionary, a layer's shards are decompressed once into a binary16 working buffer in
  *   the workspace that the projections then read (every weight would otherwise be
@@ -433,7 +434,7 @@ sti_status sti_plan_bitwidths(const sti_plan_tables *tables, int32_t n, int32_t 
  *
  *  weights        DEVICE float32 [n_heads][Wsh]: the layer's shards at full precision
  *                 (the logical layout of Table 1), 16-byte aligned; Wsh % 1024 == 0
- *                 (STI_ERR_UNSUPPORTED otherwise); finite values.
+ *                 (STI_ERR_UNSUPPORTED otherwise); infinite and NaN: see below.
  *  packed         DEVICE out [n_heads][Wsh*k/8] bytes.
  *  codebook       DEVICE out float32 [2^k], ascending.
  *  outlier_pos/val DEVICE out [n_heads][max_outliers_per_shard]; entries beyond a
@@ -445,9 +446,11 @@ sti_status sti_plan_bitwidths(const sti_plan_tables *tables, int32_t n, int32_t 
  *                 (nothing to cluster; packed and codebook are meaningless).
  *  workspace      DEVICE, >= sti_quantize_workspace_bytes(dims), 256-byte aligned.
  * The moments (mean, variance) are accumulated in float64 in a fixed order.  The sum of a
- * cluster is formed from integer sums (weights times a power of two that leaves at least 46
- * bits below the largest) of fixed parts of the layer, added in float64 in a fixed order, so
- * that codebook, streams, dictionaries and outlier decisions are reproducible bit for bit.
+ * cluster is formed from integer sums of fixed parts of the layer, which hold every weight
+ * exactly, added in float64 in a fixed order, so that codebook, streams, dictionaries and
+ * outlier decisions are reproducible bit for bit.  An infinite or NaN weight makes the moments
+ * NaN: nothing is an outlier then, clusters follow the order of the bit patterns (-NaN below
+ * -infinity, NaN above infinity), and a cluster with such a weight has the mean that follows.
  * Errors as for the other entry points.
  * ------------------------------------------------------------------------- */
 typedef struct {
