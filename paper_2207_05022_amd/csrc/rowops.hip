@@ -97,8 +97,9 @@ __device__ inline float row_sum(float v)
     return v;
 }
 
-template <int DT, typename RT, bool TILED, int LPR, int MAXC>   // TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC
-__global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, int n_partials,
+// TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC; PLANES: partial sums requested together
+template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES>
+__global__ __launch_bounds__(LPR == 64 ? 64 : 256) void layernorm_vec_kernel(const float *pre, int n_partials,
                                                             int64_t partial_stride,
                                                             const float *bias, const RT *resid,
                                                             int resid_layout, int y_layout,
@@ -106,13 +107,13 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, in
                                                             const float *g, const float *b, int T,
                                                             int d, float eps)
 {
-    constexpr int ROWS = 256 / LPR;               // rows per workgroup
+    constexpr int ROWS = LPR == 64 ? 1 : 256 / LPR;   // rows per workgroup
     const int sub = threadIdx.x % LPR;
     const int row = blockIdx.x * ROWS + threadIdx.x / LPR;
     if (row >= T) return;   // whole row groups leave together; shuffles stay inside a group
     const int nchunk = d >> 2;
     // Every load of this row is independent of the others: they are issued in groups (bias and
-    // residual first, then the partial sums two planes at a time) and only then added, in the
+    // residual first, then the partial sums PLANES planes at a time) and only then added, in the
     // fixed order plane 0, 1, ..., bias, residual.  (Written as load-then-use per chunk, each of
     // up to 8 planes x 8 chunks cost a round trip to memory of its own.)  Lanes past the end of
     // the row load its last chunk and drop the value.
@@ -140,19 +141,20 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *pre, in
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float *rp = pre + (int64_t)row * d;
-    for (int sp = 0; sp < n_partials; sp += 2) {
-        const bool two = sp + 1 < n_partials;   // uniform
-        f32x4 t0[MAXC], t1[MAXC];
+    for (int sp = 0; sp < n_partials; sp += PLANES) {
+        f32x4 t[PLANES][MAXC];
 #pragma unroll
-        for (int j = 0; j < MAXC; ++j) {
-            t0[j] = *(const f32x4 *)(rp + (int64_t)sp * partial_stride + 4 * cj[j]);
-            t1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (two) t1[j] = *(const f32x4 *)(rp + (int64_t)(sp + 1) * partial_stride + 4 * cj[j]);
+        for (int k = 0; k < PLANES; ++k) {   // (planes past the last one: that one again, not added)
+            const int64_t plane = (int64_t)(PLANES > 1 ? min(sp + k, n_partials - 1) : sp) * partial_stride;
+#pragma unroll
+            for (int j = 0; j < MAXC; ++j) t[k][j] = *(const f32x4 *)(rp + plane + 4 * cj[j]);
         }
 #pragma unroll
-        for (int j = 0; j < MAXC; ++j) {
-            v[j] = sp == 0 ? t0[j] : v[j] + t0[j];
-            if (two) v[j] += t1[j];
+        for (int k = 0; k < PLANES; ++k) {
+            if (sp + k < n_partials) {       // uniform
+#pragma unroll
+                for (int j = 0; j < MAXC; ++j) v[j] = sp + k == 0 ? t[k][j] : v[j] + t[k][j];
+            }
         }
     }
     float s = 0.f;
@@ -335,23 +337,30 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
                      int T, int d, float eps, bool vec, hipStream_t stream)
 {
     typedef typename Elem<DT>::type O;
-    dim3 grid((T + 3) / 4);
-#define STI_LN_VEC(LPR, MAXC, GRID) \
-    launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC>), GRID, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, \
-           (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps)
-    // many rows: 32 lanes per row (8 rows per workgroup); few rows: a whole wave per row; chunks
-    // per lane sized to the row, so that the registers hold no more loads in flight than it has
+#define STI_LN_PLANES(LPR, MAXC, PLANES, GRID) \
+    launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC, PLANES>), dim3(GRID), dim3(LPR == 64 ? 64 : 256), 0, stream, pre, n_partials, \
+           partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps)
+#define STI_LN_VEC(LPR, MAXC, GRID)                                       \
+    do {                                                                  \
+        if (n_partials <= 1) STI_LN_PLANES(LPR, MAXC, 1, GRID);           \
+        else if (n_partials == 2) STI_LN_PLANES(LPR, MAXC, 2, GRID);      \
+        else STI_LN_PLANES(LPR, MAXC, 4, GRID);                           \
+    } while (0)
+    // many rows: 32 lanes per row (8 rows per workgroup); few rows: a wave and a workgroup per row, so that the rows spread
+    // over as many compute units as there are; chunks per lane sized to the row, so that the registers hold no more
+    // loads in flight than it has
     if (vec && T >= 2048 && d <= 1024) {
-        if (d <= 768) STI_LN_VEC(32, 6, dim3((T + 7) / 8));
-        else STI_LN_VEC(32, 8, dim3((T + 7) / 8));
+        if (d <= 768) STI_LN_VEC(32, 6, (T + 7) / 8);
+        else STI_LN_VEC(32, 8, (T + 7) / 8);
     } else if (vec) {
-        if (d <= 768) STI_LN_VEC(64, 3, grid);
-        else if (d <= 1024) STI_LN_VEC(64, 4, grid);
-        else STI_LN_VEC(64, 8, grid);
+        if (d <= 768) STI_LN_VEC(64, 3, T);
+        else if (d <= 1024) STI_LN_VEC(64, 4, T);
+        else STI_LN_VEC(64, 8, T);
     } else {
-        launch((layernorm_kernel<DT, RT>), grid, dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps);
+        launch((layernorm_kernel<DT, RT>), dim3((T + 3) / 4), dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps);
     }
 #undef STI_LN_VEC
+#undef STI_LN_PLANES
 }
 
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
