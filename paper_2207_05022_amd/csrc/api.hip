@@ -270,13 +270,8 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     if (prec != STI_PREC_F32) {
         out_planes = down_planes = gemm_wide_max_k_splits(T, (int)dm);
         if (few_token_path(d, T)) {
-            GemmProblem p;
-            memset(&p, 0, sizeof(p));
-            p.n_blocks = d.n_heads;
-            p.kind = GEMM_OUT; p.block_cols = d.d_head;
-            out_planes = few_k_splits(p);
-            p.kind = GEMM_FFN_DOWN; p.block_cols = d.ffn_per_shard;
-            down_planes = few_k_splits(p);
+            out_planes = few_max_k_splits(d.n_heads * d.d_head / 64);
+            down_planes = few_max_k_splits(d.n_heads * (d.ffn_per_shard / 64));
         }
     }
     if (!compact) {

@@ -173,6 +173,7 @@ hipError_t launch_attention_few(const void *qkv, void *ctx, int B, int L, int m,
 constexpr int kFewMaxTokens = 1024;
 constexpr int kFewMaxSplits = 8;
 int few_k_splits(const GemmProblem &p);
+int few_max_k_splits(int k_tiles);   // the most it can be for up to so many 64-wide K tiles (workspace sizing)
 hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                               int64_t partial_stride, hipStream_t stream);
 

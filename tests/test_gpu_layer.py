@@ -321,6 +321,12 @@ def test_mfma_full_size_every_term_matters(gpu, oracle_mod):
     (1024, 16, 256, 1, 300, True, False),  # more workgroups than compute units; ten key blocks for four waves
     (256, 4, 64, 2, 512, False, False),    # the longest sequence
     (512, 20, 64, 1, 130, False, False),   # more than 16 weight blocks
+    (320, 4, 320, 1, 97, True, False),     # K of 5 tiles and blocks of 5; four row blocks, the last with one row
+    (576, 9, 192, 1, 128, False, False),   # K of 9 tiles: twelve waves, three without one
+    (832, 13, 64, 2, 32, True, False),     # K of 13 tiles: sixteen waves
+    (1088, 17, 64, 1, 65, False, True),    # K of 17 tiles: eight waves, of which one has three
+    (960, 8, 256, 1, 330, True, False),    # K of 15 tiles over four waves
+    (896, 16, 192, 2, 200, False, False),  # 16 tiles to a K split of FFN2
 ])
 def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, outliers):
     """Edges of the few-token route: part row blocks, K splits, both attention kernels, float32 and binary16
