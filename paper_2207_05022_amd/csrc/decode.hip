@@ -251,15 +251,16 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Table table, uint64_t 
 namespace {
 
 template <typename Table>
-__global__ __launch_bounds__(256) void decode_tiled_kernel(Table tab, int total_cells,
-                                                           int d, int dh, int f, uint8_t *out)
+__global__ __launch_bounds__(256) void decode_tiled_kernel(uint8_t *out, int total_cells, int d, int dh, int f, int per_shard,
+                                                           uint32_t recip_shard, uint32_t recip_d, uint32_t recip_dh, uint32_t recip_f,
+                                                           Table tab)
 {
     __shared__ uint16_t lut[4][kLutEntries];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cell = blockIdx.x * 4 + wave;
     if (cell >= total_cells) return;   // whole wave; no workgroup barrier is used
-    decode_tiled_cell(tab, cell, d, dh, f, out, lut[wave], lane);
+    decode_tiled_cell(tab, cell, CellMap{d, dh, f, per_shard, recip_shard, recip_d, recip_dh, recip_f}, out, lut[wave], lane);
 }
 
 }  // namespace
@@ -394,8 +395,9 @@ hipError_t launch_decode_tiled(const InlineShardTable &table, int n_shards, int 
     const int64_t cells = wsh / 2048 * n_shards;
     if (cells == 0) return hipSuccess;
     if (d % 64 || dh % 64 || f % 64 || cells > 0x7FFFFFF0) return hipErrorInvalidValue;
-    launch((decode_tiled_kernel<TableInline>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, 
-        TableInline{table}, (int)cells, d, dh, f, (uint8_t *)out);
+    const CellMap m = cell_map(d, dh, f);
+    launch((decode_tiled_kernel<TableInline>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint8_t *)out, (int)cells,
+           d, dh, f, m.per_shard, m.recip_shard, m.recip_d, m.recip_dh, m.recip_f, TableInline{table});
     return hipGetLastError();
 }
 
@@ -406,8 +408,9 @@ hipError_t launch_decode_tiled_table(const ShardDesc *device_table, int n_shards
     const int64_t cells = wsh / 2048 * n_shards;
     if (cells == 0) return hipSuccess;
     if (d % 64 || dh % 64 || f % 64 || cells > 0x7FFFFFF0) return hipErrorInvalidValue;
-    launch((decode_tiled_kernel<TablePtr>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, 
-        TablePtr{device_table}, (int)cells, d, dh, f, (uint8_t *)out);
+    const CellMap m = cell_map(d, dh, f);
+    launch((decode_tiled_kernel<TablePtr>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint8_t *)out, (int)cells,
+           d, dh, f, m.per_shard, m.recip_shard, m.recip_d, m.recip_dh, m.recip_f, TablePtr{device_table});
     return hipGetLastError();
 }
 

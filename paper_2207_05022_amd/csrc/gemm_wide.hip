@@ -178,7 +178,7 @@ __device__ inline void decode_next_layer(const GemmProblem &p, int d, unsigned c
             const int cell = first + c * stride;
             bits[c] = 0;   // (no cell)
             if (cell < total) {
-                t[c] = locate_tiled_cell(cell, d, dh, f);
+                t[c] = locate_tiled_cell(cell, p.next_cells);
                 bits[c] = bits_of[t[c].shard];
                 raw[c] = load_tiled_cell_raw(t[c], bits[c], as_global(data_of[t[c].shard]), lane);
             }
@@ -246,9 +246,11 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // what the first loads of a workgroup depend on, as leading scalar arguments: these arrive
     // preloaded in scalar registers (the build asks for kernel-argument preloading), so that the
     // first A fetches and weight loads are not behind a round trip to the argument buffer
-    // (14 dwords fit: block_shape = block_rows | block_cols << 16, blocks_splits = n_blocks | k_splits << 16)
+    // (14 dwords fit: block_shape = block_rows | block_cols << 16, blocks_splits = n_blocks | k_splits << 16; reciprocals of the
+    // tiles of a band of the tile order and of a weight block's 32-row strips (N split) or K tiles: divisions in their place,
+    // one of them in every step of the K loop of O and FFN2, made 24 layers of d_model 1024, 24 x 384 tokens 1.2 % slower)
     const void *hot_A, const void *hot_w0, const void *hot_resid, const float *hot_bias0, int32_t hot_w_stride,
-    int32_t hot_T, int32_t hot_lda, int32_t hot_ldr, uint32_t hot_block_shape, uint32_t hot_blocks_splits,
+    int32_t hot_T, uint32_t hot_band_recip, uint32_t hot_block_recip, uint32_t hot_block_shape, uint32_t hot_blocks_splits,
     GemmProblem p, ShardIds shard_of)   // (of p, only the fields that are not among the leading arguments are read)
 {
     const int hot_block_rows = hot_block_shape & 0xffff, hot_block_cols = hot_block_shape >> 16;
@@ -272,7 +274,9 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // K is split over the KS wave groups of the workgroup and, for few tiles, over
     // gridDim.y workgroups per tile as well (raw float32 partial sums, see the epilogue)
     const int splits = (!n_split && hot_k_splits > 1) ? hot_k_splits : 1;
-    const int nkt = K / BK / KS / splits;  // K tiles of this wave's group
+    const int hot_lda = K, hot_ldr = hot_block_rows;   // (rows of A and of the residual follow each other)
+    int nkt = K / BK / KS;                 // K tiles of this wave's group
+    if (splits > 1) nkt /= splits;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = wave_all / NW, wave = wave_all - half * NW;   // K group, column strip
@@ -305,10 +309,12 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     }
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= total_tiles) return;
     const int group = n_tiles > kRowMajorColumnTiles ? kGroupRows : 1;
-    const int band = tile / (group * n_tiles);
+    const int band = quotient(tile, group * n_tiles, hot_band_recip);
     const int band_rows = min(group, m_tiles - band * group);   // the last band may be short
     const int in_band = tile - band * (group * n_tiles);
-    const int tile_n = in_band / band_rows;
+    int tile_n = in_band;
+    if (band_rows == kGroupRows) tile_n = in_band / kGroupRows;
+    else if (band_rows > 1) tile_n = in_band / band_rows;
     const int tile_m = band * group + (in_band - tile_n * band_rows);
     const int m0 = tile_m * BM;
     // N and the block widths are multiples of 64, so a wave's columns are all inside or all
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     const int nw = nw_real < N ? nw_real : 0;
     int nblk = 0, nrow0 = nw;
     if (n_split) {
-        nblk = nw / hot_block_rows;
+        nblk = quotient(nw >> 5, hot_block_rows >> 5, hot_block_recip);
         nrow0 = nw - nblk * hot_block_rows;
     }
     const int tiles_per_kblock = n_split ? nkt * KS : hot_block_cols / BK;
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
         if (n_split) {
             blk = nblk; ktb = kt; row = nrow0 + r * 32;
         } else {
-            blk = kt / tiles_per_kblock; ktb = kt - blk * tiles_per_kblock; row = nw + r * 32;
+            blk = quotient(kt, tiles_per_kblock, hot_block_recip); ktb = kt - blk * tiles_per_kblock; row = nw + r * 32;
         }
         // (the blocks of a working buffer lie at a constant distance: no look-up in the block table)
         const uint8_t *base = (const uint8_t *)hot_w0 + (int64_t)blk * hot_w_stride;   // (stride < 2^31)
@@ -417,8 +423,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             const float *bp;
             if constexpr (qkv) {
                 const int nrow = nrow0 + c;
-                const int which = nrow / p.d_head, e0 = nrow - which * p.d_head;
-                bp = (which == 0 ? hot_bias0 : (which == 1 ? p.bias1 : p.bias2)) + shard_of.id(nblk) * p.d_head + e0;
+                const int which = nrow / ATT_DH, e0 = nrow - which * ATT_DH;
+                bp = (which == 0 ? hot_bias0 : (which == 1 ? p.bias1 : p.bias2)) + shard_of.id(nblk) * ATT_DH + e0;
             } else if constexpr (KIND == GEMM_FFN_UP) {
                 bp = hot_bias0 + shard_of.id(nblk) * hot_block_rows + nrow0 + c;
             } else {
@@ -730,14 +736,19 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
         if (!p.next_table || !p.next_out || p.next_shards <= 0 || p.next_ffn_per_shard <= 0) return hipErrorInvalidValue;
         grid.x += p.next_shards * ((p.next_outliers + NT - 1) / NT);
     }
+    GemmProblem q = p;
+    if (p.next_workgroups > 0) q.next_cells = cell_map(p.block_cols, p.d_head, p.next_ffn_per_shard);
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
     ShardIds shard_of;   // (the kernel takes these instead of the block table: a shorter argument list is a cheaper launch)
     for (int b = 0; b < kMaxShardsPerLayer; b += 4)
         shard_of.id4[b / 4] = (uint32_t)blocks.b[b].shard | (uint32_t)blocks.b[b + 1].shard << 8 |
                               (uint32_t)blocks.b[b + 2].shard << 16 | (uint32_t)blocks.b[b + 3].shard << 24;
+    const int n_tiles = (N + BN - 1) / BN;
+    const uint32_t band_recip = reciprocal((n_tiles > kRowMajorColumnTiles ? kGroupRows : 1) * n_tiles);
+    const uint32_t block_recip = reciprocal(n_split ? p.block_rows / 32 : p.block_cols / BK);
     launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY, RB>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
-           p.resid, p.bias0, (int32_t)w_stride, p.T, p.lda, p.ldr, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
-           (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, p, shard_of);
+           p.resid, p.bias0, (int32_t)w_stride, p.T, band_recip, block_recip, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
+           (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, q, shard_of);
     return hipGetLastError();
 }
 
@@ -921,7 +932,11 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
     const int N = n_split ? p.n_blocks * p.block_rows : p.block_rows;
     if (p.T <= 0 || N <= 0) return hipSuccess;
     if (!gemm_wide_supported(p, blocks)) return hipErrorInvalidValue;
-    if (N % 32 || p.block_rows % 32 || p.block_cols % BK || p.lda % 8 || p.ldc % 8) return hipErrorInvalidValue;
+    if (N % 32 || p.block_rows % 32 || p.block_cols % BK || p.ldc % 8) return hipErrorInvalidValue;
+    // (the kernel takes these distances from the products' shapes)
+    if (p.lda != (n_split ? p.block_cols : p.n_blocks * p.block_cols) || (!n_split && p.ldr != p.block_rows) ||
+        ((p.kind == GEMM_QKV || p.kind == GEMM_QKV_ATTN) && p.d_head != ATT_DH))
+        return hipErrorInvalidValue;
     if (p.kind == GEMM_QKV_ATTN) {
         if (p.T % ATT_L || p.block_rows != 3 * ATT_DH || p.d_head != ATT_DH || p.ldc < p.n_blocks * ATT_DH)
             return hipErrorInvalidValue;

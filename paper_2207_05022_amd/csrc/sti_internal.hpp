@@ -78,12 +78,31 @@ __host__ __device__ inline int64_t tiled_offset(int row, int col, int cells)
            (col & 7);
 }
 
+// Quotients by a divisor that is the same for a whole launch: 5 instructions instead of the 35 dependent ones of a division of two
+// scalars.  q = c * floor(2^32 / d) / 2^32 is the quotient or one less, for every c.
+__host__ __device__ inline uint32_t reciprocal(uint32_t d) { return d <= 1 ? 0xFFFFFFFFu : (uint32_t)(((uint64_t)1 << 32) / d); }
+__device__ inline int quotient(int c, int d, uint32_t recip)   // c >= 0, d > 0
+{
+    const uint32_t q = __umulhi((uint32_t)c, recip);
+    return (int)(q + ((uint32_t)c - q * (uint32_t)d >= (uint32_t)d ? 1u : 0u));
+}
+
 // two values rounded to binary16 (nearest even) in one dword: one conversion instruction
 __device__ inline uint32_t f16_pair_bits(float lo, float hi)
 {
     typedef _Float16 half2v __attribute__((ext_vector_type(2)));
     const half2v h = {(_Float16)lo, (_Float16)hi};
     return __builtin_bit_cast(uint32_t, h);
+}
+
+struct CellMap {       // cells of the fragment-tiled working buffer (weight_loader.hpp): what a launch's cells have in common
+    int d, dh, f, per_shard;
+    uint32_t recip_shard, recip_d, recip_dh, recip_f;
+};
+inline CellMap cell_map(int d, int dh, int f)
+{
+    const int per_shard = (3 * dh / 32) * (d / 64) + (d / 32) * (dh / 64) + (f / 32) * (d / 64) + (d / 32) * (f / 64);
+    return CellMap{d, dh, f, per_shard, reciprocal(per_shard), reciprocal(d / 64), reciprocal(dh / 64), reciprocal(f / 64)};
 }
 
 struct GemmBlock {
@@ -127,6 +146,7 @@ struct GemmProblem {
     // wide-tile kernel, GEMM_OUT: with next_outliers > 0 workgroups beyond those of the tiles put the outlier dictionaries
     // of the next_shards shards of next_table (at most next_outliers entries each) into next_out
     int32_t next_outliers;
+    CellMap next_cells;   // (filled in by the launch)
 };
 
 // float32 path (layer_f32.hip): A and C are float32; weights are float32 blocks at a constant distance.

@@ -171,20 +171,20 @@ struct TiledCell {
     int strip, kt;     // 32-row strip and 64-column tile inside the sub-block
 };
 
-__device__ inline TiledCell locate_tiled_cell(int cell, int d, int dh, int f)
+__device__ inline TiledCell locate_tiled_cell(int cell, const CellMap &m)
 {
-    const int c_qkv = (3 * dh / 32) * (d / 64), c_o = (d / 32) * (dh / 64);
-    const int c_1 = (f / 32) * (d / 64), c_2 = (d / 32) * (f / 64);
-    const int per_shard = c_qkv + c_o + c_1 + c_2;
+    const int d = m.d, dh = m.dh, f = m.f;
+    const int c_qkv = (3 * dh / 32) * (d / 64), c_o = (d / 32) * (dh / 64), c_1 = (f / 32) * (d / 64);
     TiledCell t;
-    t.shard = cell / per_shard;
-    int c = cell - t.shard * per_shard;
-    if (c < c_qkv) { t.cols = d; t.sub_off = 0; }
-    else if (c < c_qkv + c_o) { c -= c_qkv; t.cols = dh; t.sub_off = (int64_t)3 * dh * d; }
-    else if (c < c_qkv + c_o + c_1) { c -= c_qkv + c_o; t.cols = d; t.sub_off = (int64_t)4 * dh * d; }
-    else { c -= c_qkv + c_o + c_1; t.cols = f; t.sub_off = (int64_t)4 * dh * d + (int64_t)f * d; }
+    t.shard = quotient(cell, m.per_shard, m.recip_shard);
+    int c = cell - t.shard * m.per_shard;
+    uint32_t recip;
+    if (c < c_qkv) { t.cols = d; recip = m.recip_d; t.sub_off = 0; }
+    else if (c < c_qkv + c_o) { c -= c_qkv; t.cols = dh; recip = m.recip_dh; t.sub_off = (int64_t)3 * dh * d; }
+    else if (c < c_qkv + c_o + c_1) { c -= c_qkv + c_o; t.cols = d; recip = m.recip_d; t.sub_off = (int64_t)4 * dh * d; }
+    else { c -= c_qkv + c_o + c_1; t.cols = f; recip = m.recip_f; t.sub_off = (int64_t)4 * dh * d + (int64_t)f * d; }
     const int tiles = t.cols >> 6;
-    t.strip = c / tiles;
+    t.strip = quotient(c, tiles, recip);
     t.kt = c - t.strip * tiles;
     return t;
 }
@@ -209,10 +209,10 @@ __device__ inline void store_tiled_cell(const TiledCell &t, int d, int dh, int f
 // One wave decodes cell number `cell` into the working buffer at `out`.  lut: 64 entries of LDS that
 // belong to this wave alone.
 template <typename Table>
-__device__ inline void decode_tiled_cell(const Table &tab, int cell, int d, int dh, int f, uint8_t *out,
+__device__ inline void decode_tiled_cell(const Table &tab, int cell, const CellMap &m, uint8_t *out,
                                          uint16_t *lut, int lane)
 {
-    const TiledCell t = locate_tiled_cell(cell, d, dh, f);
+    const TiledCell t = locate_tiled_cell(cell, m);
     const ShardDesc sd = tab.get(t.shard);
     const int bits = sd.bits;
     if (bits <= 6) {
@@ -228,7 +228,7 @@ __device__ inline void decode_tiled_cell(const Table &tab, int cell, int d, int 
     const Raw raw = load_tiled_cell_raw(t, bits, sd.data, lane);
     half8 fr[4];
     decode_raw_any(bits, raw, lut, fr);
-    store_tiled_cell(t, d, dh, f, fr, out, lane);
+    store_tiled_cell(t, m.d, m.dh, m.f, fr, out, lane);
 }
 
 // shard table in device memory
