@@ -201,16 +201,25 @@ sti_status check_decode_shard(const sti_shard &s)
 // Which GEMM family a matrix-core layer takes.  The few-token kernels decode every weight once per
 // 64-row block and take partial sums through LayerNorm; from some row blocks on it is cheaper to
 // decompress the layer once into the working buffer and run the wide-tile kernels.  Measured per layer (us,
-// few-token against working buffer, 6-bit mix, full shard set): BERT-base 128 tokens 34 / 51, 256 41 / 54,
-// 512 46 / 56, 640 53 / 59, 768 61 / 60; d_model 1024 x 16 shards 256 49 / 66, 512 68 / 85, 640 79 / 77; 512 x 8
-// shards of 128 neurons 1024 41 / 45, 1536 48 / 48; 256 x 4 of 64 1024 32 / 36; 1024 x 16 of 64 768 62 / 59, 1024 72 / 60;
-// 1024 x 8 of 256 768 57 / 61, 1024 68 / 62.  The work of a row block is its workgroups: columns of Q/K/V and FFN1, and
-// those of O and FFN2, which also split K and cost LayerNorm a plane per split.  Over 84 shapes (d_model 256 .. 1024, 64
-// to 256 neurons) at 256 .. 1024 tokens a line on n_heads (192 + ffn) + 4 d_model, counted per row block, is within 0.1 %
-// of the faster route on average; one on the workgroups of FFN1 alone had cost up to 27 %.  Dictionaries and
-// float32 shards, which this route decompresses to the working buffer or reads once per row block, leave the
-// line where it is (BERT-base 640 tokens 676 / 723 and 731 / 758 us per 12 layers).  Outside d_model 256 .. 1024 the line is
-// the older one, 128 tokens, or 192 when d_model <= 768.
+// few-token against working buffer, 6-bit mix, full shard set): BERT-base 640 tokens 48 / 57, 768 56 / 58, 896 62 / 59; d_model
+// 1024 x 16 shards 512 60 / 70, 640 68 / 71; 1024 x 16 of 64 neurons 768 54 / 58, 1024 59 / 59; 1024 x 8 of 256 896 59 / 60;
+// 640 x 9 of 192 1024 51 / 54; 512 x 8 of 128 1024 38 / 45.  What a row block costs grows with the columns of Q/K/V and FFN1, what
+// the other route costs with d_model: the line is 1 / tokens = a columns + b, a tenth below where the two meet, which is where they
+// meet for layers with outlier dictionaries (they take the working buffer on either route, here in launches of their own:
+// BERT-base 640 tokens 53 / 56, 768 58 / 56).  26 random shapes (d_model 256 .. 1024, 2 to 16 shards of 64 to 256 neurons, up to
+// half of them absent, a third with dictionaries) half a row block below the line: 0.5 % slower at most, 9 % faster on average.
+inline int64_t few_token_limit(const sti_dims &d);
+inline bool few_token_path(const sti_dims &d, int64_t T)
+{
+    if (T <= few_token_limit(d)) return true;
+    if (d.d_model < 256 || d.d_model > 1024 || d.ffn_per_shard > 256 || T > kFewMaxTokens) return false;
+    const int64_t columns = (int64_t)d.n_heads * (3 * d.d_head + d.ffn_per_shard);
+    return T <= 14000000 / (153 * columns + 420000) * 64;
+}
+
+// Up to here the workspace queries leave room for the few-token kernels only; between this and the line above for either family,
+// so that what is asked for and what is accepted does not depend on where that line lies (a call with less workspace than
+// the few-token kernels take there goes the other way).  128 tokens, or 192 when d_model <= 768, outside d_model 256 .. 1024.
 inline int64_t few_token_limit(const sti_dims &d)
 {
     const int64_t small = d.d_model <= 768 ? 192 : 128;
@@ -220,23 +229,17 @@ inline int64_t few_token_limit(const sti_dims &d)
                                         1024 / ((int64_t)d.n_heads * (d.ffn_per_shard / 32)));   // more than 256 neurons: FFN1 alone
     return std::max(small, std::min<int64_t>(kFewMaxTokens, row_blocks * 64));
 }
-inline bool few_token_path(const sti_dims &d, int64_t T) { return T <= few_token_limit(d); }
-
-// Layers of few tokens keep their activations tiled.
-inline ActLayout inner_layout(const sti_dims &d, int64_t T, sti_precision prec)
-{
-    return prec == STI_PREC_F16_MFMA && few_token_path(d, T) ? LAYOUT_TILED : LAYOUT_ROWS;
-}
 
 constexpr uint64_t kRidingEntries = 65536;
 constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
 
 
 // Offsets of the scratch regions of one layer call (sized for all M shards present).
-WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers, bool compact)
+WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, bool few, int model_layers, bool compact)
 {
     WorkspaceLayout L;
-    L.inner = compact ? LAYOUT_ROWS : inner_layout(d, T, prec);
+    L.few = few && prec == STI_PREC_F16_MFMA;
+    L.inner = L.few && !compact ? LAYOUT_TILED : LAYOUT_ROWS;   // (layers of few tokens keep their activations tiled)
     const size_t es = (prec == STI_PREC_F32) ? 4 : 2;
     const size_t M = d.n_heads, dm = d.d_model, dh = d.d_head, f = d.ffn_per_shard;
     if (prec != STI_PREC_F32 && model_layers > 1) {
@@ -269,7 +272,7 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     size_t out_planes = 1, down_planes = 1;
     if (prec != STI_PREC_F32) {
         out_planes = down_planes = gemm_wide_max_k_splits(T, (int)dm);
-        if (few_token_path(d, T)) {
+        if (L.few) {
             out_planes = few_max_k_splits(d.n_heads * d.d_head / 64);
             down_planes = few_max_k_splits(d.n_heads * (d.ffn_per_shard / 64));
         }
@@ -295,19 +298,30 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     return L;
 }
 
+WorkspaceLayout layout_within(const sti_dims &d, int64_t T, sti_precision prec, size_t bytes)
+{
+    const bool few = few_token_path(d, T);
+    const WorkspaceLayout wl = workspace_layout(d, T, prec, few);
+    return wl.total <= bytes || !few || T <= few_token_limit(d) ? wl : workspace_layout(d, T, prec, false);
+}
+
 // What a caller has to provide for up to T tokens: a smaller call can need more than a larger one where
 // the larger one takes another route or fewer partial sums, so the numbers of tokens at which that happens
 // are looked at, too.
 size_t workspace_query(const sti_dims &d, int64_t T, sti_precision prec, int n_layers)
 {
     auto bytes = [&](int64_t t) {
-        const bool whole_model = prec == STI_PREC_F16_MFMA && !few_token_path(d, t) && n_layers > 1;
-        return workspace_layout(d, t, prec, whole_model ? n_layers : 1).total;
+        const bool wide = prec == STI_PREC_F16_MFMA && t > few_token_limit(d);
+        const size_t w = workspace_layout(d, t, prec, !wide, wide && n_layers > 1 ? n_layers : 1).total;
+        return wide && few_token_path(d, t) ? std::max(w, workspace_layout(d, t, prec, true).total) : w;
     };
     size_t most = bytes(T);
-    if (prec == STI_PREC_F16_MFMA)
-        for (int64_t t : {few_token_limit(d), gemm_wide_most_tokens(4, d.d_model), gemm_wide_most_tokens(2, d.d_model)})
+    if (prec == STI_PREC_F16_MFMA) {
+        int64_t last_few = few_token_limit(d);   // the last number of tokens that the few-token kernels take
+        for (int64_t t = last_few + 64; t <= std::min<int64_t>(T, kFewMaxTokens) && few_token_path(d, t); t += 64) last_few = t;
+        for (int64_t t : {few_token_limit(d), last_few, gemm_wide_most_tokens(4, d.d_model), gemm_wide_most_tokens(2, d.d_model)})
             if (t < T) most = std::max(most, bytes(t));
+    }
     return most ? most : 256;
 }
 
@@ -378,7 +392,7 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
 // binary16 (MFMA precision); `out` is written as out_dtype.
 int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_next, bool grouped, sti_precision prec)
 {
-    if (prec != STI_PREC_F16_MFMA || m <= 0 || few_token_path(d, (int64_t)B * Lseq)) return 0;
+    if (prec != STI_PREC_F16_MFMA || m <= 0) return 0;
     GemmProblem p;
     memset(&p, 0, sizeof(p));
     p.kind = gemm_wide_fuses_attention(B, Lseq, m, d.d_head) ? GEMM_QKV_ATTN : GEMM_QKV;
@@ -415,7 +429,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         if (shards[present[p]].n_outliers > max_outliers) max_outliers = shards[present[p]].n_outliers;
     // shards with an outlier dictionary always go through the working buffer, where the
     // outliers are scattered back after the substitution pass
-    const bool predecode = !f32 && m > 0 && (predecoded || !few_token_path(d, T) || max_outliers > 0);
+    const bool predecode = !f32 && m > 0 && (predecoded || !wl.few || max_outliers > 0);
     const _Float16 *w16 = predecoded ? (const _Float16 *)predecoded : (const _Float16 *)(ws + wl.w16);
     if (predecode && !predecoded) {
         InlineShardTable t;
@@ -462,7 +476,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     const sti_dtype act_dtype = f32 ? STI_F32 : STI_F16;
     // (a layer with every shard absent has nothing to multiply: its two LayerNorms run alone, over
     //  bias + residual, like those behind the few-token kernels)
-    const bool skinny = !f32 && (few_token_path(d, T) || m == 0);
+    const bool skinny = !f32 && (wl.few || m == 0);
     const bool no_products = m == 0;
     const int64_t partial_stride = (int64_t)T * dm;
     int pre_partials = 1;   // partial sums the last K-split GEMM left in `pre`
@@ -632,8 +646,8 @@ hipError_t static_scratch(uint8_t **out)
 // The usual buffers if they fit `bytes`, else as few bytes as the layer can do with.
 WorkspaceLayout fitting_layout(const sti_dims &d, int64_t T, sti_precision prec, size_t bytes)
 {
-    const WorkspaceLayout wl = workspace_layout(d, T, prec);
-    return wl.total <= bytes || prec == STI_PREC_F32 ? wl : workspace_layout(d, T, prec, 1, true);
+    const WorkspaceLayout wl = layout_within(d, T, prec, bytes);
+    return wl.total <= bytes || prec == STI_PREC_F32 ? wl : workspace_layout(d, T, prec, T <= few_token_limit(d), 1, true);
 }
 
 // masked: the call came through a *_masked entry point and key_lengths must be usable
@@ -661,7 +675,7 @@ sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
         if (st != STI_OK) return st;
     }
     const WorkspaceLayout wl = fixed_workspace ? fitting_layout(*dims, T, precision, workspace_bytes)
-                                               : workspace_layout(*dims, T, precision);
+                                               : layout_within(*dims, T, precision, workspace_bytes);
     if (!workspace || workspace_bytes < wl.total) return STI_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return STI_ERR_ALIGN;
     if (T == 0) return STI_OK;
@@ -937,19 +951,19 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
     // With room for every layer's working buffer (sti_model_workspace_bytes) the model is
     // decompressed a few layers per launch (below); otherwise each layer decompresses into the
     // one buffer just before it runs.
-    WorkspaceLayout wl = workspace_layout(*dims, T, precision);
+    WorkspaceLayout wl = layout_within(*dims, T, precision, workspace_bytes);
     hipStream_t stream = (hipStream_t)hip_stream;
     // (under stream capture the grouped route, whose shard table goes through the staging
     //  ring, is not taken: the per-layer route records kernel launches only)
     bool whole_model_fits =
-        precision == STI_PREC_F16_MFMA && !few_token_path(*dims, T) && n_layers > 1 && workspace &&
-        aligned(workspace, 256) && workspace_bytes >= workspace_layout(*dims, T, precision, n_layers).total;
+        precision == STI_PREC_F16_MFMA && !wl.few && n_layers > 1 && workspace &&
+        aligned(workspace, 256) && workspace_bytes >= workspace_layout(*dims, T, precision, false, n_layers).total;
     if (whole_model_fits) {
         bool capturing = false;
         if (stream_is_capturing(stream, &capturing) != hipSuccess) return STI_ERR_HIP;
         if (capturing) whole_model_fits = false;
     }
-    if (whole_model_fits) wl = workspace_layout(*dims, T, precision, n_layers);
+    if (whole_model_fits) wl = workspace_layout(*dims, T, precision, false, n_layers);
     if (!workspace || workspace_bytes < wl.total) return STI_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return STI_ERR_ALIGN;
     if (T == 0) return STI_OK;

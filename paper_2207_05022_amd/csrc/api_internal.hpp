@@ -17,6 +17,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct WorkspaceLayout {
     size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
     size_t pre_out = 0, pre_down = 0;   // sums before LayerNorm of the O and of the FFN2 product (compact: over other buffers)
+    bool few = false;                   // the layers take the few-token kernels
     ActLayout inner = LAYOUT_ROWS;      // how the layers of the call hand activations on
     int w16_layers = 1;   // layers the binary16 working buffer holds at once (a ring: layer l in slot l % w16_layers)
     int decode_group = 1; // layers that one decompression launch of sti_model_forward takes (<= w16_layers)
@@ -25,7 +26,10 @@ struct WorkspaceLayout {
 // layers as one decompression launch takes (64 MiB worth), at least two, so that a layer can be
 // decompressed while the one before it computes - and the device copy of the whole model's shard table.
 // compact (binary16 only): activations row by row without padding, sums before LayerNorm over buffers that are read by then.
-WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, int model_layers = 1, bool compact = false);
+// few (binary16 only): for the few-token kernels.
+WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision prec, bool few, int model_layers = 1, bool compact = false);
+// That of one layer at a time on the route that T tokens take with a workspace of `bytes` (its total may be more than that).
+WorkspaceLayout layout_within(const sti_dims &d, int64_t T, sti_precision prec, size_t bytes);
 
 sti_status check_dims(const sti_dims *dims, int batch, int seq, sti_precision prec);
 sti_status check_decode_shard(const sti_shard &s);   // bitwidth 2..6 or 32, pointers, alignment

@@ -249,7 +249,7 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
             c = v;
         }
     }
-    const WorkspaceLayout wl = workspace_layout(*dims, T, precision);
+    const WorkspaceLayout wl = layout_within(*dims, T, precision, workspace_bytes);
     if (!workspace || workspace_bytes < wl.total) return STI_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return STI_ERR_ALIGN;
     if (T == 0) return STI_OK;

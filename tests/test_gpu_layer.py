@@ -327,6 +327,7 @@ def test_mfma_full_size_every_term_matters(gpu, oracle_mod):
     (1088, 17, 64, 1, 65, False, True),    # K of 17 tiles: eight waves, of which one has three
     (960, 8, 256, 1, 330, True, False),    # K of 15 tiles over four waves
     (896, 16, 192, 2, 200, False, False),  # 16 tiles to a K split of FFN2
+    (768, 12, 256, 5, 140, True, False),   # where the workspace queries leave room for either route
 ])
 def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, outliers):
     """Edges of the few-token route: part row blocks, K splits, both attention kernels, float32 and binary16
@@ -344,6 +345,21 @@ def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, o
         want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x, key_lengths=lens)
         got = _run_masked(gpu, wl, "mfma", lens, "model").float().cpu().numpy()
         assert_parity(got, want, TOL["mfma"], io)
+
+
+def test_less_workspace_than_the_few_token_kernels_take(gpu, oracle_mod):
+    """Between the two lines a call that has room for the wide-tile kernels only is accepted and takes those."""
+    torch, P, D = gpu
+    wl = S.small_workload(41900, S.Dims(768, 12, 64, 256, 1e-12), 1, 5, 140, n_absent=1)
+    S.make_every_term_matter(wl, 3, amp=2.0)
+    want = oracle_mod.model_forward(wl.dims, wl.shards, wl.params, wl.x)
+    shards, params, x = D.upload_workload(wl)
+    nbytes = P.sti_workspace_bytes(wl.dims, 5, 140, P.STI_PREC_F16_MFMA)
+    for n in (nbytes, nbytes - 1):
+        y = torch.full_like(x, float("nan"))
+        P.sti_layer_forward(wl.dims, shards[0], params[0], x, y, P.STI_PREC_F16_MFMA, torch.empty(n, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert_parity(y.cpu().numpy(), want, TOL["mfma"])
 
 
 @pytest.mark.parametrize("prec,dims,B,L", [("f32", SMALL, 2, 19), ("mfma", MID, 1, 66), ("mfma", MID, 12, 100), ("mfma", MID, 64, 128)])
