@@ -230,6 +230,40 @@ inline int64_t few_token_limit(const sti_dims &d)
     return std::max(small, std::min<int64_t>(kFewMaxTokens, row_blocks * 64));
 }
 
+// Whether float32 layers go through the bfloat16 matrix cores (three planes per operand, gemm_f32_split.hip): from 3e9 multiplications
+// per layer on.  4 layers, us, float32 against bfloat16 matrix instructions: BERT-base 256 tokens (1.8e9) 332 / 329, 512 (3.6e9)
+// 470 / 435, 2046 (14.5e9) 1308 / 1088; d_model 704 x 11 shards, 450 tokens (2.2e9) 374 / 402; 1024 x 16, 256 tokens (3.2e9) 464 / 421;
+// 512 x 8 of 128 neurons, 1024 tokens (2.1e9) 341 / 325, 2048 (4.3e9) 512 / 453; 384 x 6, 2048 tokens (3.6e9) 486 / 446.
+inline bool split_path(const sti_dims &d, int64_t T)
+{
+    if (d.d_head != 64 || d.d_model % 64 || d.ffn_per_shard % 64) return false;
+    return (double)T * d.n_heads * d.d_model * (4 * d.d_head + 2 * d.ffn_per_shard) >= 3e9;
+}
+
+// Planes take six bytes where float32 values take four.  They lie in the buffers of the float32 layer all the same, so that no call needs
+// more workspace: of the weights Q, K, V and O are there at first, both FFN matrices later; of the activations, from the place of Q/K/V on,
+//   [ context, then first LayerNorm's rows | Q/K/V, then sums of O          |      input ]
+//   [ sums of FFN2            |                 neurons, then the next layer's input     ]
+// and the first LayerNorm's rows in float32 behind them.  Layers whose dimensions do not let that fit stay as they are.
+void place_split(const sti_dims &d, int64_t T, WorkspaceLayout &L)
+{
+    const size_t M = d.n_heads, dm = d.d_model, dh = d.d_head, f = d.ffn_per_shard;
+    const size_t Tb = ((size_t)T + 31) / 32 * 32, sums = (size_t)T * dm * 4;
+    if (L.total < sums + 256) return;
+    const size_t begin = L.qkv, h32 = (L.total - sums) / 256 * 256;
+    const size_t in = Tb * dm * 6, ctx = Tb * M * dh * 6, u = Tb * M * f * 6, qkv = (size_t)T * M * 3 * dh * 4;
+    const size_t at_qkv = align_up(begin + std::max(in, ctx), 256);
+    if (M * dm * f * 12 > M * dm * (4 * dh + 2 * f) * 4) return;                       // both FFN matrices in the place of the weights
+    if (h32 < begin + u + in || h32 < in + at_qkv + qkv || h32 < at_qkv + sums) return;
+    L.s_end = h32;
+    L.s_h32 = h32;
+    L.s_ctx = L.s_h = begin;
+    L.s_qkv = at_qkv;
+    L.s_in = (h32 - in) / 256 * 256;
+    L.s_u = (h32 - u) / 256 * 256;
+    L.split = L.s_in >= at_qkv + qkv && L.s_u >= begin + in && L.s_in >= L.s_u && L.s_u >= begin + sums;
+}
+
 constexpr uint64_t kRidingEntries = 65536;
 constexpr int kF32MaxSplits = 8;   // K splits of the float32 products (planes LayerNorm adds)
 
@@ -295,6 +329,7 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     L.u = take(Tb * M * f * es);
     if (L.w16_layers > 1) L.table = take((size_t)model_layers * M * sizeof(ShardDesc));
     L.total = off;
+    if (prec == STI_PREC_F32 && split_path(d, T)) place_split(d, T, L);
     return L;
 }
 
@@ -310,18 +345,20 @@ WorkspaceLayout layout_within(const sti_dims &d, int64_t T, sti_precision prec, 
 // are looked at, too.
 size_t workspace_query(const sti_dims &d, int64_t T, sti_precision prec, int n_layers)
 {
+    if (prec == STI_PREC_F32) {
+        const size_t most = workspace_layout(d, T, prec, false).total;
+        return most ? most : 256;
+    }
     auto bytes = [&](int64_t t) {
-        const bool wide = prec == STI_PREC_F16_MFMA && t > few_token_limit(d);
+        const bool wide = t > few_token_limit(d);
         const size_t w = workspace_layout(d, t, prec, !wide, wide && n_layers > 1 ? n_layers : 1).total;
         return wide && few_token_path(d, t) ? std::max(w, workspace_layout(d, t, prec, true).total) : w;
     };
     size_t most = bytes(T);
-    if (prec == STI_PREC_F16_MFMA) {
-        int64_t last_few = few_token_limit(d);   // the last number of tokens that the few-token kernels take
-        for (int64_t t = last_few + 64; t <= std::min<int64_t>(T, kFewMaxTokens) && few_token_path(d, t); t += 64) last_few = t;
-        for (int64_t t : {few_token_limit(d), last_few, gemm_wide_most_tokens(4, d.d_model), gemm_wide_most_tokens(2, d.d_model)})
-            if (t < T) most = std::max(most, bytes(t));
-    }
+    int64_t last_few = few_token_limit(d);   // the last number of tokens that the few-token kernels take
+    for (int64_t t = last_few + 64; t <= std::min<int64_t>(T, kFewMaxTokens) && few_token_path(d, t); t += 64) last_few = t;
+    for (int64_t t : {few_token_limit(d), last_few, gemm_wide_most_tokens(4, d.d_model), gemm_wide_most_tokens(2, d.d_model)})
+        if (t < T) most = std::max(most, bytes(t));
     return most ? most : 256;
 }
 
@@ -378,13 +415,16 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
     *in = x;
     *in_layout = LAYOUT_ROWS;
     *in_buffer = io_dtype != act;
-    if (io_dtype == act) return STI_OK;
-    *in = ws + wl.act[0];
-    *in_layout = wl.inner;
-    STI_TRY(timed(STI_K_CONVERT, stream, [&] {
-        return *in_layout == LAYOUT_TILED ? launch_tile_rows(x, io_dtype, ws + wl.act[0], (int)T, d.d_model, stream)
-                                          : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
-    }));
+    if (*in_buffer) {
+        *in = ws + wl.act[0];
+        *in_layout = wl.inner;
+        STI_TRY(timed(STI_K_CONVERT, stream, [&] {
+            return *in_layout == LAYOUT_TILED ? launch_tile_rows(x, io_dtype, ws + wl.act[0], (int)T, d.d_model, stream)
+                                              : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
+        }));
+    }
+    if (wl.split)
+        STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)*in, ws + wl.s_in, (int)T, d.d_model, stream); }));
     return STI_OK;
 }
 
@@ -405,7 +445,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded, const int32_t *key_lengths, const NextLayerDecode *next,
-                     ActLayout in_layout, ActLayout out_layout)
+                     ActLayout in_layout, ActLayout out_layout, bool last)
 {
     const int dm = d.d_model, M = d.n_heads, dh = d.d_head, f = d.ffn_per_shard;
     const int T = B * Lseq;
@@ -430,6 +470,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     // shards with an outlier dictionary always go through the working buffer, where the
     // outliers are scattered back after the substitution pass
     const bool predecode = !f32 && m > 0 && (predecoded || !wl.few || max_outliers > 0);
+    const bool split = wl.split && max_outliers == 0;   // (dictionaries are put into float32 weights)
     const _Float16 *w16 = predecoded ? (const _Float16 *)predecoded : (const _Float16 *)(ws + wl.w16);
     if (predecode && !predecoded) {
         InlineShardTable t;
@@ -448,7 +489,10 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             const sti_shard &s = shards[present[p]];
             t.d[p] = make_desc(s, present[p]);
         }
-        STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode(nullptr, &t, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream); }));
+        STI_TRY(timed(STI_K_DECODE, stream, [&] {
+            return split ? launch_decode_split(t, m, dm, dh, f, false, ws + wl.w32, stream)
+                         : launch_decode(nullptr, &t, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream);
+        }));
     }
     for (int p = 0; p < m; ++p) {
         const sti_shard &s = shards[present[p]];
@@ -458,6 +502,13 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             bo.b[p] = GemmBlock{w + off_o, nullptr, 32, present[p]};
             b1.b[p] = GemmBlock{w + off_1, nullptr, 32, present[p]};
             b2.b[p] = GemmBlock{w + off_2, nullptr, 32, present[p]};
+            if (split) {   // Q, K, V and O shard by shard; later all of FFN2, then all of FFN1
+                const uint8_t *w6 = ws + wl.w32;
+                bq.b[p].w = w6 + (size_t)p * off_1 * 6;
+                bo.b[p].w = w6 + ((size_t)p * off_1 + off_o) * 6;
+                b2.b[p].w = w6 + (size_t)p * (off_2 - off_1) * 6;
+                b1.b[p].w = w6 + (size_t)(m + p) * (off_2 - off_1) * 6;
+            }
         } else if (predecode) {
             const _Float16 *w = w16 + (size_t)p * wsh;
             bq.b[p] = GemmBlock{w, nullptr, 17, present[p]};
@@ -471,7 +522,8 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             b2.b[p] = GemmBlock{block_start(s, off_2), s.codebook, s.bitwidth, present[p]};
         }
     }
-    void *qkv = ws + wl.qkv, *ctx = ws + wl.ctx, *h = ws + wl.h, *u = ws + wl.u;
+    void *qkv = ws + (split ? wl.s_qkv : wl.qkv), *ctx = ws + (split ? wl.s_ctx : wl.ctx), *h = ws + (split ? wl.s_h32 : wl.h);
+    void *u = ws + (split ? wl.s_u : wl.u);
     float *pre = (float *)(ws + wl.pre_out);
     const sti_dtype act_dtype = f32 ? STI_F32 : STI_F16;
     // (a layer with every shard absent has nothing to multiply: its two LayerNorms run alone, over
@@ -483,9 +535,9 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     // float32: the O and FFN2 products leave partial sums in buffers that are free by then (O: Q/K/V;
     // FFN2: Q/K/V, context and `pre`, which lie behind each other)
     int f32_planes = 1;
-    auto f32_sums = [&](size_t end) {
-        f32_planes = (int)std::min<size_t>(kF32MaxSplits, (end - wl.qkv) / ((size_t)partial_stride * 4));
-        pre = (float *)(ws + (f32_planes >= 1 ? wl.qkv : wl.pre_out));
+    auto f32_sums = [&](size_t begin, size_t end) {
+        f32_planes = (int)std::min<size_t>(kF32MaxSplits, (end - begin) / ((size_t)partial_stride * 4));
+        pre = (float *)(ws + (f32_planes >= 1 ? begin : wl.pre_out));
         if (f32_planes < 1) f32_planes = 1;
     };
     auto gemm = [&](const GemmProblem &p, const GemmBlocks &blk) {
@@ -496,7 +548,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                 GemmProblem q = p;
                 q.partial_stride = partial_stride;
                 int splits = 1;
-                const hipError_t e = launch_gemm_f32(q, blk, f32_planes, &splits, stream);
+                const hipError_t e = split ? launch_gemm_split(q, blk, f32_planes, &splits, stream) : launch_gemm_f32(q, blk, f32_planes, &splits, stream);
                 if (p.kind == GEMM_OUT || p.kind == GEMM_FFN_DOWN) pre_partials = splits;
                 return e;
             }
@@ -516,12 +568,12 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     };
     // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM
     auto layernorm = [&](void *dst, sti_dtype dt, ActLayout dst_layout, const float *g, const float *b,
-                         const float *bias, const void *resid, ActLayout resid_layout) {
+                         const float *bias, const void *resid, ActLayout resid_layout, void *planes) {
         return timed(STI_K_LAYERNORM, stream, [&] {
             if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
             return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32, resid_layout, dst, dt, dst_layout,
-                                    g, b, T, dm, d.ln_eps, stream);
+                                    g, b, T, dm, d.ln_eps, stream, planes);
         });
     };
 
@@ -533,7 +585,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         memset(&p, 0, sizeof(p));
         p.a_layout = in_layout; p.c_layout = few_attention ? LAYOUT_TILED : LAYOUT_ROWS;
         p.kind = GEMM_QKV; p.T = T; p.n_blocks = m; p.block_rows = 3 * dh; p.block_cols = dm;
-        p.d_head = dh; p.A = in; p.lda = dm; p.C = qkv; p.ldc = m * 3 * dh;
+        p.d_head = dh; p.A = split ? ws + wl.s_in : in; p.lda = dm; p.C = qkv; p.ldc = m * 3 * dh;
         p.bias0 = prm.bq; p.bias1 = prm.bk; p.bias2 = prm.bv;
         if (!f32 && !skinny && gemm_wide_fuses_attention(B, Lseq, m, dh)) {
             // sequences of 128 tokens: the projection's 128-row tiles are whole sequences, and its
@@ -552,14 +604,14 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             }
             STI_TRY(gemm(p, bq));
             STI_TRY(timed(STI_K_ATTENTION, stream, [&] {
-                if (f32) return launch_attention_f32((const float *)qkv, (float *)ctx, B, Lseq, m, dh, key_lengths, stream);
+                if (f32) return launch_attention_f32((const float *)qkv, ctx, split, B, Lseq, m, dh, key_lengths, stream);
                 if (few_attention) return launch_attention_few(qkv, ctx, B, Lseq, m, dh, key_lengths, stream);
                 return launch_attention_mfma(qkv, ctx, inner, B, Lseq, m, dh, key_lengths, stream);
             }));
         }
     }
     memset(&p, 0, sizeof(p));
-    if (f32) f32_sums(wl.ctx);
+    if (f32) f32_sums(split ? wl.s_qkv : wl.qkv, split ? wl.s_end : wl.ctx);
     p.a_layout = inner;
     p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
     p.A = ctx; p.lda = m * dh; p.C = pre; p.ldc = dm; p.bias0 = prm.bo; p.resid = in; p.ldr = dm;
@@ -569,16 +621,26 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     }
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, bo));
-    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout));
+    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, split ? ws + wl.s_h : nullptr));
+    if (split) {
+        InlineShardTable t;
+        memset(&t, 0, sizeof(t));
+        for (int p = 0; p < m; ++p) t.d[p] = make_desc(shards[present[p]], present[p]);
+        STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode_split(t, m, dm, dh, f, true, ws + wl.w32, stream); }));
+    }
     if (m > 0) {
         memset(&p, 0, sizeof(p));
         p.a_layout = inner; p.c_layout = inner;
         p.kind = GEMM_FFN_UP; p.T = T; p.n_blocks = m; p.block_rows = f; p.block_cols = dm;
-        p.d_head = dh; p.A = h; p.lda = dm; p.C = u; p.ldc = m * f; p.bias0 = prm.b1;
+        p.d_head = dh; p.A = split ? ws + wl.s_h : h; p.lda = dm; p.C = u; p.ldc = m * f; p.bias0 = prm.b1;
         STI_TRY(gemm(p, b1));
     }
     memset(&p, 0, sizeof(p));
-    if (f32) f32_sums(wl.h);
+    if (split) {   // in front of the neurons, or where FFN1's weights were: whichever takes more
+        const size_t ffn = (size_t)m * (off_2 - off_1) * 6;
+        if (ffn > wl.s_u - wl.s_ctx) f32_sums(align_up(wl.w32 + ffn, 256), wl.w32 + 2 * ffn);
+        else f32_sums(wl.s_ctx, wl.s_u);
+    } else if (f32) f32_sums(wl.qkv, wl.h);
     else pre = (float *)(ws + wl.pre_down);
     p.a_layout = inner;
     p.kind = GEMM_FFN_DOWN; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = f;
@@ -586,7 +648,9 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.ldr = dm;
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
-    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner));
+    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && !last ? ws + wl.s_in : nullptr));
+    if (wl.split && !split && !last)   // (the buffers of such a layer lie otherwise: its rows cannot go there before it has ended)
+        STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)out, ws + wl.s_in, T, dm, stream); }));
     return STI_OK;
 }
 
@@ -1087,7 +1151,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         const void *predecoded = whole_model_fits ? (const void *)w16_of(l) : nullptr;
         st = run_layer(*dims, &chosen[(size_t)l * M], params[l], cur, out, last ? io_dtype : act,
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
-                       next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner);
+                       next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner, last);
         if (st != STI_OK) return st;
         if (next_decode.workgroups > 0 && next_decode.max_outliers == 0) {
             st = patch_layer(l + 1);

@@ -18,6 +18,10 @@ struct WorkspaceLayout {
     size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
     size_t pre_out = 0, pre_down = 0;   // sums before LayerNorm of the O and of the FFN2 product (compact: over other buffers)
     bool few = false;                   // the layers take the few-token kernels
+    bool split = false;                 // float32 layers without outlier dictionaries take the bfloat16 matrix cores
+    // ... whose buffers lie over those of the others: planes of a layer's input, context, first LayerNorm's rows, neurons; Q/K/V and
+    // the first LayerNorm's rows in float32; the end of the region that holds all but the last of these
+    size_t s_in = 0, s_ctx = 0, s_h = 0, s_u = 0, s_qkv = 0, s_h32 = 0, s_end = 0;
     ActLayout inner = LAYOUT_ROWS;      // how the layers of the call hand activations on
     int w16_layers = 1;   // layers the binary16 working buffer holds at once (a ring: layer l in slot l % w16_layers)
     int decode_group = 1; // layers that one decompression launch of sti_model_forward takes (<= w16_layers)
@@ -58,7 +62,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded = nullptr, const int32_t *key_lengths = nullptr,
                      const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
-                     ActLayout out_layout = LAYOUT_ROWS);
+                     ActLayout out_layout = LAYOUT_ROWS, bool last = true);
 // The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
 // otherwise converted into the first activation buffer (in_buffer: whether it is there).
 sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
@@ -66,6 +70,7 @@ sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_
 // `predecoded`: the layer's present shards already sit there in fragment-tiled binary16 order
 // (outliers applied); run_layer then decompresses nothing.
 // `key_lengths` (device, [B]): real positions per padded sequence; null = every position is real.
+// `last`: no layer of the call follows (otherwise `out` is left as planes, too, where wl.split).
 // `next` (only with `predecoded`, and only when spare_decode_workgroups says so for this layer).
 // Layouts of `in` and `out`: tiled only where wl.inner is.
 sti_status check_key_lengths(const int32_t *key_lengths);   // non-null, 4-byte aligned

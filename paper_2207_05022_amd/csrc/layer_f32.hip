@@ -1,13 +1,15 @@
 // float32 kernels of the layer: the decompress-into-a-working-buffer route of
 // the paper (Section "Submodel execution": shards are decompressed into a
 // buffer holding one layer of FP32 weights, then the layer is computed), with
-// float32 storage and arithmetic throughout.  Any dimensions are accepted.
+// float32 storage and arithmetic throughout.  Any dimensions are accepted; the projections of larger layers whose dimensions are
+// multiples of 64 go through gemm_f32_split.hip instead.
 //
 // Products run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32: 256 flops per clock and
 // compute unit, float32 multiply and accumulate), in the projections as well as in the attention.
 #include <float.h>
 #include <type_traits>
 #include "sti_internal.hpp"
+#include "split_planes.hpp"
 
 namespace sti {
 namespace {
@@ -15,8 +17,6 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kComputeUnits = 256;
-
-__device__ inline float gelu_erf(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f)); }
 
 // ---------------------------------------------------------------------------
 // Projections: C[T x N] = A[T x K] * W^T.
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Args p)
             if constexpr (n_split) x += bias;
             if constexpr (KIND == GEMM_FFN_UP) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = gelu_erf(x[v]);
+                for (int v = 0; v < 4; ++v) x[v] = gelu_f32(x[v]);
             }
             float *dst = p.C + (n_split ? 0 : (int64_t)blockIdx.y * p.partial_stride) + (int64_t)m * p.ldc + n;
             if (VEC) {
@@ -304,8 +304,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Args p)
 // ---------------------------------------------------------------------------
 constexpr int KB = 64;   // keys per block
 
-template <int DB, bool VEC>
-__global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qkv, float *ctx, int L, int m, int dh,
+// PLANES: the context goes to the output projection as planes of bfloat16 values (gemm_f32_split.hip).
+template <int DB, bool VEC, bool PLANES>
+__global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qkv, void *ctx, int L, int m, int dh,
                                                                  const int32_t *key_lengths)
 {
     constexpr int DP = DB * 16;        // padded features
@@ -431,11 +432,13 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qk
     run_sum += __shfl_xor(run_sum, 32, 64);
     if (q >= L) return;
     const float inv = 1.0f / run_sum;
-    float *out = ctx + ((int64_t)b * L + q) * ((int64_t)m * dh) + (int64_t)head * dh;
+    float *out = (float *)ctx + ((int64_t)b * L + q) * ((int64_t)m * dh) + (int64_t)head * dh;
 #pragma unroll
     for (int c = 0; c < DB; ++c) {
         const int e = c * 16 + g * 4;
-        if (VEC) {
+        if constexpr (PLANES) {
+            store_planes4((uint16_t *)ctx, b * L + q, head * 64 + e, m, o[c] * inv);
+        } else if (VEC) {
             if (e < dh) *(f32x4 *)(out + e) = o[c] * inv;
         } else {
 #pragma unroll
@@ -578,12 +581,12 @@ hipError_t launch_f32_kind(const F32Args &a, int tile, bool vec, int splits, hip
 }
 
 template <bool VEC>
-void launch_attention_blocks(const float *qkv, float *ctx, int B, int L, int m, int dh, const int32_t *key_lengths,
+void launch_attention_blocks(const float *qkv, void *ctx, int B, int L, int m, int dh, const int32_t *key_lengths,
                              hipStream_t stream)
 {
     const dim3 grid((L + 63) / 64, m, B);
 #define STI_ATT_F32(DB) \
-    launch((attention_f32_mfma_kernel<DB, VEC>), grid, dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths)
+    launch((attention_f32_mfma_kernel<DB, VEC, false>), grid, dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths)
     if (dh <= 32) STI_ATT_F32(2);
     else if (dh <= 64) STI_ATT_F32(4);
     else if (dh <= 96) STI_ATT_F32(6);
@@ -627,10 +630,15 @@ hipError_t launch_gemm_f32(const GemmProblem &p, const GemmBlocks &blocks, int m
     }
 }
 
-hipError_t launch_attention_f32(const float *qkv, float *ctx, int B, int L, int m, int dh,
+hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B, int L, int m, int dh,
                                 const int32_t *key_lengths, hipStream_t stream)
 {
     if (B <= 0 || L <= 0 || m <= 0) return hipSuccess;
+    if (planes) {
+        if (dh != 64 || ((uintptr_t)qkv & 15) || ((uintptr_t)ctx & 15)) return hipErrorInvalidValue;
+        launch((attention_f32_mfma_kernel<4, true, true>), dim3((L + 63) / 64, m, B), dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths);
+        return hipGetLastError();
+    }
     if (dh <= 128) {
         const bool vec = dh % 4 == 0 && ((uintptr_t)qkv & 15) == 0 && ((uintptr_t)ctx & 15) == 0;
         if (vec) launch_attention_blocks<true>(qkv, ctx, B, L, m, dh, key_lengths, stream);
@@ -639,7 +647,7 @@ hipError_t launch_attention_f32(const float *qkv, float *ctx, int B, int L, int 
     }
     dim3 grid((L + 3) / 4, m, B);
     size_t lds = (size_t)4 * (L + dh) * sizeof(float);
-    launch(attention_f32_wide_head_kernel, grid, dim3(256), lds, stream, qkv, ctx, L, m, dh, key_lengths);
+    launch(attention_f32_wide_head_kernel, grid, dim3(256), lds, stream, qkv, (float *)ctx, L, m, dh, key_lengths);
     return hipGetLastError();
 }
 

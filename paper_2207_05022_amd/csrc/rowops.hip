@@ -3,6 +3,7 @@
 // and activation type conversion.
 #include <type_traits>
 #include "sti_internal.hpp"
+#include "split_planes.hpp"
 
 namespace sti {
 namespace {
@@ -98,16 +99,15 @@ __device__ inline float row_sum(float v)
 }
 
 // TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC; PLANES: partial sums requested together
-template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES>
-__global__ __launch_bounds__(LPR == 64 ? 64 : 256) void layernorm_vec_kernel(const float *pre, int n_partials,
+template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>   // ROWS: rows per workgroup
+__global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, int n_partials,
                                                             int64_t partial_stride,
                                                             const float *bias, const RT *resid,
                                                             int resid_layout, int y_layout,
                                                             typename Elem<DT>::type *y,
                                                             const float *g, const float *b, int T,
-                                                            int d, float eps)
+                                                            int d, float eps, uint16_t *planes)
 {
-    constexpr int ROWS = LPR == 64 ? 1 : 256 / LPR;   // rows per workgroup
     const int sub = threadIdx.x % LPR;
     const int row = blockIdx.x * ROWS + threadIdx.x / LPR;
     if (row >= T) return;   // whole row groups leave together; shuffles stay inside a group
@@ -186,6 +186,9 @@ __global__ __launch_bounds__(LPR == 64 ? 64 : 256) void layernorm_vec_kernel(con
             const f32x4 t = (v[j] - mean) * inv * gg[j] + bb[j];
             if constexpr (DT == STI_F32) {
                 *(f32x4 *)o = t;
+                if constexpr (std::is_same<RT, float>::value) {
+                    if (planes) store_planes4(planes, row, 4 * c, d >> 6, t);
+                }
             } else if constexpr (DT == STI_F16) {
                 *(half4 *)o = half4{(_Float16)t.x, (_Float16)t.y, (_Float16)t.z, (_Float16)t.w};
             } else {
@@ -334,28 +337,34 @@ hipError_t convert_from(const void *src, void *dst, sti_dtype dst_dtype, uint64_
 template <int DT, typename RT, bool TILED>
 void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, const float *bias,
                      const void *resid, ActLayout resid_layout, ActLayout y_layout, void *y, const float *g, const float *b,
-                     int T, int d, float eps, bool vec, hipStream_t stream)
+                     int T, int d, float eps, bool vec, hipStream_t stream, uint16_t *planes)
 {
     typedef typename Elem<DT>::type O;
-#define STI_LN_PLANES(LPR, MAXC, PLANES, GRID) \
-    launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC, PLANES>), dim3(GRID), dim3(LPR == 64 ? 64 : 256), 0, stream, pre, n_partials, \
-           partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps)
-#define STI_LN_VEC(LPR, MAXC, GRID)                                       \
+#define STI_LN_PLANES(LPR, MAXC, PLANES, ROWS) \
+    launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC, PLANES, ROWS>), dim3((T + ROWS - 1) / ROWS), dim3(LPR * ROWS), 0, stream, pre, \
+           n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps, planes)
+#define STI_LN_VEC(LPR, MAXC, ROWS)                                       \
     do {                                                                  \
-        if (n_partials <= 1) STI_LN_PLANES(LPR, MAXC, 1, GRID);           \
-        else if (n_partials == 2) STI_LN_PLANES(LPR, MAXC, 2, GRID);      \
-        else STI_LN_PLANES(LPR, MAXC, 4, GRID);                           \
+        if (n_partials <= 1) STI_LN_PLANES(LPR, MAXC, 1, ROWS);           \
+        else if (n_partials == 2) STI_LN_PLANES(LPR, MAXC, 2, ROWS);      \
+        else STI_LN_PLANES(LPR, MAXC, 4, ROWS);                           \
     } while (0)
     // many rows: 32 lanes per row (8 rows per workgroup); few rows: a wave and a workgroup per row, so that the rows spread
     // over as many compute units as there are; chunks per lane sized to the row, so that the registers hold no more
     // loads in flight than it has
-    if (vec && T >= 2048 && d <= 1024) {
-        if (d <= 768) STI_LN_VEC(32, 6, (T + 7) / 8);
-        else STI_LN_VEC(32, 8, (T + 7) / 8);
+    if (vec && !planes && T >= 2048 && d <= 1024) {
+        if (d <= 768) STI_LN_VEC(32, 6, 8);
+        else STI_LN_VEC(32, 8, 8);
+    } else if (vec && planes) {
+        if constexpr (DT == STI_F32 && std::is_same<RT, float>::value) {
+            if (d <= 768) STI_LN_VEC(64, 3, 4);
+            else if (d <= 1024) STI_LN_VEC(64, 4, 4);
+            else STI_LN_VEC(64, 8, 4);
+        }
     } else if (vec) {
-        if (d <= 768) STI_LN_VEC(64, 3, T);
-        else if (d <= 1024) STI_LN_VEC(64, 4, T);
-        else STI_LN_VEC(64, 8, T);
+        if (d <= 768) STI_LN_VEC(64, 3, 1);
+        else if (d <= 1024) STI_LN_VEC(64, 4, 1);
+        else STI_LN_VEC(64, 8, 1);
     } else {
         launch((layernorm_kernel<DT, RT>), dim3((T + 3) / 4), dim3(256), 0, stream, pre, n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps);
     }
@@ -367,9 +376,10 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
-                            hipStream_t stream)
+                            hipStream_t stream, void *planes)
 {
     if (T <= 0 || d <= 0) return hipSuccess;
+    if (planes && (d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
     if (n_partials < 0 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
     if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || resid_f32)) return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
@@ -379,14 +389,15 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
         typedef decltype(resid_type) RT;
         constexpr bool TL = decltype(tiled)::value;
         switch (out_dtype) {
-            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
-            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
-            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream); break;
+            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
+            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
+            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
         }
     };
     if (resid_f32) go(float{}, std::false_type{});
     else if (resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) go(_Float16{}, std::true_type{});
     else go(_Float16{}, std::false_type{});
+    if (planes && !vec) return launch_split_rows((const float *)y, planes, T, d, stream);
     return hipGetLastError();
 }
 

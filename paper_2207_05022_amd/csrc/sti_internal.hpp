@@ -154,9 +154,16 @@ struct GemmProblem {
 // K split s at C + s * partial_stride, with at most max_splits of them (the number comes back in splits_used).
 hipError_t launch_gemm_f32(const GemmProblem &p, const GemmBlocks &blocks, int max_splits, int *splits_used,
                            hipStream_t stream);
-// qkv [T x m*3*dh] float32 (per shard: q, k, v each dh wide) -> ctx [T x m*dh] float32.
+// The same on the bfloat16 matrix cores (gemm_f32_split.hip): A and the weight blocks are planes of three bfloat16 values per
+// float32, in cells; FFN_UP leaves planes, the others as above.
+hipError_t launch_gemm_split(const GemmProblem &p, const GemmBlocks &blocks, int max_splits, int *splits_used, hipStream_t stream);
+// rows [T x d] of float32 -> planes; a layer's shards (no outlier dictionaries) -> planes, Q, K, V and O shard by shard, or (ffn) all of
+// FFN2 and then all of FFN1
+hipError_t launch_split_rows(const float *src, void *dst, int T, int d, hipStream_t stream);
+hipError_t launch_decode_split(const InlineShardTable &table, int n_shards, int d, int dh, int f, bool ffn, void *out, hipStream_t stream);
+// qkv [T x m*3*dh] float32 (per shard: q, k, v each dh wide) -> ctx [T x m*dh] float32, or planes (heads of 64 features).
 // key_lengths (device, [B], may be null): keys of sequence b beyond key_lengths[b] take no part.
-hipError_t launch_attention_f32(const float *qkv, float *ctx, int B, int L, int m, int dh,
+hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B, int L, int m, int dh,
                                 const int32_t *key_lengths, hipStream_t stream);
 
 // binary16 MFMA path (gemm_wide.hip, attention_mfma.hip): A and C are binary16.  QKV / FFN_UP
@@ -200,12 +207,13 @@ hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k
 // rowops.hip
 // v = sum_{s < n_partials} pre[s * partial_stride + t*d + :] + bias[:] + resid[t][:]  (n_partials may be 0);
 // y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid (binary16, or float32
-// with resid_f32, [T x d]) may be NULL; y of out_dtype.  A residual or a binary16 y may be tiled.
+// with resid_f32, [T x d]) may be NULL; y of out_dtype.  A residual or a binary16 y may be tiled.  planes (may be NULL;
+// float32 y and resid_f32 only): y as planes of bfloat16 values, too.
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
-                            hipStream_t stream);
+                            hipStream_t stream, void *planes = nullptr);
 // y[t][:] = LayerNorm(pre_f16[t][:]) * g + b for rows that already hold sum + bias + residual.
 hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dtype, const float *g,
                                   const float *b, int T, int d, float eps, hipStream_t stream);

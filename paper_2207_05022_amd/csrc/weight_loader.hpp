@@ -171,13 +171,12 @@ struct TiledCell {
     int strip, kt;     // 32-row strip and 64-column tile inside the sub-block
 };
 
-__device__ inline TiledCell locate_tiled_cell(int cell, const CellMap &m)
+__device__ inline TiledCell locate_cell_of_shard(int shard, int c, const CellMap &m)
 {
     const int d = m.d, dh = m.dh, f = m.f;
     const int c_qkv = (3 * dh / 32) * (d / 64), c_o = (d / 32) * (dh / 64), c_1 = (f / 32) * (d / 64);
     TiledCell t;
-    t.shard = quotient(cell, m.per_shard, m.recip_shard);
-    int c = cell - t.shard * m.per_shard;
+    t.shard = shard;
     uint32_t recip;
     if (c < c_qkv) { t.cols = d; recip = m.recip_d; t.sub_off = 0; }
     else if (c < c_qkv + c_o) { c -= c_qkv; t.cols = dh; recip = m.recip_dh; t.sub_off = (int64_t)3 * dh * d; }
@@ -187,6 +186,11 @@ __device__ inline TiledCell locate_tiled_cell(int cell, const CellMap &m)
     t.strip = quotient(c, tiles, recip);
     t.kt = c - t.strip * tiles;
     return t;
+}
+__device__ inline TiledCell locate_tiled_cell(int cell, const CellMap &m)
+{
+    const int shard = quotient(cell, m.per_shard, m.recip_shard);
+    return locate_cell_of_shard(shard, cell - shard * m.per_shard, m);
 }
 
 // this lane's 32 weights of the cell (row lane % 32, columns (lane / 32) * 32 .. + 32 of the tile), as stored

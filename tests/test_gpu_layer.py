@@ -178,6 +178,34 @@ def test_f32_random_shapes(gpu, oracle_mod):
         assert_parity(got, want, tol, (case, d, M, dh, f, B, L, n_abs, n_layers, io))
 
 
+@pytest.mark.parametrize("d,M,f,B,L,masked", [
+    (768, 12, 256, 4, 107, False),    # the last 128 rows with 44; 96-column tiles
+    (768, 12, 256, 1, 430, True),     # one sequence; the last row block with 14 rows
+    (1024, 16, 128, 3, 171, True),    # Q, K, V and O take more room than both FFN matrices
+    (448, 12, 192, 25, 39, False),    # d_model of 7 cells, columns that are no multiple of a tile's
+    (768, 13, 256, 2, 513 // 2, False),
+])
+def test_f32_on_bfloat16_matrix_cores(gpu, oracle_mod, d, M, f, B, L, masked):
+    """float32 layers of 3e9 multiplications and more (three bfloat16 values per operand): three layers, the second with outlier
+    dictionaries (float32 matrix instructions, planes handed on behind it), the third with every shard absent but two."""
+    torch, P, D = gpu
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    wl = S.small_workload(43000 + d + L, dims, 3, B, L, n_absent=1)
+    wl.plan[2, :M - 2] = 0
+    for i in range(M - 2):
+        wl.shards[2][i] = None
+    plain = wl.shards
+    wl = _with_outliers(wl, 7, fraction=0.002)
+    wl.shards[0], wl.shards[2] = plain[0], plain[2]
+    S.make_every_term_matter(wl, L, amp=2.0)
+    lens = _key_lengths(L, B, L) if masked else None
+    if masked and B == 1:
+        lens[0] = L - 3
+    want = oracle_mod.model_forward(wl.dims, wl.shards, wl.params, wl.x, key_lengths=lens)
+    got = _run_masked(gpu, wl, "f32", lens, "model").float().cpu().numpy()
+    assert_parity(got, want, TOL["f32"])
+
+
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
     (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
     (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows
