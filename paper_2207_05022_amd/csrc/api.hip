@@ -408,13 +408,18 @@ inline const void *block_start(const sti_shard &s, size_t elem_off)
     return (const uint8_t *)s.data + elem_off * (size_t)s.bitwidth / 8;
 }
 
-sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+sti_status bring_in(const sti_dims &d, int m, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
                     const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer)
 {
     const sti_dtype act = (prec == STI_PREC_F32) ? STI_F32 : STI_F16;
     *in = x;
     *in_layout = LAYOUT_ROWS;
     *in_buffer = io_dtype != act;
+    if (io_dtype == STI_F32 && wl.few && wl.inner == LAYOUT_TILED && few_takes_f32_rows((int)T, m, 3 * d.d_head, d.d_model)) {
+        *in_layout = LAYOUT_ROWS_F32;
+        *in_buffer = false;
+        return STI_OK;
+    }
     if (*in_buffer) {
         *in = ws + wl.act[0];
         *in_layout = wl.inner;
@@ -572,7 +577,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         return timed(STI_K_LAYERNORM, stream, [&] {
             if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
-            return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32, resid_layout, dst, dt, dst_layout,
+            return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32 || resid_layout == LAYOUT_ROWS_F32, resid_layout, dst, dt, dst_layout,
                                     g, b, T, dm, d.ln_eps, stream, planes);
         });
     };
@@ -749,7 +754,9 @@ sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
     const void *in;
     ActLayout in_layout;
     bool in_buffer;
-    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &in, &in_layout, &in_buffer);
+    int m = 0;
+    for (int i = 0; i < dims->n_heads; ++i) m += shards[i].bitwidth != 0;
+    st = bring_in(*dims, m, x, io_dtype, T, precision, ws, wl, stream, &in, &in_layout, &in_buffer);
     if (st != STI_OK) return st;
     return run_layer(*dims, shards, *params, in, y, io_dtype, batch, seq, precision, ws, wl, stream,
                      nullptr, masked ? key_lengths : nullptr, nullptr, in_layout, LAYOUT_ROWS);
@@ -1123,7 +1130,9 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;
-    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    int first_present = 0;
+    for (int i = 0; i < M; ++i) first_present += plan[i] != 0;
+    st = bring_in(*dims, first_present, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
     if (st != STI_OK) return st;
     int next_buf = in_buffer ? 1 : 0;
     int decoded_upto = 0;   // layers [0, decoded_upto) have their working buffers (as far as the stream is concerned)

@@ -64,8 +64,10 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
                      ActLayout out_layout = LAYOUT_ROWS, bool last = true);
 // The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
-// otherwise converted into the first activation buffer (in_buffer: whether it is there).
-sti_status bring_in(const sti_dims &d, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+// otherwise converted into the first activation buffer (in_buffer: whether it is there); few tokens: float32 rows as they are, where the
+// Q/K/V projection takes them.
+// m: present shards of that layer.
+sti_status bring_in(const sti_dims &d, int m, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
                     const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer);
 // `predecoded`: the layer's present shards already sit there in fragment-tiled binary16 order
 // (outliers applied); run_layer then decompresses nothing.

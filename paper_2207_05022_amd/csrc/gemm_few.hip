@@ -108,7 +108,8 @@ constexpr int kDHead = 64;   // features of a head on this path
 // grid: x = 32-column strip (KIND QKV, FFN_UP: of a weight block), y = weight block (QKV, FFN_UP) or K split (OUT, which
 // stands for FFN_DOWN too), z = group of RA row blocks.  ONE: no wave has more than one K tile.  Otherwise the waves
 // walk K side by side (a cache line of packed weights holds 3 to 8 tiles of a row).
-template <int KIND, int NW, int RA, int NB, bool ONE>
+// AF32: A is the caller's float32 rows, rounded on arrival.
+template <int KIND, int NW, int RA, int NB, bool ONE, bool AF32>
 __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
     // leading scalar arguments arrive preloaded in scalar registers: what the first loads of a workgroup depend on, with
     // every quotient already formed.  (A division of two scalars is 35 dependent instructions of 4 to 8 clocks.)
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
     int32_t hot_kt_per_split, uint32_t hot_kblock_magic, int32_t a_rows, int64_t partial_stride,
     FewTail tail, FewBlocks<NB> blocks)
 {
+    static_assert(!AF32 || (KIND == GEMM_QKV && ONE), "the first projection, one tile per wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     FewSmem<NW, RA> &sm = *reinterpret_cast<FewSmem<NW, RA> *>(smem_raw);
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP);
@@ -175,18 +177,41 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
         const GemmBlock desc = blocks.b[blk];
         const int ktb = n_split ? k : k - blk * (hot_block_cols / BK);
         Operand a[RA];
-        request_a(l, k, 0, a[0]);
+        FloatTile fa[AF32 ? RA : 1];
+        // (row blocks past the last one: the last one again; the last 32 rows at most begin before the first of their block)
+        auto request_rows = [&](int i) {
+            const int r0 = min((rb0 + i) * 32, (hot_T - 1) & ~31);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                fa[AF32 ? i : 0].v[j] = *(const f32x4 *)((const float *)hot_A + (uint32_t)min(r0 + 4 * j + (l >> 4), hot_T - 1) * (uint32_t)hot_lda + k * BK + (l & 15) * 4);
+        };
+        if constexpr (AF32) request_rows(0);
+        else request_a(l, k, 0, a[0]);
         __builtin_amdgcn_sched_barrier(0);
         // behind the first request for weights: the other row blocks, and what the epilogue adds
         auto request_rest = [&]() {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 1; i < RA; ++i) request_a(l, k, i, a[i]);
+            for (int i = 1; i < RA; ++i) {
+                if constexpr (AF32) request_rows(i);
+                else request_a(l, k, i, a[i]);
+            }
             if (first) request_bias(desc.shard);
             __builtin_amdgcn_sched_barrier(0);
         };
         const int64_t start = (int64_t)row * hot_block_cols + ktb * BK;                    // of the tile in its block, uniform
         const uint32_t lane_elem = (uint32_t)(l & 31) * hot_block_cols + (l >> 5) * 32;     // of the lane in the tile
+        auto rows_to_operands = [&]() {
+            if constexpr (AF32) {
+#pragma unroll
+                for (int i = 0; i < RA; ++i) {
+                    half8 f[4];
+                    float_fragments(fa[i], sm.wave[wave].tile, l, f);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) a[i][s] = __builtin_bit_cast(u32x4, f[s]);
+                }
+            }
+        };
         // One tile after the other: the next one's weights and this one's activations are on their way while fragments(raw, f)
         // turns its weights into operands
         auto walk = [&](auto request, auto fragments, auto &raw) {
@@ -204,6 +229,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
             if constexpr (ONE || !n_split) {
                 half8 f[4];
                 fragments(raw[0], f);
+                rows_to_operands();
                 multiply(f, a);
             } else {
                 for (int j = 0; j < count; j += 2) {
@@ -255,6 +281,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
                 }
                 half8 f[4];
                 float_fragments(t, sm.wave[wave].tile, l, f);
+                rows_to_operands();
                 multiply(f, a);
                 if constexpr (ONE || !n_split) break;
             }
@@ -316,7 +343,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_few_kernel(
     }
 }
 
-template <int KIND, int NW, int RA, int NB, bool ONE>
+template <int KIND, int NW, int RA, int NB, bool ONE, bool AF32 = false>
 hipError_t launch_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits, int64_t partial_stride, hipStream_t stream)
 {
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP);
@@ -327,7 +354,7 @@ hipError_t launch_few(const GemmProblem &p, const GemmBlocks &blocks, int k_spli
     // more than 64 KiB of dynamic LDS needs an explicit opt-in: once per instantiation, and safe
     // when several host threads make their first call together
     static const hipError_t attr_status =
-        hipFuncSetAttribute((const void *)gemm_few_kernel<KIND, NW, RA, NB, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipFuncSetAttribute((const void *)gemm_few_kernel<KIND, NW, RA, NB, ONE, AF32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_status != hipSuccess) return attr_status;
     FewBlocks<NB> table;
     memcpy(table.b, blocks.b, sizeof(table.b));
@@ -335,7 +362,7 @@ hipError_t launch_few(const GemmProblem &p, const GemmBlocks &blocks, int k_spli
     const FewTail tail = {p.C, p.bias0, p.bias1, p.bias2, p.ldc, (int32_t)p.c_layout};
     // kt / tiles = the upper half of kt * ceil(2^32 / tiles) while kt * tiles < 2^32 (kt < 2^16, tiles <= 2^10); 0: one tile per block
     const uint32_t tiles = p.block_cols / BK, magic = tiles == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + tiles - 1) / tiles);
-    launch((gemm_few_kernel<KIND, NW, RA, NB, ONE>), grid, dim3(NW * 64), lds, stream, p.A, p.T, p.lda, nkt, p.block_rows, p.block_cols,
+    launch((gemm_few_kernel<KIND, NW, RA, NB, ONE, AF32>), grid, dim3(NW * 64), lds, stream, p.A, p.T, p.lda, nkt, p.block_rows, p.block_cols,
            per_split, magic, (int32_t)(p.a_layout == LAYOUT_ROWS), partial_stride, tail, table);
     return hipGetLastError();
 }
@@ -343,6 +370,10 @@ hipError_t launch_few(const GemmProblem &p, const GemmBlocks &blocks, int k_spli
 template <int KIND, int NW, int RA, bool ONE>
 hipError_t launch_blocks(const GemmProblem &p, const GemmBlocks &blocks, int k_splits, int64_t partial_stride, hipStream_t stream)
 {
+    if (p.a_layout == LAYOUT_ROWS_F32) {
+        if constexpr (KIND == GEMM_QKV && ONE && NW <= 12) return launch_few<KIND, NW, RA, 16, ONE, true>(p, blocks, k_splits, partial_stride, stream);
+        return hipErrorInvalidValue;
+    }
     if (p.n_blocks <= 16) return launch_few<KIND, NW, RA, 16, ONE>(p, blocks, k_splits, partial_stride, stream);
     return launch_few<KIND, NW, RA, kMaxShardsPerLayer, ONE>(p, blocks, k_splits, partial_stride, stream);
 }
@@ -387,6 +418,33 @@ int few_k_splits(const GemmProblem &p)
 
 int few_max_k_splits(int tiles) { return splits_of(tiles, 12); }
 
+namespace {
+
+struct FewShape {
+    int ra, nw;   // row blocks and waves of a workgroup
+};
+FewShape few_shape(int T, int strips, int k_splits, int tiles)   // tiles: of a K split
+{
+    // 32 rows to a workgroup where every workgroup then has a compute unit of its own (half the activations to fetch and the
+    // sums to exchange per unit: BERT-base with 9 of 12 shards, 128 tokens 361 -> 354 us per 12 layers; 320 or 512 workgroups:
+    // 362 to 371), else 64.  One wave per K tile while workgroups have units of their own; beyond that four waves, so that
+    // three workgroups share a unit and cover each other's round trips (BERT-base, 256 tokens 442 us, 476 with eight waves).
+    const int row_blocks = (T + 31) / 32;
+    const int ra = row_blocks < 2 || (int64_t)strips * k_splits * row_blocks <= kComputeUnits ? 1 : 2;
+    const int64_t workgroups = (int64_t)strips * k_splits * ((row_blocks + ra - 1) / ra);
+    return {ra, tiles <= 4 || workgroups > kComputeUnits ? 4 : tiles <= 8 || tiles > kMaxWaves ? 8 : tiles <= 12 ? 12 : 16};
+}
+
+}  // namespace
+
+// One tile per wave and no more than twelve waves (registers for two row blocks of float32).  The rows are twice the bytes and pass
+// through LDS, but the launch that would round and tile them is on the chain: 2 us, and 2.8 on the host.
+bool few_takes_f32_rows(int T, int n_blocks, int block_rows, int d_model)
+{
+    const FewShape sh = few_shape(T, n_blocks * block_rows / 32, 1, d_model / BK);
+    return n_blocks > 0 && n_blocks <= 16 && d_model / BK <= sh.nw && sh.nw <= 12;
+}
+
 hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                            int64_t partial_stride, hipStream_t stream)
 {
@@ -394,17 +452,11 @@ hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k
     const int N = n_split ? p.n_blocks * p.block_rows : p.block_rows;
     if (p.T <= 0 || N <= 0) return hipSuccess;
     if (N % 32 || p.block_rows % 32 || p.block_cols % BK || p.ldc % 4 || k_splits < 1 || (p.c_layout != LAYOUT_ROWS && p.ldc % 64) ||
-        (p.a_layout == LAYOUT_ROWS && p.lda % 8) || (p.kind == GEMM_QKV && p.d_head != kDHead))
+        (p.a_layout == LAYOUT_ROWS && p.lda % 8) || (p.a_layout == LAYOUT_ROWS_F32 && (p.lda % 4 || p.kind != GEMM_QKV)) || (p.kind == GEMM_QKV && p.d_head != kDHead))
         return hipErrorInvalidValue;
     const int tiles = (k_tiles(p) + k_splits - 1) / k_splits;
-    // 32 rows to a workgroup where every workgroup then has a compute unit of its own (half the activations to fetch and the
-    // sums to exchange per unit: BERT-base with 9 of 12 shards, 128 tokens 361 -> 354 us per 12 layers; 320 or 512 workgroups:
-    // 362 to 371), else 64.  One wave per K tile while workgroups have units of their own; beyond that four waves, so that
-    // three workgroups share a unit and cover each other's round trips (BERT-base, 256 tokens 442 us, 476 with eight waves).
-    const int row_blocks = (p.T + 31) / 32;
-    const int ra = row_blocks < 2 || (int64_t)(N / 32) * k_splits * row_blocks <= kComputeUnits ? 1 : 2;
-    const int64_t workgroups = (int64_t)(N / 32) * k_splits * ((row_blocks + ra - 1) / ra);
-    const int nw = tiles <= 4 || workgroups > kComputeUnits ? 4 : tiles <= 8 || tiles > kMaxWaves ? 8 : tiles <= 12 ? 12 : 16;
+    const FewShape sh = few_shape(p.T, N / 32, k_splits, tiles);
+    const int nw = sh.nw, ra = sh.ra;
 #define STI_FEW(NW, RA, ONE) case NW * 4 + RA * 2 + ONE: return launch_kind<NW, RA, ONE>(p, blocks, k_splits, partial_stride, stream)
     switch (nw * 4 + ra * 2 + (tiles <= nw)) {
     STI_FEW(4, 1, true); STI_FEW(4, 2, true); STI_FEW(4, 1, false); STI_FEW(4, 2, false);

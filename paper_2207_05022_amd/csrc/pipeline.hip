@@ -294,7 +294,9 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;
-    st = bring_in(*dims, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    int first_present = 0;
+    for (int i = 0; i < M; ++i) first_present += plan[i] != 0;
+    st = bring_in(*dims, first_present, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
     if (st != STI_OK) return st;
     int next_buf = in_buffer ? 1 : 0;
     size_t want_pos = 0;   // next entry of `want` (entries are in layer, shard order)

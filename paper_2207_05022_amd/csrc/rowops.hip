@@ -385,7 +385,8 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
     if (T <= 0 || d <= 0) return hipSuccess;
     if (planes && (d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
     if (n_partials < 0 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
-    if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || resid_f32)) return hipErrorInvalidValue;
+    if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || (resid_f32 && (resid_layout == LAYOUT_TILED || out_dtype != STI_F16))))
+        return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
     const bool vec = d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) &&
                      (!bias || al16(bias)) && (!resid || al16(resid));
@@ -398,7 +399,9 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
             case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
         }
     };
-    if (resid_f32) go(float{}, std::false_type{});
+    if (resid_f32 && y_layout == LAYOUT_TILED)
+        launch_ln_typed<STI_F16, float, true>(pre, n_partials, partial_stride, bias, resid, LAYOUT_ROWS, y_layout, y, g, b, T, d, eps, vec, stream, nullptr);
+    else if (resid_f32) go(float{}, std::false_type{});
     else if (resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) go(_Float16{}, std::true_type{});
     else go(_Float16{}, std::false_type{});
     if (planes && !vec) return launch_split_rows((const float *)y, planes, T, d, stream);

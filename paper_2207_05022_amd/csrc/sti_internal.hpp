@@ -69,7 +69,8 @@ enum GemmKind : int32_t {
 // buffer: 32 rows x 64 columns = 4 KiB, [row block][column cell][fragment q][lane][8 values], lane l of
 // fragment q owning row l % 32, columns (l / 32) * 32 + q * 8 .. + 8 - a matrix-core operand of a wave is one contiguous
 // 1 KiB load.  Buffers of tiled matrices hold whole row blocks; what lies in rows past the last token is arbitrary.
-enum ActLayout : int32_t { LAYOUT_ROWS = 0, LAYOUT_TILED = 1 };
+// LAYOUT_ROWS_F32: row by row in float32 (the caller's x, read by the few-token Q/K/V projection and as a residual).
+enum ActLayout : int32_t { LAYOUT_ROWS = 0, LAYOUT_TILED = 1, LAYOUT_ROWS_F32 = 2 };
 
 // element offset of (row, col) in a tiled matrix of `cells` 64-column cells per row block
 __host__ __device__ inline int64_t tiled_offset(int row, int col, int cells)
@@ -200,6 +201,8 @@ hipError_t launch_attention_few(const void *qkv, void *ctx, int B, int L, int m,
 constexpr int kFewMaxTokens = 1024;
 constexpr int kFewMaxSplits = 8;
 int few_k_splits(const GemmProblem &p);
+// whether the Q/K/V projection of T tokens takes float32 rows as they are
+bool few_takes_f32_rows(int T, int n_blocks, int block_rows, int d_model);
 int few_max_k_splits(int k_tiles);   // the most it can be for up to so many 64-wide K tiles (workspace sizing)
 hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                               int64_t partial_stride, hipStream_t stream);
