@@ -8,7 +8,7 @@
 // No sort is needed for equal-population clusters: only the 2^k - 1 boundary values are.  Four passes
 // stream the layer, each with a workgroup per compute unit and results of its own per workgroup:
 //   moments -> histogram of the inliers over 4096 equal bins of their value range, outliers per 512 weights
-//   -> (merge, ranks -> boundary bins) -> values of the boundary bins into one list per bin
+//   -> (merge) -> ranks -> boundary bins, values of those into one list per bin
 //   -> (boundary values: radix selection inside a list) -> cluster indexes: packed streams, outlier
 //   dictionaries and sums per cluster -> (centroids).
 // The steps in brackets are small kernels in between.  Every result is independent of the order in
@@ -19,8 +19,8 @@
 // the same kernels: one bin for all weights, clusters by comparison of keys, sums beside the integers.
 //
 // What bounds it: 28 MB read four times (one BERT-base layer; the last three out of the memory-side
-// cache) and eight dependent launches.  BERT-base at 4 bits: 56 us, against 149 us of the version with
-// histograms of 65536 bins in two levels, device-wide atomics and separate sum and pack passes.
+// cache) and seven dependent launches.  BERT-base at 4 bits: 54 us, 56 with a launch of one workgroup for the boundary bins, 149 of the
+// version with histograms of 65536 bins in two levels, device-wide atomics and separate sum and pack passes.
 #include "api_internal.hpp"
 
 namespace sti {
@@ -47,9 +47,7 @@ struct QuantState {
     uint32_t non_finite;            // some weight is infinite or NaN
     unsigned long long n_inliers;
     uint32_t error;                 // 1: no inliers
-    uint32_t n_slots;               // bins that hold a boundary
     uint32_t slot_fill[kMaxClusters];            // list entries taken so far
-    unsigned long long slot_begin[kMaxClusters]; // first list entry
     // boundary c = 1 .. C-1 at [c-1]: the lowest member of cluster c
     unsigned long long edge_begin[kMaxClusters];                 // its bin's list
     uint32_t edge_count[kMaxClusters], edge_rank[kMaxClusters];  // ... and the rank inside it
@@ -273,11 +271,12 @@ constexpr int kMergeGroups = kBins / 64;
 
 __global__ __launch_bounds__(256) void merge_kernel(const uint32_t *hist_part, int groups, uint32_t *hist,
                                                     const uint32_t *unit_count, uint32_t *unit_off, int units_per_shard,
-                                                    uint32_t *shard_count, uint32_t *outlier_count)
+                                                    uint32_t *shard_count, uint32_t *outlier_count, QuantState *st)
 {
     __shared__ uint32_t red[8][64];
     __shared__ uint32_t wave_total[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x == 0 && tid < kMaxClusters) st->slot_fill[tid] = 0;   // (collect_kernel counts here)
     if (blockIdx.x < kMergeGroups) {
         const int pair = tid & 31, row = tid >> 5;
         uint32_t a = 0, b = 0;
@@ -337,16 +336,28 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint32_t *hist_part, i
     }
 }
 
-// Single workgroup: for every boundary the bin that holds its rank; the bins that hold one become slots with a
+// For every boundary the bin that holds its rank; the bins that hold one become slots with a
 // list each.  table[bin] = (boundaries in lower bins) | (slot + 1, or 0) << 8 | kSeveral where there are two or more.
+// Every workgroup of the collecting pass works this out for itself while its first weights are on their way (3.9 us; a launch of
+// one workgroup took 4.6 and the way from one launch to the next); the first one leaves it in memory for those behind.
 constexpr uint32_t kSeveral = 0x8000;
 
-__global__ __launch_bounds__(1024) void boundary_bins_kernel(QuantState *st, const uint32_t *hist, uint16_t *table, uint64_t n,
-                                                             const uint32_t *shard_count, int n_shards, int n_clusters)
+struct BoundaryScratch {
+    uint64_t before[kBins];              // inliers in lower bins
+    uint64_t wave_sum[16];
+    uint32_t edge_bin[kMaxClusters + 1], edge_slot[kMaxClusters];
+};
+
+// table: of the workgroup (LDS); slot_begin, n_slots: what the caller needs of the state, in LDS, too.  The state and table_out
+// are written where `keep`.
+__device__ inline void boundary_bins(BoundaryScratch &sc, QuantState *st, const uint32_t *hist, uint16_t *table, uint16_t *table_out,
+                                     uint64_t *slot_begin, uint32_t *n_slots, bool keep, uint64_t n, const uint32_t *shard_count,
+                                     int n_shards, int n_clusters)
 {
-    __shared__ uint64_t before[kBins];   // inliers in lower bins
-    __shared__ uint64_t wave_sum[16];
-    __shared__ uint32_t edge_bin[kMaxClusters + 1], edge_slot[kMaxClusters];
+    uint64_t (&before)[kBins] = sc.before;
+    uint64_t (&wave_sum)[16] = sc.wave_sum;
+    uint32_t (&edge_bin)[kMaxClusters + 1] = sc.edge_bin;
+    uint32_t (&edge_slot)[kMaxClusters] = sc.edge_slot;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint4 h = ((const uint4 *)hist)[tid];
     const uint32_t outl = lane < n_shards ? shard_count[lane] : 0;   // (kMaxShardsPerLayer lanes)
@@ -395,20 +406,19 @@ __global__ __launch_bounds__(1024) void boundary_bins_kernel(QuantState *st, con
         begin -= mine;
         // (the begin of a boundary's own list: that of its bin's first boundary)
         const uint64_t list_begin = __shfl(begin, 63 - __builtin_clzll((firsts & ((2ull << lane) - 1)) | 1ull), 64);
-        if (edge) st->edge_begin[lane] = list_begin;
-        if (first) {
-            st->slot_begin[slot] = begin;
-            st->slot_fill[slot] = 0;
-        }
+        if (first) slot_begin[slot] = begin;
+        if (lane == 0) *n_slots = __popcll(firsts);
         if (edge) {
-            st->edge_count[lane] = count;
-            st->edge_rank[lane] = (uint32_t)(rank - before[lo]);
-            st->edge_before[lane] = before[lo];
             edge_bin[lane] = lo;
             edge_slot[lane] = slot;
         }
-        if (lane == 0) {
-            st->n_slots = __popcll(firsts);
+        if (keep && edge) {
+            st->edge_begin[lane] = list_begin;
+            st->edge_count[lane] = count;
+            st->edge_rank[lane] = (uint32_t)(rank - before[lo]);
+            st->edge_before[lane] = before[lo];
+        }
+        if (keep && lane == 0) {
             st->n_inliers = n_in;
             st->error = n_in == 0 ? 1 : 0;
         }
@@ -430,6 +440,7 @@ __global__ __launch_bounds__(1024) void boundary_bins_kernel(QuantState *st, con
         packed[b >> 1] |= entry << (16 * (b & 1));
     }
     ((uint2 *)table)[tid] = uint2{packed[0], packed[1]};
+    if (keep) ((uint2 *)table_out)[tid] = uint2{packed[0], packed[1]};
 }
 
 // The keys of the weights in boundary bins, one list per bin (in no particular order).  A workgroup
@@ -437,13 +448,16 @@ __global__ __launch_bounds__(1024) void boundary_bins_kernel(QuantState *st, con
 // do not fit (a bin holds a large part of the layer), it reads its weights again instead.
 constexpr uint32_t kFound = 8192;
 
-__global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint64_t n, QuantState *st, const uint16_t *table_in,
-                                                           uint32_t *lists)
+__global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint64_t n, QuantState *st, const uint32_t *hist,
+                                                           const uint32_t *shard_count, int n_shards, int n_clusters,
+                                                           uint16_t *table_out, uint32_t *lists)
 {
-    __shared__ float found[kFound];
-    __shared__ uint16_t table[kBins + 2];      // (one entry for outliers)
-    __shared__ uint32_t n_found, count[kMaxClusters];
-    __shared__ uint64_t at[kMaxClusters];
+    static_assert(kThreads == 1024 && sizeof(BoundaryScratch) >= kFound * sizeof(float), "four bins per thread; one piece of LDS for both");
+    __shared__ BoundaryScratch scratch;
+    float *found = (float *)&scratch;          // (once the table is there)
+    __shared__ __attribute__((aligned(8))) uint16_t table[kBins + 4];      // (one entry for outliers)
+    __shared__ uint32_t n_found, n_slots, count[kMaxClusters];
+    __shared__ uint64_t at[kMaxClusters], slot_begin[kMaxClusters];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t n_units = n / kUnit, stride = (uint64_t)gridDim.x * kWaves, u0 = (uint64_t)blockIdx.x * kWaves + wave;
     uint64_t u = u0;
@@ -453,10 +467,10 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
         for (int h = 0; h < 2; ++h) next[h] = ((const f32x4 *)(w + unit * kUnit))[h * 64 + lane];
     };
     if (u < n_units) request(u);
-    ((uint2 *)table)[tid] = ((const uint2 *)table_in)[tid];
     const float xlo = st->xlo, xhi = st->xhi, scale = st->bin_scale, shift = st->bin_shift;
     if (tid < kMaxClusters) count[tid] = 0;
     if (tid == 0) { n_found = 0; table[kBins] = 0; }
+    boundary_bins(scratch, st, hist, table, table_out, slot_begin, &n_slots, blockIdx.x == 0, n, shard_count, n_shards, n_clusters);
     __syncthreads();
     auto slot_of = [&](float x) -> uint32_t {   // slot + 1, or 0
         return (table[is_inlier(x, xlo, xhi) ? bin_of(x, scale, shift) : kBins] & ~kSeveral) >> 8;
@@ -487,8 +501,8 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
         }
     }
     __syncthreads();
-    if (tid < (int)st->n_slots) {
-        at[tid] = count[tid] ? st->slot_begin[tid] + atomicAdd(&st->slot_fill[tid], count[tid]) : 0;
+    if (tid < (int)n_slots) {
+        at[tid] = count[tid] ? slot_begin[tid] + atomicAdd(&st->slot_fill[tid], count[tid]) : 0;
         count[tid] = 0;
     }
     __syncthreads();
@@ -817,9 +831,8 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
     moments_kernel<<<dim3(nm), dim3(256), 0, stream>>>(weights, n, partials);
     histogram_kernel<<<grid, block, 0, stream>>>(weights, n, partials, nm, loglik_threshold, reg_covar, st, unit_count, hist_part);
     merge_kernel<<<dim3(kMergeGroups + M), dim3(256), 0, stream>>>(hist_part, L.groups, hist, unit_count, unit_off,
-                                                                   (int)units_per_shard, shard_count, outlier_count);
-    boundary_bins_kernel<<<dim3(1), dim3(1024), 0, stream>>>(st, hist, table, n, shard_count, M, C);
-    collect_kernel<<<grid, block, 0, stream>>>(weights, n, st, table, lists);
+                                                                   (int)units_per_shard, shard_count, outlier_count, st);
+    collect_kernel<<<grid, block, 0, stream>>>(weights, n, st, hist, shard_count, M, C, table, lists);
     boundary_values_kernel<<<dim3(C - 1), dim3(1024), 0, stream>>>(st, lists);
 #define STI_PACK(K) \
     pack_kernel<K><<<grid, block, 0, stream>>>(weights, n, st, table, unit_off, units_per_shard, packed, outlier_pos, outlier_val, max_outliers_per_shard, csum)
