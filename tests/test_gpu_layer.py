@@ -1157,6 +1157,7 @@ def test_padded_sequences_ignore_what_the_padding_holds(gpu):
     ("mfma", MID, 7, 93, "model"), ("mfma", MID, 4, 200, "whole"),    # keys staged in LDS: all of them, block by block
     ("mfma", MID, 64, 128, "model"),                                  # attention inside the Q/K/V projection
     ("f32", MID, 3, 70, "model"),
+    ("f32", S.Dims(768, 12, 64, 256, 1e-12), 4, 119, "model"),        # bfloat16 matrix cores; rows of a tile behind the last token
 ])
 def test_no_value_in_the_padding_reaches_a_real_row(gpu, prec, dims, B, L, route):
     """Real rows have the bits they have over zero padding when the padding holds values beyond binary16's range,
