@@ -231,7 +231,7 @@ def bench_few_token(P, D, torch, S, steps, warmup, with_oracle):
     Resident shards, float32 in and out.  Fractions are of the matrix-core and HBM peaks for the
     algorithmic flops and bytes (selected shards as stored + input + output); a forward is a chain
     of dependent launches of a few microseconds each, so both are small by construction."""
-    out = {"regime": "latency-bound: 8 dependent launches per layer; fractions of both rooflines are "
+    out = {"regime": "latency-bound: 7 dependent launches per layer; fractions of both rooflines are "
                      "reported for completeness"}
     prec = P.STI_PREC_F16_MFMA
     for name, make in (("config0", S.config0), ("config2", S.config2), ("config3", S.config3)):
