@@ -206,6 +206,19 @@ def test_f32_on_bfloat16_matrix_cores(gpu, oracle_mod, d, M, f, B, L, masked):
     assert_parity(got, want, TOL["f32"])
 
 
+@pytest.mark.parametrize("io,empty", [("f32", 1), ("f16", 0), ("f32", 2)])
+def test_f32_planes_through_a_layer_without_shards(gpu, oracle_mod, io, empty):
+    """A first, middle or last layer with every shard absent hands its rows on to layers on the bfloat16 matrix cores."""
+    wl = S.small_workload(43100 + empty, S.Dims(768, 12, 64, 256, 1e-12), 3, 3, 151, io_dtype=io)
+    wl.plan[empty, :] = 0
+    for i in range(12):
+        wl.shards[empty][i] = None
+    S.make_every_term_matter(wl, empty, amp=2.0)
+    want = oracle_mod.model_forward(wl.dims, wl.shards, wl.params, wl.x)
+    got = _run_masked(gpu, wl, "f32", None, "model").float().cpu().numpy()
+    assert_parity(got, want, TOL["f32"] if io == "f32" else 2e-3)    # binary16 output: half an ulp of the largest value
+
+
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
     (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
     (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows

@@ -326,13 +326,14 @@ def test_pipeline_rejected_calls_write_nothing_and_keep_the_preload_buffer(gpu, 
     rig.pipe.close()
 
 
-@pytest.mark.parametrize("prec", ["f32", "mfma"])
-def test_pipeline_padded_sequences(gpu, oracle_mod, prec):
+@pytest.mark.parametrize("prec,dims,B,L", [
+    ("f32", SMALL, 5, 70), ("mfma", MID, 5, 70),
+    ("f32", S.Dims(768, 12, 64, 256, 1e-12), 5, 90),   # bfloat16 matrix cores: a layer's shards are read twice
+], ids=["f32", "mfma", "f32-planes"])
+def test_pipeline_padded_sequences(gpu, oracle_mod, prec, dims, B, L):
     """sti_pipeline_forward_masked gives the bits of sti_model_forward_masked (and the oracle's
     values), cold and warm."""
     torch, P, D = gpu
-    dims = SMALL if prec == "f32" else MID
-    B, L = 5, 70
     wl = S.small_workload(91, dims, 3, B, L, n_absent=1)
     S.make_every_term_matter(wl, 9, amp=3.0)
     total = sum(plan_bytes(dims, wl.plan))
