@@ -408,9 +408,24 @@ inline const void *block_start(const sti_shard &s, size_t elem_off)
     return (const uint8_t *)s.data + elem_off * (size_t)s.bitwidth / 8;
 }
 
-sti_status bring_in(const sti_dims &d, int m, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+// (outlier dictionaries are put into float32 weights)
+bool takes_planes(const sti_dims &d, const sti_shard *shards, const WorkspaceLayout &wl)
+{
+    if (!wl.split) return false;
+    int m = 0;
+    for (int i = 0; i < d.n_heads; ++i) {
+        if (shards[i].bitwidth == 0) continue;
+        if (shards[i].n_outliers > 0) return false;
+        ++m;
+    }
+    return m > 0;
+}
+
+sti_status bring_in(const sti_dims &d, const sti_shard *shards, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
                     const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer)
 {
+    int m = 0;
+    for (int i = 0; i < d.n_heads; ++i) m += shards[i].bitwidth != 0;
     const sti_dtype act = (prec == STI_PREC_F32) ? STI_F32 : STI_F16;
     *in = x;
     *in_layout = LAYOUT_ROWS;
@@ -428,7 +443,7 @@ sti_status bring_in(const sti_dims &d, int m, const void *x, sti_dtype io_dtype,
                                               : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
         }));
     }
-    if (wl.split)
+    if (takes_planes(d, shards, wl))
         STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)*in, ws + wl.s_in, (int)T, d.d_model, stream); }));
     return STI_OK;
 }
@@ -450,7 +465,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded, const int32_t *key_lengths, const NextLayerDecode *next,
-                     ActLayout in_layout, ActLayout out_layout, bool last)
+                     ActLayout in_layout, ActLayout out_layout, bool planes_out)
 {
     const int dm = d.d_model, M = d.n_heads, dh = d.d_head, f = d.ffn_per_shard;
     const int T = B * Lseq;
@@ -475,7 +490,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     // shards with an outlier dictionary always go through the working buffer, where the
     // outliers are scattered back after the substitution pass
     const bool predecode = !f32 && m > 0 && (predecoded || !wl.few || max_outliers > 0);
-    const bool split = wl.split && max_outliers == 0;   // (dictionaries are put into float32 weights)
+    const bool split = wl.split && (m == 0 || takes_planes(d, shards, wl));   // (two LayerNorms alone: the buffers in which the second can leave planes)
     const _Float16 *w16 = predecoded ? (const _Float16 *)predecoded : (const _Float16 *)(ws + wl.w16);
     if (predecode && !predecoded) {
         InlineShardTable t;
@@ -626,8 +641,8 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     }
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, bo));
-    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, split ? ws + wl.s_h : nullptr));
-    if (split) {
+    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, split && m > 0 ? ws + wl.s_h : nullptr));
+    if (split && m > 0) {
         InlineShardTable t;
         memset(&t, 0, sizeof(t));
         for (int p = 0; p < m; ++p) t.d[p] = make_desc(shards[present[p]], present[p]);
@@ -653,8 +668,8 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.ldr = dm;
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
-    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && !last ? ws + wl.s_in : nullptr));
-    if (wl.split && !split && !last)   // (the buffers of such a layer lie otherwise: its rows cannot go there before it has ended)
+    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && planes_out ? ws + wl.s_in : nullptr));
+    if (!split && planes_out)   // (the buffers of such a layer lie otherwise: its rows cannot go there before it has ended)
         STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)out, ws + wl.s_in, T, dm, stream); }));
     return STI_OK;
 }
@@ -754,9 +769,7 @@ sti_status layer_forward(const sti_dims *dims, const sti_shard *shards,
     const void *in;
     ActLayout in_layout;
     bool in_buffer;
-    int m = 0;
-    for (int i = 0; i < dims->n_heads; ++i) m += shards[i].bitwidth != 0;
-    st = bring_in(*dims, m, x, io_dtype, T, precision, ws, wl, stream, &in, &in_layout, &in_buffer);
+    st = bring_in(*dims, shards, x, io_dtype, T, precision, ws, wl, stream, &in, &in_layout, &in_buffer);
     if (st != STI_OK) return st;
     return run_layer(*dims, shards, *params, in, y, io_dtype, batch, seq, precision, ws, wl, stream,
                      nullptr, masked ? key_lengths : nullptr, nullptr, in_layout, LAYOUT_ROWS);
@@ -1130,9 +1143,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;
-    int first_present = 0;
-    for (int i = 0; i < M; ++i) first_present += plan[i] != 0;
-    st = bring_in(*dims, first_present, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    st = bring_in(*dims, chosen.data(), x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
     if (st != STI_OK) return st;
     int next_buf = in_buffer ? 1 : 0;
     int decoded_upto = 0;   // layers [0, decoded_upto) have their working buffers (as far as the stream is concerned)
@@ -1160,7 +1171,8 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         const void *predecoded = whole_model_fits ? (const void *)w16_of(l) : nullptr;
         st = run_layer(*dims, &chosen[(size_t)l * M], params[l], cur, out, last ? io_dtype : act,
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
-                       next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner, last);
+                       next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner,
+                       !last && takes_planes(*dims, &chosen[(size_t)(l + 1) * M], wl));
         if (st != STI_OK) return st;
         if (next_decode.workgroups > 0 && next_decode.max_outliers == 0) {
             st = patch_layer(l + 1);

@@ -18,7 +18,7 @@ struct WorkspaceLayout {
     size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
     size_t pre_out = 0, pre_down = 0;   // sums before LayerNorm of the O and of the FFN2 product (compact: over other buffers)
     bool few = false;                   // the layers take the few-token kernels
-    bool split = false;                 // float32 layers without outlier dictionaries take the bfloat16 matrix cores
+    bool split = false;                 // there is room for float32 layers on the bfloat16 matrix cores (takes_planes)
     // ... whose buffers lie over those of the others: planes of a layer's input, context, first LayerNorm's rows, neurons; Q/K/V and
     // the first LayerNorm's rows in float32; the end of the region that holds all but the last of these
     size_t s_in = 0, s_ctx = 0, s_h = 0, s_u = 0, s_qkv = 0, s_h32 = 0, s_end = 0;
@@ -57,22 +57,25 @@ struct NextLayerDecode {
 // layers if `grouped` - costs less).
 int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_next, bool grouped, sti_precision prec);
 
+// Whether a layer over these shards goes through the bfloat16 matrix cores in three planes per float32 (gemm_f32_split.hip).
+bool takes_planes(const sti_dims &d, const sti_shard *shards, const WorkspaceLayout &wl);
+
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded = nullptr, const int32_t *key_lengths = nullptr,
                      const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
-                     ActLayout out_layout = LAYOUT_ROWS, bool last = true);
+                     ActLayout out_layout = LAYOUT_ROWS, bool planes_out = false);
 // The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
 // otherwise converted into the first activation buffer (in_buffer: whether it is there); few tokens: float32 rows as they are, where the
-// Q/K/V projection takes them.
-// m: present shards of that layer.
-sti_status bring_in(const sti_dims &d, int m, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
+// Q/K/V projection takes them.  As planes, too, where that layer takes them.
+// shards: that layer's.
+sti_status bring_in(const sti_dims &d, const sti_shard *shards, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
                     const WorkspaceLayout &wl, hipStream_t stream, const void **in, ActLayout *in_layout, bool *in_buffer);
 // `predecoded`: the layer's present shards already sit there in fragment-tiled binary16 order
 // (outliers applied); run_layer then decompresses nothing.
 // `key_lengths` (device, [B]): real positions per padded sequence; null = every position is real.
-// `last`: no layer of the call follows (otherwise `out` is left as planes, too, where wl.split).
+// `planes_out`: `out` (float32, in the workspace) is left as planes, too: the layer that follows takes them.
 // `next` (only with `predecoded`, and only when spare_decode_workgroups says so for this layer).
 // Layouts of `in` and `out`: tiled only where wl.inner is.
 sti_status check_key_lengths(const int32_t *key_lengths);   // non-null, 4-byte aligned

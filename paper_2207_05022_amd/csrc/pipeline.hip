@@ -294,9 +294,7 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
     const void *cur;
     ActLayout cur_layout;
     bool in_buffer;
-    int first_present = 0;
-    for (int i = 0; i < M; ++i) first_present += plan[i] != 0;
-    st = bring_in(*dims, first_present, x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
+    st = bring_in(*dims, chosen.data(), x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
     if (st != STI_OK) return st;
     int next_buf = in_buffer ? 1 : 0;
     size_t want_pos = 0;   // next entry of `want` (entries are in layer, shard order)
@@ -355,7 +353,7 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
         void *out = last ? y : (void *)(ws + wl.act[next_buf]);
         st = run_layer(*dims, row, params[l], cur, out, last ? io_dtype : act, batch, seq, precision,
                        ws, wl, stream, nullptr, masked ? key_lengths : nullptr, nullptr, cur_layout,
-                       last ? LAYOUT_ROWS : inner, last);
+                       last ? LAYOUT_ROWS : inner, !last && takes_planes(*dims, row + M, wl));
         if (st != STI_OK) return st;
         if (slot_off > 0) {
             STI_TRY(hipEventRecord(pl->computed[slot], stream));

@@ -219,6 +219,28 @@ def test_f32_planes_through_a_layer_without_shards(gpu, oracle_mod, io, empty):
     assert_parity(got, want, TOL["f32"] if io == "f32" else 2e-3)    # binary16 output: half an ulp of the largest value
 
 
+@pytest.mark.parametrize("layers,converted", [("oo", 0), ("po", 1), ("op", 1), ("oopeo", 1), ("pep", 1), ("e", 0)])
+def test_f32_planes_are_written_for_layers_that_take_them(gpu, oracle_mod, layers, converted):
+    """p: a layer without, o: with outlier dictionaries, e: with every shard absent.  Rows become planes in a launch of their own only in
+    front of a p: at the beginning and behind an o."""
+    torch, P, D = gpu
+    wl = S.small_workload(43200 + len(layers), S.Dims(768, 12, 64, 256, 1e-12), len(layers), 3, 151, n_absent=1)
+    rng = np.random.default_rng(17)
+    for l, kind in enumerate(layers):
+        for i, s in enumerate(wl.shards[l]):
+            if kind == "o" and s is not None:
+                S.add_outliers(rng, s, wl.dims.weights_per_shard, 0.002)
+            elif kind == "e":
+                wl.plan[l, i], wl.shards[l][i] = 0, None
+    S.make_every_term_matter(wl, 5, amp=2.0)
+    want = oracle_mod.model_forward(wl.dims, wl.shards, wl.params, wl.x)
+    P.sti_profile_begin()
+    got = _run_masked(gpu, wl, "f32", None, "model").float().cpu().numpy()
+    count = {k: n for k, (n, _) in P.sti_profile_end().items()}
+    assert_parity(got, want, TOL["f32"])
+    assert count["convert"] == converted and count["decode"] == layers.count("o") + 2 * layers.count("p")
+
+
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
     (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
     (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows
