@@ -231,13 +231,20 @@ inline int64_t few_token_limit(const sti_dims &d)
 }
 
 // Whether float32 layers go through the bfloat16 matrix cores (three planes per operand, gemm_f32_split.hip): from 3e9 multiplications
-// per layer on.  4 layers, us, float32 against bfloat16 matrix instructions: BERT-base 256 tokens (1.8e9) 332 / 329, 512 (3.6e9)
-// 470 / 435, 2046 (14.5e9) 1308 / 1088; d_model 704 x 11 shards, 450 tokens (2.2e9) 374 / 402; 1024 x 16, 256 tokens (3.2e9) 464 / 421;
-// 512 x 8 of 128 neurons, 1024 tokens (2.1e9) 341 / 325, 2048 (4.3e9) 512 / 453; 384 x 6, 2048 tokens (3.6e9) 486 / 446.
+// per layer on, its present shards 1.2e9 of them.  4 layers, us, float32 against bfloat16 matrix instructions: BERT-base 256 tokens
+// (1.8e9) 332 / 329, 512 (3.6e9) 470 / 435, 2046 (14.5e9) 1308 / 1088; d_model 704 x 11 shards, 450 tokens (2.2e9) 374 / 402; 1024 x 16, 256
+// tokens (3.2e9) 464 / 421; 512 x 8 of 128 neurons, 1024 tokens (2.1e9) 341 / 325, 2048 (4.3e9) 512 / 453; 384 x 6, 2048 tokens (3.6e9)
+// 486 / 446.  Shards absent (multiplications of those present): BERT-base 4 x 107 tokens, 9 of 12 shards (2.3e9) 356 / 360, 6 (1.5e9)
+// 298 / 288, 3 (0.76e9) 251 / 263; 5 x 130 tokens, 3 (1.15e9) 277 / 284; 7 x 100 tokens, 3 (1.24e9) 295 / 273; d_model 1024 2 x 122
+// tokens, 8 of 16 (1.5e9) 341 / 334; 384 x 6 14 x 130 tokens, 3 (1.6e9) 333 / 315.
+inline double multiplications(const sti_dims &d, int64_t T, int shards)
+{
+    return (double)T * shards * d.d_model * (4 * d.d_head + 2 * d.ffn_per_shard);
+}
 inline bool split_path(const sti_dims &d, int64_t T)
 {
     if (d.d_head != 64 || d.d_model % 64 || d.ffn_per_shard % 64) return false;
-    return (double)T * d.n_heads * d.d_model * (4 * d.d_head + 2 * d.ffn_per_shard) >= 3e9;
+    return multiplications(d, T, d.n_heads) >= 3e9;
 }
 
 // Planes take six bytes where float32 values take four.  They lie in the buffers of the float32 layer all the same, so that no call needs
@@ -409,7 +416,7 @@ inline const void *block_start(const sti_shard &s, size_t elem_off)
 }
 
 // (outlier dictionaries are put into float32 weights)
-bool takes_planes(const sti_dims &d, const sti_shard *shards, const WorkspaceLayout &wl)
+bool takes_planes(const sti_dims &d, const sti_shard *shards, int64_t T, const WorkspaceLayout &wl)
 {
     if (!wl.split) return false;
     int m = 0;
@@ -418,7 +425,7 @@ bool takes_planes(const sti_dims &d, const sti_shard *shards, const WorkspaceLay
         if (shards[i].n_outliers > 0) return false;
         ++m;
     }
-    return m > 0;
+    return multiplications(d, T, m) >= 1.2e9;
 }
 
 sti_status bring_in(const sti_dims &d, const sti_shard *shards, const void *x, sti_dtype io_dtype, int64_t T, sti_precision prec, uint8_t *ws,
@@ -443,7 +450,7 @@ sti_status bring_in(const sti_dims &d, const sti_shard *shards, const void *x, s
                                               : launch_convert(x, io_dtype, ws + wl.act[0], act, (uint64_t)T * d.d_model, stream);
         }));
     }
-    if (takes_planes(d, shards, wl))
+    if (takes_planes(d, shards, T, wl))
         STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)*in, ws + wl.s_in, (int)T, d.d_model, stream); }));
     return STI_OK;
 }
@@ -490,7 +497,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     // shards with an outlier dictionary always go through the working buffer, where the
     // outliers are scattered back after the substitution pass
     const bool predecode = !f32 && m > 0 && (predecoded || !wl.few || max_outliers > 0);
-    const bool split = wl.split && (m == 0 || takes_planes(d, shards, wl));   // (two LayerNorms alone: the buffers in which the second can leave planes)
+    const bool split = wl.split && (m == 0 || takes_planes(d, shards, T, wl));   // (two LayerNorms alone: the buffers in which the second can leave planes)
     const _Float16 *w16 = predecoded ? (const _Float16 *)predecoded : (const _Float16 *)(ws + wl.w16);
     if (predecode && !predecoded) {
         InlineShardTable t;
@@ -1172,7 +1179,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
         st = run_layer(*dims, &chosen[(size_t)l * M], params[l], cur, out, last ? io_dtype : act,
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
                        next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner,
-                       !last && takes_planes(*dims, &chosen[(size_t)(l + 1) * M], wl));
+                       !last && takes_planes(*dims, &chosen[(size_t)(l + 1) * M], T, wl));
         if (st != STI_OK) return st;
         if (next_decode.workgroups > 0 && next_decode.max_outliers == 0) {
             st = patch_layer(l + 1);

@@ -58,7 +58,7 @@ struct NextLayerDecode {
 int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_next, bool grouped, sti_precision prec);
 
 // Whether a layer over these shards goes through the bfloat16 matrix cores in three planes per float32 (gemm_f32_split.hip).
-bool takes_planes(const sti_dims &d, const sti_shard *shards, const WorkspaceLayout &wl);
+bool takes_planes(const sti_dims &d, const sti_shard *shards, int64_t T, const WorkspaceLayout &wl);
 
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,

@@ -353,7 +353,7 @@ sti_status pipeline_forward(sti_pipeline *pl, int n_layers, const sti_shard *sto
         void *out = last ? y : (void *)(ws + wl.act[next_buf]);
         st = run_layer(*dims, row, params[l], cur, out, last ? io_dtype : act, batch, seq, precision,
                        ws, wl, stream, nullptr, masked ? key_lengths : nullptr, nullptr, cur_layout,
-                       last ? LAYOUT_ROWS : inner, !last && takes_planes(*dims, row + M, wl));
+                       last ? LAYOUT_ROWS : inner, !last && takes_planes(*dims, row + M, T, wl));
         if (st != STI_OK) return st;
         if (slot_off > 0) {
             STI_TRY(hipEventRecord(pl->computed[slot], stream));

@@ -219,18 +219,19 @@ def test_f32_planes_through_a_layer_without_shards(gpu, oracle_mod, io, empty):
     assert_parity(got, want, TOL["f32"] if io == "f32" else 2e-3)    # binary16 output: half an ulp of the largest value
 
 
-@pytest.mark.parametrize("layers,converted", [("oo", 0), ("po", 1), ("op", 1), ("oopeo", 1), ("pep", 1), ("e", 0)])
+@pytest.mark.parametrize("layers,converted", [("oo", 0), ("po", 1), ("op", 1), ("oopeo", 1), ("pep", 1), ("e", 0),
+                                              ("s", 0), ("sp", 1), ("ps", 1)])
 def test_f32_planes_are_written_for_layers_that_take_them(gpu, oracle_mod, layers, converted):
-    """p: a layer without, o: with outlier dictionaries, e: with every shard absent.  Rows become planes in a launch of their own only in
-    front of a p: at the beginning and behind an o."""
+    """p: a layer without, o: with outlier dictionaries, s: with 3 of 12 shards, e: with every shard absent.  Rows become planes in a
+    launch of their own only in front of a p: at the beginning and behind an o or s."""
     torch, P, D = gpu
-    wl = S.small_workload(43200 + len(layers), S.Dims(768, 12, 64, 256, 1e-12), len(layers), 3, 151, n_absent=1)
+    wl = S.small_workload(43200 + len(layers), S.Dims(768, 12, 64, 256, 1e-12), len(layers), 3, 151, n_absent=0)
     rng = np.random.default_rng(17)
     for l, kind in enumerate(layers):
         for i, s in enumerate(wl.shards[l]):
             if kind == "o" and s is not None:
                 S.add_outliers(rng, s, wl.dims.weights_per_shard, 0.002)
-            elif kind == "e":
+            elif kind == "e" or (kind == "s" and i not in (1, 4, 11)):
                 wl.plan[l, i], wl.shards[l][i] = 0, None
     S.make_every_term_matter(wl, 5, amp=2.0)
     want = oracle_mod.model_forward(wl.dims, wl.shards, wl.params, wl.x)
@@ -238,7 +239,7 @@ def test_f32_planes_are_written_for_layers_that_take_them(gpu, oracle_mod, layer
     got = _run_masked(gpu, wl, "f32", None, "model").float().cpu().numpy()
     count = {k: n for k, (n, _) in P.sti_profile_end().items()}
     assert_parity(got, want, TOL["f32"])
-    assert count["convert"] == converted and count["decode"] == layers.count("o") + 2 * layers.count("p")
+    assert count["convert"] == converted and count["decode"] == layers.count("o") + layers.count("s") + 2 * layers.count("p")
 
 
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
