@@ -214,7 +214,9 @@ inline bool few_token_path(const sti_dims &d, int64_t T)
     if (T <= few_token_limit(d)) return true;
     if (d.d_model < 256 || d.d_model > 1024 || d.ffn_per_shard > 256 || T > kFewMaxTokens) return false;
     const int64_t columns = (int64_t)d.n_heads * (3 * d.d_head + d.ffn_per_shard);
-    return T <= 14000000 / (153 * columns + 420000) * 64;
+    if (T > 14000000 / (153 * columns + 420000) * 64) return false;
+    // (sti_layer_forward_static gives the bits of sti_layer_forward: no other kernels there for want of room)
+    return workspace_layout(d, (T + 63) / 64 * 64, STI_PREC_F16_MFMA, true).total <= kStaticScratchBytes;
 }
 
 // Up to here the workspace queries leave room for the few-token kernels only; between this and the line above for either family,
@@ -708,7 +710,6 @@ namespace {
 // Scratch memory of sti_layer_forward_static: what sti_layer_forward takes as `workspace`
 // (working buffer, projections' outputs, partial sums), for callers that cannot allocate.
 // One copy per GPU, at an address of its own on each, held until the process ends.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // Device address of `scratch` on the current device, looked up once per device (in host code

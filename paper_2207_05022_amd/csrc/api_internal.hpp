@@ -13,6 +13,8 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
         if ((expr) != hipSuccess) return STI_ERR_HIP; \
     } while (0)
 
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // of sti_layer_forward_static
+
 // Offsets of the scratch regions of one layer call inside the caller's workspace.
 struct WorkspaceLayout {
     size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
