@@ -439,7 +439,7 @@ sti_status bring_in(const sti_dims &d, const sti_shard *shards, const void *x, s
     *in = x;
     *in_layout = LAYOUT_ROWS;
     *in_buffer = io_dtype != act;
-    if (io_dtype == STI_F32 && wl.few && wl.inner == LAYOUT_TILED && few_takes_f32_rows((int)T, m, 3 * d.d_head, d.d_model)) {
+    if (io_dtype == STI_F32 && wl.few && few_takes_f32_rows((int)T, m, 3 * d.d_head, d.d_model)) {
         *in_layout = LAYOUT_ROWS_F32;
         *in_buffer = false;
         return STI_OK;

@@ -86,6 +86,17 @@ def test_layers_that_fit_only_row_by_row(gpu, oracle_mod, d, M, f, B, L, outlier
     assert_parity(y_static.float().cpu().numpy(), want, TOL[1])
 
 
+@pytest.mark.parametrize("B,L,io", [(4, 47, "f32"), (4, 47, "f16"), (5, 35, "f32")])
+def test_float32_rows_in_layers_that_fit_only_row_by_row(gpu, oracle_mod, B, L, io):
+    """Q/K/V of few shards reads the caller's float32 rows in either layout: the first LayerNorm's residual is the same unrounded row."""
+    torch, P, D = gpu
+    wl = S.small_workload(55, S.Dims(640, 55, 64, 256, 1e-12), 1, B, L, n_absent=42, io_dtype=io)
+    y_static, y_ws = _call_both(gpu, wl, 1)
+    assert torch.equal(y_static, y_ws)
+    want = oracle_mod.layer_forward(wl.dims, wl.shards[0], wl.params[0], wl.x)
+    assert_parity(y_static.float().cpu().numpy(), want, TOL[1])
+
+
 @pytest.mark.parametrize("d,M,f,B,L,io", [(768, 42, 256, 1, 225, "f16"), (768, 42, 256, 5, 45, "f32"), (832, 47, 192, 1, 225, "f16")])
 def test_layers_near_the_route_line_take_the_same_kernels(gpu, oracle_mod, d, M, f, B, L, io):
     """A few tokens beyond the line, where the few-token kernels' buffers would not fit the array but the others' do."""
