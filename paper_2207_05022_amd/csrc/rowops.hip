@@ -356,9 +356,11 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
     // many rows: 32 lanes per row (8 rows per workgroup); few rows: a wave and a workgroup per row, so that the rows spread
     // over as many compute units as there are; chunks per lane sized to the row, so that the registers hold no more
     // loads in flight than it has
-    if (vec && !planes && T >= 2048 && d <= 1024) {
-        if (d <= 768) STI_LN_VEC(32, 6, 8);
-        else STI_LN_VEC(32, 8, 8);
+    if (!TILED && vec && !planes && T >= 2048 && d <= 1024) {   // (tiled: at most kFewMaxTokens rows)
+        if constexpr (!TILED) {
+            if (d <= 768) STI_LN_VEC(32, 6, 8);
+            else STI_LN_VEC(32, 8, 8);
+        }
     } else if (vec && planes) {
         if constexpr (DT == STI_F32 && std::is_same<RT, float>::value) {
             if (d <= 768) STI_LN_VEC(64, 3, 4);
