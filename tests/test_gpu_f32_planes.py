@@ -1,0 +1,93 @@
+"""Accuracy of float32 layers, beyond what the general tolerance of the float32 path (1e-5 of the largest value) shows."""
+import numpy as np
+import pytest
+
+import sti_synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    import paper_2207_05022_amd as P
+    from paper_2207_05022_amd import device as D
+    assert torch.cuda.is_available(), "needs a GPU"
+    return torch, P, D
+
+
+def forward(gpu, wl, want_planes):
+    torch, P, D = gpu
+    shards, params, x = D.upload_workload(wl)
+    y = torch.full_like(x, float("nan"))
+    ws = torch.empty(P.sti_workspace_bytes(wl.dims, wl.batch, wl.seq, P.STI_PREC_F32), dtype=torch.uint8, device="cuda")
+    P.sti_profile_begin()
+    P.sti_layer_forward(wl.dims, shards[0], params[0], x, y, P.STI_PREC_F32, ws)
+    torch.cuda.synchronize()
+    launches = {k: n for k, (n, _) in P.sti_profile_end().items()}
+    assert launches["decode"] == (2 if want_planes else 1)   # planes: attention's weights, then the FFN's
+    return y.cpu().numpy()
+
+
+def norm_error(got, want):
+    return float(np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want))
+
+
+def pack(index, k):
+    bits = (index[:, None] >> np.arange(k)) & 1
+    return np.packbits(bits.astype(np.uint8).ravel(), bitorder="little")
+
+
+def one_product(live, bits, dims, tokens):
+    """A layer in which one projection multiplies random weights and the others select or are zero: its product, exact on the way
+    in and out but for LayerNorm and GELU, is the output's largest term."""
+    rng = np.random.default_rng([44, bits, len(live)])
+    d, M, dh, f = dims.d_model, dims.n_heads, dims.d_head, dims.ffn_per_shard
+    random = rng.normal(0.0, 0.2, 1 << min(bits, 6)).astype(np.float32)
+    random[0], random[1] = 0.0, 1.0
+
+    def dense(rows, cols):
+        return rng.normal(0.0, 0.2, (rows, cols)).astype(np.float32) if bits == 32 else rng.integers(2, 64, (rows, cols))
+
+    def zeros(rows, cols):
+        return np.zeros((rows, cols), np.float32 if bits == 32 else np.int64)
+
+    def select(rows, cols, row0, col0):     # rows row0 .. of an identity over the concatenated shards
+        w = zeros(rows, cols)
+        for r in range(rows):
+            c = (row0 + r - col0) % (M * dh if cols == dh else max(d, M * f))
+            if c < cols:
+                w[r, c] = 1
+        return w
+    shards = []
+    for i in range(M):
+        v = dense(dh, d) if live == "v" else select(dh, d, i * dh, 0) if live == "o" else zeros(dh, d)
+        o = dense(d, dh) if live == "o" else select(d, dh, 0, i * dh) if live == "v" else zeros(d, dh)
+        w1 = dense(f, d) if live == "ffn1" else select(f, d, i * f % d, 0) if live == "ffn2" else zeros(f, d)
+        w2 = dense(d, f) if live == "ffn2" else select(d, f, 0, i * f) if live in ("ffn1", "gelu") else zeros(d, f)
+        flat = np.concatenate([m.ravel() for m in (zeros(dh, d), zeros(dh, d), v, o, w1, w2)])
+        shards.append(S.Shard(32, flat.astype(np.float32), None) if bits == 32 else S.Shard(bits, pack(flat, bits), random))
+    prm = {n: np.zeros(M * dh if n in ("bq", "bk", "bv") else M * f if n == "b1" else d, np.float32) for n in S.LayerParams.NAMES}
+    prm["ln1_g"][:] = prm["ln2_g"][:] = 1.0
+    x = rng.normal(0.0, 1.0, (tokens, 1, d)).astype(np.float32)
+    return S.Workload(live, dims, tokens, 1, np.full((1, M), bits, np.int8), [shards], [S.LayerParams(**prm)], x)
+
+
+@pytest.mark.parametrize("tokens,spread", [(1, 0.05), (1, 0.3), (1, 1.0), (856, 0.05), (856, 1.0)])
+def test_gelu_is_as_accurate_as_one_from_erf(gpu, oracle_mod, tokens, spread):
+    """The neurons' arguments are the bias, the second LayerNorm sees the GELU alone; mean and scale, which all features
+    share, are fitted out.  z / 2 (1 + erf) in float32 has 3.7e-8 to 4.1e-8 (2-norm), the two roundings of LayerNorm 3.5e-8 together: 5.4e-8."""
+    dims = S.Dims(768, 12, 64, 128, 1e-12)
+    wl = one_product("gelu", 32, dims, tokens)
+    prm = wl.params[0]
+    prm.ln1_g[:] = 0.0
+    z = np.random.default_rng(7).normal(0.0, spread, 768).astype(np.float32)
+    prm.b1[:768] = z
+    for s in wl.shards[0]:
+        s.data *= np.float32(64.0)
+    want = oracle_mod.layer_forward(dims, wl.shards[0], prm, wl.x).reshape(tokens, 768)
+    got = forward(gpu, wl, tokens > 1).reshape(tokens, 768).astype(np.float64)
+    assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+    fit = np.polyfit(want[0], got[0], 1)
+    assert abs(fit[0] - 1.0) < 5e-7
+    assert norm_error(got[0], np.polyval(fit, want[0])) <= 5.5e-8
