@@ -1,8 +1,14 @@
-"""Accuracy of float32 layers, beyond what the general tolerance of the float32 path (1e-5 of the largest value) shows."""
+"""float32 layers on the bfloat16 matrix cores: every tile width, and accuracy that a lost term of a product would spoil.
+
+The general tolerance of the float32 path (1e-5 of the largest value) leaves room for a product without one of its six
+terms (2.4e-6 of it, 2-norm).  Here single products decide the output and the 2-norm of the error is bounded: 768 and 3072 products of
+random operands summed in float32 leave 3.9e-7 and 8.6e-7, LayerNorm about 1e-7.
+"""
 import numpy as np
 import pytest
 
 import sti_synth as S
+from parity import assert_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -31,6 +37,30 @@ def forward(gpu, wl, want_planes):
 
 def norm_error(got, want):
     return float(np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want))
+
+
+# tile widths (32-column strips) and K splits of Q/K/V, O, FFN1, FFN2 as chosen for these sizes; the last 128 rows and most of
+# the last column tiles are cut
+@pytest.mark.parametrize("d,M,f,B,L", [
+    (768, 12, 256, 7, 143),    # 3, 1, 3, 3 with 4 K splits
+    (960, 8, 192, 7, 88),      # 1, 1, 1, 2 with 3
+    (576, 15, 64, 5, 181),     # 3, 2 with 3, 1, 2 with 3
+    (576, 9, 192, 5, 181),     # 2, 2 with 3, 2, 2 with 3
+    (448, 11, 64, 26, 61),     # 4, 1, 2, 1
+    (832, 15, 64, 21, 57),     # 4, 4 with 3, 2, 4 with 3
+    (128, 11, 192, 34, 98),    # 4, 1 with 2, 4, 1 with 2
+    (640, 7, 128, 33, 98),     # 3, 3, 4, 3
+    (320, 5, 192, 33, 98),     # 4, 2, 4, 4 with 3
+    (320, 8, 64, 33, 98),      # 3, 3 with 2, 2, 3 with 2
+    (832, 7, 192, 37, 98),     # 3, 4, 3, 4
+])
+def test_tile_widths(gpu, oracle_mod, d, M, f, B, L):
+    wl = S.small_workload(44000 + d + M, S.Dims(d, M, 64, f, 1e-12), 1, B, L)
+    S.make_every_term_matter(wl, M, amp=2.0)
+    want = oracle_mod.layer_forward(wl.dims, wl.shards[0], wl.params[0], wl.x)
+    got = forward(gpu, wl, True)
+    assert_parity(got, want, 1e-5)
+    assert norm_error(got, want) <= 2e-6
 
 
 def pack(index, k):
@@ -71,6 +101,28 @@ def one_product(live, bits, dims, tokens):
     prm["ln1_g"][:] = prm["ln2_g"][:] = 1.0
     x = rng.normal(0.0, 1.0, (tokens, 1, d)).astype(np.float32)
     return S.Workload(live, dims, tokens, 1, np.full((1, M), bits, np.int8), [shards], [S.LayerParams(**prm)], x)
+
+
+def two_planes(w):
+    """w without the lowest of its three bfloat16 values."""
+    def bf16(v):
+        u = v.astype(np.float32).view(np.uint32)
+        return ((u + 0x7FFF + (u >> 16 & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+    h = bf16(w)
+    return h.astype(np.float64) + bf16(w - h)
+
+
+@pytest.mark.parametrize("bits", [32, 6])
+@pytest.mark.parametrize("live,f,bound", [("v", 128, 1e-6), ("o", 128, 1e-6), ("ffn1", 128, 1e-6), ("ffn2", 256, 1.5e-6)])
+def test_no_term_of_a_product_is_lost(gpu, oracle_mod, live, f, bound, bits):
+    wl = one_product(live, bits, S.Dims(768, 12, 64, f, 1e-12), 856)
+    want = oracle_mod.layer_forward(wl.dims, wl.shards[0], wl.params[0], wl.x)
+    assert norm_error(forward(gpu, wl, True), want) <= bound
+    # what a lost term leaves in the product is beyond that
+    rng = np.random.default_rng(5)
+    a, w = rng.normal(size=(64, 768)).astype(np.float32), rng.normal(0.0, 0.2, (768, 64)).astype(np.float32)
+    exact = a.astype(np.float64) @ w
+    assert norm_error(a.astype(np.float64) @ two_planes(w), exact) > 1.5 * bound
 
 
 @pytest.mark.parametrize("tokens,spread", [(1, 0.05), (1, 0.3), (1, 1.0), (856, 0.05), (856, 1.0)])
