@@ -71,12 +71,16 @@ typedef enum {
 
 typedef enum { STI_F32 = 0, STI_F16 = 1, STI_BF16 = 2 } sti_dtype;
 
-/* STI_PREC_F32: float32 storage and arithmetic end to end (decode to a float32
- *   working buffer, then float32 kernels); any dimensions.
+/* STI_PREC_F32: float32 weights (decoded into a working buffer in the workspace), activations, products and
+ *   sums; any dimensions.  In layers of 3e9 multiplications and more (1.2e9 of them in present shards)
+ *   with d_head == 64, d_model and ffn_per_shard multiples of 64 and no outlier dictionaries the projections
+ *   multiply on the bfloat16 matrix cores: each operand is the sum of three bfloat16 values, which
+ *   hold its 24 bits, and six of the nine products of those are summed in float32 (the three left out
+ *   are below 2^-23 of the product).
  * STI_PREC_F16_MFMA: binary16 operands on the matrix cores with float32
  *   accumulation.  With few tokens per call (up to 128; up to 192 when d_model <= 768; up to
- *   between 128 and 1024, fewer for larger layers, at d_model 256 .. 1024: BERT-base 640,
- *   d_model 1024 with 16 shards 512) the projections decode the packed streams
+ *   between 128 and 1024, fewer for larger layers, at d_model 256 .. 1024: BERT-base 704,
+ *   d_model 1024 with 16 shards 576) the projections decode the packed streams
  *   inside their weight loader; with more tokens, and for shards that carry an outlier
  *   dictionary, a layer's shards are decompressed once into a binary16 working buffer in
  *   the workspace that the projections then read (every weight would otherwise be
@@ -175,7 +179,9 @@ sti_status sti_decode_shards(const sti_shard *shards, int n_shards, uint64_t wei
  *
  * sti_workspace_bytes returns 0 for invalid arguments.  With the other arguments equal it does not
  * shrink as batch * seq grows, and neither does sti_model_workspace_bytes: a workspace sized for the
- * largest call serves the smaller ones.
+ * largest call serves the smaller ones.  Less than sti_workspace_bytes is STI_ERR_WORKSPACE, except where
+ * other kernels can do with it (STI_PREC_F16_MFMA, a range of token counts between the two routes of
+ * sti_precision: BERT-base 641 .. 704): their results differ in rounding.
  * ------------------------------------------------------------------------- */
 size_t sti_workspace_bytes(const sti_dims *dims, int batch, int seq, sti_precision precision);
 
@@ -298,9 +304,11 @@ sti_status sti_model_forward_masked(const sti_dims *dims, int n_layers, const st
  * enough of them - and otherwise a few layers are decompressed by one launch right before the
  * first of them runs).  Applies to STI_PREC_F16_MFMA whenever
  * the layer goes through the working buffer (many tokens, see sti_precision); otherwise, and for
- * n_layers <= 1, it equals sti_workspace_bytes.
- * sti_model_forward takes this whole-model route whenever workspace_bytes is at least this value
- * and the per-layer route otherwise: same results either way.  The whole-model route uploads
+ * n_layers <= 1, it equals sti_workspace_bytes.  (Near the number of tokens where the routes meet - BERT-base
+ * 641 .. 704 - it asks for the ring although the layers do not go through the working buffer.)
+ * Where they do, sti_model_forward takes this whole-model route whenever workspace_bytes is at least
+ * this value and the per-layer route otherwise.  From sti_workspace_bytes on the results do not depend on
+ * the size of the workspace.  The whole-model route uploads
  * a shard table through a pinned host buffer that later calls reuse and is therefore
  * never taken while `hip_stream` is capturing: a captured call runs the per-layer route
  * (kernel launches only), whatever the workspace size.  0 on invalid arguments. */

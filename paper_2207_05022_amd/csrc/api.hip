@@ -219,9 +219,10 @@ inline bool few_token_path(const sti_dims &d, int64_t T)
     return workspace_layout(d, (T + 63) / 64 * 64, STI_PREC_F16_MFMA, true).total <= kStaticScratchBytes;
 }
 
-// Up to here the workspace queries leave room for the few-token kernels only; between this and the line above for either family,
-// so that what is asked for and what is accepted does not depend on where that line lies (a call with less workspace than
-// the few-token kernels take there goes the other way).  128 tokens, or 192 when d_model <= 768, outside d_model 256 .. 1024.
+// Up to here the workspace queries leave room for the few-token kernels only; between this and the line above for either family, the
+// buffers of several layers among them.  A call there with less than the few-token kernels take, but enough for the others
+// (BERT-base, 700 tokens: 34.7 and 30.3 MB for one layer), goes the other way instead of being refused.  128 tokens, or 192 when
+// d_model <= 768, outside d_model 256 .. 1024.
 inline int64_t few_token_limit(const sti_dims &d)
 {
     const int64_t small = d.d_model <= 768 ? 192 : 128;
