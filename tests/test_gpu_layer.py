@@ -426,7 +426,48 @@ def test_less_workspace_than_the_few_token_kernels_take(gpu, oracle_mod):
         assert_parity(y.cpu().numpy(), want, TOL["mfma"])
 
 
-@pytest.mark.parametrize("prec,dims,B,L", [("f32", SMALL, 2, 19), ("mfma", MID, 1, 66), ("mfma", MID, 12, 100), ("mfma", MID, 64, 128)])
+@pytest.mark.parametrize("d,M", [(768, 16), (768, 17), (832, 13), (832, 17), (512, 8), (1024, 16)])
+@pytest.mark.parametrize("B,L,masked", [(1, 1, False), (1, 33, False), (2, 61, True)])
+def test_few_token_rows_in_float32_and_binary16_give_the_same(gpu, d, M, B, L, masked):
+    """The Q/K/V projection reads float32 rows as they are with up to 12 K tiles and 16 blocks of weights, else a launch in front of
+    it rounds and tiles them: rows that binary16 holds exactly give the layers of binary16 rows on either side of both limits, up to the last
+    rounding (to binary16 or not, by two instantiations of LayerNorm: half an ulp of binary16 and a few float32 roundings)."""
+    torch, P, D = gpu
+    wl = S.small_workload(42000 + d + M, S.Dims(d, M, 64, 128, 1e-12), 2, B, L, n_absent=0, io_dtype="f16")
+    S.make_every_term_matter(wl, 5, amp=2.0)
+    lens = _key_lengths(L, B, L) if masked else None
+    y16 = _run_masked(gpu, wl, "mfma", lens, "model")
+    wl.x, wl.io_dtype = wl.x.astype(np.float32), "f32"
+    P.sti_profile_begin()
+    y32 = _run_masked(gpu, wl, "mfma", lens, "model")
+    converted = {k: n for k, (n, _) in P.sti_profile_end().items()}["convert"]
+    assert converted == (0 if d <= 768 and M <= 16 else 1)
+    assert y32.dtype == torch.float32 and torch.isfinite(y32).all()
+    assert ((y32 - y16.float()).abs() <= 2.0 ** -11 * y32.abs() + 2.0 ** -20).all()
+
+
+def test_any_sufficient_workspace_gives_the_same(gpu):
+    """Between the two lines: one layer's buffers, those of several, and the fixed array."""
+    torch, P, D = gpu
+    wl = S.small_workload(41901, S.Dims(768, 12, 64, 256, 1e-12), 1, 5, 140, n_absent=1)
+    S.make_every_term_matter(wl, 3, amp=2.0)
+    outs = [_run_masked(gpu, wl, "mfma", None, route) for route in ("layer", "model", "whole")]
+    shards, params, x = D.upload_workload(wl)
+    store = D.store_from_plan(shards * 3)
+    for nbytes in (P.sti_workspace_bytes(wl.dims, 5, 140, P.STI_PREC_F16_MFMA), P.sti_model_workspace_bytes(wl.dims, 3, 5, 140, P.STI_PREC_F16_MFMA)):
+        y = torch.full_like(x, float("nan"))
+        P.sti_model_forward(wl.dims, store, params * 3, np.concatenate([wl.plan] * 3), x, y, P.STI_PREC_F16_MFMA,
+                            torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        outs.append(y)
+    y = torch.full_like(x, float("nan"))
+    P.sti_layer_forward_static(wl.dims, shards[0], params[0], x, y, P.STI_PREC_F16_MFMA)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, y) for o in outs[:3]) and torch.equal(outs[3], outs[4])
+
+
+@pytest.mark.parametrize("prec,dims,B,L", [("f32", SMALL, 2, 19), ("mfma", MID, 1, 66), ("mfma", MID, 12, 100), ("mfma", MID, 64, 128),
+                                           ("f32", S.Dims(768, 12, 64, 256, 1e-12), 4, 107)])   # (planes made behind the LayerNorm)
 def test_parameters_begin_at_any_float(gpu, prec, dims, B, L):
     """Biases and LayerNorm parameters 4, 8 and 12 bytes past a 16-byte boundary."""
     import types
