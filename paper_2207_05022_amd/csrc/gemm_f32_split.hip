@@ -1,13 +1,14 @@
 // float32 layers on the bfloat16 matrix cores (any number of tokens that fills them; d_model and neurons multiples of 64,
 // heads of 64 features): every float32 operand is the sum of three bfloat16 values,
 //   x = h + m + l,   h = bf16(x), m = bf16(x - h), l = bf16(x - h - m)
-// (8 + 8 + 8 significant bits, rounded to nearest: what is left is below 2^-25 of x), and a product keeps the six
-// terms down to 2^-17 of it,  h h' + (h m' + m h') + (m m' + h l' + l h');  the three left out are below 2^-26.
-// Six products at 16 times the rate of the float32 matrix instruction.
+// (three times 8 significant bits, rounded to nearest: all 24 of x, unless l is too small for a bfloat16), and a product keeps six terms,
+//   h h' + (h m' + m h') + (m m' + h l' + l h');
+// the other three come to 2^-23 of it at worst, over random pairs 2^-24.2 at most and 2^-27.4 in the 2-norm.  Six products at 16 times the rate of the float32 matrix instruction.  (The method is that of G. Henry, P. T. P.
+// Tang and A. Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019.)
 //
-// Every product is exact in float32 and a matrix instruction adds sixteen of them before it rounds, where the float32 one
-// rounds after four: against float64, random operands, K = 768 and 3072: 3.9e-7 and 8.6e-7 (2-norm, relative) where
-// v_mfma_f32_16x16x4_f32 has 5.0e-7 and 1.01e-6.
+// Products of bfloat16 values are exact in float32; the terms are added smallest first.  Measured against float64, random operands, K = 768
+// and 3072: 3.9e-7 and 8.6e-7 (2-norm, relative); v_mfma_f32_16x16x4_f32 5.0e-7 and 1.01e-6, which is what one rounding per
+// product gives.
 //
 // What bounds it: BERT-base, 8 x 128 tokens, us per launch, float32 against these matrix instructions: Q/K/V 34 / 27, O 13 / 12, FFN1 43 / 33,
 // FFN2 43 / 31; the K loops run at 1.1 to 1.4 PFLOP/s of bfloat16 products, near what the chip's clock under this load allows, around them

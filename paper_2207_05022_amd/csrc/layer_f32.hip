@@ -1,8 +1,9 @@
 // float32 kernels of the layer: the decompress-into-a-working-buffer route of
 // the paper (Section "Submodel execution": shards are decompressed into a
 // buffer holding one layer of FP32 weights, then the layer is computed), with
-// float32 storage and arithmetic throughout.  Any dimensions are accepted; the projections of larger layers whose dimensions are
-// multiples of 64 go through gemm_f32_split.hip instead.
+// float32 storage and arithmetic.  Any dimensions are accepted.  The projections of larger layers without outlier dictionaries whose
+// dimensions are multiples of 64 go through gemm_f32_split.hip instead, three bfloat16 values to a float32; attention and LayerNorm
+// are those of this path.
 //
 // Products run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32: 256 flops per clock and
 // compute unit, float32 multiply and accumulate), in the projections as well as in the attention.
