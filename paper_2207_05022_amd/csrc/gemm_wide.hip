@@ -248,7 +248,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // first A fetches and weight loads are not behind a round trip to the argument buffer
     // (14 dwords fit: block_shape = block_rows | block_cols << 16, blocks_splits = n_blocks | k_splits << 16; reciprocals of the
     // tiles of a band of the tile order and of a weight block's 32-row strips (N split) or K tiles: divisions in their place,
-    // one of them in every step of the K loop of O and FFN2, made 24 layers of d_model 1024, 24 x 384 tokens 1.2 % slower)
+    // one of them in every step of the K loop of O and FFN2, made 24 layers of d_model 1024, 24 x 384 tokens 0.9 to 1.8 % slower,
+    // from box to box)
     const void *hot_A, const void *hot_w0, const void *hot_resid, const float *hot_bias0, int32_t hot_w_stride,
     int32_t hot_T, uint32_t hot_band_recip, uint32_t hot_block_recip, uint32_t hot_block_shape, uint32_t hot_blocks_splits,
     GemmProblem p, ShardIds shard_of)   // (of p, only the fields that are not among the leading arguments are read)
