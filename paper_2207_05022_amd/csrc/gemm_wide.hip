@@ -7,8 +7,8 @@
 //
 // One workgroup of NW waves owns a (RA*32) x (NW*32) tile and is sized so that a compute
 // unit holds all its waves at once (12 wave slots at this register budget): all waves of a
-// unit then move through the K loop in step, share one copy of the A tile and finish together - or, with
-// many tiles, so that two workgroups share a unit (RB = 2 below).
+// unit then move through the K loop in step, share one copy of the A tile and finish together.  Launches of
+// many tiles go to the kernel with larger ones (gemm_large.hip); the choice is made here, for both.
 //   - the A tile [BM x 64] goes global -> LDS directly (global_load_lds_dwordx4, no
 //     registers, no LDS store instructions), three stages; its 16-byte chunks are XOR-swizzled
 //     by row pair so that the unpadded rows read without bank conflicts;
@@ -30,6 +30,7 @@
 #include <math.h>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
+#include "gemm_tile.hpp"
 #include "attention_core.hpp"
 
 // STI_PHASE_STAMPS (the phase-budget build libsti_phases.so only, never the product library): wave 0
@@ -83,41 +84,17 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const void global_cptr;
 typedef __attribute__((address_space(3))) void lds_ptr;
 
-// GELU with the Gaussian CDF (the erf form, not the tanh form):  z * Phi(z),
-// Phi(z) = 1/2 + z * R(z^2).  R is a degree-8 polynomial in u = 2 z^2 / 4.5^2 - 1, fitted in
-// float64 (weighted least squares on Chebyshev nodes) to (Phi(z) - 1/2) / z on |z| <= 4.5;
-// beyond that Phi is taken at the clamped argument (1 - Phi(4.5) = 3.4e-6).  Evaluated in
-// float32 the absolute error of the result is below 5e-5 for all z (0.1 of a binary16 ulp at
-// 0.35, the value at z = 0.6 where the error peaks) and its relative error below 1e-4 for
-// z > -1; 13 arithmetic instructions per value and no transcendental ones, which matters
-// because the epilogue of the FFN1 projection is bound by exactly these instructions.
-__device__ inline float gelu_erf(float z)
-{
-    const float zc = __builtin_amdgcn_fmed3f(z, -4.5f, 4.5f);
-    const float u = fmaf(zc * zc, 2.0f / 20.25f, -1.0f);
-    float r = 3.174704981e-03f;
-    r = fmaf(r, u, -9.158361878e-03f);
-    r = fmaf(r, u, 1.244540513e-02f);
-    r = fmaf(r, u, -1.696567595e-02f);
-    r = fmaf(r, u, 2.754268719e-02f);
-    r = fmaf(r, u, -4.047719455e-02f);
-    r = fmaf(r, u, 5.482644199e-02f);
-    r = fmaf(r, u, -7.717846451e-02f);
-    r = fmaf(r, u, 1.569020774e-01f);
-    return z * fmaf(zc, r, 0.5f);
-}
-
 // LDS of the attention that follows the Q/K/V tile (GEMM_QKV_ATTN): per head Q and K row-major
 // with padded rows and V transposed, for 128 positions of 64 features
 constexpr int ATT_L = 128, ATT_DH = 64, ATT_KPAD = ATT_DH + 8, ATT_VTS = ATT_L + 8;
 constexpr int ATT_HEAD_HALVES = 2 * ATT_L * ATT_KPAD + ATT_DH * ATT_VTS;
 constexpr size_t kAttentionLdsBytes = (size_t)2 * ATT_HEAD_HALVES * 2;
 
-template <int RA, int NW, int KS, int RB>
+template <int RA, int NW, int KS>
 constexpr size_t wide_lds_bytes()
 {
-    constexpr size_t stages = (size_t)KS * (RB == 2 ? 2 : 3) * (RA * 32) * BK * 2;
-    constexpr size_t tile = (size_t)(RA * 32) * (NW * RB * 32 + 8) * 2;
+    constexpr size_t stages = (size_t)KS * 3 * (RA * 32) * BK * 2;
+    constexpr size_t tile = (size_t)(RA * 32) * (NW * 32 + 8) * 2;
     constexpr size_t partial = (size_t)(KS - 1) * (RA * 32) * (NW * 32) * 4;
     constexpr size_t m = stages > tile ? stages : tile;
     return m > partial ? m : partial;
@@ -226,23 +203,12 @@ __device__ inline void patch_next_layer(const GemmProblem &p, int d, int dh, int
     }
 }
 
-struct ShardIds {   // original shard id of every weight block (selects the bias slice), four to a scalar-loadable dword
-    uint32_t id4[kMaxShardsPerLayer / 4];
-    __device__ inline int id(int block) const { return (id4[block >> 2] >> (8 * (block & 3))) & 0xFF; }
-};
-
 // KS = 2 (outputs as narrow as d_model, long K): the workgroup has two groups of NW waves that
 // each take one half of K for the same tile, with A stages of their own; the second group
 // hands its accumulators over through LDS at the end.  Twice the waves per compute unit for
 // a tile count that is fixed by the output size.
-//
-// RB = 2 (many tiles): a wave owns two 32-column strips, 128 x 64 outputs, so that an A fragment out of LDS serves two
-// products; four waves are a workgroup and two workgroups share a compute unit without waiting for
-// each other: one multiplies while the other is in its start-up or epilogue.  128 accumulators leave room for
-// one K tile of weights in flight instead of two.  9216 tokens, d_model 1024: FFN1 89 us (121 with the best of the other
-// shapes), Q/K/V 69 (85).
-template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
-__global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kernel(
+template <int KIND, int RA, int NW, int KS, bool EARLY>
+__global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // what the first loads of a workgroup depend on, as leading scalar arguments: these arrive
     // preloaded in scalar registers (the build asks for kernel-argument preloading), so that the
     // first A fetches and weight loads are not behind a round trip to the argument buffer
@@ -261,10 +227,10 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     const unsigned long long wall0 = wall_clock64();
     STI_STAMP(0);
 #endif
-    constexpr int BM = RA * 32, BN = NW * RB * 32, NT = NW * KS * 64, NTH = NW * 64, STAGES = RB == 2 ? 2 : 3;
+    constexpr int BM = RA * 32, BN = NW * 32, NT = NW * KS * 64, NTH = NW * 64, STAGES = 3;
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
     constexpr bool qkv = (KIND == GEMM_QKV || KIND == GEMM_QKV_ATTN);
-    static_assert(KIND != GEMM_QKV_ATTN || (RA == 4 && NW == 12 && KS == 1 && RB == 1), "two heads of one 128-token sequence per tile");
+    static_assert(KIND != GEMM_QKV_ATTN || (RA == 4 && NW == 12 && KS == 1), "two heads of one 128-token sequence per tile");
     constexpr int STAGE = BM * BK;              // halves per A stage
     constexpr int FETCHES = BM / 8;             // fetch instructions per A stage: 8 rows (1 KiB) each
     constexpr int FPW = (FETCHES + NW - 1) / NW;   // per wave: wave w issues fetches w, w + NW, ...
@@ -321,7 +287,7 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // N and the block widths are multiples of 64, so a wave's columns are all inside or all
     // outside the matrix and inside one block; a wave outside recomputes the first columns and its results are
     // dropped by the column mask of the stores
-    const int nw_real = tile_n * BN + wave * (RB * 32);
+    const int nw_real = tile_n * BN + wave * 32;
     const int nw = nw_real < N ? nw_real : 0;
     int nblk = 0, nrow0 = nw;
     if (n_split) {
@@ -330,13 +296,11 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     }
     const int tiles_per_kblock = n_split ? nkt * KS : hot_block_cols / BK;
 
-    float16v acc[RA][RB];
+    float16v acc[RA];
 #pragma unroll
     for (int i = 0; i < RA; ++i)
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][r][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
 
     // ---- A tile: lane l of a fetch instruction fills LDS slot (row l/8, chunk l%8) of its 8
     //      rows with the chunk (l%8) ^ ((row/2)%8) of that row, so that the 16 rows that one
@@ -371,13 +335,13 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     for (int s = 0; s < 4; ++s) frag_off[s] = lr * (BK * 2) + (((g * 4 + s) ^ ((lr >> 1) & 7)) * 16);
 
     const uint32_t lane16 = lane * 16;
-    auto frag_ptr = [&](int kt, int r) -> const uint8_t * {
+    auto frag_ptr = [&](int kt) -> const uint8_t * {
         int blk, ktb, row;
         kt += kt0;
         if (n_split) {
-            blk = nblk; ktb = kt; row = nrow0 + r * 32;
+            blk = nblk; ktb = kt; row = nrow0;
         } else {
-            blk = quotient(kt, tiles_per_kblock, hot_block_recip); ktb = kt - blk * tiles_per_kblock; row = nw + r * 32;
+            blk = quotient(kt, tiles_per_kblock, hot_block_recip); ktb = kt - blk * tiles_per_kblock; row = nw;
         }
         // (the blocks of a working buffer lie at a constant distance: no look-up in the block table)
         const uint8_t *base = (const uint8_t *)hot_w0 + (int64_t)blk * hot_w_stride;   // (stride < 2^31)
@@ -390,21 +354,18 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // barrier: measured 2 % faster end to end than issuing at the top, while the split-K
     // shapes are faster with the issue at the top).  The wait in front of the barrier is
     // written by hand: it lets the loads of tile t+1, the last ones issued, stay in flight.
-    u32x4 bw[STAGES][RB][4];
+    u32x4 bw[STAGES][4];
     int n_fetch = 0;   // A fetches this wave issues per stage
 #pragma unroll
     for (int j = 0; j < FPW; ++j) n_fetch += (wave + NW * j < FETCHES) ? 1 : 0;
-    auto issue = [&](int kt, u32x4 (&dst)[RB][4]) {
+    auto issue = [&](int kt, u32x4 (&dst)[4]) {
         fetch_a(kt, kt % STAGES);
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const uint8_t *q = frag_ptr(kt, r);
-            asm volatile("global_load_dwordx4 %0, %4, %5\n\t"
-                         "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
-                         "global_load_dwordx4 %2, %4, %5 offset:2048\n\t"
-                         "global_load_dwordx4 %3, %4, %5 offset:3072"
-                         : "=&v"(dst[r][0]), "=&v"(dst[r][1]), "=&v"(dst[r][2]), "=&v"(dst[r][3]) : "v"(lane16), "s"(q) : "memory");
-        }
+        const uint8_t *q = frag_ptr(kt);
+        asm volatile("global_load_dwordx4 %0, %4, %5\n\t"
+                     "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
+                     "global_load_dwordx4 %2, %4, %5 offset:2048\n\t"
+                     "global_load_dwordx4 %3, %4, %5 offset:3072"
+                     : "=&v"(dst[0]), "=&v"(dst[1]), "=&v"(dst[2]), "=&v"(dst[3]) : "v"(lane16), "s"(q) : "memory");
     };
 #define STI_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
     // EARLY (64-row tiles of the d_model-wide projections, K not split over workgroups): what
@@ -413,14 +374,14 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     // clock kernel).  They are the oldest loads in flight, so the first wait of the K loop
     // covers them.  (A variant of its own: with K split over workgroups nothing is added here.)
     constexpr bool PRE = EARLY;
-    static_assert(!EARLY || (!n_split && RA <= 2 && RB == 1), "early operands: 64-row tiles of OUT / FFN_DOWN");
+    static_assert(!EARLY || (!n_split && RA <= 2), "early operands: 64-row tiles of OUT / FFN_DOWN");
     const _Float16 *R = (const _Float16 *)hot_resid;
-    f32x4 bias[RB][2][2];
+    f32x4 bias[2][2];
     u32x4 resv[PRE ? RA : 1][2];
     auto load_epilogue_operands = [&]() {
 #pragma unroll
-        for (int rq = 0; rq < 2 * RB; ++rq) {
-            const int c = 16 * rq + 8 * g;    // first column of the piece inside the wave's columns
+        for (int q = 0; q < 2; ++q) {
+            const int c = 16 * q + 8 * g;    // first column of the piece inside the wave's columns
             const float *bp;
             if constexpr (qkv) {
                 const int nrow = nrow0 + c;
@@ -431,8 +392,8 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             } else {
                 bp = hot_bias0 + nw + c;
             }
-            bias[rq >> 1][rq & 1][0] = *(const f32x4_any *)bp;
-            bias[rq >> 1][rq & 1][1] = *(const f32x4_any *)(bp + 4);
+            bias[q][0] = *(const f32x4_any *)bp;
+            bias[q][1] = *(const f32x4_any *)(bp + 4);
         }
         if constexpr (PRE) {
 #pragma unroll
@@ -443,11 +404,11 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             }
         }
     };
-    auto step = [&](int kt, u32x4 (&bcur)[RB][4], u32x4 (&bnew)[RB][4]) {
+    auto step = [&](int kt, u32x4 (&bcur)[4], u32x4 (&bnew)[4]) {
         constexpr int AHEAD = STAGES - 1;   // K tiles in flight
         // the weight fragments and the A stage of tile kt have landed (the barrier below is a
         // scheduling boundary: no MFMA of this step is placed above the wait) ...
-        if (AHEAD > 1 && kt + 1 < nkt) {
+        if (kt + 1 < nkt) {
             if (n_fetch == 2) STI_WAIT_LOADS(6);
             else if (n_fetch == 1) STI_WAIT_LOADS(5);
             else STI_WAIT_LOADS(4);
@@ -476,10 +437,7 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < RA; ++i)
-#pragma unroll
-                for (int r = 0; r < RB; ++r)
-                    acc[i][r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[r][s]), a_cur[i],
-                                                                     acc[i][r], 0, 0, 0);
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[s]), a_cur[i], acc[i], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if (KS == 1 && s == 0 && kt + AHEAD < nkt) issue(kt + AHEAD, bnew);
             __builtin_amdgcn_sched_barrier(0);
@@ -489,22 +447,15 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             }
         }
     };
-    static_assert(FPW <= 2 || RB == 2, "the hand-written waits cover up to two A fetches per wave");
+    static_assert(FPW <= 2, "the hand-written waits cover up to two A fetches per wave");
     if (PRE && half == 0) load_epilogue_operands();
     if (nkt > 0) issue(0, bw[0]);
-    if (STAGES > 2 && nkt > 1) issue(1, bw[1]);
+    if (nkt > 1) issue(1, bw[1]);
     STI_STAMP(1);
-    if constexpr (RB == 2) {
-        for (int kt = 0; kt < nkt; kt += 2) {
-            step(kt, bw[0], bw[1]);
-            if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
-        }
-    } else {
-        for (int kt = 0; kt < nkt; kt += 3) {
-            step(kt, bw[0], bw[2]);
-            if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
-            if (kt + 2 < nkt) step(kt + 2, bw[2], bw[1]);
-        }
+    for (int kt = 0; kt < nkt; kt += 3) {
+        step(kt, bw[0], bw[2]);
+        if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
+        if (kt + 2 < nkt) step(kt + 2, bw[2], bw[1]);
     }
 #undef STI_WAIT_LOADS
     STI_STAMP(3);
@@ -537,12 +488,12 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
                 half8 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float lo = acc[i][0][(2 * q) * 4 + e], hi = acc[i][0][(2 * q + 1) * 4 + e];
+                    const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
                     const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                      __builtin_bit_cast(uint32_t, hi), false, false);
                     const uint32_t s0 = sw[0], s1 = sw[1];
-                    o[e] = (_Float16)(__builtin_bit_cast(float, s0) + bias[0][q][0][e]);
-                    o[4 + e] = (_Float16)(__builtin_bit_cast(float, s1) + bias[0][q][1][e]);
+                    o[e] = (_Float16)(__builtin_bit_cast(float, s0) + bias[q][0][e]);
+                    o[4 + e] = (_Float16)(__builtin_bit_cast(float, s1) + bias[q][1][e]);
                 }
                 const int c = ch + 16 * q + 8 * g;
                 if (part < 2) {
@@ -590,14 +541,14 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) part[(i * 16 + v) * NTH + th] = acc[i][0][v];
+                for (int v = 0; v < 16; ++v) part[(i * 16 + v) * NTH + th] = acc[i][v];
         }
         __syncthreads();
         if (half == 0) {
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][0][v] += part[(i * 16 + v) * NTH + th];
+                for (int v = 0; v < 16; ++v) acc[i][v] += part[(i * 16 + v) * NTH + th];
         }
         __syncthreads();   // the sums are in registers: the buffer can take the staged tile
     }
@@ -613,7 +564,7 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
                     float x[8];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float lo = acc[i][0][(2 * q) * 4 + e], hi = acc[i][0][(2 * q + 1) * 4 + e];
+                        const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
                         const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                          __builtin_bit_cast(uint32_t, hi), false, false);
                         const uint32_t s0 = sw[0], s1 = sw[1];
@@ -636,27 +587,26 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
         const int row = i * 32 + lr;          // row inside the tile
-        half8 res[2 * RB];
+        half8 res[2];
         if constexpr (PRE) {
             res[0] = __builtin_bit_cast(half8, resv[i][0]);
             res[1] = __builtin_bit_cast(half8, resv[i][1]);
         } else if constexpr (!n_split) {
             const int m = m0 + row;
 #pragma unroll
-            for (int q = 0; q < 2 * RB; ++q) {
+            for (int q = 0; q < 2; ++q) {
                 u32x4 v = {0, 0, 0, 0};
                 if (m < hot_T) v = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
                 res[q] = __builtin_bit_cast(half8, v);
             }
         }
 #pragma unroll
-        for (int rq = 0; rq < 2 * RB; ++rq) {
-            const int r = rq >> 1, q = rq & 1;
+        for (int q = 0; q < 2; ++q) {
             float x[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // (element values first: a bit cast applied to a vector element itself reads element 0)
-                const float lo = acc[i][r][(2 * q) * 4 + e], hi = acc[i][r][(2 * q + 1) * 4 + e];
+                const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
                 const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
                                                                  __builtin_bit_cast(uint32_t, hi), false, false);
                 const uint32_t s0 = sw[0], s1 = sw[1];
@@ -666,12 +616,12 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
             half8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float y = x[e] + bias[r][q][e >> 2][e & 3];
-                if constexpr (KIND == GEMM_FFN_UP) y = gelu_erf(y);
-                if constexpr (!n_split) y += (float)res[rq][e];
+                float y = x[e] + bias[q][e >> 2][e & 3];
+                if constexpr (KIND == GEMM_FFN_UP) y = gelu_polynomial(y);
+                if constexpr (!n_split) y += (float)res[q][e];
                 o[e] = (_Float16)y;
             }
-            *(half8 *)(tile_out + row * LDT + wave * (RB * 32) + 16 * rq + 8 * g) = o;
+            *(half8 *)(tile_out + row * LDT + wave * 32 + 16 * q + 8 * g) = o;
         }
     }
     }
@@ -697,28 +647,28 @@ __global__ __launch_bounds__(NW * KS * 64, RB == 2 ? 2 : 3) void gemm_wide_kerne
     STI_STAMPS_OUT();
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
+template <int KIND, int RA, int NW, int KS, bool EARLY>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream);
 
-template <int KIND, int RA, int NW, int KS, int RB = 1>
+template <int KIND, int RA, int NW, int KS>
 hipError_t launch_shape(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
     if constexpr (!n_split && RA <= 2) {
-        if (p.k_splits <= 1) return launch_variant<KIND, RA, NW, KS, true, RB>(p, blocks, N, stream);
+        if (p.k_splits <= 1) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
     }
-    return launch_variant<KIND, RA, NW, KS, false, RB>(p, blocks, N, stream);
+    return launch_variant<KIND, RA, NW, KS, false>(p, blocks, N, stream);
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY, int RB>
+template <int KIND, int RA, int NW, int KS, bool EARLY>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
-    constexpr int BM = RA * 32, BN = NW * RB * 32;
-    constexpr size_t lds = (KIND == GEMM_QKV_ATTN && kAttentionLdsBytes > wide_lds_bytes<RA, NW, KS, RB>())
-                               ? kAttentionLdsBytes : wide_lds_bytes<RA, NW, KS, RB>();
+    constexpr int BM = RA * 32, BN = NW * 32;
+    constexpr size_t lds = (KIND == GEMM_QKV_ATTN && kAttentionLdsBytes > wide_lds_bytes<RA, NW, KS>())
+                               ? kAttentionLdsBytes : wide_lds_bytes<RA, NW, KS>();
     // once per instantiation, and safe when several host threads make their first call together
     static const hipError_t attr_status =
-        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, EARLY, RB>,
+        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, EARLY>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_status != hipSuccess) return attr_status;
     const int total = ((N + BN - 1) / BN) * ((p.T + BM - 1) / BM);
@@ -740,48 +690,50 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
     GemmProblem q = p;
     if (p.next_workgroups > 0) q.next_cells = cell_map(p.block_cols, p.d_head, p.next_ffn_per_shard);
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
-    ShardIds shard_of;   // (the kernel takes these instead of the block table: a shorter argument list is a cheaper launch)
-    for (int b = 0; b < kMaxShardsPerLayer; b += 4)
-        shard_of.id4[b / 4] = (uint32_t)blocks.b[b].shard | (uint32_t)blocks.b[b + 1].shard << 8 |
-                              (uint32_t)blocks.b[b + 2].shard << 16 | (uint32_t)blocks.b[b + 3].shard << 24;
+    const ShardIds shard_of = shard_ids(blocks);
     const int n_tiles = (N + BN - 1) / BN;
     const uint32_t band_recip = reciprocal((n_tiles > kRowMajorColumnTiles ? kGroupRows : 1) * n_tiles);
     const uint32_t block_recip = reciprocal(n_split ? p.block_rows / 32 : p.block_cols / BK);
-    launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY, RB>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
+    launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
            p.resid, p.bias0, (int32_t)w_stride, p.T, band_recip, block_recip, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
            (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, q, shard_of);
     return hipGetLastError();
 }
 
-template <int RA, int NW, int RB>
+template <int RA, int NW>
 hipError_t launch_kind(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     switch (p.kind) {
-    case GEMM_QKV: return launch_shape<GEMM_QKV, RA, NW, 1, RB>(p, blocks, N, stream);
-    case GEMM_FFN_UP: return launch_shape<GEMM_FFN_UP, RA, NW, 1, RB>(p, blocks, N, stream);
-    case GEMM_OUT: return launch_shape<GEMM_OUT, RA, NW, 1, RB>(p, blocks, N, stream);
-    case GEMM_FFN_DOWN: return launch_shape<GEMM_FFN_DOWN, RA, NW, 1, RB>(p, blocks, N, stream);
+    case GEMM_QKV: return launch_shape<GEMM_QKV, RA, NW, 1>(p, blocks, N, stream);
+    case GEMM_FFN_UP: return launch_shape<GEMM_FFN_UP, RA, NW, 1>(p, blocks, N, stream);
+    case GEMM_OUT: return launch_shape<GEMM_OUT, RA, NW, 1>(p, blocks, N, stream);
+    case GEMM_FFN_DOWN: return launch_shape<GEMM_FFN_DOWN, RA, NW, 1>(p, blocks, N, stream);
     case GEMM_QKV_ATTN: break;   // one shape only, launched by launch_gemm_wide itself
     }
     return hipErrorInvalidValue;
 }
 
-// Tile shapes: (32 ra) x (32 nw rb).  Time of a workgroup, fitted to launches of all four projections at 8 token
-// counts from 1056 to 9216 and d_model 768 and 1024: block_us per 32 x 32 outputs and 1024 of K, start_us
-// for start-up and epilogue (GELU: 3.5 us more).  shared: two workgroups on a compute unit also share
-// out its last round.
+// Tile shapes, rows x columns, and the time of a launch: start_us + rounds * (K tiles * (tile_us + full_us * fill) + round_us (+ gelu_us for
+// FFN1, resid_us for O and FFN2)), rounds = tiles on the busiest compute unit (shared: two workgroups on a unit, half way between that and
+// the average), fill = average / busiest: a chip with idle units clocks higher.  Fitted to launches of 64 layer shapes drawn
+// over 700 .. 9216 tokens, d_model 256 .. 1024, 2 to 16 shards, each projection with each shape: off by 3 to 5 % (root mean square; 64 x 192: 8 %).
+// large: gemm_large.hip.
+// The shape so chosen costs 0.4 % more than the fastest of all on average (geometric mean of the 256 launches); with the shapes of this file
+// alone, 128 x 256 tiles of four waves among them, it was 3 % more.  9216 tokens, d_model 1024, 12 shards, us, these against those: Q/K/V
+// 192 x 256 47 / 52, FFN1 256 x 256 66 / 69, O 192 x 256 21.6 / 23.5, FFN2 192 x 256 59 / 66; 5000 tokens, d_model 768 Q/K/V 22.5 / 27.2;
+// 3000 tokens, 10 shards Q/K/V 128 x 256 14.5 / 17.3.
 struct Shape {
-    int ra, nw, rb;
-    float block_us, start_us;
-    bool shared;
+    int rows, cols;
+    bool shared, large;
+    float start_us, tile_us, full_us, round_us, gelu_us, resid_us;
 };
-constexpr Shape kShapes[] = {{4, 12, 1, 0.37f, 6.5f, false}, {4, 9, 1, 0.38f, 8.f, false}, {2, 12, 1, 0.48f, 6.f, false},
-                             {2, 6, 1, 0.72f, 3.f, false},   {4, 4, 2, 0.54f, 4.f, true}};
-constexpr float kSplitBlockUs = 0.45f, kSplitStartUs = 5.5f;   // {2, 6} with K split over two wave groups (one workgroup per unit)
-constexpr float kGeluUs = 3.5f;
-// two {2, 6} workgroups on a unit: the second one's residual is not hidden.  768 x 6 shards, 4608 tokens, O: 3 us a launch slower than
-// {2, 12}, estimated 1 us faster without this
-constexpr float kSecondResidualUs = 3.f;
+// The first is for Q/K/V and FFN1, the second for Q/K/V beside a decompression (below): elsewhere others are faster.
+constexpr Shape kShapes[] = {{128, 384, false, false, 1.12f, 0.729f, 0.628f, 4.57f, 3.34f, 1.56f}, {128, 288, false, false, 0.57f, 0.694f, 0.425f, 4.96f, 3.08f, 1.32f},
+                             {64, 384, false, false, 0.15f, 0.475f, 0.337f, 3.71f, 1.75f, 1.68f},  {64, 192, true, false, 1.47f, 0.423f, 0.090f, 1.22f, 0.84f, 1.50f},
+                             {128, 256, false, true, 1.38f, 0.587f, 0.441f, 2.25f, 2.08f, 1.15f},  {192, 256, false, true, 2.12f, 0.773f, 0.588f, 2.21f, 3.25f, 1.99f},
+                             {256, 256, false, true, 2.87f, 0.915f, 0.773f, 2.96f, 4.37f, 2.44f}};
+constexpr int kNarrow = 3;
+constexpr Shape kSplitShape = {64, 192, false, false, 2.97f, 0.294f, 0.133f, 0.f, 0.f, 1.49f};   // K split over two wave groups, one workgroup per unit
 
 // Workgroups beside `tiles` that still find a compute unit of their own in the first round; fewer than an eighth of the
 // chip are not used.
@@ -797,8 +749,9 @@ inline int spare_units(long tiles)
 // it.  What a Q/K/V shape costs is therefore not its own time alone: 768 x 10 shards at 3584 tokens took
 // 789 us per 8 layers where 32 workgroups of four waves were left to the decompression (now 706), 768 at 4096 tokens where
 // none were (now 741).
+// (In the chain: 13.8 us for four layers of 12 shards of BERT-base, 6.8 for one.  With 1.3 us less, 1824 tokens took launches of their own: 2.5 % slower.)
 inline float beside_us(float cells, int spare, int nw) { return (1.0f + 0.035f * nw) * cells / (spare * nw) + 4.f + 0.5f * nw; }
-inline float in_chain_us(float cells, bool grouped) { return cells * 2048.f * 0.4e-6f + (grouped ? -0.7f : 2.7f); }
+inline float in_chain_us(float cells, bool grouped) { return cells * 2048.f * 0.4e-6f + (grouped ? 0.7f : 4.f); }
 
 // 2048-weight cells of the layer that p.next_shards and p.next_ffn_per_shard describe
 inline float next_cells(const GemmProblem &p)
@@ -839,29 +792,26 @@ Choice choose(const GemmProblem &p, int N)
 {
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN);
     const int nkt = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
-    const float k = nkt * BK / 1024.f;
     const bool beside = p.kind == GEMM_QKV && p.next_workgroups > 0;
     Choice best = {};
     best.us = INFINITY;
-    for (int c = 0; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
-        const Shape &sh = kShapes[c];
-        const int bm = sh.ra * 32, bn = sh.nw * sh.rb * 32, blocks = sh.ra * sh.nw * sh.rb;
-        const long tiles = (long)((N + bn - 1) / bn) * ((p.T + bm - 1) / bm);
+    for (int c = n_split ? 0 : 2; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
+        if (c == 1 && !beside) continue;
+        // (the large tiles have no workgroups for the next layer's shards or dictionaries, two K tiles at least, and 256 rows only without residual)
+        if (kShapes[c].large && (beside || p.next_outliers > 0 || nkt < 2 || (!n_split && kShapes[c].rows > 192))) continue;
+        const long tiles = (long)((N + kShapes[c].cols - 1) / kShapes[c].cols) * ((p.T + kShapes[c].rows - 1) / kShapes[c].rows);
         const float avg = (float)tiles / kComputeUnits;
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
         // one 6-wave workgroup per unit: K is split inside the workgroup to fill the unit
-        const bool ks2 = !n_split && sh.ra == 2 && sh.nw == 6 && per_cu == 1 && nkt % 2 == 0 && nkt >= 4;
-        const float start = (ks2 ? kSplitStartUs : sh.start_us) + (p.kind == GEMM_FFN_UP ? kGeluUs : 0.f);
-        const float products = blocks * k * (ks2 ? kSplitBlockUs : sh.block_us);
-        // (workgroups that share a unit: half way between average and busiest, start-up and epilogue hidden but for one;
-        //  two 6-wave workgroups share a unit too, but a unit with one more than its neighbours holds all up)
-        float us = per_cu * (products + start);
-        if (sh.shared) us = (avg < 1.f ? 1.f : (avg + per_cu) / 2) * products + start;
-        else if (sh.nw == 6) us = per_cu * products + start + (!n_split && per_cu == 2 ? kSecondResidualUs : 0.f);
+        const bool ks2 = !n_split && c == kNarrow && per_cu == 1 && nkt % 2 == 0 && nkt >= 4;
+        const Shape &sh = ks2 ? kSplitShape : kShapes[c];
+        const float rounds = sh.shared ? std::max(1.f, (avg + per_cu) / 2) : (float)per_cu;
+        float us = sh.start_us + rounds * (nkt * (sh.tile_us + sh.full_us * avg / per_cu) + sh.round_us + (p.kind == GEMM_FFN_UP ? sh.gelu_us : 0.f) +
+                                           (n_split ? 0.f : sh.resid_us));
         if (beside) {
             const int spare = spare_units(tiles);
             if (spare == 0) continue;
-            us = std::max(us, beside_us(next_cells(p), spare, sh.nw));
+            us = std::max(us, beside_us(next_cells(p), spare, sh.cols / 32));
         }
         if (us < best.us) {
             best.us = us;
@@ -951,11 +901,11 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
                                   : launch_shape<GEMM_FFN_DOWN, 2, 6, 2>(p, blocks, N, stream);
     }
     switch (ch.shape) {
-    case 0: return launch_kind<4, 12, 1>(p, blocks, N, stream);
-    case 1: return launch_kind<4, 9, 1>(p, blocks, N, stream);
-    case 2: return launch_kind<2, 12, 1>(p, blocks, N, stream);
-    case 3: return launch_kind<2, 6, 1>(p, blocks, N, stream);
-    default: return launch_kind<4, 4, 2>(p, blocks, N, stream);
+    case 0: return p.kind == GEMM_QKV ? launch_shape<GEMM_QKV, 4, 12, 1>(p, blocks, N, stream) : launch_shape<GEMM_FFN_UP, 4, 12, 1>(p, blocks, N, stream);
+    case 1: return launch_shape<GEMM_QKV, 4, 9, 1>(p, blocks, N, stream);
+    case 2: return launch_kind<2, 12>(p, blocks, N, stream);
+    case kNarrow: return launch_kind<2, 6>(p, blocks, N, stream);
+    default: return launch_gemm_large(p, blocks, N, kShapes[ch.shape].rows / 64, stream);
     }
 }
 

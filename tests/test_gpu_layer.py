@@ -843,6 +843,27 @@ def test_mfma_output_projections_with_shared_compute_units(gpu, oracle_mod, n_ab
         assert_parity(got[b:b + 1], want, TOL["mfma"], b)
 
 
+@pytest.mark.parametrize("d,M,f,B,L,n_absent", [
+    (128, 32, 256, 23, 259, 0),    # Q/K/V, FFN1: 192 x 256, three and four tiles to a workgroup, K of two tiles, bands of row tiles
+    (1024, 16, 64, 44, 125, 0),    # Q/K/V 192 rows, O and FFN2 128 with residual, a last tile of 124 rows
+    (448, 14, 128, 25, 360, 0),    # FFN1 256 rows, O and FFN2 128 with 192 columns in the last column tile
+    (1024, 2, 64, 31, 297, 0),     # O and FFN2 192 rows, K of two tiles
+    (256, 12, 256, 40, 150, 1),    # Q/K/V 256 rows, 64 columns in the last column tile
+    (128, 29, 256, 7, 200, 0),     # Q/K/V 128 rows
+])
+def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent):
+    """Tiles of 128, 192 and 256 rows x 256 columns: first, middle and last sequences against the oracle (sequences do not
+    depend on each other), all rows finite."""
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    wl = S.small_workload(54000 + d + M, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
+    S.make_every_term_matter(wl, 8, amp=2.0)
+    got = run_gpu(gpu, wl, "mfma")
+    assert np.all(np.isfinite(got))
+    for b in (0, B // 2, B - 1):
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
+        assert_parity(got[b:b + 1], want, TOL["mfma"], b)
+
+
 @pytest.mark.parametrize("B,L", [(1, 64), (3, 100)])   # few-token route / working-buffer route
 def test_mfma_widest_supported_model(gpu, oracle_mod, B, L):
     """d_model 2048 (rows of 2048 features in LayerNorm, K = 2048 in the projections, 22-26 column
