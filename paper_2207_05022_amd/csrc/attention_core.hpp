@@ -13,6 +13,7 @@
 // maxima once), so the output accumulators are never rescaled.
 #pragma once
 #include "sti_internal.hpp"
+#include "lane_ops.hpp"
 
 namespace sti {
 
@@ -61,7 +62,7 @@ __device__ inline float attention_scores_in_registers(const att_half8 (&qf)[4], 
 #pragma unroll
         for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[kb][v]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = pair_max(across_32(mx));
     const float shift = -mx * scale;   // (scale > 0: the maximum of the scaled scores)
     float run_sum = 0.f;
 #pragma unroll
@@ -91,7 +92,7 @@ __device__ inline float attention_scores_in_registers(const att_half8 (&qf)[4], 
             }
         }
     }
-    run_sum += __shfl_xor(run_sum, 32, 64);
+    run_sum = pair_sum(across_32(run_sum));
     return run_sum;
 }
 

@@ -12,6 +12,7 @@
 #include <float.h>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
+#include "lane_ops.hpp"
 
 namespace sti {
 namespace {
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
             s_acc[v] = x;
             bmax = fmaxf(bmax, x);
         }
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        bmax = pair_max(across_32(bmax));
         const float new_max = fmaxf(run_max, bmax);
         const float alpha = __builtin_amdgcn_exp2f(run_max - new_max);
         run_max = new_max;
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(W * 64) void attention_few_kernel(const _Float16 *q
                 o[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, v_now[e * 2 + s2]), __builtin_bit_cast(half8, pv), o[e], 0, 0, 0);
         }
     }
-    run_sum += __shfl_xor(run_sum, 32, 64);
+    run_sum = pair_sum(across_32(run_sum));
     // o[e][4 v4 + i]: feature e*32 + v4*8 + g*4 + i of query lr -> 16-byte chunk (v4, e*32 + lr) of the context's cell
     _Float16 *out = ctx + ((int64_t)rb * m + head) * 2048 + g * 4;
     auto store = [&](int e, int v4, f32x4 x, float inv) {

@@ -217,7 +217,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
         return s;
     };
     auto rescale = [&](float bmax) {
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        bmax = pair_max(across_32(bmax));
         if (__ballot(bmax > run_max)) {
             const float new_max = fmaxf(run_max, bmax);
             const float alpha = __builtin_amdgcn_exp2f((run_max - new_max) * scale);
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
         rescale(bmax);
         weigh(s, buf, t, -run_max * scale);
     }
-    run_sum += __shfl_xor(run_sum, 32, 64);
+    run_sum = pair_sum(across_32(run_sum));
     // (worked out again instead of kept: the loop uses all 128 registers of four waves per SIMD)
     int t2 = threadIdx.x;
     asm volatile("" : "+v"(t2));

@@ -10,6 +10,7 @@
 #include <float.h>
 #include <type_traits>
 #include "sti_internal.hpp"
+#include "lane_ops.hpp"
 #include "split_planes.hpp"
 
 namespace sti {
@@ -403,8 +404,7 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qk
                 mx = fmaxf(mx, x);
             }
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = pair_max(across_32(pair_max(across_16(mx))));
         const float new_max = fmaxf(run_max, mx);
         const float alpha = expf(run_max - new_max);
         run_max = new_max;
@@ -429,8 +429,7 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qk
                     o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(Vs[(t * 16 + g * 4 + v) * LDR + c * 16 + lr], s[t][v], o[c], 0, 0, 0);
         }
     }
-    run_sum += __shfl_xor(run_sum, 16, 64);
-    run_sum += __shfl_xor(run_sum, 32, 64);
+    run_sum = pair_sum(across_32(pair_sum(across_16(run_sum))));
     if (q >= L) return;
     const float inv = 1.0f / run_sum;
     float *out = (float *)ctx + ((int64_t)b * L + q) * ((int64_t)m * dh) + (int64_t)head * dh;

@@ -3,17 +3,11 @@
 // and activation type conversion.
 #include <type_traits>
 #include "sti_internal.hpp"
+#include "lane_ops.hpp"
 #include "split_planes.hpp"
 
 namespace sti {
 namespace {
-
-__device__ inline float wave_sum(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 __device__ inline uint16_t f32_to_bf16_bits(float v)
 {
@@ -71,13 +65,13 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_
     };
     float s = 0.f;
     for (int c = lane; c < d; c += 64) s += value(c);
-    const float mean = wave_sum(s) / (float)d;
+    const float mean = lane_sum<64>(s) / (float)d;
     float q = 0.f;
     for (int c = lane; c < d; c += 64) {
         float t = value(c) - mean;
         q = fmaf(t, t, q);
     }
-    const float var = wave_sum(q) / (float)d;
+    const float var = lane_sum<64>(q) / (float)d;
     const float inv = 1.0f / sqrtf(var + eps);
     for (int c = lane; c < d; c += 64)
         Elem<DT>::store(y + act_offset(y_layout, row, c, d), (value(c) - mean) * inv * g[c] + b[c]);
@@ -88,26 +82,17 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *pre, int n_
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
-// LPR lanes share one row (64, 32 or 16): fewer lanes per row keep more bytes in flight per
-// lane and shorten the two reductions.
-template <int LPR>
-__device__ inline float row_sum(float v)
+// LPR lanes share one row.  TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC; PLANES: partial sums
+// requested together; ROWS: rows per workgroup.
+// Few rows: bound by latency (the launch, one round trip, two sums over the row).  The leading 14 dwords of the arguments arrive preloaded
+// in scalar registers: everything the requests of a row depend on.  shape: n_partials | resid_layout << 8 | y_layout << 16.
+template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>
+__global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, const float *bias, const RT *resid, const float *g,
+                                                            const float *b, int T, int d, int shape, float eps, int64_t partial_stride,
+                                                            typename Elem<DT>::type *y, uint16_t *planes)
 {
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC; PLANES: partial sums requested together
-template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>   // ROWS: rows per workgroup
-__global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, int n_partials,
-                                                            int64_t partial_stride,
-                                                            const float *bias, const RT *resid,
-                                                            int resid_layout, int y_layout,
-                                                            typename Elem<DT>::type *y,
-                                                            const float *g, const float *b, int T,
-                                                            int d, float eps, uint16_t *planes)
-{
+    const float inv_d = 1.0f / (float)d;   // (formed while the row is on its way)
+    const int n_partials = shape & 0xff, resid_layout = shape >> 8 & 0xff, y_layout = shape >> 16;
     const int sub = threadIdx.x % LPR;
     int row = blockIdx.x * ROWS + threadIdx.x / LPR;
     // A cache line of a tiled matrix holds 16 bytes of each of eight rows: such rows go to workgroups of one XCD (workgroups are handed
@@ -171,7 +156,7 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
         v[j] = x;
         s += (x.x + x.y) + (x.z + x.w);
     }
-    const float mean = row_sum<LPR>(s) / (float)d;
+    const float mean = lane_sum<LPR>(s) * inv_d;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
@@ -180,7 +165,7 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
             q += (t.x * t.x + t.y * t.y) + (t.z * t.z + t.w * t.w);
         }
     }
-    const float var = row_sum<LPR>(q) / (float)d;
+    const float var = lane_sum<LPR>(q) * inv_d;
     const float inv = 1.0f / sqrtf(var + eps);
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
@@ -215,6 +200,7 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 {
     typedef _Float16 half8 __attribute__((ext_vector_type(8)));
     constexpr int ROWS = 256 / LPR;
+    const float inv_d = 1.0f / (float)d;
     const int sub = threadIdx.x % LPR;
     const int row = blockIdx.x * ROWS + threadIdx.x / LPR;
     if (row >= T) return;   // whole row groups leave together; shuffles stay inside a group
@@ -238,7 +224,7 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 #pragma unroll
         for (int e = 0; e < 8; ++e) { v[j][e] = in ? (float)h[j][e] : 0.f; s += v[j][e]; }
     }
-    const float mean = row_sum<LPR>(s) / (float)d;
+    const float mean = lane_sum<LPR>(s) * inv_d;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j)
@@ -246,7 +232,7 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[j][e] - mean; q = fmaf(t, t, q); }
         }
-    const float var = row_sum<LPR>(q) / (float)d;
+    const float var = lane_sum<LPR>(q) * inv_d;
     const float inv = 1.0f / sqrtf(var + eps);
     typename Elem<DT>::type *o = y + (int64_t)row * d;
 #pragma unroll
@@ -291,14 +277,14 @@ __global__ __launch_bounds__(256) void layernorm_f16in_long_kernel(const _Float1
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += (float)h[e];
     }
-    const float mean = wave_sum(s) / (float)d;
+    const float mean = lane_sum<64>(s) / (float)d;
     float q = 0.f;
     for (int c = lane; c < nchunk; c += 64) {
         const half8 h = r[c];
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const float t = (float)h[e] - mean; q = fmaf(t, t, q); }
     }
-    const float inv = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
+    const float inv = 1.0f / sqrtf(lane_sum<64>(q) / (float)d + eps);
     typename Elem<DT>::type *o = y + (int64_t)row * d;
     for (int c = lane; c < nchunk; c += 64) {
         const half8 h = r[c];
@@ -346,7 +332,7 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
     typedef typename Elem<DT>::type O;
 #define STI_LN_PLANES(LPR, MAXC, PLANES, ROWS) \
     launch((layernorm_vec_kernel<DT, RT, TILED, LPR, MAXC, PLANES, ROWS>), dim3(TILED && ROWS == 1 ? (T + 63) / 64 * 64 : (T + ROWS - 1) / ROWS), dim3(LPR * ROWS), 0, stream, pre, \
-           n_partials, partial_stride, bias, (const RT *)resid, (int)resid_layout, (int)y_layout, (O *)y, g, b, T, d, eps, planes)
+           bias, (const RT *)resid, g, b, T, d, n_partials | (int)resid_layout << 8 | (int)y_layout << 16, eps, partial_stride, (O *)y, planes)
 #define STI_LN_VEC(LPR, MAXC, ROWS)                                       \
     do {                                                                  \
         if (n_partials <= 1) STI_LN_PLANES(LPR, MAXC, 1, ROWS);           \
@@ -386,7 +372,7 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
 {
     if (T <= 0 || d <= 0) return hipSuccess;
     if (planes && (d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
-    if (n_partials < 0 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
+    if (n_partials < 0 || n_partials > 255 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
     if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || (resid_f32 && (resid_layout == LAYOUT_TILED || out_dtype != STI_F16))))
         return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
