@@ -18,10 +18,12 @@
 // Infinite and NaN weights (the moments are NaN then, so that nothing is an outlier) take the general ways through
 // the same kernels: one bin for all weights, clusters by comparison of keys, sums beside the integers.
 //
-// What bounds it: 28 MB read four times (one BERT-base layer; the last three out of the memory-side
-// cache) and seven dependent launches.  BERT-base at 4 bits: 54 us, 56 with a launch of one workgroup for the boundary bins, 149 of the
-// version with histograms of 65536 bins in two levels, device-wide atomics and separate sum and pack passes.
+// What bounds it: seven dependent launches, and in the streaming passes the LDS (a look-up and an atomic per weight, 3.4 units of 512
+// weights per wave) behind what each works out before its first weight: 6500 clocks of the histogram pass (the Gaussian), 3800 of the
+// collecting pass.  More units on their way at once change nothing.  BERT-base at 4 bits: 48 us, 54 with the boundary bins looked up by one
+// wave, the atomics behind the weights and up to three rounds for a boundary value; d_model 384, 3 bits 36.9 -> 30.5.
 #include "api_internal.hpp"
+#include "lane_ops.hpp"
 
 namespace sti {
 namespace {
@@ -108,11 +110,13 @@ __device__ inline int bin_of(float x, float scale, float shift)
     return (int)__builtin_amdgcn_fmed3f(fmaf(x, scale, shift), 0.0f, (float)(kBins - 1));
 }
 
-__device__ inline double wave_sum_f64(double v)
+__device__ inline double wave_sum_f64(double v)   // (in lane 0)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;
+    return lane_tree(v, [](double a, double b) { return a + b; });
+}
+__device__ inline double wave_max_f64(double v)   // (in lane 0; of values that are not negative, or NaN)
+{
+    return lane_tree(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // per workgroup: sum, sum of squares (float64, fixed order), largest magnitude
@@ -136,8 +140,7 @@ __global__ __launch_bounds__(256) void moments_kernel(const float *w, uint64_t n
     }
     for (; i < n4; i += step) add(((const f32x4 *)w)[i]);
     const double s = wave_sum_f64(s0 + s1), q = wave_sum_f64(q0 + q1);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o, 64));
+    mx = (float)wave_max_f64((double)mx);
     if ((threadIdx.x & 63) == 0) {
         lds[threadIdx.x >> 6][0] = s;
         lds[threadIdx.x >> 6][1] = q;
@@ -227,8 +230,7 @@ __global__ __launch_bounds__(kThreads) void histogram_kernel(const float *w, uin
     for (int i = threadIdx.x; i < kBins; i += kThreads) hist[i] = 0;
     s = wave_sum_f64(s);
     q = wave_sum_f64(q);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_down(mx, o, 64));
+    mx = wave_max_f64(mx);
     if (lane == 0) { red[wave][0] = s; red[wave][1] = q; red[wave][2] = mx; }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -309,12 +311,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint32_t *hist_part, i
             v[j] = first + j < units_per_shard ? cnt[first + j] : 0;
             mine += v[j];
         }
-        uint32_t inc = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += up;
-        }
+        const uint32_t inc = lane_scan(mine);
         __syncthreads();
         if (lane == 63) wave_total[wave] = inc;
         __syncthreads();
@@ -338,125 +335,102 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint32_t *hist_part, i
 
 // For every boundary the bin that holds its rank; the bins that hold one become slots with a
 // list each.  table[bin] = (boundaries in lower bins) | (slot + 1, or 0) << 8 | kSeveral where there are two or more.
-// Every workgroup of the collecting pass works this out for itself while its first weights are on their way (3.9 us; a launch of
-// one workgroup took 4.6 and the way from one launch to the next); the first one leaves it in memory for those behind.
+// Every workgroup of the collecting pass works this out for itself while its first weights are on their way; the first one leaves it in
+// memory for those behind.  Two sums over the bins and one search of six steps per thread (1.7 us; 4.3 with the boundaries looked
+// up among the bins by one wave, a launch of one workgroup 4.6 and the way from one launch to the next).
 constexpr uint32_t kSeveral = 0x8000;
 
 struct BoundaryScratch {
-    uint64_t before[kBins];              // inliers in lower bins
-    uint64_t wave_sum[16];
-    uint32_t edge_bin[kMaxClusters + 1], edge_slot[kMaxClusters];
+    uint64_t rank[kMaxClusters];         // of boundary c = 1 .. C-1 at [c-1]; behind the last: more than there are inliers
+    uint64_t wave_sum[16], wave_slots[16];
 };
 
-// table: of the workgroup (LDS); slot_begin, n_slots: what the caller needs of the state, in LDS, too.  The state and table_out
+// Of the workgroup (LDS): the table, where each slot's list begins, its bin, the number of slots.  The state and table_out
 // are written where `keep`.
 __device__ inline void boundary_bins(BoundaryScratch &sc, QuantState *st, const uint32_t *hist, uint16_t *table, uint16_t *table_out,
-                                     uint64_t *slot_begin, uint32_t *n_slots, bool keep, uint64_t n, const uint32_t *shard_count,
-                                     int n_shards, int n_clusters)
+                                     uint64_t *slot_begin, uint32_t *slot_bin, uint32_t *n_slots, bool keep, uint64_t n,
+                                     const uint32_t *shard_count, int n_shards, int n_clusters)
 {
-    uint64_t (&before)[kBins] = sc.before;
-    uint64_t (&wave_sum)[16] = sc.wave_sum;
-    uint32_t (&edge_bin)[kMaxClusters + 1] = sc.edge_bin;
-    uint32_t (&edge_slot)[kMaxClusters] = sc.edge_slot;
+    constexpr int kSlotShift = 56;       // a sum of list lengths and, above it, of slots
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint4 h = ((const uint4 *)hist)[tid];
+    const uint4 h4 = ((const uint4 *)hist)[tid];
+    const uint32_t h[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t outl = lane < n_shards ? shard_count[lane] : 0;   // (kMaxShardsPerLayer lanes)
-    uint64_t n_out = outl;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n_out += __shfl_xor(n_out, o, 64);
+    const uint64_t out_scan = lane_scan((uint64_t)outl);
+    const uint64_t n_out = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(out_scan >> 32), 63) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)out_scan, 63);
     const uint64_t n_in = n - n_out;
-    const uint64_t own = (uint64_t)h.x + h.y + h.z + h.w;
-    uint64_t inc = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t up = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += up;
-    }
-    if (lane == 63) wave_sum[wave] = inc;
+    const uint64_t own = (uint64_t)h[0] + h[1] + h[2] + h[3], inc = lane_scan(own);
+    if (lane == 63) sc.wave_sum[wave] = inc;
+    if (tid < kMaxClusters)              // (n_clusters is a power of two)
+        sc.rank[tid] = tid < n_clusters - 1 && n_in > 0 ? ((uint64_t)(tid + 1) * n_in) >> __builtin_ctz(n_clusters) : ~0ull;
     __syncthreads();
-    uint64_t p = inc - own;
-    for (int i = 0; i < wave; ++i) p += wave_sum[i];
-    before[4 * tid] = p;
-    before[4 * tid + 1] = p + h.x;
-    before[4 * tid + 2] = p + h.x + h.y;
-    before[4 * tid + 3] = p + h.x + h.y + h.z;
-    if (tid <= kMaxClusters) edge_bin[tid] = kBins;   // (behind the last boundary: no bin)
-    __syncthreads();
-    if (wave == 0) {
-        const bool edge = lane < n_clusters - 1 && n_in > 0;
-        const uint64_t rank = ((uint64_t)(lane + 1) * n_in) / (uint64_t)n_clusters;
-        int lo = 0, hi = kBins - 1;     // last bin with before[bin] <= rank: it is not empty
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (before[mid] <= rank) lo = mid;
-            else hi = mid - 1;
-        }
-        const int up = __shfl_up(lo, 1, 64);
-        const bool first = edge && (lane == 0 || up != lo);   // (boundary bins are non-decreasing)
-        const uint64_t firsts = __ballot(first);
-        const int slot = __popcll(firsts & ((2ull << lane) - 1)) - 1;
-        const uint32_t count = edge ? hist[lo] : 0;
-        uint64_t begin = first ? count : 0;                   // list begins: scan of the slots' counts
-        const uint64_t mine = begin;
+    uint64_t before[5];                  // inliers below the thread's four bins, and behind them
+    before[0] = inc - own;
+    for (int i = 0; i < wave; ++i) before[0] += sc.wave_sum[i];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint64_t t = __shfl_up(begin, o, 64);
-            if (lane >= o) begin += t;
-        }
-        begin -= mine;
-        // (the begin of a boundary's own list: that of its bin's first boundary)
-        const uint64_t list_begin = __shfl(begin, 63 - __builtin_clzll((firsts & ((2ull << lane) - 1)) | 1ull), 64);
-        if (first) slot_begin[slot] = begin;
-        if (lane == 0) *n_slots = __popcll(firsts);
-        if (edge) {
-            edge_bin[lane] = lo;
-            edge_slot[lane] = slot;
-        }
-        if (keep && edge) {
-            st->edge_begin[lane] = list_begin;
-            st->edge_count[lane] = count;
-            st->edge_rank[lane] = (uint32_t)(rank - before[lo]);
-            st->edge_before[lane] = before[lo];
-        }
-        if (keep && lane == 0) {
-            st->n_inliers = n_in;
-            st->error = n_in == 0 ? 1 : 0;
-        }
-    }
-    __syncthreads();
-    uint32_t packed[2] = {0, 0}, lower[4] = {0, 0, 0, 0};   // boundaries in lower bins (the four searches side by side)
+    for (int b = 0; b < 4; ++b) before[b + 1] = before[b] + h[b];
+    uint32_t lower[5] = {0, 0, 0, 0, 0};   // boundaries whose rank lies below (the last entry of rank[] never does)
 #pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) lower[b] += edge_bin[lower[b] + step - 1] < 4u * tid + b ? step : 0;
+    for (int step = 32; step > 0; step >>= 1) lower[0] += sc.rank[lower[0] + step - 1] < before[0] ? step : 0;
+    uint64_t lists = 0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const uint32_t bin = 4 * tid + b, lo = lower[b];
-        uint32_t entry = lo;
-        if (edge_bin[lo] == bin) {
-            entry |= (edge_slot[lo] + 1) << 8;
-            if (edge_bin[lo + 1] == bin) entry |= kSeveral;
+        lower[b + 1] = lower[b];
+        while (sc.rank[lower[b + 1]] < before[b + 1]) ++lower[b + 1];
+        if (lower[b + 1] > lower[b]) lists += (1ull << kSlotShift) + h[b];
+    }
+    const uint64_t list_scan = lane_scan(lists);
+    if (lane == 63) sc.wave_slots[wave] = list_scan;
+    __syncthreads();
+    uint64_t at = list_scan - lists;
+    for (int i = 0; i < wave; ++i) at += sc.wave_slots[i];
+    uint32_t packed[2] = {0, 0};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        uint32_t entry = lower[b];
+        if (lower[b + 1] > lower[b]) {
+            const uint32_t slot = (uint32_t)(at >> kSlotShift);
+            const uint64_t begin = at & ((1ull << kSlotShift) - 1);
+            entry |= (slot + 1) << 8;
+            if (lower[b + 1] > lower[b] + 1) entry |= kSeveral;
+            slot_begin[slot] = begin;
+            slot_bin[slot] = 4 * tid + b;
+            if (keep) {
+                for (uint32_t c = lower[b]; c < lower[b + 1]; ++c) {
+                    st->edge_begin[c] = begin;
+                    st->edge_count[c] = h[b];
+                    st->edge_rank[c] = (uint32_t)(sc.rank[c] - before[b]);
+                    st->edge_before[c] = before[b];
+                }
+            }
+            at += (1ull << kSlotShift) + h[b];
         }
         packed[b >> 1] |= entry << (16 * (b & 1));
+    }
+    if (tid == kThreads - 1) *n_slots = (uint32_t)(at >> kSlotShift);
+    if (keep && tid == 0) {
+        st->n_inliers = n_in;
+        st->error = n_in == 0 ? 1 : 0;
     }
     ((uint2 *)table)[tid] = uint2{packed[0], packed[1]};
     if (keep) ((uint2 *)table_out)[tid] = uint2{packed[0], packed[1]};
 }
 
-// The keys of the weights in boundary bins, one list per bin (in no particular order).  A workgroup
-// keeps the weights it finds in LDS, takes room for them with one atomic per list and then writes them; if they
-// do not fit (a bin holds a large part of the layer), it reads its weights again instead.
+// The keys of the weights in boundary bins, one list per bin (in no particular order).  A workgroup has the units that it had in the
+// histogram pass, so that its own counters of that pass say how many it will find: it takes room for them with one atomic per list
+// before it looks at a weight (the answers of 256 workgroups' atomics take 1.6 us), keeps what it finds in LDS and then writes it; if
+// that does not fit (a bin holds a large part of the layer), it reads its weights again instead.
 constexpr uint32_t kFound = 8192;
 
 __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint64_t n, QuantState *st, const uint32_t *hist,
                                                            const uint32_t *shard_count, int n_shards, int n_clusters,
-                                                           uint16_t *table_out, uint32_t *lists)
+                                                           uint16_t *table_out, uint32_t *lists, const uint16_t *hist_part)
 {
-    static_assert(kThreads == 1024 && sizeof(BoundaryScratch) >= kFound * sizeof(float), "four bins per thread; one piece of LDS for both");
+    static_assert(kThreads == 1024 && kBins == 4096, "four bins per thread");
     __shared__ BoundaryScratch scratch;
-    float *found = (float *)&scratch;          // (once the table is there)
+    __shared__ float found[kFound];
     __shared__ __attribute__((aligned(8))) uint16_t table[kBins + 4];      // (one entry for outliers)
-    __shared__ uint32_t n_found, n_slots, count[kMaxClusters];
+    __shared__ uint32_t n_found, n_slots, count[kMaxClusters], slot_bin[kMaxClusters];
     __shared__ uint64_t at[kMaxClusters], slot_begin[kMaxClusters];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t n_units = n / kUnit, stride = (uint64_t)gridDim.x * kWaves, u0 = (uint64_t)blockIdx.x * kWaves + wave;
@@ -470,8 +444,13 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
     const float xlo = st->xlo, xhi = st->xhi, scale = st->bin_scale, shift = st->bin_shift;
     if (tid < kMaxClusters) count[tid] = 0;
     if (tid == 0) { n_found = 0; table[kBins] = 0; }
-    boundary_bins(scratch, st, hist, table, table_out, slot_begin, &n_slots, blockIdx.x == 0, n, shard_count, n_shards, n_clusters);
+    boundary_bins(scratch, st, hist, table, table_out, slot_begin, slot_bin, &n_slots, blockIdx.x == 0, n, shard_count, n_shards, n_clusters);
     __syncthreads();
+    uint64_t my_list = 0;                      // where this workgroup's part of list `tid` begins
+    if (tid < (int)n_slots) {
+        const uint32_t own = hist_part[(size_t)blockIdx.x * kBins + slot_bin[tid]];
+        if (own) my_list = slot_begin[tid] + atomicAdd(&st->slot_fill[tid], own);
+    }
     auto slot_of = [&](float x) -> uint32_t {   // slot + 1, or 0
         return (table[is_inlier(x, xlo, xhi) ? bin_of(x, scale, shift) : kBins] & ~kSeveral) >> 8;
     };
@@ -495,16 +474,11 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
             if (slot[e]) {
                 const uint32_t at_found = first + __popcll(mask & ((1ull << lane) - 1));
                 if (at_found < kFound) found[at_found] = v[e >> 2][e & 3];
-                atomicAdd(&count[slot[e] - 1], 1u);
             }
             first += __popcll(mask);
         }
     }
-    __syncthreads();
-    if (tid < (int)n_slots) {
-        at[tid] = count[tid] ? slot_begin[tid] + atomicAdd(&st->slot_fill[tid], count[tid]) : 0;
-        count[tid] = 0;
-    }
+    if (tid < (int)n_slots) at[tid] = my_list;
     __syncthreads();
     auto put = [&](float x, uint32_t s) { lists[at[s - 1] + atomicAdd(&count[s - 1], 1u)] = order_key(x); };
     if (n_found <= kFound) {
@@ -525,14 +499,15 @@ __global__ __launch_bounds__(kThreads) void collect_kernel(const float *w, uint6
 // One workgroup per boundary: the key at its rank in its bin's list, by rounds of radix selection over
 // the distance from the list's lowest key, 11 bits at a time from the highest bit that differs (the keys of a bin
 // share their upper bits: without that every key would count on the same few counters), and the number of
-// inliers below it.
+// inliers below it.  One round leaves a few of a list's thousands of keys: up to 64 of them are settled by one wave that
+// compares each with all, in place of one or two more rounds of four barriers.
 constexpr int kHeld = 12;   // list entries per thread kept in registers
 
 __global__ __launch_bounds__(1024) void boundary_values_kernel(QuantState *st, const uint32_t *lists)
 {
     __shared__ uint32_t hist[2048];
     __shared__ uint32_t wave_lo[16], wave_hi[16];
-    __shared__ uint32_t chosen, below;
+    __shared__ uint32_t chosen, below, in_digit, n_left, left[64];
     if (st->error) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = blockIdx.x;
@@ -544,6 +519,7 @@ __global__ __launch_bounds__(1024) void boundary_values_kernel(QuantState *st, c
     for (int i = 0; i < kHeld; ++i) held[i] = list[min(tid + 1024u * i, m - 1)];
     hist[tid] = 0;
     hist[tid + 1024] = 0;
+    if (tid == 0) n_left = 0;
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) { lo = min(lo, held[i]); hi = max(hi, held[i]); }
     for (uint32_t i = tid + 1024u * kHeld; i < m; i += 1024) { lo = min(lo, list[i]); hi = max(hi, list[i]); }
@@ -569,25 +545,44 @@ __global__ __launch_bounds__(1024) void boundary_values_kernel(QuantState *st, c
         for (uint32_t i = tid + 1024u * kHeld; i < m; i += 1024) count(list[i]);
         __syncthreads();
         const uint32_t a = hist[2 * tid], b = hist[2 * tid + 1];
-        uint32_t inc = a + b;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += up;
-        }
+        const uint32_t inc = lane_scan(a + b);
         if (lane == 63) wave_hi[wave] = inc;
         hist[2 * tid] = 0;
         hist[2 * tid + 1] = 0;
         __syncthreads();
         uint32_t p = inc - a - b;
         for (int i = 0; i < wave; ++i) p += wave_hi[i];
-        if (rank >= p && rank < p + a) { chosen = 2 * tid; below = p; }
-        else if (rank >= p + a && rank < p + a + b) { chosen = 2 * tid + 1; below = p + a; }
+        if (rank >= p && rank < p + a) { chosen = 2 * tid; below = p; in_digit = a; }
+        else if (rank >= p + a && rank < p + a + b) { chosen = 2 * tid + 1; below = p + a; in_digit = b; }
         __syncthreads();
         prefix = (top == 32 ? 0 : prefix << bits) | chosen;
         rank -= below;
         total_below += below;
         top = low;
+        if (top == 0 || in_digit > 64) continue;
+        auto keep = [&](uint32_t key) {
+            if ((key - lo) >> top == prefix) left[atomicAdd(&n_left, 1u)] = key;
+        };
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i)
+            if (tid + 1024u * i < m) keep(held[i]);
+        for (uint32_t i = tid + 1024u * kHeld; i < m; i += 1024) keep(list[i]);
+        __syncthreads();
+        if (wave == 0) {
+            const int n = (int)in_digit;
+            const uint32_t key = lane < n ? left[lane] : 0xFFFFFFFFu;
+            uint32_t less = 0, before = 0;      // keys below this one; and those of its value in front of it
+            for (int i = 0; i < n; ++i) {
+                const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)key, i);
+                less += other < key;
+                before += other == key && i < lane;
+            }
+            if (lane < n && less + before == rank) {
+                st->edge_key[c] = key;
+                st->edge_below[c] = st->edge_before[c] + total_below + less;
+            }
+        }
+        return;
     }
     if (tid == 0) {
         st->edge_key[c] = lo + prefix;
@@ -717,12 +712,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float *w, uint64_t
         }
         if (__ballot(flags != 0)) {
             const uint32_t mine = __popc(flags);
-            uint32_t inc = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t t = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += t;
-            }
+            const uint32_t inc = lane_scan(mine);
             const uint32_t shard = (uint32_t)(here / units_per_shard);
             uint32_t at = first + inc - mine;
             const uint32_t in_shard = (uint32_t)(here - (uint64_t)shard * units_per_shard) * kUnit + lane * 8;
@@ -832,7 +822,7 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
     histogram_kernel<<<grid, block, 0, stream>>>(weights, n, partials, nm, loglik_threshold, reg_covar, st, unit_count, hist_part);
     merge_kernel<<<dim3(kMergeGroups + M), dim3(256), 0, stream>>>(hist_part, L.groups, hist, unit_count, unit_off,
                                                                    (int)units_per_shard, shard_count, outlier_count, st);
-    collect_kernel<<<grid, block, 0, stream>>>(weights, n, st, hist, shard_count, M, C, table, lists);
+    collect_kernel<<<grid, block, 0, stream>>>(weights, n, st, hist, shard_count, M, C, table, lists, (const uint16_t *)hist_part);
     boundary_values_kernel<<<dim3(C - 1), dim3(1024), 0, stream>>>(st, lists);
 #define STI_PACK(K) \
     pack_kernel<K><<<grid, block, 0, stream>>>(weights, n, st, table, unit_off, units_per_shard, packed, outlier_pos, outlier_val, max_outliers_per_shard, csum)
