@@ -195,20 +195,14 @@ __device__ __forceinline__ void decode_raw(const float *data, int64_t n, int64_t
     }
 }
 
-struct TableInline {
-    InlineShardTable t;
-    __device__ inline ShardDesc get(uint32_t s) const { return t.d[s]; }
-};
-
 template <typename Out, typename Table>
-__global__ __launch_bounds__(kThreads) void decode_kernel(Table table, uint64_t n,
-                                                          uint32_t chunks_per_shard, uint32_t first_chunk,
-                                                          typename Out::bits_t *out, int patch)
+__global__ __launch_bounds__(kThreads) void decode_kernel(uint64_t n, uint32_t chunks_per_shard, uint32_t chunks_recip, uint32_t first_chunk,
+                                                          int patch, typename Out::bits_t *out, Table table)
 {
     __shared__ alignas(16) uint32_t wave_codes[kThreads / 64][kWaveWeights<Out> * 6 / 32 + 12];
     __shared__ typename Out::bits_t wave_lut[kThreads / 64][64];
     const uint32_t block = first_chunk + blockIdx.x;
-    const uint32_t s = block / chunks_per_shard;
+    const uint32_t s = quotient((int)block, (int)chunks_per_shard, chunks_recip);   // (both below 2^31)
     const uint32_t c = block - s * chunks_per_shard;
     const ShardDesc sd = table.get(s);
     const uint64_t at = (uint64_t)s * n;
@@ -296,15 +290,11 @@ hipError_t patch_typed(const ShardDesc *table, const InlineShardTable *inline_ta
     while ((uint64_t)chunks * (uint64_t)n_shards > 0x7FFFFFFFull) chunks = (chunks + 1) / 2;
     dim3 grid(chunks * (uint32_t)n_shards);
     typedef typename Out::bits_t bits_t;
-    if (table) {
-        TablePtr t{table};
-        patch_outliers_kernel<Out, TablePtr><<<grid, 256, 0, stream>>>(t, n, chunks, (bits_t *)out);
-    } else {
-        TableInline t;
-        t.t = *inline_table;
-        patch_outliers_kernel<Out, TableInline><<<grid, 256, 0, stream>>>(t, n, chunks, (bits_t *)out);
-    }
-    return hipGetLastError();
+    auto go = [&](auto t) {
+        patch_outliers_kernel<Out, decltype(t)><<<grid, 256, 0, stream>>>(t, n, chunks, (bits_t *)out);
+        return hipGetLastError();
+    };
+    return table ? go(TablePtr{table}) : with_inline_table(*inline_table, n_shards, go);
 }
 
 template <typename Out>
@@ -315,27 +305,27 @@ hipError_t launch_typed(const ShardDesc *table, const InlineShardTable *inline_t
     const uint64_t chunks = (reach + kChunkWeights<Out> - 1) / kChunkWeights<Out>;
     const uint64_t blocks = chunks * (uint64_t)n_shards;
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFFull || chunks > 0xFFFFFFFFull) return hipErrorInvalidValue;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const bool patch = max_outliers > 0 && max_outliers <= kScannedOutliers && blocks <= kScanningWorkgroups;
     typedef typename Out::bits_t bits_t;
     for (uint64_t b = 0; b < blocks; b += kLaunchWorkgroups) {
         const dim3 grid((uint32_t)(blocks - b < kLaunchWorkgroups ? blocks - b : kLaunchWorkgroups));
-        if (table)
-            launch((decode_kernel<Out, TablePtr>), grid, dim3(kThreads), 0, stream, TablePtr{table}, n, (uint32_t)chunks,
-                   (uint32_t)b, (bits_t *)out, (int)patch);
-        else
-            launch((decode_kernel<Out, TableInline>), grid, dim3(kThreads), 0, stream, TableInline{*inline_table}, n,
-                   (uint32_t)chunks, (uint32_t)b, (bits_t *)out, (int)patch);
+        auto go = [&](auto t) {
+            launch((decode_kernel<Out, decltype(t)>), grid, dim3(kThreads), 0, stream, n, (uint32_t)chunks, reciprocal((uint32_t)chunks),
+                   (uint32_t)b, (int)patch, (bits_t *)out, t);
+        };
+        if (table) go(TablePtr{table});
+        else with_inline_table(*inline_table, n_shards, go);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || patch || max_outliers == 0) return e;
     return patch_typed<Out>(table, inline_table, n_shards, max_outliers, n, out, stream);
 }
 
-__global__ __launch_bounds__(256) void patch_outliers_tiled_kernel(InlineShardTable tab, int d,
-                                                                   int dh, int f, uint8_t *out)
+template <typename Table>
+__global__ __launch_bounds__(256) void patch_outliers_tiled_kernel(int d, int dh, int f, uint8_t *out, Table tab)
 {
-    const ShardDesc sd = tab.d[blockIdx.y];
+    const ShardDesc sd = tab.get(blockIdx.y);
     const int64_t wsh = (int64_t)d * (4 * dh + 2 * f);
     uint8_t *o = out + (int64_t)blockIdx.y * wsh * 2;
     for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < sd.n_outliers; t += gridDim.x * 256) {
@@ -383,8 +373,9 @@ hipError_t launch_patch_outliers_tiled(const InlineShardTable &table, int n_shar
     if (n_shards <= 0 || max_outliers == 0) return hipSuccess;
     uint32_t chunks = (max_outliers + 255) / 256;
     if (chunks > 1024) chunks = 1024;
-    patch_outliers_tiled_kernel<<<dim3(chunks, n_shards), 256, 0, stream>>>(table, d, dh, f,
-                                                                            (uint8_t *)out);
+    with_inline_table(table, n_shards, [&](auto t) {
+        patch_outliers_tiled_kernel<<<dim3(chunks, n_shards), 256, 0, stream>>>(d, dh, f, (uint8_t *)out, t);
+    });
     return hipGetLastError();
 }
 
@@ -396,8 +387,10 @@ hipError_t launch_decode_tiled(const InlineShardTable &table, int n_shards, int 
     if (cells == 0) return hipSuccess;
     if (d % 64 || dh % 64 || f % 64 || cells > 0x7FFFFFF0) return hipErrorInvalidValue;
     const CellMap m = cell_map(d, dh, f);
-    launch((decode_tiled_kernel<TableInline>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint8_t *)out, (int)cells,
-           d, dh, f, m.per_shard, m.recip_shard, m.recip_d, m.recip_dh, m.recip_f, TableInline{table});
+    with_inline_table(table, n_shards, [&](auto t) {
+        launch((decode_tiled_kernel<decltype(t)>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint8_t *)out, (int)cells,
+               d, dh, f, m.per_shard, m.recip_shard, m.recip_d, m.recip_dh, m.recip_f, t);
+    });
     return hipGetLastError();
 }
 

@@ -223,9 +223,10 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *src, uint1
 
 // A layer's shards to planes (Section "Submodel execution": the working buffer), one wave per cell: Q, K, V and O, or (skip: the cells
 // of those) FFN1 and FFN2.  per_shard: cells of a shard that the launch decodes.
+template <typename Table>
 __global__ __launch_bounds__(256) void decode_split_kernel(uint16_t *out, int total_cells, int d, int dh, int f, int per_shard,
                                                            uint32_t recip_shard, uint32_t recip_d, uint32_t recip_dh, uint32_t recip_f,
-                                                           int skip, int n_shards, InlineShardTable tab)
+                                                           int skip, int n_shards, Table tab)
 {
     __shared__ u32x2 lut[4][kLutEntries];
     const int lane = threadIdx.x & 63;
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(256) void decode_split_kernel(uint16_t *out, int to
     if (cell >= total_cells) return;   // whole wave; no workgroup barrier is used
     const int shard = quotient(cell, per_shard, recip_shard);
     const TiledCell t = locate_cell_of_shard(shard, cell - shard * per_shard + skip, CellMap{d, dh, f, per_shard, recip_shard, recip_d, recip_dh, recip_f});
-    const ShardDesc sd = tab.d[shard];
+    const ShardDesc sd = tab.get(shard);
     const int64_t attention = (int64_t)4 * dh * d, ffn = (int64_t)f * d;
     const int64_t at = skip == 0 ? shard * attention + t.sub_off : (t.sub_off == attention ? n_shards + shard : shard) * ffn;
     u32x4 *cell_out = (u32x4 *)(out + at * 3) + ((int64_t)t.strip * (t.cols >> 6) + t.kt) * 768 + lane;
@@ -389,8 +390,10 @@ hipError_t launch_decode_split(const InlineShardTable &table, int n_shards, int 
     if (cells == 0) return hipSuccess;
     if (d % 64 || dh % 64 || f % 64 || cells > 0x7FFFFFF0) return hipErrorInvalidValue;
     const CellMap m = cell_map(d, dh, f);
-    launch(decode_split_kernel, dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint16_t *)out, (int)cells, d, dh, f,
-           (int)per_shard, reciprocal((uint32_t)per_shard), m.recip_d, m.recip_dh, m.recip_f, ffn ? (int)attention_cells : 0, n_shards, table);
+    with_inline_table(table, n_shards, [&](auto t) {
+        launch((decode_split_kernel<decltype(t)>), dim3((uint32_t)((cells + 3) / 4)), dim3(256), 0, stream, (uint16_t *)out, (int)cells, d, dh, f,
+               (int)per_shard, reciprocal((uint32_t)per_shard), m.recip_d, m.recip_dh, m.recip_f, ffn ? (int)attention_cells : 0, n_shards, t);
+    });
     return hipGetLastError();
 }
 
