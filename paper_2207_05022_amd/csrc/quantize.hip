@@ -818,14 +818,14 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
     static_assert(kMomentGroups <= kThreads && kGroupUnits % kWaves == 0 && kGroupUnits * kUnit < 65536,
                   "one partial moment per thread; 16-bit counters");
     const dim3 grid(L.groups), block(kThreads);
-    moments_kernel<<<dim3(nm), dim3(256), 0, stream>>>(weights, n, partials);
-    histogram_kernel<<<grid, block, 0, stream>>>(weights, n, partials, nm, loglik_threshold, reg_covar, st, unit_count, hist_part);
-    merge_kernel<<<dim3(kMergeGroups + M), dim3(256), 0, stream>>>(hist_part, L.groups, hist, unit_count, unit_off,
-                                                                   (int)units_per_shard, shard_count, outlier_count, st);
-    collect_kernel<<<grid, block, 0, stream>>>(weights, n, st, hist, shard_count, M, C, table, lists, (const uint16_t *)hist_part);
-    boundary_values_kernel<<<dim3(C - 1), dim3(1024), 0, stream>>>(st, lists);
+    launch(moments_kernel, dim3(nm), dim3(256), 0, stream, weights, n, partials);
+    launch(histogram_kernel, grid, block, 0, stream, weights, n, partials, nm, loglik_threshold, reg_covar, st, unit_count, hist_part);
+    launch(merge_kernel, dim3(kMergeGroups + M), dim3(256), 0, stream, hist_part, L.groups, hist, unit_count, unit_off, (int)units_per_shard,
+           shard_count, outlier_count, st);
+    launch(collect_kernel, grid, block, 0, stream, weights, n, st, hist, shard_count, M, C, table, lists, (const uint16_t *)hist_part);
+    launch(boundary_values_kernel, dim3(C - 1), dim3(1024), 0, stream, st, lists);
 #define STI_PACK(K) \
-    pack_kernel<K><<<grid, block, 0, stream>>>(weights, n, st, table, unit_off, units_per_shard, packed, outlier_pos, outlier_val, max_outliers_per_shard, csum)
+    launch(pack_kernel<K>, grid, block, 0, stream, weights, n, st, table, unit_off, units_per_shard, packed, outlier_pos, outlier_val, max_outliers_per_shard, csum)
     switch (bitwidth) {
     case 2: STI_PACK(2); break;
     case 3: STI_PACK(3); break;
@@ -834,7 +834,7 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
     default: STI_PACK(6); break;
     }
 #undef STI_PACK
-    centroids_kernel<<<dim3(C), dim3(64), 0, stream>>>(st, csum, L.groups, C, n, codebook, stats);
+    launch(centroids_kernel, dim3(C), dim3(64), 0, stream, st, csum, L.groups, C, n, codebook, stats);
     STI_TRY(hipGetLastError());
     return STI_OK;
 }

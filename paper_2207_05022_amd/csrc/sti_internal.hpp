@@ -265,6 +265,19 @@ struct LaunchEvents {
 };
 LaunchEvents take_launch_events();   // api.hip; nulls unless a timed launch is pending on this thread
 
+template <typename T>
+struct SameType {
+    typedef T type;
+};
+// (the launch call itself: the triple chevrons pass grid and stream through a thread's stack of configurations first, 0.35 us of
+// 3.6 with 400 bytes of arguments)
+template <typename... P>
+inline void launch_arguments(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream, typename SameType<P>::type... values)
+{
+    void *arguments[] = {(void *)&values...};
+    (void)hipLaunchKernel((const void *)kernel, grid, block, arguments, lds_bytes, stream);   // (its error is the caller's hipGetLastError)
+}
+
 template <typename... P, typename... A>
 inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream, A... args)
 {
@@ -272,7 +285,7 @@ inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes
     if (ev.start)
         hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds_bytes, stream, ev.start, ev.stop, 0, (P)args...);
     else
-        hipLaunchKernelGGL(kernel, grid, block, (uint32_t)lds_bytes, stream, (P)args...);
+        launch_arguments(kernel, grid, block, lds_bytes, stream, P(args)...);
 }
 
 }  // namespace sti
