@@ -38,7 +38,7 @@ __device__ inline int vt_stride(int Lp) { return Lp + 8; }
 template <int NW>
 __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float16 *qkv, _Float16 *ctx,
                                                                  int L, int Lp, int m, int ctx_tiled,
-                                                                 const int32_t *key_lengths)
+                                                                 const int32_t *key_lengths, AttentionPieces pieces)
 {
     constexpr int QB = NW * 32;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -47,7 +47,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float
     const int vts = vt_stride(Lp);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 5, lr = lane & 31;
-    const int b = blockIdx.z, p = blockIdx.y;
+    const AttentionPiece piece = attention_piece(pieces, m, (L + QB - 1) / QB);
+    if (piece.none) return;
+    const int b = piece.sequence, p = piece.head;
     const int64_t ld = (int64_t)m * 3 * DH;
     const _Float16 *base = qkv + (int64_t)b * L * ld + (int64_t)p * 3 * DH;
     int Lk = L;   // keys that take part
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_mfma_kernel(const _Float
 
     // this lane's query row as the B operand of S^T = K Q^T (asked for first: the loads below
     // and these share one round trip to memory)
-    const int q = blockIdx.x * QB + wave * 32 + lr;
+    const int q = piece.block * QB + wave * 32 + lr;
     half8 qf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -149,18 +151,20 @@ constexpr int SV = SB + 8;        // padded V^T row (halves)
 
 template <int NW>
 __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Float16 *qkv, _Float16 *ctx, int L, int m, int ctx_tiled,
-                                                                   const int32_t *key_lengths)
+                                                                   const int32_t *key_lengths, AttentionPieces pieces)
 {
     __shared__ __attribute__((aligned(16))) _Float16 Ks[2][SB * KPAD];
     __shared__ __attribute__((aligned(16))) _Float16 Vt[2][DH * SV];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 5, lr = lane & 31;
-    const int b = blockIdx.z, p = blockIdx.y;
+    const AttentionPiece piece = attention_piece(pieces, m, (L + NW * 32 - 1) / (NW * 32));
+    if (piece.none) return;
+    const int b = piece.sequence, p = piece.head;
     const int64_t ld = (int64_t)m * 3 * DH;
     const _Float16 *base = qkv + (int64_t)b * L * ld + (int64_t)p * 3 * DH;
     int Lk = L;   // keys that take part
     if (key_lengths) Lk = min(max(key_lengths[b], 1), L);
-    const int q = blockIdx.x * (NW * 32) + wave * 32 + lr;
+    const int q = piece.block * (NW * 32) + wave * 32 + lr;
     half8 qf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) qf[s] = *(const half8 *)(base + (int64_t)min(q, L - 1) * ld + s * 16 + g * 8);
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_stream_kernel(const _Flo
     // (worked out again instead of kept: the loop uses all 128 registers of four waves per SIMD)
     int t2 = threadIdx.x;
     asm volatile("" : "+v"(t2));
-    const int q2 = blockIdx.x * (NW * 32) + (t2 >> 6) * 32 + (t2 & 31), g2 = (t2 >> 5) & 1;
+    const int q2 = piece.block * (NW * 32) + (t2 >> 6) * 32 + (t2 & 31), g2 = (t2 >> 5) & 1;
     if (q2 >= L) return;
     const float inv = 1.0f / run_sum;
     _Float16 *out = ctx + ((int64_t)b * L + q2) * ((int64_t)m * DH) + (int64_t)p * DH;
@@ -321,12 +325,12 @@ hipError_t launch_attention_mfma(const void *qkv, void *ctx, ActLayout ctx_layou
     const int tiled = (int)ctx_layout;
     // The kernel with all keys in LDS up to its 128 keys (93 tokens, 11 x 12 heads: 5.3 us against 6.1); few (sequence,
     // head) pairs: 64 queries per workgroup put twice as many workgroups on the chip.
-    if (L > 128)
-        launch((attention_stream_kernel<4>), dim3((L + 127) / 128, m, B), dim3(256), 0, stream, in, out, L, m, tiled, key_lengths);
-    else if ((int64_t)B * m < 128 && L > 32)
-        launch((attention_mfma_kernel<2>), dim3((L + 63) / 64, m, B), dim3(128), lds, stream, in, out, L, Lp, m, tiled, key_lengths);
-    else
-        launch((attention_mfma_kernel<4>), dim3(1, m, B), dim3(256), lds, stream, in, out, L, Lp, m, tiled, key_lengths);
+    const int blocks = L > 128 ? (L + 127) / 128 : (int64_t)B * m < 128 && L > 32 ? (L + 63) / 64 : 1;
+    const AttentionPieces pieces = attention_pieces(B, m, blocks);
+    const dim3 grid(8 * pieces.per_xcd);
+    if (L > 128) launch((attention_stream_kernel<4>), grid, dim3(256), 0, stream, in, out, L, m, tiled, key_lengths, pieces);
+    else if ((int64_t)B * m < 128 && L > 32) launch((attention_mfma_kernel<2>), grid, dim3(128), lds, stream, in, out, L, Lp, m, tiled, key_lengths, pieces);
+    else launch((attention_mfma_kernel<4>), grid, dim3(256), lds, stream, in, out, L, Lp, m, tiled, key_lengths, pieces);
     return hipGetLastError();
 }
 

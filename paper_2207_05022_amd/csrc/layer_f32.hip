@@ -309,7 +309,7 @@ constexpr int KB = 64;   // keys per block
 // PLANES: the context goes to the output projection as planes of bfloat16 values (gemm_f32_split.hip).
 template <int DB, bool VEC, bool PLANES>
 __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qkv, void *ctx, int L, int m, int dh,
-                                                                 const int32_t *key_lengths)
+                                                                 const int32_t *key_lengths, AttentionPieces pieces)
 {
     constexpr int DP = DB * 16;        // padded features
     constexpr int LDR = DP + 4;        // LDS row (floats): conflict-free in both products
@@ -317,12 +317,14 @@ __global__ __launch_bounds__(256) void attention_f32_mfma_kernel(const float *qk
     __shared__ __attribute__((aligned(16))) float Vs[KB * LDR];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, lr = lane & 15;
-    const int b = blockIdx.z, head = blockIdx.y;
+    const AttentionPiece piece = attention_piece(pieces, m, (L + 63) / 64);
+    if (piece.none) return;
+    const int b = piece.sequence, head = piece.head;
     const int64_t ld = (int64_t)m * 3 * dh;
     const float *base = qkv + (int64_t)b * L * ld + (int64_t)head * 3 * dh;
     int Lk = L;
     if (key_lengths) Lk = min(max(key_lengths[b], 1), L);
-    const int q = blockIdx.x * 64 + wave * 16 + lr;
+    const int q = piece.block * 64 + wave * 16 + lr;
     const float *qp = base + (int64_t)min(q, L - 1) * ld;
     f32x4 qf[DB];
 #pragma unroll
@@ -584,9 +586,10 @@ template <bool VEC>
 void launch_attention_blocks(const float *qkv, void *ctx, int B, int L, int m, int dh, const int32_t *key_lengths,
                              hipStream_t stream)
 {
-    const dim3 grid((L + 63) / 64, m, B);
+    const AttentionPieces pieces = attention_pieces(B, m, (L + 63) / 64);
+    const dim3 grid(8 * pieces.per_xcd);
 #define STI_ATT_F32(DB) \
-    launch((attention_f32_mfma_kernel<DB, VEC, false>), grid, dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths)
+    launch((attention_f32_mfma_kernel<DB, VEC, false>), grid, dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths, pieces)
     if (dh <= 32) STI_ATT_F32(2);
     else if (dh <= 64) STI_ATT_F32(4);
     else if (dh <= 96) STI_ATT_F32(6);
@@ -636,7 +639,8 @@ hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B,
     if (B <= 0 || L <= 0 || m <= 0) return hipSuccess;
     if (planes) {
         if (dh != 64 || ((uintptr_t)qkv & 15) || ((uintptr_t)ctx & 15)) return hipErrorInvalidValue;
-        launch((attention_f32_mfma_kernel<4, true, true>), dim3((L + 63) / 64, m, B), dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths);
+        const AttentionPieces pieces = attention_pieces(B, m, (L + 63) / 64);
+        launch((attention_f32_mfma_kernel<4, true, true>), dim3(8 * pieces.per_xcd), dim3(256), 0, stream, qkv, ctx, L, m, dh, key_lengths, pieces);
         return hipGetLastError();
     }
     if (dh <= 128) {

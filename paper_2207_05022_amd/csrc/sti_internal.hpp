@@ -115,6 +115,38 @@ __device__ inline int quotient(int c, int d, uint32_t recip)   // c >= 0, d > 0
     return (int)(q + ((uint32_t)c - q * (uint32_t)d >= (uint32_t)d ? 1u : 0u));
 }
 
+// Workgroups are handed to the eight XCDs in turn.  Pieces of work that lie behind each other in memory go to one XCD, an eighth of
+// them to each, so that what they share is fetched into one L2.
+__host__ __device__ inline int pieces_per_xcd(int pieces) { return (pieces + 7) >> 3; }
+__device__ inline int piece_of_block(int block, int per_xcd) { return (block & 7) * per_xcd + (block >> 3); }   // (of 8 per_xcd blocks; some past the last piece)
+
+// The (sequence, head, block of queries) triples of an attention launch in that order: the blocks of a head share its keys and values, the
+// heads of a sequence the cache lines of its rows.  24 x 384 tokens, 16 heads: 32.8 -> 29.9 us; 11 x 93, 10 heads 5.6 -> 5.35; float32
+// 8 x 128, 12 heads 12.8 -> 12.3.
+struct AttentionPieces {
+    int total, per_xcd;
+    uint32_t heads_recip, blocks_recip;
+};
+inline AttentionPieces attention_pieces(int sequences, int heads, int blocks)
+{
+    const int total = sequences * heads * blocks;   // (below 2^31: at most 2^24 tokens, 64 heads, blocks of 64 queries or more)
+    return {total, pieces_per_xcd(total), reciprocal((uint32_t)heads), reciprocal((uint32_t)blocks)};
+}
+struct AttentionPiece {
+    int sequence, head, block;
+    bool none;
+};
+__device__ inline AttentionPiece attention_piece(const AttentionPieces &p, int heads, int blocks)
+{
+    const int i = piece_of_block(blockIdx.x, p.per_xcd), pair = quotient(i, blocks, p.blocks_recip);
+    AttentionPiece out;
+    out.none = i >= p.total;
+    out.block = i - pair * blocks;
+    out.sequence = quotient(pair, heads, p.heads_recip);
+    out.head = pair - out.sequence * heads;
+    return out;
+}
+
 // two values rounded to binary16 (nearest even) in one dword: one conversion instruction
 __device__ inline uint32_t f16_pair_bits(float lo, float hi)
 {
