@@ -482,7 +482,8 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
  * points above carries two events on the caller's stream that take the
  * dispatch's own begin and end time stamps; sti_profile_end() waits for them
  * and returns, per kernel class, the number of launches and the summed kernel
- * time in milliseconds.  Process wide, not re-entrant; meant for measurement
+ * time in milliseconds (attention and output projection in one launch, for few
+ * tokens: a launch and half the time in either class).  Process wide, not re-entrant; meant for measurement
  * runs, not for production calls (nor for calls under stream capture).
  * ------------------------------------------------------------------------- */
 typedef enum {

@@ -78,8 +78,8 @@ public:
         on_ = true;
         return hipSuccess;
     }
-    // events for the next launch of class `cls` (nulls when timing is off)
-    hipError_t next(int cls, LaunchEvents *ev)
+    // events for the next launch of class `cls` (nulls when timing is off); also: a second class that it does the work of, or -1
+    hipError_t next(int cls, int also, LaunchEvents *ev)
     {
         std::lock_guard<std::mutex> lock(mu_);
         *ev = LaunchEvents{};
@@ -93,6 +93,7 @@ public:
             recs_.push_back(r);
         }
         recs_[used_].cls = cls;
+        recs_[used_].also = also;
         ev->start = recs_[used_].a;
         ev->stop = recs_[used_].b;
         return hipSuccess;
@@ -114,8 +115,13 @@ public:
             float ms = 0.f;
             e = hipEventElapsedTime(&ms, recs_[i].a, recs_[i].b);
             if (e != hipSuccess) return e;
+            const int also = recs_[i].also;
             out->launches[recs_[i].cls] += 1;
-            out->ms[recs_[i].cls] += ms;
+            out->ms[recs_[i].cls] += also < 0 ? ms : ms / 2;
+            if (also >= 0) {
+                out->launches[also] += 1;
+                out->ms[also] += ms / 2;
+            }
         }
         used_ = 0;
         return hipSuccess;
@@ -124,7 +130,7 @@ public:
 private:
     struct Rec {
         hipEvent_t a = nullptr, b = nullptr;
-        int cls = 0;
+        int cls = 0, also = -1;
     };
     std::mutex mu_;
     std::vector<Rec> recs_;
@@ -142,12 +148,12 @@ thread_local LaunchEvents pending_launch_events;
 
 // Run `fn` (one kernel launch through launch(); returns hipError_t) with timing events when enabled.
 template <typename F>
-hipError_t timed(int cls, hipStream_t stream, F fn)
+hipError_t timed(int cls, hipStream_t stream, F fn, int also = -1)
 {
     (void)stream;
     Profiler &pr = profiler();
     if (!pr.enabled()) return fn();
-    hipError_t e = pr.next(cls, &pending_launch_events);
+    hipError_t e = pr.next(cls, also, &pending_launch_events);
     if (e != hipSuccess) return e;
     e = fn();
     if (pending_launch_events.start == nullptr) pr.commit();   // taken by the launch
@@ -324,7 +330,8 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     if (!compact) {
         L.qkv = take(Tb * M * 3 * dh * es);
         L.ctx = take(Tb * M * dh * es);
-        L.pre_out = L.pre_down = take(plane * std::max(out_planes, down_planes));
+        L.pre_planes = (int)std::max(out_planes, down_planes);
+        L.pre_out = L.pre_down = take(plane * L.pre_planes);
     } else {
         // those of the O product over Q/K/V, which is read by then, those of FFN2 over context and Q/K/V (measured
         // slower where there is room for buffers of their own: 24 layers of d_model 1024, 256 tokens 1163 -> 1206 us)
@@ -611,6 +618,13 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     const ActLayout inner = wl.inner;
     const bool few_attention = inner == LAYOUT_TILED && attention_few_supported(B, Lseq);
     GemmProblem p;
+    int out_with_attention = 0;   // planes of partial sums where attention and the O product go out as one launch
+    if (few_attention && Lseq <= kFewOutKeys && m > 0) {
+        memset(&p, 0, sizeof(p));
+        p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
+        out_with_attention = attention_out_few_planes(p, B, Lseq);
+        if (out_with_attention > wl.pre_planes) out_with_attention = 0;
+    }
     if (m > 0) {
         memset(&p, 0, sizeof(p));
         p.a_layout = in_layout; p.c_layout = few_attention ? LAYOUT_TILED : LAYOUT_ROWS;
@@ -633,11 +647,13 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                 p.next_workgroups = next->workgroups; p.next_ffn_per_shard = f;
             }
             STI_TRY(gemm(p, bq));
-            STI_TRY(timed(STI_K_ATTENTION, stream, [&] {
-                if (f32) return launch_attention_f32((const float *)qkv, ctx, split, B, Lseq, m, dh, key_lengths, stream);
-                if (few_attention) return launch_attention_few(qkv, ctx, B, Lseq, m, dh, key_lengths, stream);
-                return launch_attention_mfma(qkv, ctx, inner, B, Lseq, m, dh, key_lengths, stream);
-            }));
+            if (!out_with_attention) {
+                STI_TRY(timed(STI_K_ATTENTION, stream, [&] {
+                    if (f32) return launch_attention_f32((const float *)qkv, ctx, split, B, Lseq, m, dh, key_lengths, stream);
+                    if (few_attention) return launch_attention_few(qkv, ctx, B, Lseq, m, dh, key_lengths, stream);
+                    return launch_attention_mfma(qkv, ctx, inner, B, Lseq, m, dh, key_lengths, stream);
+                }));
+            }
         }
     }
     memset(&p, 0, sizeof(p));
@@ -649,8 +665,14 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         p.next_table = next->table; p.next_shards = next->n_shards; p.next_out = next->out;
         p.next_outliers = next->max_outliers; p.next_ffn_per_shard = f;
     }
-    if (no_products) pre_partials = 0;
-    else STI_TRY(gemm(p, bo));
+    if (no_products) {
+        pre_partials = 0;
+    } else if (out_with_attention) {
+        pre_partials = out_with_attention;
+        STI_TRY(timed(STI_K_GEMM_OUT, stream, [&] { return launch_attention_out_few(p, bo, qkv, B, Lseq, key_lengths, partial_stride, stream); }, STI_K_ATTENTION));
+    } else {
+        STI_TRY(gemm(p, bo));
+    }
     STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, split && m > 0 ? ws + wl.s_h : nullptr));
     if (split && m > 0) {
         InlineShardTable t;

@@ -19,6 +19,7 @@ constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // of sti_layer_forwa
 struct WorkspaceLayout {
     size_t w32 = 0, w16 = 0, act[2] = {0, 0}, qkv = 0, ctx = 0, h = 0, u = 0, table = 0, total = 0;
     size_t pre_out = 0, pre_down = 0;   // sums before LayerNorm of the O and of the FFN2 product (compact: over other buffers)
+    int pre_planes = 1;                // planes of partial sums there is room for (buffers of their own only)
     bool few = false;                   // the layers take the few-token kernels
     bool split = false;                 // there is room for float32 layers on the bfloat16 matrix cores (takes_planes)
     // ... whose buffers lie over those of the others: planes of a layer's input, context, first LayerNorm's rows, neurons; Q/K/V and

@@ -24,6 +24,7 @@
 #include <type_traits>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
+#include "few_tiles.hpp"
 
 namespace sti {
 namespace {
@@ -44,8 +45,6 @@ __device__ inline float gelu_fast(float z)
     return 0.5f * z * (1.0f + (z < 0.f ? -erf_abs : erf_abs));
 }
 
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-
 constexpr int kF32Row = BK + 8;      // LDS row of a float32 tile on its way to fragments (halves)
 
 template <int RA>
@@ -60,13 +59,6 @@ struct FewSmem {
     FewWave<RA> wave[NW];
     uint16_t lut[NW][kLutEntries];
 };
-
-__device__ inline void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // A float32 tile on its way to fragments: whole 256-byte rows are requested (16 lanes each), rounded, and
 // turned into the fragment layout through LDS.
@@ -92,11 +84,6 @@ __device__ inline void float_fragments(const FloatTile &t, _Float16 (*tile)[kF32
     wave_lds_fence();
 }
 
-// NB: room for weight blocks among the arguments (an argument list of 64 blocks costs the host 1.2 us more per launch)
-template <int NB>
-struct FewBlocks {
-    GemmBlock b[NB];
-};
 struct FewTail {   // what only the end of a workgroup needs
     void *C;
     const float *bias0, *bias1, *bias2;

@@ -256,6 +256,13 @@ bool attention_few_supported(int B, int L);
 hipError_t launch_attention_few(const void *qkv, void *ctx, int B, int L, int m, int dh, const int32_t *key_lengths,
                                 hipStream_t stream);
 
+// The same attention and the output projection (p: GEMM_OUT) in one launch: partial sums in planes of a group of heads each.
+// How many planes, or 0 where the two by themselves are faster or the forms do not fit.
+constexpr int kFewOutKeys = 64;
+int attention_out_few_planes(const GemmProblem &p, int B, int L);   // (0 beyond kFewOutKeys keys)
+hipError_t launch_attention_out_few(const GemmProblem &p, const GemmBlocks &blocks, const void *qkv, int B, int L, const int32_t *key_lengths,
+                                    int64_t partial_stride, hipStream_t stream);
+
 // Few-token variant of the MFMA GEMM (gemm_few.hip): T <= kFewMaxTokens, split-K inside the
 // workgroup and, for the K-split kinds, across `k_splits` workgroups that write float32
 // partial sums at C + s * partial_stride (to be added by launch_layernorm).

@@ -411,6 +411,33 @@ def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, o
         assert_parity(got, want, TOL["mfma"], io)
 
 
+@pytest.mark.parametrize("d,M,f,absent,B,L,masked,outliers", [
+    (256, 1, 64, 0, 1, 1, False, False),      # one head, one token
+    (256, 5, 128, 1, 1, 32, True, False),     # one whole group of heads, one whole block of keys
+    (256, 6, 256, 1, 1, 33, True, False),     # a group with one head, a second block with one key
+    (768, 12, 256, 1, 1, 64, True, True),     # the most keys; weights from the working buffer
+    (320, 9, 256, 0, 2, 32, True, False),     # several sequences
+    (512, 8, 256, 0, 2, 64, True, False),
+    (256, 20, 256, 1, 1, 40, False, False),   # more than 16 weight blocks
+    (1024, 13, 256, 1, 1, 64, False, False),  # as many workgroups as one launch takes
+    (1024, 13, 256, 0, 1, 64, False, False),  # one head more: two launches
+    (256, 12, 64, 0, 1, 23, True, False),     # no room for the planes: two launches
+])
+def test_few_token_attention_with_the_output_projection(gpu, oracle_mod, d, M, f, absent, B, L, masked, outliers):
+    """Edges of the launch that does both, and both sides of its line; every bitwidth in turn."""
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    wl = S.small_workload(52000 + d + L, dims, 2, B, L, n_absent=absent, io_dtype="f32")
+    if outliers:
+        wl = _with_outliers(wl, 5, fraction=0.005)
+    S.make_every_term_matter(wl, L, amp=2.0)
+    lens = _key_lengths(L, B, L) if masked else None
+    if B == 1 and masked:
+        lens[0] = max(1, L - 1)
+    want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x, key_lengths=lens)
+    got = _run_masked(gpu, wl, "mfma", lens, "model").float().cpu().numpy()
+    assert_parity(got, want, TOL["mfma"])
+
+
 def test_less_workspace_than_the_few_token_kernels_take(gpu, oracle_mod):
     """Between the two lines a call that has room for the wide-tile kernels only is accepted and takes those."""
     torch, P, D = gpu
