@@ -36,17 +36,18 @@ __device__ inline LanePair across_32(float v)   // partner: lane ^ 32
 __device__ inline float pair_sum(LanePair p) { return p.a + p.b; }
 __device__ inline float pair_max(LanePair p) { return fmaxf(p.a, p.b); }
 
-// sum over groups of LANES (16, 32 or 64) consecutive lanes
+// Sum over groups of LANES (16, 32 or 64) consecutive lanes, halves first: the order (and the bits) of butterflies of lane ^ 32, 16, 8, 4,
+// 2, 1, as after each step the values repeat themselves with that step's distance.
 template <int LANES>
 __device__ inline float lane_sum(float v)
 {
     static_assert(LANES == 16 || LANES == 32 || LANES == 64, "rows of 16 lanes");
+    if constexpr (LANES >= 64) v = pair_sum(across_32(v));
+    if constexpr (LANES >= 32) v = pair_sum(across_16(v));
     v += rotated<8>(v);
     v += rotated<4>(v);
     v += rotated<2>(v);
     v += rotated<1>(v);
-    if constexpr (LANES >= 32) v = pair_sum(across_16(v));
-    if constexpr (LANES >= 64) v = pair_sum(across_32(v));
     return v;
 }
 

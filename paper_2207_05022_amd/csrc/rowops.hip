@@ -91,7 +91,6 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
                                                             const float *b, int T, int d, int shape, float eps, int64_t partial_stride,
                                                             typename Elem<DT>::type *y, uint16_t *planes)
 {
-    const float inv_d = 1.0f / (float)d;   // (formed while the row is on its way)
     const int n_partials = shape & 0xff, resid_layout = shape >> 8 & 0xff, y_layout = shape >> 16;
     const int sub = threadIdx.x % LPR;
     int row = blockIdx.x * ROWS + threadIdx.x / LPR;
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
         v[j] = x;
         s += (x.x + x.y) + (x.z + x.w);
     }
-    const float mean = lane_sum<LPR>(s) * inv_d;
+    const float mean = lane_sum<LPR>(s) / (float)d;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
@@ -165,7 +164,7 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
             q += (t.x * t.x + t.y * t.y) + (t.z * t.z + t.w * t.w);
         }
     }
-    const float var = lane_sum<LPR>(q) * inv_d;
+    const float var = lane_sum<LPR>(q) / (float)d;
     const float inv = 1.0f / sqrtf(var + eps);
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
@@ -200,7 +199,6 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 {
     typedef _Float16 half8 __attribute__((ext_vector_type(8)));
     constexpr int ROWS = 256 / LPR;
-    const float inv_d = 1.0f / (float)d;
     const int sub = threadIdx.x % LPR;
     const int row = blockIdx.x * ROWS + threadIdx.x / LPR;
     if (row >= T) return;   // whole row groups leave together; shuffles stay inside a group
@@ -224,7 +222,7 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 #pragma unroll
         for (int e = 0; e < 8; ++e) { v[j][e] = in ? (float)h[j][e] : 0.f; s += v[j][e]; }
     }
-    const float mean = lane_sum<LPR>(s) * inv_d;
+    const float mean = lane_sum<LPR>(s) / (float)d;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j)
@@ -232,7 +230,7 @@ __global__ __launch_bounds__(256) void layernorm_f16in_kernel(const _Float16 *pr
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[j][e] - mean; q = fmaf(t, t, q); }
         }
-    const float var = lane_sum<LPR>(q) * inv_d;
+    const float var = lane_sum<LPR>(q) / (float)d;
     const float inv = 1.0f / sqrtf(var + eps);
     typename Elem<DT>::type *o = y + (int64_t)row * d;
 #pragma unroll

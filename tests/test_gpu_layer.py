@@ -525,6 +525,29 @@ def test_parameters_begin_at_any_float(gpu, prec, dims, B, L):
         assert rel_err(y.cpu().numpy(), outs[0].cpu().numpy().astype(np.float64)) <= (1e-6 if prec == "f32" else 2.0 ** -11)
 
 
+@pytest.mark.parametrize("prec,d,B,L,absent", [
+    ("mfma", 448, 1, 40, False),    # sums of the few-token kernels
+    ("mfma", 960, 2, 64, False),
+    ("mfma", 832, 1, 23, True),     # bias and residual alone
+    ("mfma", 448, 40, 100, False),  # finished binary16 rows, 32 lanes each
+    ("mfma", 896, 20, 200, False),
+    ("f32", 832, 1, 33, False),
+    ("f32", 448, 10, 130, False),   # planes of bfloat16 values behind the row
+])
+def test_rows_of_equal_values_have_no_variance(gpu, prec, d, B, L, absent):
+    """A row of one value throughout is its own mean, so that LayerNorm's result is the shift: sums of small integers are exact
+    in any order, and so are their quotients by d.  (Products with a rounded 1 / d are not at these widths, and the
+    square of that difference is far above an eps of 1e-12.)"""
+    M = d // 64
+    wl = S.small_workload(55000 + d + L, S.Dims(d, M, 64, 256, 1e-12), 1, B, L, plan=np.zeros((1, M), dtype=np.int8) if absent else None)
+    S.make_every_term_matter(wl, 9, amp=0.0)
+    prm = wl.params[0]
+    prm.bo[:], prm.ln1_b[:], prm.b2[:] = 1.0, 5.0, 2.0     # both rows: x + 1, and 5 + 2
+    wl.x[:] = (np.arange(B * L) % 40).reshape(B, L, 1)
+    got = run_gpu(gpu, wl, prec, model=False)
+    np.testing.assert_array_equal(got, np.broadcast_to(prm.ln2_b, got.shape))
+
+
 def test_mfma_rejects_unsupported_dims(gpu):
     torch, P, D = gpu
     assert P.sti_workspace_bytes(SMALL, 1, 8, P.STI_PREC_F16_MFMA) == 0
