@@ -797,8 +797,9 @@ Choice choose(const GemmProblem &p, int N)
     best.us = INFINITY;
     for (int c = n_split ? 0 : 2; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
         if (c == 1 && !beside) continue;
-        // (the large tiles have no workgroups for the next layer's shards or dictionaries, two K tiles at least, and 256 rows only without residual)
-        if (kShapes[c].large && (beside || p.next_outliers > 0 || nkt < 2 || (!n_split && kShapes[c].rows > 192))) continue;
+        // (the large tiles have no workgroups for the next layer's shards or dictionaries, whole strips of 64 columns, two K tiles at least,
+        // and 256 rows only without residual)
+        if (kShapes[c].large && (beside || p.next_outliers > 0 || N % 64 || nkt < 2 || (!n_split && kShapes[c].rows > 192))) continue;
         const long tiles = (long)((N + kShapes[c].cols - 1) / kShapes[c].cols) * ((p.T + kShapes[c].rows - 1) / kShapes[c].rows);
         const float avg = (float)tiles / kComputeUnits;
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
@@ -910,3 +911,16 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
 }
 
 }  // namespace sti
+
+// The tile that a projection takes in a launch of its own, for the tests of its kernels (no device is touched): rows, columns, groups of
+// waves that share K, and whether it is one of gemm_large.hip.  outliers: entries per dictionary of a next layer put in beside it.
+extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int block_rows, int block_cols, int outliers, int *tile)
+{
+    sti::GemmProblem p = {};
+    p.kind = (sti::GemmKind)kind;
+    p.T = T; p.n_blocks = n_blocks; p.block_rows = block_rows; p.block_cols = block_cols; p.next_outliers = outliers;
+    const bool n_split = kind == sti::GEMM_QKV || kind == sti::GEMM_FFN_UP;
+    const sti::Choice ch = sti::choose(p, n_split ? n_blocks * block_rows : block_rows);
+    const sti::Shape &sh = sti::kShapes[ch.shape];
+    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = ch.ks2 ? 2 : 1; tile[3] = sh.large;
+}

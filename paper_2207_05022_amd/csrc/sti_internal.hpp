@@ -233,7 +233,8 @@ hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B,
 // of the fragment-tiled binary16 working buffer (bits == kTiledBits).
 hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipStream_t stream);
 bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks);
-// the same in tiles of 64 row_blocks x 256 (gemm_large.hip); what launch_gemm_wide has checked, at least two K tiles, no next_* work
+// the same in tiles of 64 row_blocks x 256 (gemm_large.hip): N a multiple of 64, at least two K tiles, no next_* work, on top of what
+// launch_gemm_wide has checked
 hipError_t launch_gemm_large(const GemmProblem &p, const GemmBlocks &blocks, int N, int row_blocks, hipStream_t stream);
 // whether the Q/K/V projection of B sequences of L tokens over m heads should go out as GEMM_QKV_ATTN
 bool gemm_wide_fuses_attention(int B, int L, int m, int dh);

@@ -163,6 +163,23 @@ def test_workspace_of_a_larger_call_serves_the_smaller_ones(P, d, M, f):
         assert all(a <= b for a, b in zip(layer, model))
 
 
+def test_tiles_of_64_column_strips_are_for_whole_strips(P):
+    """The kernel with both operands through LDS stores strips of 64 columns and begins with two K tiles: widths that end inside a
+    strip and single K tiles stay with the other kernel, whatever is faster; so do projections that put a next layer's dictionaries in."""
+    import tiles
+    widths = range(960, 1280, 32)
+    for tokens in (2000, 5000, 7000, 9000):
+        for kind, cols in ((tiles.O, 64), (tiles.FFN2, 256)):
+            large = {n: tiles.tile(P, kind, tokens, 16, n, cols)[3] for n in widths}
+            assert not any(v for n, v in large.items() if n % 64)
+            if tokens >= 7000:
+                assert all(v for n, v in large.items() if n % 64 == 0)
+            assert not any(tiles.tile(P, kind, tokens, 16, n, cols, outliers=1)[3] for n in widths)
+        assert not any(tiles.tile(P, tiles.FFN1, tokens, 11, f, 256)[3] for f in (32, 96, 160, 224, 288))
+        assert not tiles.tile(P, tiles.O, tokens, 1, 2048, 64)[3] and not tiles.tile(P, tiles.FFN1, tokens, 16, 256, 64)[3]
+    assert tiles.tile(P, tiles.O, 9000, 2, 2048, 64)[3] and tiles.tile(P, tiles.FFN1, 9000, 16, 256, 128)[3]
+
+
 @pytest.mark.parametrize("d,M,f,last", [(768, 12, 256, 640), (1024, 16, 256, 512), (512, 8, 128, 1024), (256, 4, 64, 1024),
                                         (1024, 16, 64, 704), (1024, 16, 128, 576), (896, 14, 128, 704), (1024, 8, 256, 704),
                                         (768, 12, 192, 704), (896, 10, 192, 768), (128, 2, 64, 192), (1088, 4, 64, 128)])
