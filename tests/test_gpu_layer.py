@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 
 import sti_synth as S
+import tiles
 from parity import assert_parity
 
 pytestmark = pytest.mark.gpu
@@ -411,20 +412,22 @@ def test_few_token_tiles_and_attention(gpu, oracle_mod, d, M, f, B, L, masked, o
         assert_parity(got, want, TOL["mfma"], io)
 
 
-@pytest.mark.parametrize("d,M,f,absent,B,L,masked,outliers", [
-    (256, 1, 64, 0, 1, 1, False, False),      # one head, one token
-    (256, 5, 128, 1, 1, 32, True, False),     # one whole group of heads, one whole block of keys
-    (256, 6, 256, 1, 1, 33, True, False),     # a group with one head, a second block with one key
-    (768, 12, 256, 1, 1, 64, True, True),     # the most keys; weights from the working buffer
-    (320, 9, 256, 0, 2, 32, True, False),     # several sequences
-    (512, 8, 256, 0, 2, 64, True, False),
-    (256, 20, 256, 1, 1, 40, False, False),   # more than 16 weight blocks
-    (1024, 13, 256, 1, 1, 64, False, False),  # as many workgroups as one launch takes
-    (1024, 13, 256, 0, 1, 64, False, False),  # one head more: two launches
-    (256, 12, 64, 0, 1, 23, True, False),     # no room for the planes: two launches
+@pytest.mark.parametrize("d,M,f,absent,B,L,masked,outliers,together", [
+    (256, 1, 64, 0, 1, 1, False, False, True),       # one head, one token
+    (256, 5, 128, 1, 1, 32, True, False, True),      # one whole group of heads, one whole block of keys
+    (256, 6, 256, 1, 1, 33, True, False, True),      # a group with one head, a second block with one key
+    (768, 12, 256, 1, 1, 64, True, True, True),      # the most keys; weights from the working buffer
+    (320, 9, 256, 0, 2, 32, True, False, True),      # several sequences
+    (512, 8, 256, 0, 2, 64, True, False, True),
+    (256, 20, 256, 1, 1, 40, False, False, True),    # more than 16 weight blocks
+    (1024, 13, 256, 1, 1, 64, False, False, True),   # as many workgroups as one launch takes
+    (1024, 13, 256, 0, 1, 64, False, False, False),  # one head more
+    (256, 12, 64, 0, 1, 23, True, False, False),     # no room for the planes
+    (256, 4, 128, 0, 1, 65, True, False, False),     # one key more
 ])
-def test_few_token_attention_with_the_output_projection(gpu, oracle_mod, d, M, f, absent, B, L, masked, outliers):
-    """Edges of the launch that does both, and both sides of its line; every bitwidth in turn."""
+def test_few_token_attention_with_the_output_projection(gpu, oracle_mod, d, M, f, absent, B, L, masked, outliers, together):
+    """Edges of the launch that does both, and both sides of its line; every bitwidth in turn.  One launch counts half its time in
+    either class, so that the two sums are the same value; those of two launches are in 10 ns steps, and not the same three times."""
     dims = S.Dims(d, M, 64, f, 1e-12)
     wl = S.small_workload(52000 + d + L, dims, 2, B, L, n_absent=absent, io_dtype="f32")
     if outliers:
@@ -434,7 +437,14 @@ def test_few_token_attention_with_the_output_projection(gpu, oracle_mod, d, M, f
     if B == 1 and masked:
         lens[0] = max(1, L - 1)
     want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x, key_lengths=lens)
-    got = _run_masked(gpu, wl, "mfma", lens, "model").float().cpu().numpy()
+    same = []
+    for _ in range(3):
+        gpu[1].sti_profile_begin()
+        got = _run_masked(gpu, wl, "mfma", lens, "model").float().cpu().numpy()
+        prof = gpu[1].sti_profile_end()
+        assert prof["attention"][0] == prof["gemm_out"][0] == 2
+        same.append(prof["attention"][1] == prof["gemm_out"][1])
+    assert all(same) == together
     assert_parity(got, want, TOL["mfma"])
 
 
@@ -742,8 +752,8 @@ def test_outlier_dictionaries_beside_the_output_projection(gpu, B, L, entries):
     (768, 12, 256, (2, 2, 2), 60, 64, 3),       # the fastest tiles of Q/K/V alone would leave no compute unit ...
     (1024, 16, 256, (0, 0, 0), 40, 64, 2),
     (768, 12, 256, (2, 2, 2), 56, 64, 0),       # ... or too few
-    (1024, 4, 64, (0, 1, 1), 28, 100, 300),     # output projection in 128 x 256 tiles of four waves
-    (1024, 8, 64, (0, 1, 1), 55, 100, 257),
+    (1024, 4, 64, (0, 1, 1), 28, 100, 300),     # output projection in 64 x 384 tiles, where 128 x 256 alone would be faster ...
+    (1024, 8, 64, (0, 1, 1), 55, 100, 257),     # ... and in 64 x 192, two to a unit
 ])
 def test_a_layer_rides_where_that_is_faster_than_a_launch_of_its_own(gpu, d, M, f, absent, B, L, entries):
     """Layers behind the first are decompressed beside the Q/K/V projection in front of them (one decompression
@@ -753,6 +763,9 @@ def test_a_layer_rides_where_that_is_faster_than_a_launch_of_its_own(gpu, d, M, 
     plan = np.full((3, M), 4, dtype=np.int8)
     for l, n in enumerate(absent):
         plan[l, 1:1 + n] = 0
+    if entries:
+        beside = tiles.layer_tiles(gpu[1], dims, B * L, M - absent[0], outliers=entries)["o"]
+        assert beside == {1024 * 28 * 100: "64x384/132", 1024 * 55 * 100: "64x192/516"}.get(d * B * L, f"64x192*/{-(-d // 192) * -(-B * L // 64)}")
     wl = S.small_workload(810 + entries, dims, 3, B, L, plan=plan, io_dtype="f16")
     if entries:
         wl = _with_outliers(wl, entries, fraction=entries / dims.weights_per_shard)
@@ -871,8 +884,10 @@ def test_mfma_many_column_tiles_take_the_band_order(gpu, oracle_mod):
 
 @pytest.mark.parametrize("B,L,n_absent", [(40, 150, 0), (37, 161, 1)])
 def test_mfma_many_tiles_shared_compute_units(gpu, oracle_mod, B, L, n_absent):
-    """Enough tiles for two 128 x 256 workgroups per compute unit (Q/K/V and FFN1): part tiles in both directions."""
+    """Q/K/V in one tile of 256 x 256 per compute unit, FFN1 in up to two of 192 x 256: part tiles in both directions."""
     dims = S.Dims(256, 12, 64, 256, 1e-12)
+    chosen = tiles.layer_tiles(gpu[1], dims, B * L, dims.n_heads - n_absent)
+    assert chosen["qkv"] == "256x256L/216" and chosen["ffn1"] == ("192x256L/352" if n_absent else "192x256L/384")
     wl = S.small_workload(52000 + B, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
     S.make_every_term_matter(wl, B, amp=2.0)
     want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x)
@@ -881,9 +896,11 @@ def test_mfma_many_tiles_shared_compute_units(gpu, oracle_mod, B, L, n_absent):
 
 @pytest.mark.parametrize("n_absent", [0, 1])
 def test_mfma_output_projections_with_shared_compute_units(gpu, oracle_mod, n_absent):
-    """O and FFN2 in 128 x 256 workgroups, two per compute unit, residual and a ragged last row tile: sampled
-    sequences, the last tile's among them."""
+    """O, FFN1 and FFN2 in 128 x 256 tiles, Q/K/V in up to two of 192 x 256 per compute unit, residual and a ragged last row tile:
+    sampled sequences, the last tile's among them."""
     dims = S.Dims(1024, 16, 64, 64, 1e-12)
+    assert tiles.layer_tiles(gpu[1], dims, 5500, 16 - n_absent) == {"qkv": "192x256L/348", "o": "128x256L/172", "ffn1": "128x256L/172",
+                                                                    "ffn2": "128x256L/172"}
     wl = S.small_workload(53000, dims, 1, 55, 100, n_absent=n_absent, io_dtype="f16")
     S.make_every_term_matter(wl, 6, amp=2.0)
     got = run_gpu(gpu, wl, "mfma")
@@ -893,18 +910,19 @@ def test_mfma_output_projections_with_shared_compute_units(gpu, oracle_mod, n_ab
         assert_parity(got[b:b + 1], want, TOL["mfma"], b)
 
 
-@pytest.mark.parametrize("d,M,f,B,L,n_absent", [
-    (128, 32, 256, 23, 259, 0),    # Q/K/V, FFN1: 192 x 256, three and four tiles to a workgroup, K of two tiles, bands of row tiles
-    (1024, 16, 64, 44, 125, 0),    # Q/K/V 192 rows, O and FFN2 128 with residual, a last tile of 124 rows
-    (448, 14, 128, 25, 360, 0),    # FFN1 256 rows, O and FFN2 128 with 192 columns in the last column tile
-    (1024, 2, 64, 31, 297, 0),     # O and FFN2 192 rows, K of two tiles
-    (256, 12, 256, 40, 150, 1),    # Q/K/V 256 rows, 64 columns in the last column tile
-    (128, 29, 256, 7, 200, 0),     # Q/K/V 128 rows
+@pytest.mark.parametrize("d,M,f,B,L,n_absent,chosen", [
+    (128, 32, 256, 23, 259, 0, {"qkv": "192x256L/768", "ffn1": "192x256L/1024"}),    # three and four tiles to a workgroup, K of two tiles, bands of row tiles
+    (1024, 16, 64, 44, 125, 0, {"qkv": "192x256L/348", "o": "128x256L/172", "ffn2": "128x256L/172"}),   # residual, a last tile of 124 rows
+    (448, 14, 128, 25, 360, 0, {"ffn1": "256x256L/252", "o": "128x256L/142", "ffn2": "128x256L/142"}),  # 192 columns in the last column tile
+    (1024, 2, 64, 31, 297, 0, {"o": "192x256L/192", "ffn2": "192x256L/192"}),        # K of two tiles
+    (256, 12, 256, 40, 150, 1, {"qkv": "256x256L/216"}),                             # 64 columns in the last column tile
+    (128, 29, 256, 7, 200, 0, {"qkv": "128x256L/242"}),
 ])
-def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent):
+def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
     """Tiles of 128, 192 and 256 rows x 256 columns: first, middle and last sequences against the oracle (sequences do not
     depend on each other), all rows finite."""
     dims = S.Dims(d, M, 64, f, 1e-12)
+    assert chosen.items() <= tiles.layer_tiles(gpu[1], dims, B * L, M - n_absent).items()
     wl = S.small_workload(54000 + d + M, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
     S.make_every_term_matter(wl, 8, amp=2.0)
     got = run_gpu(gpu, wl, "mfma")
@@ -912,6 +930,30 @@ def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent):
     for b in (0, B // 2, B - 1):
         want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
         assert_parity(got[b:b + 1], want, TOL["mfma"], b)
+
+
+@pytest.mark.parametrize("d,M,f,B,L,n_absent,chosen", [
+    (128, 9, 192, 74, 125, 0, {"qkv": "128x256L/511", "ffn1": "128x256L/511"}),      # two K tiles
+    (128, 32, 512, 20, 207, 1, {"qkv": "256x256L/408", "ffn1": "192x256L/1364"}),    # bands of row tiles, up to six to a workgroup
+    (128, 12, 512, 20, 205, 0, {"ffn1": "256x256L/408"}),
+    (1024, 12, 256, 99, 93, 0, {"qkv": "192x256L/432", "ffn1": "256x256L/432"}),     # many K tiles
+    (1536, 2, 64, 27, 300, 0, {"o": "128x256L/384", "ffn2": "128x256L/384"}),        # residual rows, two K tiles
+    (2048, 8, 64, 62, 100, 0, {"o": "128x256L/392", "ffn2": "128x256L/392"}),
+    (2048, 7, 64, 60, 151, 0, {"o": "192x256L/384", "ffn2": "192x256L/384"}),        # an odd number of K tiles: stages change places
+])
+def test_mfma_large_tiles_one_after_another(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
+    """More than 256 tiles of every height, with and without residual: a workgroup's second tile begins in stages that were filled
+    during the first one's last K tiles and its epilogue.  All rows against the float32 route, the ends and the middle against
+    the oracle."""
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    assert chosen.items() <= tiles.layer_tiles(gpu[1], dims, B * L, M - n_absent).items()
+    wl = S.small_workload(56000 + d + M, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
+    S.make_every_term_matter(wl, 8, amp=2.0)
+    got = run_gpu(gpu, wl, "mfma")
+    for b in (0, B // 2, B - 1):
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
+        assert_parity(got[b:b + 1], want, TOL["mfma"], b)
+    assert_parity(got, run_gpu(gpu, wl, "f32"), TOL["mfma"])
 
 
 @pytest.mark.parametrize("B,L", [(1, 64), (3, 100)])   # few-token route / working-buffer route
