@@ -6,13 +6,6 @@ namespace sti {
 
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
-__device__ inline void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // NB: room for weight blocks among the arguments (an argument list of 64 blocks costs the host 1.2 us more per launch)
 template <int NB>
 struct FewBlocks {

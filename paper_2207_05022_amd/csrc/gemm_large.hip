@@ -24,38 +24,12 @@
 namespace sti {
 namespace {
 
-constexpr int kComputeUnits = 256;
-constexpr int BK = 64, BN = 256, kWavesN = 4, kWaves = 8;
-constexpr int kGroupRows = 8, kRowMajorColumnTiles = 12;   // tile order, as in gemm_wide.hip
+constexpr int BK = 64, BN = 256, kWaves = 8;
 
 typedef __attribute__((address_space(3))) void lds_ptr;
 
-__device__ inline void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int RA>
 constexpr size_t large_lds_bytes() { return (size_t)2 * (64 * RA + BN) * BK * 2 + kWaves * 4096; }
-
-// how the tiles lie: an XCD has a contiguous range of the tile order (row by row, or by bands of kGroupRows rows), as in gemm_wide.hip
-struct TileOrder {
-    int n_tiles, m_tiles, total, per_xcd;
-    uint32_t band_recip;
-    __device__ inline void locate(int tile, int &tile_m, int &tile_n) const
-    {
-        const int group = n_tiles > kRowMajorColumnTiles ? kGroupRows : 1;
-        const int band = quotient(tile, group * n_tiles, band_recip);
-        const int band_rows = min(group, m_tiles - band * group);   // the last band may be short
-        const int in_band = tile - band * (group * n_tiles);
-        tile_n = in_band;
-        if (band_rows == kGroupRows) tile_n = in_band / kGroupRows;
-        else if (band_rows > 1) tile_n = in_band / band_rows;
-        tile_m = band * group + (in_band - tile_n * band_rows);
-    }
-};
 
 template <int KIND, int RA>
 __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
@@ -77,16 +51,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int g = lane >> 5, lr = lane & 31;
-    TileOrder order;
-    order.n_tiles = (N + BN - 1) / BN;
-    order.m_tiles = (hot_T + BM - 1) / BM;
-    order.total = order.n_tiles * order.m_tiles;
-    order.per_xcd = (order.total + 7) / 8;
-    order.band_recip = hot_band_recip;
+    const int n_tiles = (N + BN - 1) / BN, m_tiles = (hot_T + BM - 1) / BM;
+    const int total = n_tiles * m_tiles, per_xcd = (total + 7) / 8;
     // this workgroup's tiles: first, first + step, ... of its XCD's range
     const int step_tiles = gridDim.x >> 3;
-    const int tile_end = min(((int)(blockIdx.x & 7) + 1) * order.per_xcd, order.total);
-    int tile = (int)(blockIdx.x & 7) * order.per_xcd + (int)(blockIdx.x >> 3);
+    const int tile_end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, total);
+    int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= tile_end) return;
 
     // ---- what this wave brings into LDS per K tile: RA pieces of 8 rows of A (chunks XOR-swizzled by row pair) and the 4 KiB
@@ -97,7 +67,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
     const uint8_t *f_w;
     auto enter_tile = [&]() {
         int tm, tn;
-        order.locate(f_tile, tm, tn);
+        locate_tile(f_tile, n_tiles, m_tiles, hot_band_recip, tm, tn);
         const int m0 = tm * BM, n0 = tn * BN;
         f_A = (const _Float16 *)hot_A + (int64_t)m0 * K;
 #pragma unroll
@@ -231,7 +201,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
         read_fragments(buf, 0, a[0], b[0]);
         for (int kt = 0; kt < nkt - 1; ++kt) tile_step(true);
         int tile_m, tile_n;
-        order.locate(tile, tile_m, tile_n);
+        locate_tile(tile, n_tiles, m_tiles, hot_band_recip, tile_m, tile_n);
         const int m0 = tile_m * BM + wm * WM, nw_real = tile_n * BN + wn * 64;
         const int nw = nw_real < N ? nw_real : 0;   // (results of a wave outside are dropped)
         // Residual rows, whole rows of the wave's 64 columns per request (they reach their lanes through LDS), in front of the last K tile
@@ -328,7 +298,7 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
     if (attr_status != hipSuccess) return attr_status;
     const int n_tiles = (N + BN - 1) / BN, total = n_tiles * ((p.T + 64 * RA - 1) / (64 * RA));
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
-    const uint32_t band_recip = reciprocal((n_tiles > kRowMajorColumnTiles ? kGroupRows : 1) * n_tiles);
+    const uint32_t band_recip = band_reciprocal(n_tiles);
     const uint32_t block_recip = reciprocal(n_split ? p.block_rows / 32 : p.block_cols / BK);
     launch((gemm_large_kernel<KIND, RA>), dim3(std::min((total + 7) / 8 * 8, kComputeUnits)), dim3(kWaves * 64), lds, stream, p.A, blocks.b[0].w, p.resid, p.bias0,
            (int32_t)w_stride, p.T, band_recip, block_recip, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16, (uint32_t)p.n_blocks,

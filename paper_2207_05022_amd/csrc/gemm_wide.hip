@@ -76,9 +76,6 @@ namespace sti {
 namespace {
 
 constexpr int BK = 64;   // K positions per LDS stage
-constexpr int kComputeUnits = 256;
-constexpr int kGroupRows = 8;   // row tiles per band of the tile order ...
-constexpr int kRowMajorColumnTiles = 12;   // ... used beyond this many column tiles
 
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const void global_cptr;
@@ -249,13 +246,6 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     const int half = wave_all / NW, wave = wave_all - half * NW;   // K group, column strip
     const int kt0 = ((int)blockIdx.y * KS + half) * nkt;
     const int g = lane >> 5, lr = lane & 31;
-    // Workgroups are handed to the 8 XCDs round-robin by linear id; give each XCD one
-    // contiguous range of the tile order: row by row up to kRowMajorColumnTiles column tiles;
-    // beyond that (d_model 2048: 22 column tiles) row by row would stream every weight column
-    // through the L2 once per row tile, and the order walks bands of kGroupRows row tiles column
-    // by column instead, so that the workgroups that run together share weight columns too
-    // (measured at d_model 2048, 4096 tokens: 720 -> 617 us per layer; at 8 to 11 column
-    // tiles the two orders measure the same within run-to-run noise).
     const int n_tiles = (N + BN - 1) / BN;
     const int m_tiles = (hot_T + BM - 1) / BM;
     const int total_tiles = n_tiles * m_tiles;
@@ -275,14 +265,8 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         }
     }
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= total_tiles) return;
-    const int group = n_tiles > kRowMajorColumnTiles ? kGroupRows : 1;
-    const int band = quotient(tile, group * n_tiles, hot_band_recip);
-    const int band_rows = min(group, m_tiles - band * group);   // the last band may be short
-    const int in_band = tile - band * (group * n_tiles);
-    int tile_n = in_band;
-    if (band_rows == kGroupRows) tile_n = in_band / kGroupRows;
-    else if (band_rows > 1) tile_n = in_band / band_rows;
-    const int tile_m = band * group + (in_band - tile_n * band_rows);
+    int tile_m, tile_n;
+    locate_tile(tile, n_tiles, m_tiles, hot_band_recip, tile_m, tile_n);
     const int m0 = tile_m * BM;
     // N and the block widths are multiples of 64, so a wave's columns are all inside or all
     // outside the matrix and inside one block; a wave outside recomputes the first columns and its results are
@@ -692,7 +676,7 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
     const int64_t w_stride = p.n_blocks > 1 ? (const uint8_t *)blocks.b[1].w - (const uint8_t *)blocks.b[0].w : 0;
     const ShardIds shard_of = shard_ids(blocks);
     const int n_tiles = (N + BN - 1) / BN;
-    const uint32_t band_recip = reciprocal((n_tiles > kRowMajorColumnTiles ? kGroupRows : 1) * n_tiles);
+    const uint32_t band_recip = band_reciprocal(n_tiles);
     const uint32_t block_recip = reciprocal(n_split ? p.block_rows / 32 : p.block_cols / BK);
     launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
            p.resid, p.bias0, (int32_t)w_stride, p.T, band_recip, block_recip, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,

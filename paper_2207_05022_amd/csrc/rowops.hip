@@ -85,7 +85,8 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 // LPR lanes share one row.  TILED: one of the layouts is; MAXC = 16-byte chunks per lane: d <= 4 * LPR * MAXC; PLANES: partial sums
 // requested together; ROWS: rows per workgroup.
 // Few rows: bound by latency (the launch, one round trip, two sums over the row).  The leading 14 dwords of the arguments arrive preloaded
-// in scalar registers: everything the requests of a row depend on.  shape: n_partials | resid_layout << 8 | y_layout << 16.
+// in scalar registers: everything the requests of a row depend on, but for the distance of the second and later planes of partial sums.
+// shape: n_partials | resid_layout << 8 | y_layout << 16.
 template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>
 __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, const float *bias, const RT *resid, const float *g,
                                                             const float *b, int T, int d, int shape, float eps, int64_t partial_stride,

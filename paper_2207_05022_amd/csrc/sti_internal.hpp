@@ -115,6 +115,14 @@ __device__ inline int quotient(int c, int d, uint32_t recip)   // c >= 0, d > 0
     return (int)(q + ((uint32_t)c - q * (uint32_t)d >= (uint32_t)d ? 1u : 0u));
 }
 
+// between a wave's own writes to LDS and its reads of what other lanes wrote
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroups are handed to the eight XCDs in turn.  Pieces of work that lie behind each other in memory go to one XCD, an eighth of
 // them to each, so that what they share is fetched into one L2.
 __host__ __device__ inline int pieces_per_xcd(int pieces) { return (pieces + 7) >> 3; }
