@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 # bench_config4_config1_hbm_counters.txt, calibrated against a 1 GiB device copy).  Reported
 # only while the kernel sources still hash to the value recorded with the counters.
 TRAFFIC = {
-    "gemm": {"files": ("gemm_wide.hip", "attention_core.hpp", "weight_loader.hpp", "sti_internal.hpp"),
+    "gemm": {"files": ("gemm_wide.hip", "gemm_tile.hpp", "attention_core.hpp", "lane_ops.hpp", "weight_loader.hpp", "sti_internal.hpp"),
              "sha256": "42f4bf9038445700e4994e488bea9015ef472b449affb9c18bedfddbbf57a2cb",
              "bytes_per_launch": 58893411},
     "decode": {"files": ("decode.hip", "weight_loader.hpp", "sti_internal.hpp"),
@@ -418,6 +418,36 @@ def phase_budget_child():
             "us_first_entry_to_last_exit": round(float((b[:, 7].max() - b[:, 6].min()) / 100.0), 2),
             "us_entry_after_first_entry_p90": round(float(np.percentile(b[:, 6] - b[:, 6].min(), 90) / 100.0), 2),
         }
+    # larger launches, which gemm_large_kernel takes: 24 x 384 tokens, d_model 1024, 12 of 16 shards, one layer
+    dims = S.Dims(1024, 16, 64, 256, 1e-12)
+    wl = S.small_workload(24384, dims, 1, 24, 384, n_absent=4, io_dtype="f16")
+    shards, params, x = D.upload_workload(wl)
+    y = torch.empty_like(x)
+    ws = torch.empty(P.sti_workspace_bytes(dims, 24, 384, prec), dtype=torch.uint8, device="cuda")
+    for _ in range(50):
+        P.sti_layer_forward(dims, shards[0], params[0], x, y, prec, ws)
+    torch.cuda.synchronize()
+    buf = np.zeros((4, 3, 256, 8), dtype=np.uint64)
+    P.lib.sti_phase_stamps_read_large.argtypes = [C.c_void_p]
+    rc = P.lib.sti_phase_stamps_read_large(buf.ctypes.data)
+    assert rc == 0, rc
+    for kind, name in {0: "gemm_qkv", 2: "gemm_out", 1: "gemm_ffn_up", 3: "gemm_ffn_down"}.items():
+        for height in range(3):
+            b = buf[kind, height].astype(np.int64)
+            b = b[b[:, 0] != 0]
+            if not len(b):
+                continue
+            wall_us = (b[:, 7] - b[:, 6]) / 100.0
+            out[f"9216 tokens, {name}, {128 + 64 * height} x 256 tiles"] = {
+                "workgroups": int(len(b)), "tiles": int(b[:, 4].sum()), "k_tiles_of_a_tile": int(b[0, 5]),
+                "clocks_to_the_first_stage_median": int(np.median(b[:, 1])),
+                "clocks_per_k_tile_median": int(np.median(b[:, 2] / (b[:, 4] * b[:, 5]))),
+                "products_of_a_k_tile": (2 + height) * 512,
+                "clocks_per_epilogue_median": int(np.median(b[:, 3] / b[:, 4])),
+                "clocks_entry_to_exit_median": int(np.median(b[:, 0])),
+                "clock_ticks_per_us": round(float(np.median(b[:, 0] / np.maximum(wall_us, 1e-9))), 1),
+                "us_first_entry_to_last_exit": round(float((b[:, 7].max() - b[:, 6].min()) / 100.0), 2),
+            }
     print(json.dumps(out))
 
 
@@ -474,7 +504,7 @@ def main():
                     help="also run the ceiling probes: an MFMA-only loop, HBM streams with the read : write mix of "
                          "decompression, and the vendor GEMM library on configuration 4's projection shapes")
     ap.add_argument("--phase-budget", action="store_true",
-                    help="also run configuration 4 on the build whose many-token GEMM kernel records clock stamps "
+                    help="also run configuration 4 and a layer of 9216 tokens on the build whose many-token GEMM kernels record clock stamps "
                          "(libsti_phases.so, in a process of its own) and report the clocks per kernel phase")
     ap.add_argument("--phase-budget-child", action="store_true", help=argparse.SUPPRESS)
     ap.add_argument("--quantize", action="store_true",

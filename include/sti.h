@@ -192,15 +192,17 @@ sti_status sti_layer_forward(const sti_dims *dims, const sti_shard *shards,
 
 /* ---------------------------------------------------------------------------
  * sti_layer_forward for callers that cannot allocate device memory (code under graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same layer, the
- * same kernels and the same results, with the workspace taken from an array that is
- * part of the library's device image instead of from the caller.  The call allocates
+ * capture, tight serving loops, harnesses that forbid hipMalloc): the same layer with the
+ * workspace taken from an array that is part of the library's device image instead of from
+ * the caller; where its buffers lie as usual (below) the same kernels and the same
+ * results, bit for bit, otherwise within the tolerance of the precision.  The call allocates
  * nothing (no device, pinned or pageable memory) and enqueues kernel launches only.
  *
  * The array holds sti_static_scratch_bytes() = 64 MiB on every GPU the library runs on,
  * from the first use of the library on that GPU until the process ends.  A call whose
  * sti_workspace_bytes(dims, batch, seq, precision) is at most that fits, and so do some that would
- * have more, whose buffers then lie more closely; any other call returns STI_ERR_WORKSPACE
+ * have more, whose buffers then lie more closely (few tokens: activations row by row, for which other
+ * attention kernels are there and none that does the output projection, too); any other call returns STI_ERR_WORKSPACE
  * before anything is enqueued (BERT-base dimensions fit 24 x 128 tokens with
  * STI_PREC_F16_MFMA and 8 x 128 with STI_PREC_F32; d_model 1024 with 16 shards fits
  * 14 x 128 and 2 x 128).  All calls on one GPU share the one array:
@@ -482,9 +484,13 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
  * points above carries two events on the caller's stream that take the
  * dispatch's own begin and end time stamps; sti_profile_end() waits for them
  * and returns, per kernel class, the number of launches and the summed kernel
- * time in milliseconds (attention and output projection in one launch, for few
- * tokens: a launch and half the time in either class).  Process wide, not re-entrant; meant for measurement
- * runs, not for production calls (nor for calls under stream capture).
+ * time in milliseconds.  Where one launch does the work of two classes:  Q/K/V
+ * projection and attention (sequences of 128 tokens) count as the projection;
+ * attention and output projection (up to 64 keys) as a launch of either class
+ * with half the time, so that the classes add up to one launch more than was made,
+ * and to the time that was taken; the halves say nothing about the two parts.
+ * Process wide, not re-entrant; meant for measurement runs, not for production
+ * calls (nor for calls under stream capture).
  * ------------------------------------------------------------------------- */
 typedef enum {
     STI_K_DECODE = 0,

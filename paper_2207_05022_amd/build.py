@@ -13,8 +13,8 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsti.so")
 PROBES_SRC = os.path.join(CSRC, "probes", "ceilings.hip")
 PROBES_LIB = os.path.join(HERE, "libsti_probes.so")   # ceiling probes for bench.py --ceilings, not part of libsti
-# libsti with the many-token GEMM kernel compiled to record its phase time stamps (bench.py --phase-budget)
-PHASES_SRC = os.path.join(CSRC, "gemm_wide.hip")
+# libsti with the many-token GEMM kernels compiled to record their phase time stamps (bench.py --phase-budget)
+PHASES_SRCS = [os.path.join(CSRC, name) for name in ("gemm_wide.hip", "gemm_large.hip")]
 PHASES_LIB = os.path.join(HERE, "libsti_phases.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -33,9 +33,9 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + ".o")
-    subprocess.run([HIPCC, *FLAGS, "-c", src, "-o", obj], check=True,
+def _compile(src: str, stamped: bool = False) -> str:
+    obj = os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + ("_phases.o" if stamped else ".o"))
+    subprocess.run([HIPCC, *FLAGS, *(["-DSTI_PHASE_STAMPS"] if stamped else []), "-c", src, "-o", obj], check=True,
                    stderr=subprocess.PIPE, text=True)
     return obj
 
@@ -50,12 +50,9 @@ def build(verbose: bool = False) -> str:
                        check=True, stderr=subprocess.PIPE, text=True)
         subprocess.run([HIPCC, *FLAGS, "-shared", PROBES_SRC, "-o", PROBES_LIB],
                        check=True, stderr=subprocess.PIPE, text=True)
-        stamped = os.path.join(OBJ_DIR, "gemm_wide_phases.o")
-        subprocess.run([HIPCC, *FLAGS, "-DSTI_PHASE_STAMPS", "-c", PHASES_SRC, "-o", stamped],
-                       check=True, stderr=subprocess.PIPE, text=True)
-        plain = os.path.join(OBJ_DIR, "gemm_wide.o")
+        stamped = {src: _compile(src, stamped=True) for src in PHASES_SRCS}
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", PHASES_LIB,
-                        *[stamped if o == plain else o for o in objs]],
+                        *[stamped.get(src, obj) for src, obj in zip(srcs, objs)]],
                        check=True, stderr=subprocess.PIPE, text=True)
     except subprocess.CalledProcessError as err:
         raise RuntimeError(f"hipcc failed: {' '.join(err.cmd)}\n{err.stderr}") from None

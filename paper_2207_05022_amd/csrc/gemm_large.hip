@@ -4,22 +4,43 @@
 //
 // in tiles of 64 RA rows x 256 columns (RA = 2, 3 or 4), one workgroup of eight waves per compute unit that goes from tile to tile.
 //
-// What bounds it: the power the chip may draw.  9216 tokens, K = 1024, 256 x 256 tiles: a K tile of 64 takes 2240 clocks, 2048 of them
-// products, at 1.58 GHz on all 256 units; at 2.1 GHz where 144 of them have a tile.  What costs power or leaves the matrix cores idle:
+// What bounds it: the matrix cores at the rate that the chip's power leaves them, and the epilogue, beside which they are idle.  9216 tokens,
+// 12 shards of d_model 1024, clocks of wave 0 (libsti_phases.so): FFN1, 256 x 256 tiles, 2530 per K tile of 64, 2048 of them products, at
+// 1.80 GHz; Q/K/V, 192 x 256, 2030 and 1536; O and FFN2 on 192 of the 256 units 2450 and 2160 and 1536, at 2.0 GHz.  An epilogue takes
+// 11600 with GELU, 3600 for Q/K/V, 5200 to 5400 with residual rows.  What costs power or leaves the matrix cores idle:
 //   - bytes: both operands go through LDS (an A row is read by four waves, a weight by two), so that a unit asks for 64 KiB per K tile
 //     and 256 x 256 outputs - the kernel with weights straight into registers (gemm_wide.hip) asks for 96;
 //   - requests in a burst: 64 KiB keep the unit's address path busy for 1024 clocks, and a wave whose request has to wait does not issue
 //     its products either.  Requests for A go out among the products of a K tile's last step, those for weights among the first
-//     step's of the next one (all in the last step: 2490 clocks per K tile), LDS reads one by one among the products, too (2650 with all
-//     of a step's reads in front of them);
+//     step's of the next one (all in the last step: a tenth more clocks per K tile), LDS reads one by one among the products, too (with all
+//     of a step's reads in front of them a fifth more);
 //   - start and end of a tile: a workgroup asks for the next tile's first two stages during the last two K tiles of this one.  The
-//     epilogue is each wave's own (4 KiB of LDS, no barrier; 3 to 5 thousand clocks, GELU 12), the residual rows asked for in front of
-//     the last K tile.
+//     epilogue is each wave's own (4 KiB of LDS, no barrier), the residual rows asked for in front of the last K tile.
 // Launches, us, this kernel against gemm_wide.hip before it (which held 128 x 256 tiles of four waves): see the table of shapes there.
 #include <algorithm>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
 #include "gemm_tile.hpp"
+
+// STI_PHASE_STAMPS (libsti_phases.so only, as in gemm_wide.hip): clocks of wave 0 of every workgroup, summed over its tiles, kept in scalar
+// registers and written once at its exit.
+#ifdef STI_PHASE_STAMPS
+namespace {
+constexpr int kStampKinds = 4, kStampHeights = 3, kStampSlots = 256, kStampWords = 8;
+__device__ unsigned long long sti_large_phase_stamps[kStampKinds * kStampHeights * kStampSlots * kStampWords];
+}
+// out: [kind][64-row blocks - 2][workgroup][8] = clocks from entry to exit, to the first stage, in K loops, in epilogues; tiles; K tiles of a
+// tile; wall clock (100 MHz) at entry and exit (0 = slot unused)
+extern "C" int sti_phase_stamps_read_large(unsigned long long *out)
+{
+    return (int)hipMemcpyFromSymbol(out, HIP_SYMBOL(sti_large_phase_stamps), sizeof(sti_large_phase_stamps));
+}
+#define STI_CLOCK(name) const unsigned long long name = __builtin_amdgcn_s_memtime()
+#define STI_STAMPED(...) __VA_ARGS__
+#else
+#define STI_CLOCK(name)
+#define STI_STAMPED(...)
+#endif
 
 namespace sti {
 namespace {
@@ -38,6 +59,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
     uint32_t hot_band_recip, uint32_t hot_block_recip, uint32_t hot_block_shape, uint32_t hot_n_blocks,
     void *C_out, int32_t ldc, const float *bias1, const float *bias2, ShardIds shard_of)
 {
+    STI_CLOCK(entry);
+    STI_STAMPED(const unsigned long long wall_entry = wall_clock64(); unsigned long long in_loops = 0, in_epilogues = 0; int tiles_done = 0);
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP);
     constexpr int BM = 64 * RA, WM = 32 * RA;
     constexpr int A_BYTES = BM * BK * 2, STAGE = A_BYTES + BN * BK * 2;
@@ -188,6 +211,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
     asm volatile("" ::: "memory");
     STI_FENCE();
 
+    STI_CLOCK(first_stage);
     unsigned char *mine = smem_raw + 2 * STAGE + wave * 4096;   // 32 x 64 outputs on their way to whole rows
     _Float16 *C = (_Float16 *)C_out;
     const _Float16 *R = (const _Float16 *)hot_resid;
@@ -198,6 +222,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
             for (int r = 0; r < 2; ++r)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][r][v] = 0.f;
+        STI_CLOCK(loop_begin);
         read_fragments(buf, 0, a[0], b[0]);
         for (int kt = 0; kt < nkt - 1; ++kt) tile_step(true);
         int tile_m, tile_n;
@@ -217,6 +242,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
             STI_FENCE();
         }
         tile_step(false);
+        STI_CLOCK(loop_end);
 
         // ---- epilogue, wave by wave: the first two stages of the next tile are on their way ----
         f32x4 bias[2][2][2];
@@ -285,7 +311,17 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
             }
             wave_lds_fence();
         }
+        STI_CLOCK(tile_done);
+        STI_STAMPED(in_loops += loop_end - loop_begin; in_epilogues += tile_done - loop_end; ++tiles_done);
     }
+#ifdef STI_PHASE_STAMPS
+    const unsigned long long leaving = __builtin_amdgcn_s_memtime();
+    if (tid == 0 && blockIdx.x < (unsigned)kStampSlots) {
+        unsigned long long *o = sti_large_phase_stamps + (((size_t)KIND * kStampHeights + RA - 2) * kStampSlots + blockIdx.x) * kStampWords;
+        o[0] = leaving - entry; o[1] = first_stage - entry; o[2] = in_loops; o[3] = in_epilogues;
+        o[4] = tiles_done; o[5] = nkt; o[6] = wall_entry; o[7] = wall_clock64();
+    }
+#endif
 }
 
 template <int KIND, int RA>
