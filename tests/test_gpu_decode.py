@@ -122,6 +122,19 @@ def test_outlier_dictionary(gpu, oracle_mod, dtype):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("n_shards", [1, 4, 5, 16, 17, 64])
+@pytest.mark.parametrize("dtype,n,count", [("f16", 1000, 3), ("f32", 8193, 40), ("bf16", 6000, 4097)])
+def test_shard_tables_of_every_length_among_the_arguments(gpu, oracle_mod, n_shards, dtype, n, count):
+    """Room for 4, 16 or 64 shards among a kernel's arguments; one and several workgroups per shard, dictionaries put in by the decoding
+    launch and by one of their own."""
+    rng = np.random.default_rng(n_shards * 100 + count)
+    shards = [S.make_shard(rng, n, (2, 3, 4, 5, 6, 32)[i % 6]) for i in range(n_shards)]
+    for s in (shards[0], shards[-1]):
+        if s.bitwidth != 32:
+            S.add_outliers(rng, s, n, fraction=count / n)
+    assert np.array_equal(run_decode(gpu, shards, n, dtype), oracle_bits(oracle_mod, shards, n, dtype))
+
+
 @pytest.mark.parametrize("dtype", ["f16", "f32", "bf16"])
 @pytest.mark.parametrize("n,count", [(8192, 40), (8193, 41), (4096 * 3 - 1, 4096), (4096 * 3 + 5, 4097), (1024 * 9 + 3, 300)])
 def test_stretches_and_dictionaries_end_anywhere(gpu, oracle_mod, dtype, n, count):
