@@ -28,6 +28,7 @@
 // heads' attention itself (kind GEMM_QKV_ATTN): no Q/K/V buffer in memory and no attention launch.
 #include <algorithm>
 #include <math.h>
+#include <type_traits>
 #include "sti_internal.hpp"
 #include "weight_loader.hpp"
 #include "gemm_tile.hpp"
@@ -76,6 +77,10 @@ namespace sti {
 namespace {
 
 constexpr int BK = 64;   // K positions per LDS stage
+
+// At most N of the loads of this wave still on their way
+template <int N>
+__device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const void global_cptr;
@@ -300,17 +305,16 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     }
     // The loads of the K loop are written as instructions rather than through the compiler:
     // its own bookkeeping would wait for every outstanding fetch into LDS before the next LDS
-    // read, which is exactly the overlap this loop is built for.  The waits are in step().
+    // read, which is exactly the overlap this loop is built for.  The waits are in k_loop().
     const uint32_t lds_base = (uint32_t)(size_t)(lds_ptr *)smem_raw;
-    auto fetch_a = [&](int kt, int buf) {
+    auto fetch_a = [&](int kt, int buf, auto fetches) {   // (fetches: those of this wave)
 #pragma unroll
-        for (int j = 0; j < FPW; ++j) {
-            if (wave + NW * j < FETCHES) {
-                const _Float16 *gp = A + (kt0 + kt) * BK;   // scalar base, per-lane 32-bit offset
-                const uint32_t dst = lds_base + (uint32_t)(((half * STAGES + buf) * STAGE + (wave + NW * j) * 8 * BK) * 2);
-                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                             :: "v"(src[j]), "s"(gp), "s"(dst) : "memory", "m0");
-            }
+        for (int j = 0; j < decltype(fetches)::value; ++j) {
+            const _Float16 *gp = A + (kt0 + kt) * BK;   // scalar base, per-lane 32-bit offset
+            const uint32_t at = src[j];
+            const uint32_t dst = lds_base + (uint32_t)(((half * STAGES + buf) * STAGE + (wave + NW * j) * 8 * BK) * 2);
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                         :: "v"(at), "s"(gp), "s"(dst) : "memory", "m0");
         }
     };
     // byte offset of this lane's fragment of k-step s inside row block 0 of a stage
@@ -339,11 +343,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // shapes are faster with the issue at the top).  The wait in front of the barrier is
     // written by hand: it lets the loads of tile t+1, the last ones issued, stay in flight.
     u32x4 bw[STAGES][4];
-    int n_fetch = 0;   // A fetches this wave issues per stage
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) n_fetch += (wave + NW * j < FETCHES) ? 1 : 0;
-    auto issue = [&](int kt, u32x4 (&dst)[4]) {
-        fetch_a(kt, kt % STAGES);
+    auto fetch_w = [&](int kt, u32x4 (&dst)[4]) {
         const uint8_t *q = frag_ptr(kt);
         asm volatile("global_load_dwordx4 %0, %4, %5\n\t"
                      "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
@@ -351,7 +351,6 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                      "global_load_dwordx4 %3, %4, %5 offset:3072"
                      : "=&v"(dst[0]), "=&v"(dst[1]), "=&v"(dst[2]), "=&v"(dst[3]) : "v"(lane16), "s"(q) : "memory");
     };
-#define STI_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
     // EARLY (64-row tiles of the d_model-wide projections, K not split over workgroups): what
     // the epilogue adds (bias and residual rows) is asked for before the K loop: asked for in
     // the epilogue, these loads cost a whole round trip (3-4 thousand clocks of a 20-50 thousand
@@ -388,60 +387,76 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             }
         }
     };
-    auto step = [&](int kt, u32x4 (&bcur)[4], u32x4 (&bnew)[4]) {
-        constexpr int AHEAD = STAGES - 1;   // K tiles in flight
-        // the weight fragments and the A stage of tile kt have landed (the barrier below is a
-        // scheduling boundary: no MFMA of this step is placed above the wait) ...
-        if (kt + 1 < nkt) {
-            if (n_fetch == 2) STI_WAIT_LOADS(6);
-            else if (n_fetch == 1) STI_WAIT_LOADS(5);
-            else STI_WAIT_LOADS(4);
-        } else {
-            STI_WAIT_LOADS(0);
-        }
-        // ... for every wave, and every wave is done reading the stage that is refilled next
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+    // fetches: A fetches this wave issues per stage.  Rounds of three K tiles whose loads all exist run without a branch: every taken
+    // one holds up all waves of the workgroup behind the same barrier, and with a condition around each load and wait there were about
+    // ten per K tile.  Clocks of a K loop before and now: 128 x 384 tiles, 12 K tiles, 22350 / 20800; 64 x 192, 12 K tiles, 10370 / 8370;
+    // K shared by two groups, 24 K tiles each, 34000 / 30600.  Power takes part of it back (1.88 -> 1.81 GHz): 4096 tokens, 12 layers
+    // 1155 -> 1133 us, 12 x 384 tokens of d_model 1024, 6 layers, 1140 -> 1112.
+    auto k_loop = [&](auto fetches) {
+        constexpr int PER_TILE = decltype(fetches)::value + 4;   // loads of a K tile
+        auto issue = [&](int kt, int buf, u32x4 (&dst)[4]) {
+            fetch_a(kt, buf, fetches);
+            fetch_w(kt, dst);
+        };
+        auto step = [&](int kt, int buf, u32x4 (&bcur)[4], u32x4 (&bnew)[4], auto whole) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            const bool more = WHOLE || kt + STAGES - 1 < nkt;
+            const int next = buf == 0 ? STAGES - 1 : buf - 1;
+            // the weight fragments and the A stage of tile kt have landed (the barrier below is a
+            // scheduling boundary: no MFMA of this step is placed above the wait) ...
+            if (WHOLE || kt + 1 < nkt) wait_loads<PER_TILE>();
+            else wait_loads<0>();
+            // ... for every wave, and every wave is done reading the stage that is refilled next
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
 #ifdef STI_PHASE_STAMPS
-        if (kt == 0) STI_STAMP(2);
+            if (kt == 0) STI_STAMP(2);
 #endif
-        if (KS == 2 && kt + AHEAD < nkt) issue(kt + AHEAD, bnew);
-        const unsigned char *stage = smem_raw + (half * STAGES + kt % STAGES) * (STAGE * 2);
-        half8 a_cur[RA], a_nxt[RA];
+            if (KS == 2 && more) issue(kt + STAGES - 1, next, bnew);
+            const unsigned char *stage = smem_raw + (half * STAGES + buf) * (STAGE * 2);
+            half8 a_cur[RA], a_nxt[RA];
 #pragma unroll
-        for (int i = 0; i < RA; ++i) a_cur[i] = *(const half8 *)(stage + i * (32 * BK * 2) + frag_off[0]);
+            for (int i = 0; i < RA; ++i) a_cur[i] = *(const half8 *)(stage + i * (32 * BK * 2) + frag_off[0]);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if (s < 3) {
+            for (int s = 0; s < 4; ++s) {
+                if (s < 3) {
+#pragma unroll
+                    for (int i = 0; i < RA; ++i)
+                        a_nxt[i] = *(const half8 *)(stage + i * (32 * BK * 2) + frag_off[s + 1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int i = 0; i < RA; ++i)
-                    a_nxt[i] = *(const half8 *)(stage + i * (32 * BK * 2) + frag_off[s + 1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[s]), a_cur[i], acc[i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (KS == 1 && s == 0 && more) issue(kt + STAGES - 1, next, bnew);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s < 3) {
 #pragma unroll
-            for (int i = 0; i < RA; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bcur[s]), a_cur[i], acc[i], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (KS == 1 && s == 0 && kt + AHEAD < nkt) issue(kt + AHEAD, bnew);
-            __builtin_amdgcn_sched_barrier(0);
-            if (s < 3) {
-#pragma unroll
-                for (int i = 0; i < RA; ++i) a_cur[i] = a_nxt[i];
+                    for (int i = 0; i < RA; ++i) a_cur[i] = a_nxt[i];
+                }
             }
+        };
+        if (nkt > 0) issue(0, 0, bw[0]);
+        if (nkt > 1) issue(1, 1, bw[1]);
+        STI_STAMP(1);
+        int kt = 0;
+        for (; kt + 4 < nkt; kt += 3) {
+            step(kt, 0, bw[0], bw[2], std::true_type{});
+            step(kt + 1, 1, bw[1], bw[0], std::true_type{});
+            step(kt + 2, 2, bw[2], bw[1], std::true_type{});
+        }
+        for (; kt < nkt; kt += 3) {
+            step(kt, 0, bw[0], bw[2], std::false_type{});
+            if (kt + 1 < nkt) step(kt + 1, 1, bw[1], bw[0], std::false_type{});
+            if (kt + 2 < nkt) step(kt + 2, 2, bw[2], bw[1], std::false_type{});
         }
     };
     static_assert(FPW <= 2, "the hand-written waits cover up to two A fetches per wave");
     if (PRE && half == 0) load_epilogue_operands();
-    if (nkt > 0) issue(0, bw[0]);
-    if (nkt > 1) issue(1, bw[1]);
-    STI_STAMP(1);
-    for (int kt = 0; kt < nkt; kt += 3) {
-        step(kt, bw[0], bw[2]);
-        if (kt + 1 < nkt) step(kt + 1, bw[1], bw[0]);
-        if (kt + 2 < nkt) step(kt + 2, bw[2], bw[1]);
-    }
-#undef STI_WAIT_LOADS
+    if (FETCHES % NW == 0 || wave < FETCHES % NW) k_loop(std::integral_constant<int, FPW>{});
+    else k_loop(std::integral_constant<int, FPW - 1>{});
     STI_STAMP(3);
 
     // ---- epilogue ----

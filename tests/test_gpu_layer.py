@@ -932,6 +932,24 @@ def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
         assert_parity(got[b:b + 1], want, TOL["mfma"], b)
 
 
+@pytest.mark.parametrize("k_tiles", range(1, 10))
+def test_mfma_k_tiles_in_and_out_of_whole_rounds(gpu, oracle_mod, k_tiles):
+    """K loops of one to nine K tiles (rounds of three whose loads all exist, then the rest): 64-row tiles with unsplit K (Q/K/V and
+    FFN1) and with K shared by two groups of waves (O and FFN2), Q/K/V tiles of whole sequences, and tiles of 192 rows."""
+    for M, B, L, chosen in ((k_tiles + 1, 11, 100, {"qkv": "64x192", "ffn1": "64x192", "ffn2": "64x192*" if k_tiles % 2 and k_tiles > 1 else "64x192"}),
+                            (8, 32, 128, None), (32, 17, 100, {"qkv": "192x256L"} if k_tiles > 1 else None)):
+        dims = S.Dims(64 * k_tiles, M, 64, 64, 1e-12)
+        have = tiles.layer_tiles(gpu[1], dims, B * L, M)
+        assert chosen is None or all(have[name].split("/")[0] == shape for name, shape in chosen.items()), have
+        wl = S.small_workload(58000 + 10 * k_tiles + B, dims, 1, B, L, io_dtype="f16")
+        S.make_every_term_matter(wl, 8, amp=2.0)
+        got = run_gpu(gpu, wl, "mfma")
+        assert np.all(np.isfinite(got))
+        for b in (0, B // 2, B - 1):
+            want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
+            assert_parity(got[b:b + 1], want, TOL["mfma"], (M, b))
+
+
 @pytest.mark.parametrize("d,M,f,B,L,n_absent,chosen", [
     (128, 9, 192, 74, 125, 0, {"qkv": "128x256L/511", "ffn1": "128x256L/511"}),      # two K tiles
     (128, 32, 512, 20, 207, 1, {"qkv": "256x256L/408", "ffn1": "192x256L/1364"}),    # bands of row tiles, up to six to a workgroup
