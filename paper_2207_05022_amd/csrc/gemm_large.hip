@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     float y = x[e] + bias[r][q][e >> 2][e & 3];
-                    if constexpr (KIND == GEMM_FFN_UP) y = gelu_polynomial(y);
+                    if constexpr (KIND == GEMM_FFN_UP) y = gelu_wide(y);
                     if constexpr (!n_split) y += (float)res[e];
                     o[e] = (_Float16)y;
                 }

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float y = x[e] + bias[q][e >> 2][e & 3];
-                if constexpr (KIND == GEMM_FFN_UP) y = gelu_polynomial(y);
+                if constexpr (KIND == GEMM_FFN_UP) y = gelu_wide(y);
                 if constexpr (!n_split) y += (float)res[q][e];
                 o[e] = (_Float16)y;
             }
