@@ -482,7 +482,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded, const int32_t *key_lengths, const NextLayerDecode *next,
-                     ActLayout in_layout, ActLayout out_layout, bool planes_out)
+                     ActLayout in_layout, ActLayout out_layout, bool planes_out, SplitChain *chain)
 {
     const int dm = d.d_model, M = d.n_heads, dh = d.d_head, f = d.ffn_per_shard;
     const int T = B * Lseq;
@@ -519,16 +519,17 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode_tiled(t, m, dm, dh, f, ws + wl.w16, stream); }));
         STI_TRY(launch_patch_outliers_tiled(t, m, max_outliers, dm, dh, f, ws + wl.w16, stream));
     }
+    const bool ready = chain && chain->ready;
+    if (chain) chain->ready = false;
+    InlineShardTable t32;   // float32: this layer's shards
     if (f32 && m > 0) {
-        InlineShardTable t;
-        memset(&t, 0, sizeof(t));
-        for (int p = 0; p < m; ++p) {
-            const sti_shard &s = shards[present[p]];
-            t.d[p] = make_desc(s, present[p]);
-        }
+        memset(&t32, 0, sizeof(t32));
+        for (int p = 0; p < m; ++p) t32.d[p] = make_desc(shards[present[p]], present[p]);
+    }
+    if (f32 && m > 0 && !(split && ready)) {
         STI_TRY(timed(STI_K_DECODE, stream, [&] {
-            return split ? launch_decode_split(t, m, dm, dh, f, false, ws + wl.w32, stream)
-                         : launch_decode(nullptr, &t, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream);
+            return split ? launch_decode_split(t32, m, dm, dh, f, false, ws + wl.w32, stream)
+                         : launch_decode(nullptr, &t32, m, max_outliers, wsh, ws + wl.w32, STI_F32, stream);
         }));
     }
     for (int p = 0; p < m; ++p) {
@@ -605,13 +606,13 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     };
     // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM
     auto layernorm = [&](void *dst, sti_dtype dt, ActLayout dst_layout, const float *g, const float *b,
-                         const float *bias, const void *resid, ActLayout resid_layout, void *planes) {
+                         const float *bias, const void *resid, ActLayout resid_layout, void *planes, const SplitRide *ride = nullptr) {
         return timed(STI_K_LAYERNORM, stream, [&] {
             if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
             return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32 || resid_layout == LAYOUT_ROWS_F32, resid_layout, dst, dt, dst_layout,
-                                    g, b, T, dm, d.ln_eps, stream, planes);
-        });
+                                    g, b, T, dm, d.ln_eps, stream, planes, ride);
+        }, ride ? STI_K_DECODE : -1);
     };
 
     // few tokens: activations inside the layer are tiled, Q/K/V too where the few-token attention takes them
@@ -673,13 +674,9 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     } else {
         STI_TRY(gemm(p, bo));
     }
-    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, split && m > 0 ? ws + wl.s_h : nullptr));
-    if (split && m > 0) {
-        InlineShardTable t;
-        memset(&t, 0, sizeof(t));
-        for (int p = 0; p < m; ++p) t.d[p] = make_desc(shards[present[p]], present[p]);
-        STI_TRY(timed(STI_K_DECODE, stream, [&] { return launch_decode_split(t, m, dm, dh, f, true, ws + wl.w32, stream); }));
-    }
+    const SplitRide ffn_weights = {&t32, m, dh, f, true, ws + wl.w32};   // (over Q, K, V and O, which are read by then)
+    const bool ffn_rides = split && m > 0;
+    STI_TRY(layernorm(h, act_dtype, inner, prm.ln1_g, prm.ln1_b, prm.bo, in, in_layout, ffn_rides ? ws + wl.s_h : nullptr, ffn_rides ? &ffn_weights : nullptr));
     if (m > 0) {
         memset(&p, 0, sizeof(p));
         p.a_layout = inner; p.c_layout = inner;
@@ -700,7 +697,20 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.ldr = dm;
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
-    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && planes_out ? ws + wl.s_in : nullptr));
+    // the next layer's Q, K, V and O go where FFN2 and, behind it, FFN1 were: not over sums that LayerNorm reads from there
+    SplitRide next_weights = {&t32, 0, dh, f, false, ws + wl.w32};
+    if (split && planes_out && chain && chain->next) {
+        int m_next = 0;
+        memset(&t32, 0, sizeof(t32));
+        for (int i = 0; i < M; ++i)
+            if (chain->next[i].bitwidth != 0) t32.d[m_next++] = make_desc(chain->next[i], i);
+        const uint8_t *begin = ws + wl.w32, *end = begin + (size_t)m_next * off_1 * 6, *sums = (const uint8_t *)pre;
+        if (pre_partials == 0 || sums >= end || sums + (size_t)pre_partials * partial_stride * 4 <= begin) next_weights.n_shards = m_next;
+    }
+    const bool next_rides = next_weights.n_shards > 0;
+    STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && planes_out ? ws + wl.s_in : nullptr,
+                      next_rides ? &next_weights : nullptr));
+    if (chain) chain->ready = next_rides;
     if (!split && planes_out)   // (the buffers of such a layer lie otherwise: its rows cannot go there before it has ended)
         STI_TRY(timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)out, ws + wl.s_in, T, dm, stream); }));
     return STI_OK;
@@ -1177,6 +1187,7 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
     st = bring_in(*dims, chosen.data(), x, io_dtype, T, precision, ws, wl, stream, &cur, &cur_layout, &in_buffer);
     if (st != STI_OK) return st;
     int next_buf = in_buffer ? 1 : 0;
+    SplitChain chain = {nullptr, false};
     int decoded_upto = 0;   // layers [0, decoded_upto) have their working buffers (as far as the stream is concerned)
     for (int l = 0; l < n_layers; ++l) {
         const bool last = (l == n_layers - 1);
@@ -1200,10 +1211,12 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
             }
         }
         const void *predecoded = whole_model_fits ? (const void *)w16_of(l) : nullptr;
+        const bool planes_out = !last && takes_planes(*dims, &chosen[(size_t)(l + 1) * M], T, wl);
+        chain.next = planes_out ? &chosen[(size_t)(l + 1) * M] : nullptr;
         st = run_layer(*dims, &chosen[(size_t)l * M], params[l], cur, out, last ? io_dtype : act,
                        batch, seq, precision, ws, wl, stream, predecoded, masked ? key_lengths : nullptr,
                        next_decode.workgroups > 0 ? &next_decode : nullptr, cur_layout, last ? LAYOUT_ROWS : inner,
-                       !last && takes_planes(*dims, &chosen[(size_t)(l + 1) * M], T, wl));
+                       planes_out, &chain);
         if (st != STI_OK) return st;
         if (next_decode.workgroups > 0 && next_decode.max_outliers == 0) {
             st = patch_layer(l + 1);

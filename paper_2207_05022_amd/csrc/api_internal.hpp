@@ -63,12 +63,19 @@ int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_nex
 // Whether a layer over these shards goes through the bfloat16 matrix cores in three planes per float32 (gemm_f32_split.hip).
 bool takes_planes(const sti_dims &d, const sti_shard *shards, int64_t T, const WorkspaceLayout &wl);
 
+// Layers one after another whose weights become planes (takes_planes): the Q, K, V and O of the next one can be decompressed beside a layer's last
+// LayerNorm.
+struct SplitChain {
+    const sti_shard *next;   // shards of the layer behind this one, which takes planes; or null
+    bool ready;              // on entry: this layer's are there; on return: the next one's are
+};
+
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
                      const void *predecoded = nullptr, const int32_t *key_lengths = nullptr,
                      const NextLayerDecode *next = nullptr, ActLayout in_layout = LAYOUT_ROWS,
-                     ActLayout out_layout = LAYOUT_ROWS, bool planes_out = false);
+                     ActLayout out_layout = LAYOUT_ROWS, bool planes_out = false, SplitChain *chain = nullptr);
 // The caller's x as the first layer takes it: itself where it already has the type (and, few tokens, row by row),
 // otherwise converted into the first activation buffer (in_buffer: whether it is there); few tokens: float32 rows as they are, where the
 // Q/K/V projection takes them.  As planes, too, where that layer takes them.

@@ -5,6 +5,7 @@
 #include "sti_internal.hpp"
 #include "lane_ops.hpp"
 #include "split_planes.hpp"
+#include "split_decode.hpp"
 
 namespace sti {
 namespace {
@@ -94,7 +95,7 @@ __device__ inline float row_quotient(float sum, double inv_d) { return (float)((
 // in scalar registers: everything the requests of a row depend on, but for the distance of the second and later planes of partial sums.
 // shape: n_partials | resid_layout << 8 | y_layout << 16.
 template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>
-__global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, const float *bias, const RT *resid, const float *g,
+__device__ __forceinline__ void layernorm_rows(const float *pre, const float *bias, const RT *resid, const float *g,
                                                             const float *b, int T, int d, int shape, float eps, int64_t partial_stride,
                                                             typename Elem<DT>::type *y, uint16_t *planes, double inv_d)
 {
@@ -193,6 +194,29 @@ __global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *
         }
     }
 }
+template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>
+__global__ __launch_bounds__(LPR * ROWS) void layernorm_vec_kernel(const float *pre, const float *bias, const RT *resid, const float *g,
+                                                            const float *b, int T, int d, int shape, float eps, int64_t partial_stride,
+                                                            typename Elem<DT>::type *y, uint16_t *planes, double inv_d)
+{
+    layernorm_rows<DT, RT, TILED, LPR, MAXC, PLANES, ROWS>(pre, bias, resid, g, b, T, d, shape, eps, partial_stride, y, planes, inv_d);
+}
+
+// The same with planes (float32 layers on the bfloat16 matrix cores) and, in the workgroups behind those of the rows, the decompression of
+// the weights that the launches to come multiply with: FFN1 and FFN2 beside the first LayerNorm of a layer, the next layer's Q, K, V and O beside
+// the second.  LayerNorm waits for its rows while the decompression writes.  8 x 128 tokens of BERT-base, 12 layers: 1723 -> 1627 us, 4 x 128
+// tokens 1262 -> 1172.
+template <int MAXC, int PLANES, typename Table>
+__global__ __launch_bounds__(256) void layernorm_decode_kernel(const float *pre, const float *bias, const float *resid, const float *g, const float *b, int T, int d,
+                                                              int shape, float eps, int64_t partial_stride, float *y, uint16_t *planes, double inv_d,
+                                                              SplitDecodeJob job, Table tab)
+{
+    __shared__ u32x2 lut[4][kLutEntries];
+    const int ahead = (T + 3) / 4;
+    if ((int)blockIdx.x < ahead) layernorm_rows<STI_F32, float, false, 64, MAXC, PLANES, 4>(pre, bias, resid, g, b, T, d, shape, eps, partial_stride, y, planes, inv_d);
+    else decode_split_block(job, tab, (int)blockIdx.x - ahead, lut);
+}
+
 
 // LayerNorm of rows that already hold sum + bias + residual in binary16 (written by the
 // matrix-core GEMM); d a multiple of 8 and at most 8 * LPR * MAXC; LPR lanes per row.  All
@@ -332,7 +356,7 @@ hipError_t convert_from(const void *src, void *dst, sti_dtype dst_dtype, uint64_
 template <int DT, typename RT, bool TILED>
 void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, const float *bias,
                      const void *resid, ActLayout resid_layout, ActLayout y_layout, void *y, const float *g, const float *b,
-                     int T, int d, float eps, bool vec, hipStream_t stream, uint16_t *planes)
+                     int T, int d, float eps, bool vec, hipStream_t stream, uint16_t *planes, const SplitRide *ride)
 {
     typedef typename Elem<DT>::type O;
 #define STI_LN_PLANES(LPR, MAXC, PLANES, ROWS) \
@@ -354,6 +378,25 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
         }
     } else if (vec && planes) {
         if constexpr (DT == STI_F32 && std::is_same<RT, float>::value) {
+            SplitDecodeJob job;
+            if (ride && split_decode_job(ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, &job)) {
+                with_inline_table(*ride->table, ride->n_shards, [&](auto t) {
+#define STI_LN_RIDE(MAXC, PLANES) \
+    launch((layernorm_decode_kernel<MAXC, PLANES, decltype(t)>), dim3((uint32_t)((T + 3) / 4 + (job.cells + 3) / 4)), dim3(256), 0, stream, pre, bias, (const float *)resid, g, b, \
+           T, d, n_partials | (int)resid_layout << 8 | (int)y_layout << 16, eps, partial_stride, (float *)y, planes, 1.0 / d, job, t)
+#define STI_LN_RIDES(MAXC)                              \
+    do {                                                \
+        if (n_partials <= 1) STI_LN_RIDE(MAXC, 1);      \
+        else if (n_partials == 2) STI_LN_RIDE(MAXC, 2); \
+        else STI_LN_RIDE(MAXC, 4);                      \
+    } while (0)
+                    if (d <= 768) STI_LN_RIDES(3);
+                    else STI_LN_RIDES(4);
+#undef STI_LN_RIDES
+#undef STI_LN_RIDE
+                });
+                return;
+            }
             if (d <= 768) STI_LN_VEC(64, 3, 4);
             else if (d <= 1024) STI_LN_VEC(64, 4, 4);
             else STI_LN_VEC(64, 8, 4);
@@ -373,32 +416,40 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
-                            hipStream_t stream, void *planes)
+                            hipStream_t stream, void *planes, const SplitRide *ride)
 {
     if (T <= 0 || d <= 0) return hipSuccess;
     if (planes && (d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
+    SplitDecodeJob job;
+    if (ride && (!planes || !split_decode_job(ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, &job))) return hipErrorInvalidValue;
     if (n_partials < 0 || n_partials > 255 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
     if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || (resid_f32 && (resid_layout == LAYOUT_TILED || out_dtype != STI_F16))))
         return hipErrorInvalidValue;
     auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
     const bool vec = d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) &&
                      (!bias || al16(bias)) && (!resid || al16(resid));
+    const bool together = ride && vec && d <= 1024 && job.cells > 0;   // (longer rows: registers for one workgroup of four waves per unit)
     auto go = [&](auto resid_type, auto tiled) {
         typedef decltype(resid_type) RT;
         constexpr bool TL = decltype(tiled)::value;
         switch (out_dtype) {
-            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
-            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
-            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes); break;
+            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
+            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
+            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
         }
     };
     if (resid_f32 && y_layout == LAYOUT_TILED)
-        launch_ln_typed<STI_F16, float, true>(pre, n_partials, partial_stride, bias, resid, LAYOUT_ROWS, y_layout, y, g, b, T, d, eps, vec, stream, nullptr);
+        launch_ln_typed<STI_F16, float, true>(pre, n_partials, partial_stride, bias, resid, LAYOUT_ROWS, y_layout, y, g, b, T, d, eps, vec, stream, nullptr, nullptr);
     else if (resid_f32) go(float{}, std::false_type{});
     else if (resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) go(_Float16{}, std::true_type{});
     else go(_Float16{}, std::false_type{});
-    if (planes && !vec) return launch_split_rows((const float *)y, planes, T, d, stream);
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (planes && !vec) {
+        if (e == hipSuccess) e = launch_split_rows((const float *)y, planes, T, d, stream);
+    }
+    if (ride && !together && e == hipSuccess)
+        e = launch_decode_split(*ride->table, ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, stream);
+    return e;
 }
 
 hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dtype, const float *g,

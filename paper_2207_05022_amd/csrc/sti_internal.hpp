@@ -284,6 +284,15 @@ int few_max_k_splits(int k_tiles);   // the most it can be for up to so many 64-
 hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                               int64_t partial_stride, hipStream_t stream);
 
+// A launch_decode_split that goes out with a LayerNorm that leaves planes (in one launch where its rows are read with wide loads): n_shards of
+// the table, of d_model d.  Nothing that LayerNorm reads or writes lies in `out`.
+struct SplitRide {
+    const InlineShardTable *table;
+    int n_shards, d_head, ffn_per_shard;
+    bool ffn;
+    void *out;
+};
+
 // rowops.hip
 // v = sum_{s < n_partials} pre[s * partial_stride + t*d + :] + bias[:] + resid[t][:]  (n_partials may be 0);
 // y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid (binary16, or float32
@@ -293,7 +302,7 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,
                             const float *g, const float *b, int T, int d, float eps,
-                            hipStream_t stream, void *planes = nullptr);
+                            hipStream_t stream, void *planes = nullptr, const SplitRide *ride = nullptr);
 // y[t][:] = LayerNorm(pre_f16[t][:]) * g + b for rows that already hold sum + bias + residual.
 hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dtype, const float *g,
                                   const float *b, int T, int d, float eps, hipStream_t stream);

@@ -243,6 +243,47 @@ def test_f32_planes_are_written_for_layers_that_take_them(gpu, oracle_mod, layer
     assert count["convert"] == converted and count["decode"] == layers.count("o") + layers.count("s") + 2 * layers.count("p")
 
 
+@pytest.mark.parametrize("d,M,f,B,L,shift,present", [
+    (768, 12, 256, 8, 128, 0, (12, 12, 6, 12, 0, 12)),     # more shards than the layer before has: over its sums, not beside its LayerNorm
+    (1024, 16, 256, 3, 101, 0, (16, 14, 15, 16)),
+    (1088, 17, 256, 3, 101, 0, (17, 17, 17)),              # rows too long for one launch of both, more than 16 descriptors
+    (320, 32, 64, 7, 150, 0, (32, 32, 30, 32)),            # few neurons per shard
+    (768, 4, 256, 20, 100, 0, (4, 4)),                     # room for four descriptors
+    (768, 12, 256, 5, 100, 1, (12, 12)),                   # unaligned parameters: a LayerNorm of single features
+])
+def test_f32_weights_decompressed_beside_a_layernorm(gpu, d, M, f, B, L, shift, present):
+    """Layers one after another give the bits of one call per layer: what a LayerNorm's launch decompresses for the next layer is what
+    that layer decompresses for itself, and nothing that is still read lies below it."""
+    import types
+    torch, P, D = gpu
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    wl = S.small_workload(44000 + d + M, dims, len(present), B, L)
+    for l, m in enumerate(present):
+        for i in range(m, M):
+            wl.plan[l, (i * 5 + l) % M], wl.shards[l][(i * 5 + l) % M] = 0, None
+    S.make_every_term_matter(wl, 4, amp=2.0)
+    shards, params, x = D.upload_workload(wl)
+    if shift:
+        moved = []
+        for p in params:
+            q = types.SimpleNamespace()
+            for n, _ in P.StiLayerParams._fields_:
+                setattr(q, n, torch.cat([torch.zeros(shift, device="cuda"), getattr(p, n).reshape(-1)])[shift:])
+            moved.append(q)
+        params = moved
+    prec = P.STI_PREC_F32
+    ws = torch.empty(P.sti_workspace_bytes(dims, B, L, prec), dtype=torch.uint8, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    P.sti_model_forward(dims, D.store_from_plan(shards), params, wl.plan, x, y, prec, ws)
+    cur = x
+    for l in range(len(present)):
+        nxt = torch.full_like(x, float("nan"))
+        P.sti_layer_forward(dims, shards[l], params[l], cur, nxt, prec, ws)
+        cur = nxt
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.equal(y, cur)
+
+
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
     (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
     (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows
