@@ -662,10 +662,19 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.a_layout = inner;
     p.kind = GEMM_OUT; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = dh; p.d_head = dh;
     p.A = ctx; p.lda = m * dh; p.C = pre; p.ldc = dm; p.bias0 = prm.bo; p.resid = in; p.ldr = dm;
-    if (next && next->workgroups > 0) {
-        p.next_table = next->table; p.next_shards = next->n_shards; p.next_out = next->out;
-        p.next_outliers = next->max_outliers; p.next_ffn_per_shard = f;
+    // the next layer's dictionaries, beside this product or FFN2's
+    const int riding = next && next->workgroups > 0 && !no_products ? next->max_outliers : 0;
+    auto carry = [&](GemmProblem &q) {
+        q.next_table = next->table; q.next_shards = next->n_shards; q.next_out = next->out;
+        q.next_outliers = riding; q.next_ffn_per_shard = f;
+    };
+    bool out_carries = false;
+    if (riding > 0) {
+        GemmProblem down = p;
+        down.kind = GEMM_FFN_DOWN; down.block_cols = f;
+        out_carries = gemm_wide_out_carries(p, down, riding);
     }
+    if (out_carries) carry(p);
     if (no_products) {
         pre_partials = 0;
     } else if (out_with_attention) {
@@ -695,6 +704,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     p.kind = GEMM_FFN_DOWN; p.T = T; p.n_blocks = m; p.block_rows = dm; p.block_cols = f;
     p.d_head = dh; p.A = u; p.lda = m * f; p.C = pre; p.ldc = dm; p.bias0 = prm.b2; p.resid = h;
     p.ldr = dm;
+    if (riding > 0 && !out_carries) carry(p);
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
     // the next layer's Q, K, V and O go where FFN2 and, behind it, FFN1 were: not over sums that LayerNorm reads from there

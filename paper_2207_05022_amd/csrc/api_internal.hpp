@@ -53,7 +53,7 @@ struct NextLayerDecode {
     int n_shards;
     void *out;
     int workgroups;
-    int max_outliers;   // > 0: the layer's output projection puts the outlier dictionaries in
+    int max_outliers;   // > 0: the layer's O or FFN2 projection puts the outlier dictionaries in
 };
 // Workgroups such a launch of a layer of m present shards gives to the m_next of the next layer (0: the layer does not go
 // through the many-token route, its projection fills the chip, or a decompression launch in the chain - for several

@@ -186,7 +186,7 @@ __device__ inline void decode_next_layer(const GemmProblem &p, int d, unsigned c
     }
 }
 
-// Workgroups of an output projection beyond those of its tiles: the outlier dictionaries of the layer that this
+// Workgroups of an O or FFN2 projection (gemm_wide_out_carries) beyond those of its tiles: the outlier dictionaries of the layer that this
 // layer's Q/K/V launch has decompressed.  One entry per thread, chunks workgroups per shard: three round trips
 // (descriptor, entry, store) beside the projection, where a launch of its own is on the chain of launches.
 // 1023 tokens, 10 shards of BERT-base with about 900 entries each: 61.8 -> 58.6 us per layer.
@@ -244,12 +244,12 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // gridDim.y workgroups per tile as well (raw float32 partial sums, see the epilogue)
     const int splits = (!n_split && hot_k_splits > 1) ? hot_k_splits : 1;
     const int hot_lda = K, hot_ldr = hot_block_rows;   // (rows of A and of the residual follow each other)
-    int nkt = K / BK / KS;                 // K tiles of this wave's group
-    if (splits > 1) nkt /= splits;
+    const int nkt_all = splits > 1 ? K / BK / splits : K / BK;   // K tiles of the workgroup; of this wave's group: nkt, from kt0 on
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = wave_all / NW, wave = wave_all - half * NW;   // K group, column strip
-    const int kt0 = ((int)blockIdx.y * KS + half) * nkt;
+    const int nkt = KS == 1 ? nkt_all : nkt_all / KS + (half < nkt_all % KS ? 1 : 0);
+    const int kt0 = (int)blockIdx.y * nkt_all + (KS == 1 ? 0 : half * (nkt_all / KS) + min(half, nkt_all % KS));
     const int g = lane >> 5, lr = lane & 31;
     const int n_tiles = (N + BN - 1) / BN;
     const int m_tiles = (hot_T + BM - 1) / BM;
@@ -262,10 +262,10 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             return;
         }
     }
-    if constexpr (KIND == GEMM_OUT) {
+    if constexpr (KIND == GEMM_OUT || KIND == GEMM_FFN_DOWN) {
         if ((int)(blockIdx.x >> 3) >= per_xcd) {   // behind the tiles' workgroups: the next layer's outlier dictionaries
             if (p.next_outliers > 0 && blockIdx.y == 0)
-                patch_next_layer<NT>(p, hot_block_rows, hot_block_cols, (int)blockIdx.x - 8 * per_xcd);
+                patch_next_layer<NT>(p, hot_block_rows, p.d_head, (int)blockIdx.x - 8 * per_xcd);
             return;
         }
     }
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         nblk = quotient(nw >> 5, hot_block_rows >> 5, hot_block_recip);
         nrow0 = nw - nblk * hot_block_rows;
     }
-    const int tiles_per_kblock = n_split ? nkt * KS : hot_block_cols / BK;
+    const int tiles_per_kblock = n_split ? nkt : hot_block_cols / BK;
 
     float16v acc[RA];
 #pragma unroll
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #ifdef STI_PHASE_STAMPS
             if (kt == 0) STI_STAMP(2);
 #endif
-            if (KS == 2 && more) issue(kt + STAGES - 1, next, bnew);
+            if (KS > 1 && more) issue(kt + STAGES - 1, next, bnew);
             const unsigned char *stage = smem_raw + (half * STAGES + buf) * (STAGE * 2);
             half8 a_cur[RA], a_nxt[RA];
 #pragma unroll
@@ -453,10 +453,12 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             if (kt + 2 < nkt) step(kt + 2, 2, bw[2], bw[1], std::false_type{});
         }
     };
-    static_assert(FPW <= 2, "the hand-written waits cover up to two A fetches per wave");
+    static_assert(FPW <= 8, "loads of two K tiles in the counter of the waits");
     if (PRE && half == 0) load_epilogue_operands();
     if (FETCHES % NW == 0 || wave < FETCHES % NW) k_loop(std::integral_constant<int, FPW>{});
     else k_loop(std::integral_constant<int, FPW - 1>{});
+    // (a group with a K tile less than the first one: that one's last barrier)
+    if (KS > 1 && nkt * KS < nkt_all && nkt < (nkt_all + KS - 1) / KS) __builtin_amdgcn_s_barrier();
     STI_STAMP(3);
 
     // ---- epilogue ----
@@ -532,22 +534,24 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         STI_STAMPS_OUT();
         return;
     }
-    if constexpr (KS == 2) {
-        // second K group -> LDS -> first K group (same lane, same registers)
+    if constexpr (KS > 1) {
+        // the other K groups -> LDS -> first K group (same lane, same registers), in their order
         float *part = (float *)smem_raw;
         const int th = tid - half * NTH;
-        if (half == 1) {
+        if (half > 0) {
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) part[(i * 16 + v) * NTH + th] = acc[i][v];
+                for (int v = 0; v < 16; ++v) part[((half - 1) * RA * 16 + i * 16 + v) * NTH + th] = acc[i][v];
         }
         __syncthreads();
         if (half == 0) {
 #pragma unroll
-            for (int i = 0; i < RA; ++i)
+            for (int k = 0; k < KS - 1; ++k)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][v] += part[(i * 16 + v) * NTH + th];
+                for (int i = 0; i < RA; ++i)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][v] += part[(k * RA * 16 + i * 16 + v) * NTH + th];
         }
         __syncthreads();   // the sums are in registers: the buffer can take the staged tile
     }
@@ -629,19 +633,18 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // BN/8 lanes per tile row: every store instruction writes whole rows of the tile
     _Float16 *C = (_Float16 *)p.C;
     constexpr int PIECES_PER_ROW = BN / 8;
-    constexpr int PASSES = BM * PIECES_PER_ROW / NT;
-    static_assert(PASSES * NT == BM * PIECES_PER_ROW, "whole passes");
+    constexpr int PIECES = BM * PIECES_PER_ROW, PASSES = (PIECES + NT - 1) / NT;
     u32x4 piece[PASSES];
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
-        const int pc = tid + NT * j;
+        const int pc = min(tid + NT * j, PIECES - 1);
         piece[j] = *(const u32x4 *)(tile_out + (pc / PIECES_PER_ROW) * LDT + (pc % PIECES_PER_ROW) * 8);
     }
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
         const int pc = tid + NT * j;
         const int m = m0 + pc / PIECES_PER_ROW, n = tile_n * BN + (pc % PIECES_PER_ROW) * 8;
-        if (m < hot_T && n < N) *(u32x4 *)(C + (int64_t)m * p.ldc + n) = piece[j];
+        if (pc < PIECES && m < hot_T && n < N) *(u32x4 *)(C + (int64_t)m * p.ldc + n) = piece[j];
     }
     STI_STAMPS_OUT();
 }
@@ -681,9 +684,9 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
             return hipErrorInvalidValue;
         grid.x += p.next_workgroups;
     }
-    if (KIND == GEMM_OUT && p.next_outliers > 0) {
+    if ((KIND == GEMM_OUT || KIND == GEMM_FFN_DOWN) && p.next_outliers > 0) {
         constexpr int NT = NW * KS * 64;
-        if (!p.next_table || !p.next_out || p.next_shards <= 0 || p.next_ffn_per_shard <= 0) return hipErrorInvalidValue;
+        if (!p.next_table || !p.next_out || p.next_shards <= 0 || p.next_ffn_per_shard <= 0 || p.d_head <= 0) return hipErrorInvalidValue;
         grid.x += p.next_shards * ((p.next_outliers + NT - 1) / NT);
     }
     GemmProblem q = p;
@@ -712,27 +715,43 @@ hipError_t launch_kind(const GemmProblem &p, const GemmBlocks &blocks, int N, hi
     return hipErrorInvalidValue;
 }
 
+template <int RA, int NW>   // K shared by two groups of waves
+hipError_t launch_groups(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
+{
+    return p.kind == GEMM_OUT ? launch_shape<GEMM_OUT, RA, NW, 2>(p, blocks, N, stream) : launch_shape<GEMM_FFN_DOWN, RA, NW, 2>(p, blocks, N, stream);
+}
+
 // Tile shapes, rows x columns, and the time of a launch: start_us + rounds * (K tiles * (tile_us + full_us * fill) + round_us (+ gelu_us for
-// FFN1, resid_us for O and FFN2)), rounds = tiles on the busiest compute unit (shared: two workgroups on a unit, half way between that and
-// the average), fill = average / busiest: a chip with idle units clocks higher.  Fitted to launches of 64 layer shapes drawn
-// over 700 .. 9216 tokens, d_model 256 .. 1024, 2 to 16 shards, each projection with each shape: off by 3 to 5 % (root mean square; 64 x 192: 8 %).
+// FFN1, resid_us for O and FFN2)), rounds = tiles on the busiest compute unit (shared: several workgroups on a unit, half way between that and
+// the average), fill = average / busiest: a chip with idle units clocks higher.  The shapes of 12000 values and more: fitted
+// to 256 launches of 64 layer shapes with the K loops of then, 0.95 of that today; the smaller ones to 936 launches of 234 layer shapes (350 to
+// 9216 tokens, d_model 256 .. 1024, 2 to 16 shards), off by 6 % (root mean square).  The shape so chosen costs 0.8 % (Q/K/V, FFN1) and 1.6 % (O,
+// FFN2) more than the fastest of all over those 936.
+// What a small tile is for: a unit takes in about 48 bytes a clock whatever runs on it, rows + columns of a tile per K position, so that
+// with few tokens the launch ends sooner the smaller and squarer the tiles are, as long as every one has a unit of its own; and four or six
+// waves start sooner than twelve.  Without 64 x 128 and the shapes of fewer than 12000 values Q/K/V and FFN1 cost 6 %, O and FFN2 22 % more than the
+// fastest.  FFN2 of 1116 tokens, BERT-base, us: 64 x 192 with twelve waves 19.4, 32 x 192 16.3; 12 layers of it: 64 x 192 782, 64 x 96 702, 64 x 64
+// 664 (with four groups of waves 683, six 711); 1023 tokens, 10 shards: 32 x 96 584, 64 x 64 602, 64 x 96 633.  More than 256 of these tiles
+// lose to the next larger shape (1792 tokens: 64 x 96 781, 64 x 64 862), and more groups than two to two.
 // large: gemm_large.hip.
-// The shape so chosen costs 0.4 % more than the fastest of all on average (geometric mean of the 256 launches); with the shapes of this file
-// alone, 128 x 256 tiles of four waves among them, it was 3 % more.  9216 tokens, d_model 1024, 12 shards, us, these against those: Q/K/V
-// 192 x 256 47 / 52, FFN1 256 x 256 66 / 69, O 192 x 256 21.6 / 23.5, FFN2 192 x 256 59 / 66; 5000 tokens, d_model 768 Q/K/V 22.5 / 27.2;
-// 3000 tokens, 10 shards Q/K/V 128 x 256 14.5 / 17.3.
 struct Shape {
-    int rows, cols;
+    int rows, cols, groups;   // groups of waves that share K: O and FFN2, a workgroup to a unit
     bool shared, large;
     float start_us, tile_us, full_us, round_us, gelu_us, resid_us;
 };
-// The first is for Q/K/V and FFN1, the second for Q/K/V beside a decompression (below): elsewhere others are faster.
-constexpr Shape kShapes[] = {{128, 384, false, false, 1.12f, 0.729f, 0.628f, 4.57f, 3.34f, 1.56f}, {128, 288, false, false, 0.57f, 0.694f, 0.425f, 4.96f, 3.08f, 1.32f},
-                             {64, 384, false, false, 0.15f, 0.475f, 0.337f, 3.71f, 1.75f, 1.68f},  {64, 192, true, false, 1.47f, 0.423f, 0.090f, 1.22f, 0.84f, 1.50f},
-                             {128, 256, false, true, 1.38f, 0.587f, 0.441f, 2.25f, 2.08f, 1.15f},  {192, 256, false, true, 2.12f, 0.773f, 0.588f, 2.21f, 3.25f, 1.99f},
-                             {256, 256, false, true, 2.87f, 0.915f, 0.773f, 2.96f, 4.37f, 2.44f}};
-constexpr int kNarrow = 3;
-constexpr Shape kSplitShape = {64, 192, false, false, 2.97f, 0.294f, 0.133f, 0.f, 0.f, 1.49f};   // K split over two wave groups, one workgroup per unit
+enum ShapeId { W128x384, W128x288, W64x384, W64x192, W64x128, G64x192, G64x96, G64x64, G32x96, L128x256, L192x256, L256x256, kShapeCount };
+constexpr Shape kShapes[kShapeCount] = {{128, 384, 1, false, false, 1.064f, 0.693f, 0.597f, 4.341f, 3.173f, 1.482f},   // Q/K/V and FFN1
+                                        {128, 288, 1, false, false, 0.541f, 0.659f, 0.404f, 4.712f, 2.926f, 1.254f},   // Q/K/V beside a decompression
+                                        {64, 384, 1, false, false, 0.142f, 0.451f, 0.32f, 3.524f, 1.662f, 1.596f},
+                                        {64, 192, 1, true, false, 1.396f, 0.402f, 0.085f, 1.159f, 0.798f, 1.425f},
+                                        {64, 128, 1, true, false, 3.13f, 0.264f, 0.007f, 0.34f, 0.22f, 0.12f},
+                                        {64, 192, 2, false, false, 2.821f, 0.279f, 0.126f, 0.f, 0.f, 1.415f},
+                                        {64, 96, 2, false, false, 3.84f, 0.197f, 0.034f, 0.f, 0.f, 0.f},
+                                        {64, 64, 2, false, false, 3.63f, 0.144f, 0.032f, 0.f, 0.f, 0.f},
+                                        {32, 96, 2, false, false, 3.18f, 0.097f, 0.091f, 0.f, 0.f, 0.f},
+                                        {128, 256, 1, false, true, 1.311f, 0.558f, 0.419f, 2.137f, 1.976f, 1.092f},
+                                        {192, 256, 1, false, true, 2.014f, 0.734f, 0.559f, 2.099f, 3.087f, 1.89f},
+                                        {256, 256, 1, false, true, 2.727f, 0.869f, 0.734f, 2.812f, 4.151f, 2.318f}};
 
 // Workgroups beside `tiles` that still find a compute unit of their own in the first round; fewer than an eighth of the
 // chip are not used.
@@ -780,7 +799,6 @@ namespace {
 
 struct Choice {
     int shape;       // index into kShapes
-    bool ks2;        // K split over two wave groups inside the workgroup
     long tiles;
     int nkt_total;
     float us;        // estimated; infinite: no shape has workgroups to spare
@@ -794,17 +812,18 @@ Choice choose(const GemmProblem &p, int N)
     const bool beside = p.kind == GEMM_QKV && p.next_workgroups > 0;
     Choice best = {};
     best.us = INFINITY;
-    for (int c = n_split ? 0 : 2; c < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++c) {
-        if (c == 1 && !beside) continue;
+    for (int c = 0; c < kShapeCount; ++c) {
+        const Shape &sh = kShapes[c];
+        if ((c == W128x288 && !beside) || (!n_split && sh.rows >= 128 && !sh.large) || (sh.groups > 1 && (n_split || nkt < 4))) continue;
         // (the large tiles have no workgroups for the next layer's shards or dictionaries, whole strips of 64 columns, two K tiles at least,
         // and 256 rows only without residual)
-        if (kShapes[c].large && (beside || p.next_outliers > 0 || N % 64 || nkt < 2 || (!n_split && kShapes[c].rows > 192))) continue;
-        const long tiles = (long)((N + kShapes[c].cols - 1) / kShapes[c].cols) * ((p.T + kShapes[c].rows - 1) / kShapes[c].rows);
+        if (sh.large && (beside || p.next_outliers > 0 || N % 64 || nkt < 2 || (!n_split && sh.rows > 192))) continue;
+        const long tiles = (long)((N + sh.cols - 1) / sh.cols) * ((p.T + sh.rows - 1) / sh.rows);
         const float avg = (float)tiles / kComputeUnits;
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
-        // one 6-wave workgroup per unit: K is split inside the workgroup to fill the unit
-        const bool ks2 = !n_split && c == kNarrow && per_cu == 1 && nkt % 2 == 0 && nkt >= 4;
-        const Shape &sh = ks2 ? kSplitShape : kShapes[c];
+        if ((sh.groups > 1 && per_cu > 1) || (c == W64x128 && per_cu > 2)) continue;
+        // (an output projection with dictionaries beside it: an entry per thread, workgroups of twelve waves while a unit has one)
+        if (p.kind == GEMM_OUT && p.next_outliers > 0 && (c == W64x128 || sh.cols < 192 || (c == W64x192 && per_cu == 1 && nkt >= 4))) continue;
         const float rounds = sh.shared ? std::max(1.f, (avg + per_cu) / 2) : (float)per_cu;
         float us = sh.start_us + rounds * (nkt * (sh.tile_us + sh.full_us * avg / per_cu) + sh.round_us + (p.kind == GEMM_FFN_UP ? sh.gelu_us : 0.f) +
                                            (n_split ? 0.f : sh.resid_us));
@@ -816,7 +835,6 @@ Choice choose(const GemmProblem &p, int N)
         if (us < best.us) {
             best.us = us;
             best.shape = c;
-            best.ks2 = ks2;
             best.tiles = tiles;
             best.nkt_total = nkt;
         }
@@ -836,10 +854,23 @@ int gemm_wide_k_splits(const GemmProblem &p)
 {
     if (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN || p.n_blocks <= 0 || p.T <= 0) return 1;
     const Choice ch = choose(p, p.block_rows);
-    if (!ch.ks2) return 1;
+    if (kShapes[ch.shape].groups == 1) return 1;
     for (int s = 4; s >= 2; s >>= 1)
         if (ch.tiles * s <= kComputeUnits / 2 && ch.nkt_total % (2 * s) == 0 && ch.nkt_total / (2 * s) >= 3) return s;
     return 1;
+}
+
+// Which of a layer's two d_model-wide projections loses less when the next layer's dictionaries go out beside it.  1023 tokens, 10 shards of
+// BERT-base: O in 64 x 192 tiles where 32 x 96 take half the time, FFN2 keeps its own; many tokens: FFN2 would do without the large ones.
+bool gemm_wide_out_carries(GemmProblem out, GemmProblem down, int entries)
+{
+    auto lost = [&](GemmProblem &p) {
+        p.next_outliers = 0;
+        const float alone = choose(p, p.block_rows).us;
+        p.next_outliers = entries;
+        return choose(p, p.block_rows).us - alone;
+    };
+    return lost(out) <= lost(down);
 }
 
 int gemm_wide_max_k_splits(int64_t T, int N)
@@ -895,16 +926,17 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
     }
     const Choice ch = choose(p, N);
     if (!(ch.us < INFINITY)) return hipErrorInvalidValue;
-    if (p.k_splits > 1 && (!ch.ks2 || p.k_splits != gemm_wide_k_splits(p))) return hipErrorInvalidValue;
-    if (ch.ks2) {
-        return p.kind == GEMM_OUT ? launch_shape<GEMM_OUT, 2, 6, 2>(p, blocks, N, stream)
-                                  : launch_shape<GEMM_FFN_DOWN, 2, 6, 2>(p, blocks, N, stream);
-    }
+    if (p.k_splits > 1 && p.k_splits != gemm_wide_k_splits(p)) return hipErrorInvalidValue;
     switch (ch.shape) {
-    case 0: return p.kind == GEMM_QKV ? launch_shape<GEMM_QKV, 4, 12, 1>(p, blocks, N, stream) : launch_shape<GEMM_FFN_UP, 4, 12, 1>(p, blocks, N, stream);
-    case 1: return launch_shape<GEMM_QKV, 4, 9, 1>(p, blocks, N, stream);
-    case 2: return launch_kind<2, 12>(p, blocks, N, stream);
-    case kNarrow: return launch_kind<2, 6>(p, blocks, N, stream);
+    case W128x384: return p.kind == GEMM_QKV ? launch_shape<GEMM_QKV, 4, 12, 1>(p, blocks, N, stream) : launch_shape<GEMM_FFN_UP, 4, 12, 1>(p, blocks, N, stream);
+    case W128x288: return launch_shape<GEMM_QKV, 4, 9, 1>(p, blocks, N, stream);
+    case W64x384: return launch_kind<2, 12>(p, blocks, N, stream);
+    case W64x192: return launch_kind<2, 6>(p, blocks, N, stream);
+    case W64x128: return launch_kind<2, 4>(p, blocks, N, stream);
+    case G64x192: return launch_groups<2, 6>(p, blocks, N, stream);
+    case G64x96: return launch_groups<2, 3>(p, blocks, N, stream);
+    case G64x64: return launch_groups<2, 2>(p, blocks, N, stream);
+    case G32x96: return launch_groups<1, 3>(p, blocks, N, stream);
     default: return launch_gemm_large(p, blocks, N, kShapes[ch.shape].rows / 64, stream);
     }
 }
@@ -921,5 +953,5 @@ extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int 
     const bool n_split = kind == sti::GEMM_QKV || kind == sti::GEMM_FFN_UP;
     const sti::Choice ch = sti::choose(p, n_split ? n_blocks * block_rows : block_rows);
     const sti::Shape &sh = sti::kShapes[ch.shape];
-    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = ch.ks2 ? 2 : 1; tile[3] = sh.large;
+    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large;
 }

@@ -211,7 +211,7 @@ struct GemmProblem {
     const ShardDesc *next_table;
     void *next_out;
     int32_t next_shards, next_workgroups, next_ffn_per_shard;
-    // wide-tile kernel, GEMM_OUT: with next_outliers > 0 workgroups beyond those of the tiles put the outlier dictionaries
+    // wide-tile kernel, GEMM_OUT and GEMM_FFN_DOWN: with next_outliers > 0 workgroups beyond those of the tiles put the outlier dictionaries
     // of the next_shards shards of next_table (at most next_outliers entries each) into next_out
     int32_t next_outliers;
     CellMap next_cells;   // (filled in by the launch)
@@ -240,6 +240,7 @@ hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B,
 // launch_layernorm completes, like the few-token variant below).  Every block is a cell array
 // of the fragment-tiled binary16 working buffer (bits == kTiledBits).
 hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipStream_t stream);
+bool gemm_wide_out_carries(GemmProblem out, GemmProblem down, int entries);
 bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks);
 // the same in tiles of 64 row_blocks x 256 (gemm_large.hip): N a multiple of 64, at least two K tiles, no next_* work, on top of what
 // launch_gemm_wide has checked

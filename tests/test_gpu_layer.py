@@ -976,9 +976,9 @@ def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
 @pytest.mark.parametrize("k_tiles", range(1, 10))
 def test_mfma_k_tiles_in_and_out_of_whole_rounds(gpu, oracle_mod, k_tiles):
     """K loops of one to nine K tiles (rounds of three whose loads all exist, then the rest): 64-row tiles with unsplit K (Q/K/V and
-    FFN1) and with K shared by two groups of waves (O and FFN2), Q/K/V tiles of whole sequences, and tiles of 192 rows."""
-    for M, B, L, chosen in ((k_tiles + 1, 11, 100, {"qkv": "64x192", "ffn1": "64x192", "ffn2": "64x192*" if k_tiles % 2 and k_tiles > 1 else "64x192"}),
-                            (8, 32, 128, None), (32, 17, 100, {"qkv": "192x256L"} if k_tiles > 1 else None)):
+    FFN1), K shared evenly and unevenly by two groups of waves (O and FFN2), Q/K/V tiles of whole sequences, and tiles of 192 rows."""
+    for M, B, L, chosen in ((k_tiles + 1, 11, 100, {"ffn2": "32x96*"} if k_tiles > 2 else None), (8, 32, 128, None),
+                            (32, 17, 100, {"qkv": "192x256L"} if k_tiles > 1 else None)):
         dims = S.Dims(64 * k_tiles, M, 64, 64, 1e-12)
         have = tiles.layer_tiles(gpu[1], dims, B * L, M)
         assert chosen is None or all(have[name].split("/")[0] == shape for name, shape in chosen.items()), have
@@ -989,6 +989,27 @@ def test_mfma_k_tiles_in_and_out_of_whole_rounds(gpu, oracle_mod, k_tiles):
         for b in (0, B // 2, B - 1):
             want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
             assert_parity(got[b:b + 1], want, TOL["mfma"], (M, b))
+
+
+@pytest.mark.parametrize("d,M,f,B,L,n_absent,chosen", [
+    (768, 12, 256, 11, 93, 2, {"qkv": "64x128/240", "o": "32x96*/256", "ffn2": "64x64*/192"}),
+    (768, 12, 256, 12, 93, 1, {"o": "64x64*/216", "ffn1": "64x128/396", "ffn2": "64x64*/216"}),    # eleven K tiles to two groups
+    (768, 12, 256, 16, 127, 0, {"o": "64x96*/256"}),
+    (704, 7, 192, 13, 111, 0, {"qkv": "64x128/253", "o": "64x64*/253"}),
+    (832, 8, 64, 13, 111, 0, {"o": "64x96*/207", "ffn2": "64x96*/207"}),   # 64 columns in the last column tile, a ragged last row tile
+    (448, 5, 64, 5, 301, 0, {"o": "32x96*/240", "ffn1": "64x128/72"}),   # 64 columns in the last column tile, five K tiles
+])
+def test_mfma_small_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
+    """Tiles of few values, K shared by two groups of waves or not: all rows against the float32 route, some against the oracle."""
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    assert chosen.items() <= tiles.layer_tiles(gpu[1], dims, B * L, M - n_absent).items()
+    wl = S.small_workload(59000 + d + L, dims, 1, B, L, n_absent=n_absent, io_dtype="f16")
+    S.make_every_term_matter(wl, 8, amp=2.0)
+    got = run_gpu(gpu, wl, "mfma")
+    for b in (0, B - 1):
+        want = oracle_mod.model_forward(dims, wl.shards, wl.params, wl.x[b:b + 1])
+        assert_parity(got[b:b + 1], want, TOL["mfma"], b)
+    assert_parity(got, run_gpu(gpu, wl, "f32"), TOL["mfma"])
 
 
 @pytest.mark.parametrize("d,M,f,B,L,n_absent,chosen", [
