@@ -12,8 +12,8 @@
 //
 // What bounds it: BERT-base, 8 x 128 tokens, us per launch, float32 against these matrix instructions: Q/K/V 34 / 27, O 13 / 12, FFN1 43 / 33,
 // FFN2 43 / 31; the K loops run at 1.1 to 1.4 PFLOP/s of bfloat16 products, near what the chip's clock under this load allows, around them
-// start-up and epilogue of the one tile per compute unit.  Planes cost the decompression 7 and the two LayerNorms 6 us more: a layer
-// 178 -> 148 us.  Error of 12 layers against float64 (2-norm, relative): 1.28e-6 -> 0.92e-6.
+// start-up and epilogue of the one tile per compute unit.  Planes cost the two LayerNorms 6 us more, and as much again since they carry the
+// decompression beside them, which took two launches of 7 us: a layer 178 -> 148 -> 136 us.  Error of 12 layers against float64 (2-norm, relative): 1.28e-6 -> 0.92e-6.
 //
 // Layout: an operand matrix is cut into cells of 32 rows x 64 columns as the binary16 working buffer is (weight_loader.hpp), a cell
 // holding its three planes one after the other: [row block][column cell][plane][fragment q][lane][8 values], 12 KiB.

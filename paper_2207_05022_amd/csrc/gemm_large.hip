@@ -5,9 +5,10 @@
 // in tiles of 64 RA rows x 256 columns (RA = 2, 3 or 4), one workgroup of eight waves per compute unit that goes from tile to tile.
 //
 // What bounds it: the matrix cores at the rate that the chip's power leaves them, and the epilogue, beside which they are idle.  9216 tokens,
-// 12 shards of d_model 1024, clocks of wave 0 (libsti_phases.so): FFN1, 256 x 256 tiles, 2530 per K tile of 64, 2048 of them products, at
-// 1.80 GHz; Q/K/V, 192 x 256, 2030 and 1536; O and FFN2 on 192 of the 256 units 2450 and 2160 and 1536, at 2.0 GHz.  An epilogue takes
-// 11600 with GELU, 3600 for Q/K/V, 5200 to 5400 with residual rows.  What costs power or leaves the matrix cores idle:
+// 12 shards of d_model 1024, clocks of wave 0 (libsti_phases.so): FFN1, 256 x 256 tiles, 2350 per K tile of 64, 2048 of them products, at
+// 1.6 GHz; Q/K/V, 192 x 256, 1840 and 1536; O and FFN2 on 192 of the 256 units 2180 and 1900 and 1536, at 1.7 GHz (with a branch around every
+// request 2530, 2030, 2450 and 2160, at 1.8 and 2.0: the denser the products the lower the clock).  An epilogue takes
+// 9600 with GELU, 3600 for Q/K/V, 5100 to 5200 with residual rows.  160-row tiles, which put O and FFN2 on 232 units, gave 0 to 0.6 %.  What costs power or leaves the matrix cores idle:
 //   - bytes: both operands go through LDS (an A row is read by four waves, a weight by two), so that a unit asks for 64 KiB per K tile
 //     and 256 x 256 outputs - the kernel with weights straight into registers (gemm_wide.hip) asks for 96;
 //   - requests in a burst: 64 KiB keep the unit's address path busy for 1024 clocks, and a wave whose request has to wait does not issue
