@@ -208,8 +208,8 @@ __device__ inline void patch_next_layer(const GemmProblem &p, int d, int dh, int
 }
 
 // KS = 2 (outputs as narrow as d_model, long K): the workgroup has two groups of NW waves that
-// each take one half of K for the same tile, with A stages of their own; the second group
-// hands its accumulators over through LDS at the end.  Twice the waves per compute unit for
+// each take one half of K for the same tile, with A stages of their own; at the end each
+// hands half of its accumulators over through LDS and ends the other half of the tile.  Twice the waves per compute unit for
 // a tile count that is fixed by the output size.
 template <int KIND, int RA, int NW, int KS, bool EARLY>
 __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
@@ -361,12 +361,15 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     constexpr bool PRE = EARLY;
     static_assert(!EARLY || (!n_split && RA <= 2), "early operands: 64-row tiles of OUT / FFN_DOWN");
     const _Float16 *R = (const _Float16 *)hot_resid;
+    static_assert(KS <= 2, "two groups, each of which ends half of the tile's pieces");
+    constexpr int PIECES_OWN = RA * 2 / KS, BIASES = PIECES_OWN < 2 ? 1 : 2;   // pieces of 32 rows x 16 columns per wave
+    const int first_piece = KS == 1 ? 0 : half * PIECES_OWN;                    // (piece n: rows 32 (n / 2), columns 16 (n % 2))
     f32x4 bias[2][2];
-    u32x4 resv[PRE ? RA : 1][2];
+    u32x4 resv[PRE ? PIECES_OWN : 1];
     auto load_epilogue_operands = [&]() {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int c = 16 * q + 8 * g;    // first column of the piece inside the wave's columns
+        for (int q = 0; q < BIASES; ++q) {
+            const int c = 16 * (BIASES == 1 ? first_piece : q) + 8 * g;    // first column of the piece inside the wave's columns
             const float *bp;
             if constexpr (qkv) {
                 const int nrow = nrow0 + c;
@@ -382,10 +385,9 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         }
         if constexpr (PRE) {
 #pragma unroll
-            for (int i = 0; i < RA; ++i) {
-                const int m = min(m0 + i * 32 + lr, hot_T - 1);   // (rows past T: row T-1 again, never stored)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) resv[i][q] = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
+            for (int j = 0; j < PIECES_OWN; ++j) {
+                const int m = min(m0 + (first_piece + j >> 1) * 32 + lr, hot_T - 1);   // (rows past T: row T-1 again, never stored)
+                resv[j] = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * (first_piece + j & 1) + 8 * g);
             }
         }
     };
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         }
     };
     static_assert(FPW <= 8, "loads of two K tiles in the counter of the waits");
-    if (PRE && half == 0) load_epilogue_operands();
+    if (PRE) load_epilogue_operands();
     if (FETCHES % NW == 0 || wave < FETCHES % NW) k_loop(std::integral_constant<int, FPW>{});
     else k_loop(std::integral_constant<int, FPW - 1>{});
     // (a group with a K tile less than the first one: that one's last barrier)
@@ -536,77 +538,37 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         STI_STAMPS_OUT();
         return;
     }
-    if constexpr (KS > 1) {
-        // the other K groups -> LDS -> first K group (same lane, same registers), in their order
-        float *part = (float *)smem_raw;
-        const int th = tid - half * NTH;
-        if (half > 0) {
+    // Two K groups: each ends half of the tile's pieces, adds to them what the other has of them (through LDS, from the same lane and
+    // registers) and asked for their bias and residual rows alone.  With all of it left to the first group (the same bits) 12 layers of BERT-base took,
+    // us: 1023 tokens with dictionaries 586, now 575, 1116 tokens 622 / 614, 2048 808 / 801, 4096 1086 / 1079; d_model 1024, 1200 tokens 941 / 931.
+    auto end_pieces = [&](auto group) {
+        constexpr int G = decltype(group)::value, FIRST = G * PIECES_OWN;
+        if constexpr (KS > 1) {
+            f32x4 *part = (f32x4 *)smem_raw;
+            const int th = tid - G * NTH;
 #pragma unroll
-            for (int i = 0; i < RA; ++i)
+            for (int j = 0; j < PIECES_OWN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) part[((half - 1) * RA * 16 + i * 16 + v) * NTH + th] = acc[i][v];
-        }
-        __syncthreads();
-        if (half == 0) {
-#pragma unroll
-            for (int k = 0; k < KS - 1; ++k)
-#pragma unroll
-                for (int i = 0; i < RA; ++i)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[i][v] += part[(k * RA * 16 + i * 16 + v) * NTH + th];
-        }
-        __syncthreads();   // the sums are in registers: the buffer can take the staged tile
-    }
-    if (splits > 1) {
-        // one of several workgroups of this tile: raw float32 sums, 32 bytes per lane and piece
-        if (half == 0 && nw_real < N) {
-            float *Cf = (float *)p.C + (int64_t)blockIdx.y * p.partial_stride;
-#pragma unroll
-            for (int i = 0; i < RA; ++i) {
-                const int m = m0 + i * 32 + lr;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    float x[8];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float lo = acc[i][(2 * q) * 4 + e], hi = acc[i][(2 * q + 1) * 4 + e];
-                        const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo),
-                                                                         __builtin_bit_cast(uint32_t, hi), false, false);
-                        const uint32_t s0 = sw[0], s1 = sw[1];
-                        x[e] = __builtin_bit_cast(float, s0);
-                        x[4 + e] = __builtin_bit_cast(float, s1);
-                    }
-                    if (m < hot_T) {
-                        float *dst = Cf + (int64_t)m * p.ldc + nw + 16 * q + 8 * g;
-                        *(f32x4 *)dst = f32x4{x[0], x[1], x[2], x[3]};
-                        *(f32x4 *)(dst + 4) = f32x4{x[4], x[5], x[6], x[7]};
-                    }
+                for (int h = 0; h < 2; ++h) {
+                    const int n = (1 - G) * PIECES_OWN + j, v = (n & 1) * 8 + h * 4;
+                    part[((G * PIECES_OWN + j) * 2 + h) * NTH + th] = f32x4{acc[n >> 1][v], acc[n >> 1][v + 1], acc[n >> 1][v + 2], acc[n >> 1][v + 3]};
                 }
-            }
-        }
-        STI_STAMP(4);
-        STI_STAMPS_OUT();
-        return;
-    }
-    if (half == 0) {
+            __syncthreads();
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-        const int row = i * 32 + lr;          // row inside the tile
-        half8 res[2];
-        if constexpr (PRE) {
-            res[0] = __builtin_bit_cast(half8, resv[i][0]);
-            res[1] = __builtin_bit_cast(half8, resv[i][1]);
-        } else if constexpr (!n_split) {
-            const int m = m0 + row;
+            for (int j = 0; j < PIECES_OWN; ++j)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                u32x4 v = {0, 0, 0, 0};
-                if (m < hot_T) v = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
-                res[q] = __builtin_bit_cast(half8, v);
-            }
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 other = part[(((1 - G) * PIECES_OWN + j) * 2 + h) * NTH + th];
+                    const int n = FIRST + j, v = (n & 1) * 8 + h * 4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[n >> 1][v + e] += other[e];
+                }
+            __syncthreads();   // the sums are in registers: the buffer can take the staged tile
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int j = 0; j < PIECES_OWN; ++j) {
+            const int i = (FIRST + j) >> 1, q = (FIRST + j) & 1;
+            const int row = i * 32 + lr, m = m0 + row;   // row inside the tile, token
             float x[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -618,17 +580,39 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                 x[e] = __builtin_bit_cast(float, s0);
                 x[4 + e] = __builtin_bit_cast(float, s1);
             }
-            half8 o;
+            if (splits > 1) {
+                // one of several workgroups of this tile: raw float32 sums, 32 bytes per lane and piece
+                if (nw_real < N && m < hot_T) {
+                    float *dst = (float *)p.C + (int64_t)blockIdx.y * p.partial_stride + (int64_t)m * p.ldc + nw + 16 * q + 8 * g;
+                    *(f32x4 *)dst = f32x4{x[0], x[1], x[2], x[3]};
+                    *(f32x4 *)(dst + 4) = f32x4{x[4], x[5], x[6], x[7]};
+                }
+                continue;
+            }
+            half8 res = {}, o;
+            if constexpr (PRE) {
+                res = __builtin_bit_cast(half8, resv[j]);
+            } else if constexpr (!n_split) {
+                u32x4 v = {0, 0, 0, 0};
+                if (m < hot_T) v = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
+                res = __builtin_bit_cast(half8, v);
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float y = x[e] + bias[q][e >> 2][e & 3];
+                float y = x[e] + bias[BIASES == 1 ? 0 : q][e >> 2][e & 3];
                 if constexpr (KIND == GEMM_FFN_UP) y = gelu_wide(y);
-                if constexpr (!n_split) y += (float)res[q][e];
+                if constexpr (!n_split) y += (float)res[e];
                 o[e] = (_Float16)y;
             }
             *(half8 *)(tile_out + row * LDT + wave * 32 + 16 * q + 8 * g) = o;
         }
-    }
+    };
+    if (KS == 1 || half == 0) end_pieces(std::integral_constant<int, 0>{});
+    else end_pieces(std::integral_constant<int, KS - 1>{});
+    if (splits > 1) {
+        STI_STAMP(4);
+        STI_STAMPS_OUT();
+        return;
     }
     __syncthreads();
     STI_STAMP(4);
