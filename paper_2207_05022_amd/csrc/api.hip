@@ -321,7 +321,7 @@ WorkspaceLayout workspace_layout(const sti_dims &d, int64_t T, sti_precision pre
     const size_t plane = (size_t)T * dm * 4;
     size_t out_planes = 1, down_planes = 1;
     if (prec != STI_PREC_F32) {
-        out_planes = down_planes = gemm_wide_max_k_splits(T, (int)dm);
+        out_planes = down_planes = gemm_wide_max_sum_planes(T, (int)dm);
         if (L.few) {
             out_planes = few_max_k_splits(d.n_heads * d.d_head / 64);
             down_planes = few_max_k_splits(d.n_heads * (d.ffn_per_shard / 64));
@@ -569,7 +569,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     const bool skinny = !f32 && (wl.few || m == 0);
     const bool no_products = m == 0;
     const int64_t partial_stride = (int64_t)T * dm;
-    int pre_partials = 1;   // partial sums the last K-split GEMM left in `pre`
+    int pre_partials = 1;   // planes of sums the last O or FFN2 product left in `pre`; 0: none, or (many tokens) rows with bias and residual
     // float32: the O and FFN2 products leave partial sums in buffers that are free by then (O: Q/K/V;
     // FFN2: Q/K/V, context and `pre`, which lie behind each other)
     int f32_planes = 1;
@@ -593,7 +593,7 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             if (!skinny) {
                 GemmProblem q = p;
                 if (p.kind == GEMM_OUT || p.kind == GEMM_FFN_DOWN) {
-                    q.k_splits = gemm_wide_k_splits(p);
+                    q.k_splits = gemm_wide_sum_planes(p);
                     q.partial_stride = partial_stride;
                     pre_partials = q.k_splits;
                 }
@@ -604,11 +604,11 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
             return launch_gemm_few(p, blk, splits, partial_stride, stream);
         });
     };
-    // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM
+    // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM with more than a few tokens
     auto layernorm = [&](void *dst, sti_dtype dt, ActLayout dst_layout, const float *g, const float *b,
                          const float *bias, const void *resid, ActLayout resid_layout, void *planes, const SplitRide *ride = nullptr) {
         return timed(STI_K_LAYERNORM, stream, [&] {
-            if (!f32 && !skinny && pre_partials == 1)   // the wide MFMA GEMM already added bias and residual
+            if (!f32 && !skinny && pre_partials == 0)
                 return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
             return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32 || resid_layout == LAYOUT_ROWS_F32, resid_layout, dst, dt, dst_layout,
                                     g, b, T, dm, d.ln_eps, stream, planes, ride);

@@ -374,7 +374,7 @@ hipError_t launch_gemm_large(const GemmProblem &p, const GemmBlocks &blocks, int
 {
     // (a wave stores whole strips of 64 columns; a workgroup starts with two stages of its first tile; no partial sums, no work beside the tiles)
     const int K = p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP ? p.block_cols : p.n_blocks * p.block_cols;
-    if (N % 64 || K < 2 * BK || p.k_splits > 1 || p.next_workgroups > 0 || p.next_outliers > 0) return hipErrorInvalidValue;
+    if (N % 64 || K < 2 * BK || p.k_splits > 0 || p.next_workgroups > 0 || p.next_outliers > 0) return hipErrorInvalidValue;
     switch (row_blocks) {
     case 2: return launch_kind<2>(p, blocks, N, stream);
     case 3: return launch_kind<3>(p, blocks, N, stream);

@@ -211,7 +211,8 @@ __device__ inline void patch_next_layer(const GemmProblem &p, int d, int dh, int
 // each take one half of K for the same tile, with A stages of their own; at the end each
 // hands half of its accumulators over through LDS and ends the other half of the tile.  Twice the waves per compute unit for
 // a tile count that is fixed by the output size.
-template <int KIND, int RA, int NW, int KS, bool EARLY>
+// SUMS (O and FFN2, gemm_wide_sum_planes): raw float32 sums in hot_k_splits planes, for launch_layernorm to add bias and residual in float32.
+template <int KIND, int RA, int NW, int KS, bool SUMS>
 __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // what the first loads of a workgroup depend on, as leading scalar arguments: these arrive
     // preloaded in scalar registers (the build asks for kernel-argument preloading), so that the
@@ -243,8 +244,9 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     const int N = n_split ? hot_n_blocks * hot_block_rows : hot_block_rows;
     const int K = n_split ? hot_block_cols : hot_n_blocks * hot_block_cols;
     // K is split over the KS wave groups of the workgroup and, for few tiles, over
-    // gridDim.y workgroups per tile as well (raw float32 partial sums, see the epilogue)
-    const int splits = (!n_split && hot_k_splits > 1) ? hot_k_splits : 1;
+    // gridDim.y workgroups per tile as well, with a plane of sums each
+    static_assert(!SUMS || !n_split, "sums: O and FFN2");
+    const int splits = SUMS ? hot_k_splits : 1;
     const int hot_lda = K, hot_ldr = hot_block_rows;   // (rows of A and of the residual follow each other)
     const int nkt_all = splits > 1 ? K / BK / splits : K / BK;   // K tiles of the workgroup; of this wave's group: nkt, from kt0 on
     const int tid = threadIdx.x, lane = tid & 63;
@@ -353,19 +355,19 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                      "global_load_dwordx4 %3, %4, %5 offset:3072"
                      : "=&v"(dst[0]), "=&v"(dst[1]), "=&v"(dst[2]), "=&v"(dst[3]) : "v"(lane16), "s"(q) : "memory");
     };
-    // EARLY (64-row tiles of the d_model-wide projections, K not split over workgroups): what
+    // EARLY (O and FFN2 that end rows): what
     // the epilogue adds (bias and residual rows) is asked for before the K loop: asked for in
     // the epilogue, these loads cost a whole round trip (3-4 thousand clocks of a 20-50 thousand
     // clock kernel).  They are the oldest loads in flight, so the first wait of the K loop
-    // covers them.  (A variant of its own: with K split over workgroups nothing is added here.)
-    constexpr bool PRE = EARLY;
-    static_assert(!EARLY || (!n_split && RA <= 2), "early operands: 64-row tiles of OUT / FFN_DOWN");
+    // covers them.
+    constexpr bool EARLY = !n_split && !SUMS;
+    static_assert(n_split || RA <= 2, "registers for the residual rows through the K loop");
     const _Float16 *R = (const _Float16 *)hot_resid;
     static_assert(KS <= 2, "two groups, each of which ends half of the tile's pieces");
     constexpr int PIECES_OWN = RA * 2 / KS, BIASES = PIECES_OWN < 2 ? 1 : 2;   // pieces of 32 rows x 16 columns per wave
     const int first_piece = KS == 1 ? 0 : half * PIECES_OWN;                    // (piece n: rows 32 (n / 2), columns 16 (n % 2))
     f32x4 bias[2][2];
-    u32x4 resv[PRE ? PIECES_OWN : 1];
+    u32x4 resv[EARLY ? PIECES_OWN : 1];
     auto load_epilogue_operands = [&]() {
 #pragma unroll
         for (int q = 0; q < BIASES; ++q) {
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             bias[q][0] = *(const f32x4_any *)bp;
             bias[q][1] = *(const f32x4_any *)(bp + 4);
         }
-        if constexpr (PRE) {
+        if constexpr (EARLY) {
 #pragma unroll
             for (int j = 0; j < PIECES_OWN; ++j) {
                 const int m = min(m0 + (first_piece + j >> 1) * 32 + lr, hot_T - 1);   // (rows past T: row T-1 again, never stored)
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         }
     };
     static_assert(FPW <= 8, "loads of two K tiles in the counter of the waits");
-    if (PRE) load_epilogue_operands();
+    if (EARLY) load_epilogue_operands();
     if (FETCHES % NW == 0 || wave < FETCHES % NW) k_loop(std::integral_constant<int, FPW>{});
     else k_loop(std::integral_constant<int, FPW - 1>{});
     // (a group with a K tile less than the first one: that one's last barrier)
@@ -471,9 +473,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // 8 consecutive columns 16q + 8g .. +8 of its row: one 16-byte piece of the output row.
     constexpr int LDT = BN + 8;   // padded row of the staged tile (halves): conflict-free 16-byte writes
     _Float16 *tile_out = (_Float16 *)smem_raw;
-    // (also when K is split over workgroups and nothing is added here: leaving these loads out
-    //  made those launches 2 % slower, measured twice)
-    if (!PRE) load_epilogue_operands();
+    if (n_split) load_epilogue_operands();
     __syncthreads();   // every wave is done with the A stages
     if constexpr (KIND == GEMM_QKV_ATTN) {
         // ---- the tile is Q | K | V of heads 2 tile_n and 2 tile_n + 1 for the 128 positions of
@@ -580,8 +580,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                 x[e] = __builtin_bit_cast(float, s0);
                 x[4 + e] = __builtin_bit_cast(float, s1);
             }
-            if (splits > 1) {
-                // one of several workgroups of this tile: raw float32 sums, 32 bytes per lane and piece
+            if constexpr (SUMS) {   // 32 bytes per lane and piece
                 if (nw_real < N && m < hot_T) {
                     float *dst = (float *)p.C + (int64_t)blockIdx.y * p.partial_stride + (int64_t)m * p.ldc + nw + 16 * q + 8 * g;
                     *(f32x4 *)dst = f32x4{x[0], x[1], x[2], x[3]};
@@ -590,13 +589,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
                 continue;
             }
             half8 res = {}, o;
-            if constexpr (PRE) {
-                res = __builtin_bit_cast(half8, resv[j]);
-            } else if constexpr (!n_split) {
-                u32x4 v = {0, 0, 0, 0};
-                if (m < hot_T) v = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * q + 8 * g);
-                res = __builtin_bit_cast(half8, v);
-            }
+            if constexpr (EARLY) res = __builtin_bit_cast(half8, resv[j]);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float y = x[e] + bias[BIASES == 1 ? 0 : q][e >> 2][e & 3];
@@ -609,7 +602,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     };
     if (KS == 1 || half == 0) end_pieces(std::integral_constant<int, 0>{});
     else end_pieces(std::integral_constant<int, KS - 1>{});
-    if (splits > 1) {
+    if constexpr (SUMS) {
         STI_STAMP(4);
         STI_STAMPS_OUT();
         return;
@@ -635,20 +628,20 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     STI_STAMPS_OUT();
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY>
+template <int KIND, int RA, int NW, int KS, bool SUMS>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream);
 
 template <int KIND, int RA, int NW, int KS>
 hipError_t launch_shape(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
-    if constexpr (!n_split && RA <= 2) {
-        if (p.k_splits <= 1) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
+    if constexpr (!n_split) {
+        if (p.k_splits > 0) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
     }
     return launch_variant<KIND, RA, NW, KS, false>(p, blocks, N, stream);
 }
 
-template <int KIND, int RA, int NW, int KS, bool EARLY>
+template <int KIND, int RA, int NW, int KS, bool SUMS>
 hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
     constexpr int BM = RA * 32, BN = NW * 32;
@@ -656,12 +649,12 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
                                ? kAttentionLdsBytes : wide_lds_bytes<RA, NW, KS>();
     // once per instantiation, and safe when several host threads make their first call together
     static const hipError_t attr_status =
-        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, EARLY>,
+        hipFuncSetAttribute((const void *)gemm_wide_kernel<KIND, RA, NW, KS, SUMS>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_status != hipSuccess) return attr_status;
     const int total = ((N + BN - 1) / BN) * ((p.T + BM - 1) / BM);
     const bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
-    dim3 grid(((total + 7) / 8) * 8, (!n_split && p.k_splits > 1) ? p.k_splits : 1);
+    dim3 grid(((total + 7) / 8) * 8, SUMS ? p.k_splits : 1);
     if ((KIND == GEMM_QKV_ATTN || KIND == GEMM_QKV) && p.next_workgroups > 0) {
         static_assert((KIND != GEMM_QKV_ATTN && KIND != GEMM_QKV) || kNextDecodeLdsBytes <= lds, "the decompressing workgroups' tables fit");
         if (!p.next_table || !p.next_out || p.next_shards <= 0 || p.next_shards > kMaxShardsPerLayer ||
@@ -682,9 +675,9 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
     const int n_tiles = (N + BN - 1) / BN;
     const uint32_t band_recip = band_reciprocal(n_tiles);
     const uint32_t block_recip = reciprocal(n_split ? p.block_rows / 32 : p.block_cols / BK);
-    launch((gemm_wide_kernel<KIND, RA, NW, KS, EARLY>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
+    launch((gemm_wide_kernel<KIND, RA, NW, KS, SUMS>), grid, dim3(NW * KS * 64), lds, stream, p.A, blocks.b[0].w,
            p.resid, p.bias0, (int32_t)w_stride, p.T, band_recip, block_recip, (uint32_t)p.block_rows | (uint32_t)p.block_cols << 16,
-           (uint32_t)p.n_blocks | (uint32_t)(p.k_splits > 1 ? p.k_splits : 1) << 16, q, shard_of);
+           (uint32_t)p.n_blocks | (uint32_t)(SUMS ? p.k_splits : 1) << 16, q, shard_of);
     return hipGetLastError();
 }
 
@@ -783,6 +776,12 @@ bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks)
 
 namespace {
 
+// Whether O and FFN2 leave their sums in float32, with bias and residual added by LayerNorm, instead of rows in binary16: few tokens and K of
+// 12 tiles or more, with which K can be split over workgroups (gemm_wide_sum_planes), and then whether it is or not.  What a call of
+// so many tokens keeps by it: 12 layers of BERT-base, error against float64 with these rows in binary16 and with sums, 2-norm, 707 tokens 6.9e-4 /
+// 5.5e-4, 1024 tokens 6.6e-4 / 5.2e-4; what it costs: 557 / 567, 605 / 612 us.
+inline bool leaves_sums(int64_t T, int N, int k_tiles) { return T <= gemm_wide_most_tokens(2, N) && k_tiles >= 12; }
+
 struct Choice {
     int shape;       // index into kShapes
     long tiles;
@@ -795,6 +794,7 @@ Choice choose(const GemmProblem &p, int N)
 {
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN);
     const int nkt = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
+    const bool sums = !n_split && leaves_sums(p.T, N, nkt);
     const bool beside = p.kind == GEMM_QKV && p.next_workgroups > 0;
     Choice best = {};
     best.us = INFINITY;
@@ -802,8 +802,8 @@ Choice choose(const GemmProblem &p, int N)
         const Shape &sh = kShapes[c];
         if ((c == W128x288 && !beside) || (!n_split && sh.rows >= 128 && !sh.large) || (sh.groups > 1 && (n_split || nkt < 4))) continue;
         // (the large tiles have no workgroups for the next layer's shards or dictionaries, whole strips of 64 columns, two K tiles at least,
-        // and 256 rows only without residual)
-        if (sh.large && (beside || p.next_outliers > 0 || N % 64 || nkt < 2 || (!n_split && sh.rows > 192))) continue;
+        // no sums, and 256 rows only without residual)
+        if (sh.large && (beside || sums || p.next_outliers > 0 || N % 64 || nkt < 2 || (!n_split && sh.rows > 192))) continue;
         const long tiles = (long)((N + sh.cols - 1) / sh.cols) * ((p.T + sh.rows - 1) / sh.rows);
         const float avg = (float)tiles / kComputeUnits;
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
@@ -830,15 +830,14 @@ Choice choose(const GemmProblem &p, int N)
 
 }  // namespace
 
-// With few tiles (few tokens) a workgroup of the d_model-wide projections would walk a long K
-// range alone while most compute units idle (FFN2 at 256 tokens: 16 workgroups, 21 us): K is
-// then split over 2 or 4 workgroups per tile as well, each with at least 3 K tiles per wave
-// group, while they fill at most half the chip (measured: 3-6 % per layer from 256 to 1024
-// tokens; 8 splits, or splitting up to the whole chip, cost more in the LayerNorm that adds
-// the float32 partial sums than they save here).
-int gemm_wide_k_splits(const GemmProblem &p)
+// Planes of float32 sums that O or FFN2 leaves, 0: rows in binary16.  With the fewest tiles (narrow models, more than 256 neurons per
+// shard) a workgroup would walk a long K range alone while most compute units idle: K is then split over 2 or 4 workgroups per tile as
+// well, each with at least 3 K tiles per wave group, while they fill at most half the chip (8 splits, or splitting up to the whole
+// chip, cost more in the LayerNorm that adds the planes than they save here).
+int gemm_wide_sum_planes(const GemmProblem &p)
 {
-    if (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN || p.n_blocks <= 0 || p.T <= 0) return 1;
+    if (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN || p.n_blocks <= 0 || p.T <= 0) return 0;
+    if (!leaves_sums(p.T, p.block_rows, p.n_blocks * p.block_cols / BK)) return 0;
     const Choice ch = choose(p, p.block_rows);
     if (kShapes[ch.shape].groups == 1) return 1;
     for (int s = 4; s >= 2; s >>= 1)
@@ -859,7 +858,7 @@ bool gemm_wide_out_carries(GemmProblem out, GemmProblem down, int entries)
     return lost(out) <= lost(down);
 }
 
-int gemm_wide_max_k_splits(int64_t T, int N)
+int gemm_wide_max_sum_planes(int64_t T, int N)
 {
     for (int s = 4; s >= 2; s >>= 1)
         if (T <= gemm_wide_most_tokens(s, N)) return s;
@@ -912,7 +911,7 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
     }
     const Choice ch = choose(p, N);
     if (!(ch.us < INFINITY)) return hipErrorInvalidValue;
-    if (p.k_splits > 1 && p.k_splits != gemm_wide_k_splits(p)) return hipErrorInvalidValue;
+    if (!n_split && p.k_splits != gemm_wide_sum_planes(p)) return hipErrorInvalidValue;
     switch (ch.shape) {
     case W128x384: return p.kind == GEMM_QKV ? launch_shape<GEMM_QKV, 4, 12, 1>(p, blocks, N, stream) : launch_shape<GEMM_FFN_UP, 4, 12, 1>(p, blocks, N, stream);
     case W128x288: return launch_shape<GEMM_QKV, 4, 9, 1>(p, blocks, N, stream);
@@ -930,7 +929,8 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
 }  // namespace sti
 
 // The tile that a projection takes in a launch of its own, for the tests of its kernels (no device is touched): rows, columns, groups of
-// waves that share K, and whether it is one of gemm_large.hip.  outliers: entries per dictionary of a next layer put in beside it.
+// waves that share K, whether it is one of gemm_large.hip, and planes of float32 sums (gemm_wide_sum_planes).  outliers: entries per dictionary
+// of a next layer put in beside it.
 extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int block_rows, int block_cols, int outliers, int *tile)
 {
     sti::GemmProblem p = {};
@@ -939,5 +939,5 @@ extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int 
     const bool n_split = kind == sti::GEMM_QKV || kind == sti::GEMM_FFN_UP;
     const sti::Choice ch = sti::choose(p, n_split ? n_blocks * block_rows : block_rows);
     const sti::Shape &sh = sti::kShapes[ch.shape];
-    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large;
+    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large; tile[4] = sti::gemm_wide_sum_planes(p);
 }

@@ -199,8 +199,8 @@ struct GemmProblem {
     const void *resid;  // OUT/FFN_DOWN: [T x N] residual, row stride ldr
     int32_t ldr;
     ActLayout a_layout, c_layout;   // few-token kernel; tiled: lda / ldc are the matrices' widths
-    // wide-tile kernel, OUT/FFN_DOWN only: with k_splits > 1 the K range is also split over
-    // that many workgroups per tile, C is float32 and takes the raw partial sums of split s
+    // wide-tile kernel, OUT/FFN_DOWN only: with k_splits > 0 the K range is split over
+    // that many workgroups per tile, C is float32 and takes the raw sums of split s
     // at C + s * partial_stride (bias and residual are left to launch_layernorm)
     int32_t k_splits;
     int64_t partial_stride;
@@ -236,7 +236,7 @@ hipError_t launch_attention_f32(const float *qkv, void *ctx, bool planes, int B,
 
 // binary16 MFMA path (gemm_wide.hip, attention_mfma.hip): A and C are binary16.  QKV / FFN_UP
 // apply bias (and GELU); OUT / FFN_DOWN add bias[N] and the binary16 residual, leaving the
-// LayerNorm to launch_layernorm_f16in (or, with k_splits > 1, leave float32 partial sums that
+// LayerNorm to launch_layernorm_f16in (or, with k_splits > 0, leave float32 sums that
 // launch_layernorm completes, like the few-token variant below).  Every block is a cell array
 // of the fragment-tiled binary16 working buffer (bits == kTiledBits).
 hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipStream_t stream);
@@ -251,10 +251,10 @@ bool gemm_wide_fuses_attention(int B, int L, int m, int dh);
 // next_ffn_per_shard set) should give to the next layer's decompression: one per compute unit that its tiles leave idle
 // (0: none to spare, or a launch of its own costs less; grouped: that launch takes several layers)
 int gemm_wide_spare_workgroups(const GemmProblem &p, bool grouped);
-// K splits across workgroups the wide-tile kernel wants for this problem (1 = none), and the
-// largest value it can return for T tokens and N output columns (workspace sizing)
-int gemm_wide_k_splits(const GemmProblem &p);
-int gemm_wide_max_k_splits(int64_t T, int N);
+// k_splits of this problem, and the most planes that can be for T tokens and N output columns (workspace sizing; rows in binary16
+// lie in a plane, too)
+int gemm_wide_sum_planes(const GemmProblem &p);
+int gemm_wide_max_sum_planes(int64_t T, int N);
 // the most tokens for which it can be `splits` (2 or 4)
 int64_t gemm_wide_most_tokens(int splits, int N);
 // ctx_layout: how the context is left behind (the Q/K/V matrix is row-major)

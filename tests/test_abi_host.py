@@ -180,6 +180,22 @@ def test_tiles_of_64_column_strips_are_for_whole_strips(P):
     assert tiles.tile(P, tiles.O, 9000, 2, 2048, 64)[3] and tiles.tile(P, tiles.FFN1, 9000, 16, 256, 128)[3]
 
 
+@pytest.mark.parametrize("d,last", [(768, 1024), (1024, 640), (512, 1344), (384, 2048), (192, 4096), (1088, 640), (2048, 320)])
+def test_sums_stay_in_float32_up_to_64_tiles(P, d, last):
+    """O and FFN2 of up to 64 tiles of 64 x 192 and 12 K tiles or more leave float32 sums to LayerNorm, whichever tile they take and
+    whether K is split over workgroups or not; others finished rows in binary16."""
+    import tiles
+    for shards in (1, 2, 3, 5, 9, 10, 11, 12, 13, 16, 24):
+        for kind, cols in ((tiles.O, 64), (tiles.FFN2, 64), (tiles.FFN2, 256), (tiles.FFN2, 512)):
+            planes = [tiles.sum_planes(P, kind, n, shards, d, cols) for n in (1, 65, 130, last // 2, last - 63, last)]
+            if shards * cols >= 12 * 64:
+                assert all(1 <= n <= 4 for n in planes) and not any(tiles.tile(P, kind, n, shards, d, cols)[3] for n in (last // 2, last))
+            else:
+                assert not any(planes)
+            assert tiles.sum_planes(P, kind, last + 1, shards, d, cols) == 0
+    assert tiles.sum_planes(P, tiles.QKV, 100, 12, 192, d) == tiles.sum_planes(P, tiles.FFN1, 100, 12, 256, d) == 0
+
+
 @pytest.mark.parametrize("d,M,f,last", [(768, 12, 256, 640), (1024, 16, 256, 512), (512, 8, 128, 1024), (256, 4, 64, 1024),
                                         (1024, 16, 64, 704), (1024, 16, 128, 576), (896, 14, 128, 704), (1024, 8, 256, 704),
                                         (768, 12, 192, 704), (896, 10, 192, 768), (128, 2, 64, 192), (1088, 4, 64, 128)])

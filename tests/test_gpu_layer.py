@@ -599,6 +599,45 @@ def test_rows_of_equal_values_have_no_variance(gpu, prec, d, B, L, absent):
     np.testing.assert_array_equal(got, np.broadcast_to(prm.ln2_b, got.shape))
 
 
+@pytest.mark.parametrize("d,M,f,B,L,absent,planes", [
+    (768, 12, 256, 8, 128, 0, (1, 1)),
+    (768, 12, 192, 7, 101, 1, (0, 1)),     # 11 and 33 K tiles
+    (768, 12, 256, 11, 93, 2, (0, 1)),
+    (1024, 16, 256, 5, 128, 0, (1, 1)),
+    (768, 15, 64, 8, 128, 2, (1, 1)),      # 13 K tiles to two groups of waves
+    (512, 8, 128, 14, 96, 0, (0, 1)),
+    (384, 6, 128, 16, 128, 0, (0, 1)),     # 12 K tiles
+    (192, 12, 256, 3, 100, 0, (2, 4)),     # K split over workgroups
+    (1088, 17, 256, 2, 65, 0, (1, 2)),
+])
+def test_sums_before_layernorm_keep_what_binary16_would_lose(gpu, d, M, f, B, L, absent, planes):
+    """Biases of 0.01 on residual rows of 64, whose neighbours in binary16 are 0.06 away: LayerNorm sees the biases, since few
+    tokens' sums reach it in float32.  Bound of an output y with |y| < 5: half a unit of the sum at 64 (3.8e-6) against a spread of
+    0.01 in the row and once more in its mean, and y's own rounding, 2^-11 |y|, here twice (h, and LayerNorm over h)."""
+    torch, P, D = gpu
+    m = M - absent
+    have = tuple(tiles.sum_planes(P, kind, B * L, m, d, cols) for kind, cols in ((tiles.O, 64), (tiles.FFN2, f)))
+    assert have == planes
+    plan = np.full((1, M), 4, dtype=np.int8)
+    plan[0, 1:1 + absent] = 0
+    wl = S.small_workload(57000 + d + B, S.Dims(d, M, 64, f, 1e-12), 1, B, L, plan=plan, io_dtype="f16")
+    S.make_every_term_matter(wl, 10, amp=0.0)
+    prm, rng = wl.params[0], np.random.default_rng(d + B)
+    normalised = lambda v: (v - v.mean()) / v.std()
+    small = (rng.standard_normal(d) * 0.01).clip(-0.04, 0.04).astype(np.float32)
+    want = normalised(small.astype(np.float64)).astype(np.float32)
+    wl.x[:] = 64.0
+    prm.ln1_g[:], prm.ln1_b[:], prm.ln2_g[:], prm.ln2_b[:] = 1.0, 0.0, 1.0, 0.0
+    for bo, ln1_b, b2, n in ((small, 0.0, 0.0, planes[0]), (0.0, 64.0, small, planes[1])):     # the first LayerNorm's row, or the second one's
+        if n == 0:
+            continue
+        prm.bo[:], prm.b2[:], prm.ln1_b[:] = bo, b2, ln1_b
+        prm.ln1_g[:] = 1.0 if ln1_b == 0.0 else 0.0
+        got = run_gpu(gpu, wl, "mfma", model=False)
+        bound = 2 * 3.8e-6 / small.std() * (1 + np.abs(want)) + 2 * 2.0 ** -11 * np.abs(want)
+        assert np.all(np.abs(got - want) <= bound), float(np.max(np.abs(got - want) / bound))
+
+
 def test_mfma_rejects_unsupported_dims(gpu):
     torch, P, D = gpu
     assert P.sti_workspace_bytes(SMALL, 1, 8, P.STI_PREC_F16_MFMA) == 0
