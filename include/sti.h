@@ -486,9 +486,11 @@ sti_status sti_quantize_layer(const sti_dims *dims, const float *weights, int bi
  * and returns, per kernel class, the number of launches and the summed kernel
  * time in milliseconds.  Where one launch does the work of two classes:  Q/K/V
  * projection and attention (sequences of 128 tokens) count as the projection;
- * attention and output projection (up to 64 keys) as a launch of either class
- * with half the time, so that the classes add up to one launch more than was made,
- * and to the time that was taken; the halves say nothing about the two parts.
+ * attention and output projection (up to 64 keys), and LayerNorm and the
+ * decompression of float32 weights beside it (d_model up to 1024), as a launch of
+ * either class with half the time, so that the classes add up to one launch more
+ * than was made, and to the time that was taken; the halves say nothing about the
+ * two parts.
  * Process wide, not re-entrant; meant for measurement runs, not for production
  * calls (nor for calls under stream capture).
  * ------------------------------------------------------------------------- */

@@ -605,14 +605,22 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         });
     };
     // bias and residual are left to the LayerNorm kernel, except by the wide MFMA GEMM with more than a few tokens
+    // (planes and weights to be decompressed: with the rows' launch where it takes them, else in launches of their own)
     auto layernorm = [&](void *dst, sti_dtype dt, ActLayout dst_layout, const float *g, const float *b,
                          const float *bias, const void *resid, ActLayout resid_layout, void *planes, const SplitRide *ride = nullptr) {
-        return timed(STI_K_LAYERNORM, stream, [&] {
-            if (!f32 && !skinny && pre_partials == 0)
-                return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream);
+        if (!f32 && !skinny && pre_partials == 0)
+            return timed(STI_K_LAYERNORM, stream, [&] { return launch_layernorm_f16in(pre, dst, dt, g, b, T, dm, d.ln_eps, stream); });
+        const bool wide = planes && layernorm_reads_wide(pre, partial_stride, bias, resid, dst, g, b, dm);
+        const bool joint = ride && wide && dm <= kRideFeatures;
+        hipError_t e = timed(STI_K_LAYERNORM, stream, [&] {
             return launch_layernorm(pre, pre_partials, partial_stride, bias, resid, f32 || resid_layout == LAYOUT_ROWS_F32, resid_layout, dst, dt, dst_layout,
-                                    g, b, T, dm, d.ln_eps, stream, planes, ride);
-        }, ride ? STI_K_DECODE : -1);
+                                    g, b, T, dm, d.ln_eps, stream, wide ? planes : nullptr, joint ? ride : nullptr);
+        }, joint ? STI_K_DECODE : -1);
+        if (e == hipSuccess && planes && !wide)
+            e = timed(STI_K_CONVERT, stream, [&] { return launch_split_rows((const float *)dst, planes, T, dm, stream); });
+        if (e == hipSuccess && ride && !joint)
+            e = timed(STI_K_DECODE, stream, [&] { return launch_decode_split(*ride->table, ride->n_shards, dm, dh, f, ride->ffn, ride->out, stream); });
+        return e;
     };
 
     // few tokens: activations inside the layer are tiled, Q/K/V too where the few-token attention takes them

@@ -412,6 +412,13 @@ void launch_ln_typed(const float *pre, int n_partials, int64_t partial_stride, c
 #undef STI_LN_PLANES
 }
 
+bool layernorm_reads_wide(const float *pre, int64_t partial_stride, const float *bias, const void *resid, const void *y, const float *g, const float *b, int d)
+{
+    auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
+    return d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) && (!bias || al16(bias)) &&
+           (!resid || al16(resid));
+}
+
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,
@@ -419,23 +426,20 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
                             hipStream_t stream, void *planes, const SplitRide *ride)
 {
     if (T <= 0 || d <= 0) return hipSuccess;
-    if (planes && (d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
+    const bool vec = layernorm_reads_wide(pre, partial_stride, bias, resid, y, g, b, d);
+    if (planes && (!vec || d % 64 || !resid_f32 || out_dtype != STI_F32)) return hipErrorInvalidValue;
     SplitDecodeJob job;
-    if (ride && (!planes || !split_decode_job(ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, &job))) return hipErrorInvalidValue;
+    if (ride && (!planes || d > kRideFeatures || !split_decode_job(ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, &job))) return hipErrorInvalidValue;
     if (n_partials < 0 || n_partials > 255 || (n_partials > 0 && !pre)) return hipErrorInvalidValue;
     if ((resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) && (d % 64 || (resid_f32 && (resid_layout == LAYOUT_TILED || out_dtype != STI_F16))))
         return hipErrorInvalidValue;
-    auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
-    const bool vec = d % 4 == 0 && d <= 2048 && partial_stride % 4 == 0 && al16(pre) && al16(g) && al16(b) && al16(y) &&
-                     (!bias || al16(bias)) && (!resid || al16(resid));
-    const bool together = ride && vec && d <= 1024 && job.cells > 0;   // (longer rows: registers for one workgroup of four waves per unit)
     auto go = [&](auto resid_type, auto tiled) {
         typedef decltype(resid_type) RT;
         constexpr bool TL = decltype(tiled)::value;
         switch (out_dtype) {
-            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
-            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
-            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, together ? ride : nullptr); break;
+            case STI_F32: launch_ln_typed<STI_F32, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, ride); break;
+            case STI_F16: launch_ln_typed<STI_F16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, ride); break;
+            case STI_BF16: launch_ln_typed<STI_BF16, RT, TL>(pre, n_partials, partial_stride, bias, resid, resid_layout, y_layout, y, g, b, T, d, eps, vec, stream, (uint16_t *)planes, ride); break;
         }
     };
     if (resid_f32 && y_layout == LAYOUT_TILED)
@@ -443,13 +447,7 @@ hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_st
     else if (resid_f32) go(float{}, std::false_type{});
     else if (resid_layout == LAYOUT_TILED || y_layout == LAYOUT_TILED) go(_Float16{}, std::true_type{});
     else go(_Float16{}, std::false_type{});
-    hipError_t e = hipGetLastError();
-    if (planes && !vec) {
-        if (e == hipSuccess) e = launch_split_rows((const float *)y, planes, T, d, stream);
-    }
-    if (ride && !together && e == hipSuccess)
-        e = launch_decode_split(*ride->table, ride->n_shards, d, ride->d_head, ride->ffn_per_shard, ride->ffn, ride->out, stream);
-    return e;
+    return hipGetLastError();
 }
 
 hipError_t launch_layernorm_f16in(const void *pre_f16, void *y, sti_dtype out_dtype, const float *g,

@@ -285,8 +285,9 @@ int few_max_k_splits(int k_tiles);   // the most it can be for up to so many 64-
 hipError_t launch_gemm_few(const GemmProblem &p, const GemmBlocks &blocks, int k_splits,
                               int64_t partial_stride, hipStream_t stream);
 
-// A launch_decode_split that goes out with a LayerNorm that leaves planes (in one launch where its rows are read with wide loads): n_shards of
-// the table, of d_model d.  Nothing that LayerNorm reads or writes lies in `out`.
+// A launch_decode_split that goes out with a LayerNorm that leaves planes, of up to kRideFeatures features (longer rows: registers for one
+// workgroup of four waves per unit): n_shards of the table, of d_model d.  Nothing that LayerNorm reads or writes lies in `out`.
+constexpr int kRideFeatures = 1024;
 struct SplitRide {
     const InlineShardTable *table;
     int n_shards, d_head, ffn_per_shard;
@@ -298,7 +299,8 @@ struct SplitRide {
 // v = sum_{s < n_partials} pre[s * partial_stride + t*d + :] + bias[:] + resid[t][:]  (n_partials may be 0);
 // y[t][:] = LayerNorm(v) * g + b.  pre float32; bias (float32 [d]) and resid (binary16, or float32
 // with resid_f32, [T x d]) may be NULL; y of out_dtype.  A residual or a binary16 y may be tiled.  planes (may be NULL;
-// float32 y and resid_f32 only): y as planes of bfloat16 values, too.
+// float32 y and resid_f32, rows read with wide loads): y as planes of bfloat16 values, too.
+bool layernorm_reads_wide(const float *pre, int64_t partial_stride, const float *bias, const void *resid, const void *y, const float *g, const float *b, int d);
 hipError_t launch_layernorm(const float *pre, int n_partials, int64_t partial_stride,
                             const float *bias, const void *resid, bool resid_f32, ActLayout resid_layout, void *y,
                             sti_dtype out_dtype, ActLayout y_layout,

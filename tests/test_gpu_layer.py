@@ -284,6 +284,38 @@ def test_f32_weights_decompressed_beside_a_layernorm(gpu, d, M, f, B, L, shift, 
     assert torch.isfinite(y).all() and torch.equal(y, cur)
 
 
+@pytest.mark.parametrize("d,shift,joint", [(1024, 0, True), (1088, 0, False), (1024, 1, False)])
+def test_float32_decompressions_are_timed_with_layernorm_or_by_themselves(gpu, d, shift, joint):
+    """48 shards of 64 and of 256 neurons: as much of Q, K, V and O to decompress, four times as much of FFN1 and FFN2, half as much and
+    twice as much as of Q, K, V and O.  By itself (long rows, unaligned parameters) that is decompressions of 1.5 and of 3 units in
+    all; beside the first LayerNorm half of that launch counts as LayerNorm.  (LayerNorm by itself is not the same in both: FFN2
+    leaves more planes of sums for a longer K.)"""
+    import types
+    torch, P, D = gpu
+    prec, B, L = P.STI_PREC_F32, 2, 100
+    times = []
+    for f in (64, 256):
+        dims = S.Dims(d, 48, 64, f, 1e-12)
+        wl = S.small_workload(45000 + f, dims, 1, B, L, plan=np.full((1, 48), 2, dtype=np.int8))
+        shards, (prm,), x = D.upload_workload(wl)
+        if shift:
+            prm = types.SimpleNamespace(**{n: torch.cat([torch.zeros(1, device="cuda"), getattr(prm, n).reshape(-1)])[1:] for n, _ in P.StiLayerParams._fields_})
+        ws = torch.empty(P.sti_workspace_bytes(dims, B, L, prec), dtype=torch.uint8, device="cuda")
+        y = torch.empty_like(x)
+        runs = []
+        for _ in range(5):
+            P.sti_profile_begin()
+            P.sti_layer_forward(dims, shards[0], prm, x, y, prec, ws)
+            runs.append(P.sti_profile_end())
+        assert all((r["decode"][0], r["layernorm"][0], r["convert"][0]) == (2, 2, 1 + shift) for r in runs)
+        times.append([min(r[k][1] for r in runs) for k in ("decode", "layernorm")])
+    decode, layernorm = (b / a for a, b in zip(*times))
+    if joint:
+        assert layernorm > 1.5, times
+    else:
+        assert decode > 1.5, times
+
+
 @pytest.mark.parametrize("d,M,dh,f,B,L", [
     (768, 3, 64, 256, 1, 1),      # one token: the smallest tile, K split over workgroups
     (100, 5, 36, 64, 3, 21),      # K with a part tile, 16-byte rows
