@@ -789,9 +789,16 @@ struct Choice {
     float us;        // estimated; infinite: no shape has workgroups to spare
 };
 
-// The shape with the least estimated time; with next_workgroups, of those that have workgroups to spare.
+// The shape with the least estimated time; with next_workgroups, of those that have workgroups to spare; with next_outliers, of those that
+// add in the order of the shape without: the bits of a call do not depend on where its dictionaries go in.
 Choice choose(const GemmProblem &p, int N)
 {
+    int groups = 0;   // (0: any)
+    if (p.next_outliers > 0) {
+        GemmProblem alone = p;
+        alone.next_outliers = 0;
+        groups = kShapes[choose(alone, N).shape].groups;
+    }
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN);
     const int nkt = (n_split ? p.block_cols : p.n_blocks * p.block_cols) / BK;
     const bool sums = !n_split && leaves_sums(p.T, N, nkt);
@@ -807,9 +814,9 @@ Choice choose(const GemmProblem &p, int N)
         const long tiles = (long)((N + sh.cols - 1) / sh.cols) * ((p.T + sh.rows - 1) / sh.rows);
         const float avg = (float)tiles / kComputeUnits;
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
-        if ((sh.groups > 1 && per_cu > 1) || (c == W64x128 && per_cu > 2)) continue;
+        if ((sh.groups > 1 && per_cu > 1) || (c == W64x128 && per_cu > 2) || (groups && sh.groups != groups)) continue;
         // (an output projection with dictionaries beside it: an entry per thread, workgroups of twelve waves while a unit has one)
-        if (p.kind == GEMM_OUT && p.next_outliers > 0 && (c == W64x128 || sh.cols < 192 || (c == W64x192 && per_cu == 1 && nkt >= 4))) continue;
+        if (p.kind == GEMM_OUT && p.next_outliers > 0 && (c == W64x128 || sh.cols < 192)) continue;
         const float rounds = sh.shared ? std::max(1.f, (avg + per_cu) / 2) : (float)per_cu;
         float us = sh.start_us + rounds * (nkt * (sh.tile_us + sh.full_us * avg / per_cu) + sh.round_us + (p.kind == GEMM_FFN_UP ? sh.gelu_us : 0.f) +
                                            (n_split ? 0.f : sh.resid_us));
@@ -838,7 +845,9 @@ int gemm_wide_sum_planes(const GemmProblem &p)
 {
     if (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP || p.kind == GEMM_QKV_ATTN || p.n_blocks <= 0 || p.T <= 0) return 0;
     if (!leaves_sums(p.T, p.block_rows, p.n_blocks * p.block_cols / BK)) return 0;
-    const Choice ch = choose(p, p.block_rows);
+    GemmProblem alone = p;   // (the same number of planes with dictionaries beside it, in whatever tiles: the same bits)
+    alone.next_outliers = 0;
+    const Choice ch = choose(alone, p.block_rows);
     if (kShapes[ch.shape].groups == 1) return 1;
     for (int s = 4; s >= 2; s >>= 1)
         if (ch.tiles * s <= kComputeUnits / 2 && ch.nkt_total % (2 * s) == 0 && ch.nkt_total / (2 * s) >= 3) return s;
@@ -940,4 +949,16 @@ extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int 
     const sti::Choice ch = sti::choose(p, n_split ? n_blocks * block_rows : block_rows);
     const sti::Shape &sh = sti::kShapes[ch.shape];
     tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large; tile[4] = sti::gemm_wide_sum_planes(p);
+}
+
+// Whether O (or else FFN2) takes the next layer's dictionaries along, of at most `outliers` entries each; likewise for the tests.
+extern "C" int sti_internal_out_carries(int T, int n_shards, int d_model, int ffn_per_shard, int outliers)
+{
+    sti::GemmProblem out = {};
+    out.kind = sti::GEMM_OUT;
+    out.T = T; out.n_blocks = n_shards; out.block_rows = d_model; out.block_cols = 64;
+    sti::GemmProblem down = out;
+    down.kind = sti::GEMM_FFN_DOWN;
+    down.block_cols = ffn_per_shard;
+    return sti::gemm_wide_out_carries(out, down, outliers);
 }

@@ -180,6 +180,18 @@ def test_tiles_of_64_column_strips_are_for_whole_strips(P):
     assert tiles.tile(P, tiles.O, 9000, 2, 2048, 64)[3] and tiles.tile(P, tiles.FFN1, 9000, 16, 256, 128)[3]
 
 
+@pytest.mark.parametrize("d", [192, 256, 384, 512, 768, 896, 1024, 1088, 2048])
+def test_dictionaries_beside_a_projection_leave_its_order_of_sums(P, d):
+    """With a next layer's dictionaries beside them O and FFN2 may take other tiles, but as many groups of waves share K and as many planes
+    of sums are left as without."""
+    import tiles
+    for shards in (1, 2, 3, 6, 8, 10, 12, 16, 24):
+        for kind, cols in ((tiles.O, 64), (tiles.FFN2, 64), (tiles.FFN2, 256), (tiles.FFN2, 512)):
+            for n in range(65, 9300, 61):
+                a, b = ((*tiles.tile(P, kind, n, shards, d, cols, k), tiles.sum_planes(P, kind, n, shards, d, cols, k)) for k in (0, 100))
+                assert a[2] == b[2] and a[4] == b[4], (shards, kind, cols, n, a, b)
+
+
 @pytest.mark.parametrize("d,last", [(768, 1024), (1024, 640), (512, 1344), (384, 2048), (192, 4096), (1088, 640), (2048, 320)])
 def test_sums_stay_in_float32_up_to_64_tiles(P, d, last):
     """O and FFN2 of up to 64 tiles of 64 x 192 and 12 K tiles or more leave float32 sums to LayerNorm, whichever tile they take and

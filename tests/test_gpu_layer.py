@@ -889,6 +889,37 @@ def test_a_layer_rides_where_that_is_faster_than_a_launch_of_its_own(gpu, d, M, 
     assert torch.isfinite(whole.float()).all()
 
 
+@pytest.mark.parametrize("d,M,f,absent,B,L,entries,carrier,tile,planes", [
+    (768, 12, 256, 0, 32, 128, 885, "o", "64x192*/256", 0),
+    (1024, 8, 64, 0, 55, 100, 257, "o", "64x192/516", 0),         # 128 x 256 tiles alone ...
+    (1024, 6, 64, 0, 41, 100, 300, "o", "64x384/195", 0),         # ... and next to 64 x 384
+    (768, 12, 256, 0, 11, 93, 769, "ffn2", "64x64*/192", 1),      # one entry more than three workgroups of 256 threads take
+    (768, 12, 256, 2, 11, 93, 900, "ffn2", "64x64*/192", 1),
+    (768, 12, 256, 6, 34, 100, 100, "ffn2", "64x192*/216", 0),    # O alone with K not shared by groups of waves
+    (192, 12, 256, 0, 3, 100, 200, "ffn2", "32x96*/20", 4),       # K split over workgroups, one in four of which has entries to put in
+    (1088, 17, 256, 0, 2, 65, 400, "ffn2", "32x96*/60", 2),
+])
+def test_outlier_dictionaries_beside_o_or_ffn2(gpu, d, M, f, absent, B, L, entries, carrier, tile, planes):
+    """Which of the two projections takes the next layer's dictionaries along, in which tile and with how many planes of sums: the bits of
+    the per-layer route, where a launch of their own puts them in."""
+    torch, P, D = gpu
+    dims, m = S.Dims(d, M, 64, f, 1e-12), M - absent
+    assert tiles.out_carries(P, dims, B * L, m, entries) == (carrier == "o")
+    assert tiles.layer_tiles(P, dims, B * L, m, entries if carrier == "o" else 0)[carrier] == tile
+    assert tiles.sum_planes(P, tiles.O if carrier == "o" else tiles.FFN2, B * L, m, d, 64 if carrier == "o" else f, entries) == planes
+    plan = np.full((3, M), 4, dtype=np.int8)
+    plan[:, m:] = 0
+    wl = S.small_workload(820 + entries, dims, 3, B, L, plan=plan, io_dtype="f16")
+    wl = _with_outliers(wl, entries, fraction=entries / dims.weights_per_shard)
+    S.make_every_term_matter(wl, 31, amp=2.0)
+    prec = P.STI_PREC_F16_MFMA
+    P.sti_profile_begin()
+    whole = _run_model_route(gpu, wl, P.sti_model_workspace_bytes(dims, 3, B, L, prec))
+    assert P.sti_profile_end()["decode"][0] == 1
+    assert torch.equal(whole, _run_model_route(gpu, wl, P.sti_workspace_bytes(dims, B, L, prec)))
+    assert torch.isfinite(whole.float()).all()
+
+
 def test_layers_that_can_and_cannot_take_the_next_layer_along(gpu, oracle_mod):
     """38 sequences: a full layer has 228 tiles and no compute unit to spare, a layer with 9 or 10 shards
     190 tiles and 64; with an all-absent layer in between.  Layers 0 to 3 are decompressed as a group,

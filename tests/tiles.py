@@ -21,6 +21,11 @@ def sum_planes(P, kind, tokens, shards, block_rows, block_cols, outliers=0):
     return _ask(P, kind, tokens, shards, block_rows, block_cols, outliers)[4]
 
 
+def out_carries(P, dims, tokens, shards, entries):
+    """Whether O, or else FFN2, puts the next layer's dictionaries in."""
+    return bool(P.lib.sti_internal_out_carries(tokens, shards, dims.d_model, dims.ffn_per_shard, entries))
+
+
 def layer_tiles(P, dims, tokens, shards, outliers=0):
     """Per projection "rows x columns", * where K is shared by two groups of waves, L: the kernel with both operands through LDS,
     /: tiles in all, more than 256 of them several to a workgroup of that kernel.  outliers: entries per dictionary beside O."""
