@@ -252,8 +252,8 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = wave_all / NW, wave = wave_all - half * NW;   // K group, column strip
-    const int nkt = KS == 1 ? nkt_all : nkt_all / KS + (half < nkt_all % KS ? 1 : 0);
-    const int kt0 = (int)blockIdx.y * nkt_all + (KS == 1 ? 0 : half * (nkt_all / KS) + min(half, nkt_all % KS));
+    const int nkt = KS == 1 ? nkt_all : (nkt_all + 1 - half) >> 1;
+    const int kt0 = (int)blockIdx.y * nkt_all + (KS == 1 ? 0 : half * ((nkt_all + 1) >> 1));
     const int g = lane >> 5, lr = lane & 31;
     const int n_tiles = (N + BN - 1) / BN;
     const int m_tiles = (hot_T + BM - 1) / BM;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     constexpr bool EARLY = !n_split && !SUMS;
     static_assert(n_split || RA <= 2, "registers for the residual rows through the K loop");
     const _Float16 *R = (const _Float16 *)hot_resid;
-    static_assert(KS <= 2, "two groups, each of which ends half of the tile's pieces");
+    static_assert(KS == 1 || KS == 2, "two groups, each of which ends half of the tile's pieces");
     constexpr int PIECES_OWN = RA * 2 / KS, BIASES = PIECES_OWN < 2 ? 1 : 2;   // pieces of 32 rows x 16 columns per wave
     const int first_piece = KS == 1 ? 0 : half * PIECES_OWN;                    // (piece n: rows 32 (n / 2), columns 16 (n % 2))
     f32x4 bias[2][2];
@@ -388,8 +388,8 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
         if constexpr (EARLY) {
 #pragma unroll
             for (int j = 0; j < PIECES_OWN; ++j) {
-                const int m = min(m0 + (first_piece + j >> 1) * 32 + lr, hot_T - 1);   // (rows past T: row T-1 again, never stored)
-                resv[j] = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * (first_piece + j & 1) + 8 * g);
+                const int m = min(m0 + ((first_piece + j) >> 1) * 32 + lr, hot_T - 1);   // (rows past T: row T-1 again, never stored)
+                resv[j] = *(const u32x4 *)(R + (int64_t)m * hot_ldr + nw + 16 * ((first_piece + j) & 1) + 8 * g);
             }
         }
     };
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
 #ifdef STI_PHASE_STAMPS
             if (kt == 0) STI_STAMP(2);
 #endif
-            if (KS > 1 && more) issue(kt + STAGES - 1, next, bnew);
+            if (KS == 2 && more) issue(kt + STAGES - 1, next, bnew);
             const unsigned char *stage = smem_raw + (half * STAGES + buf) * (STAGE * 2);
             half8 a_cur[RA], a_nxt[RA];
 #pragma unroll
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     if (FETCHES % NW == 0 || wave < FETCHES % NW) k_loop(std::integral_constant<int, FPW>{});
     else k_loop(std::integral_constant<int, FPW - 1>{});
     // (a group with a K tile less than the first one: that one's last barrier)
-    if (KS > 1 && nkt * KS < nkt_all && nkt < (nkt_all + KS - 1) / KS) __builtin_amdgcn_s_barrier();
+    if (KS == 2 && nkt * 2 < nkt_all) __builtin_amdgcn_s_barrier();
     STI_STAMP(3);
 
     // ---- epilogue ----
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // us: 1023 tokens with dictionaries 586, now 575, 1116 tokens 622 / 614, 2048 808 / 801, 4096 1086 / 1079; d_model 1024, 1200 tokens 941 / 931.
     auto end_pieces = [&](auto group) {
         constexpr int G = decltype(group)::value, FIRST = G * PIECES_OWN;
-        if constexpr (KS > 1) {
+        if constexpr (KS == 2) {
             f32x4 *part = (f32x4 *)smem_raw;
             const int th = tid - G * NTH;
 #pragma unroll
@@ -612,18 +612,19 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
     // BN/8 lanes per tile row: every store instruction writes whole rows of the tile
     _Float16 *C = (_Float16 *)p.C;
     constexpr int PIECES_PER_ROW = BN / 8;
-    constexpr int PIECES = BM * PIECES_PER_ROW, PASSES = (PIECES + NT - 1) / NT;
+    constexpr int PASSES = BM * PIECES_PER_ROW / NT;
+    static_assert(PASSES * NT == BM * PIECES_PER_ROW, "whole passes");
     u32x4 piece[PASSES];
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
-        const int pc = min(tid + NT * j, PIECES - 1);
+        const int pc = tid + NT * j;
         piece[j] = *(const u32x4 *)(tile_out + (pc / PIECES_PER_ROW) * LDT + (pc % PIECES_PER_ROW) * 8);
     }
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
         const int pc = tid + NT * j;
         const int m = m0 + pc / PIECES_PER_ROW, n = tile_n * BN + (pc % PIECES_PER_ROW) * 8;
-        if (pc < PIECES && m < hot_T && n < N) *(u32x4 *)(C + (int64_t)m * p.ldc + n) = piece[j];
+        if (m < hot_T && n < N) *(u32x4 *)(C + (int64_t)m * p.ldc + n) = piece[j];
     }
     STI_STAMPS_OUT();
 }
