@@ -1075,6 +1075,25 @@ def test_mfma_large_tiles(gpu, oracle_mod, d, M, f, B, L, n_absent, chosen):
         assert_parity(got[b:b + 1], want, TOL["mfma"], b)
 
 
+@pytest.mark.parametrize("prec,d,M,f,B,L", [
+    ("mfma", 128, 4, 64, 3, 100),        # kernels for many tokens, small tiles
+    ("mfma", 768, 12, 256, 32, 128),     # 128 x 384
+    ("mfma", 128, 32, 512, 20, 207),     # 192 x 256
+    ("mfma", 256, 4, 64, 1, 50),         # for few tokens
+    ("f32", 256, 4, 64, 1, 50),
+    ("f32", 768, 12, 256, 4, 128),       # planes of three bfloat16 values
+])
+@pytest.mark.parametrize("value", [float("-inf"), float("inf"), float("nan")])
+def test_an_argument_of_gelu_that_is_no_number_is_not_lost(gpu, prec, d, M, f, B, L, value):
+    """One neuron's bias is infinite or NaN: no row of the layer is finite (-inf Phi(-inf) is -inf times zero), on any route."""
+    dims = S.Dims(d, M, 64, f, 1e-12)
+    if (d, M) in ((768, 12), (128, 32)) and prec == "mfma":
+        assert tiles.layer_tiles(gpu[1], dims, B * L, M)["ffn1"].startswith("128x384" if d == 768 else "192x256L")
+    wl = S.small_workload(61000 + d, dims, 1, B, L)
+    wl.params[0].b1[f + 5] = value
+    assert not np.isfinite(run_gpu(gpu, wl, prec)).any()
+
+
 @pytest.mark.parametrize("k_tiles", range(1, 10))
 def test_mfma_k_tiles_in_and_out_of_whole_rounds(gpu, oracle_mod, k_tiles):
     """K loops of one to nine K tiles (rounds of three whose loads all exist, then the rest): 64-row tiles with unsplit K (Q/K/V and
