@@ -478,6 +478,25 @@ int spare_decode_workgroups(const sti_dims &d, int B, int Lseq, int m, int m_nex
     return gemm_wide_spare_workgroups(p, grouped);
 }
 
+// float32 layers on the bfloat16 matrix cores: where FFN2 of m shards leaves its planes of sums, in front of the neurons or where FFN1's weights
+// were, whichever takes more
+struct SumsPlace {
+    size_t begin, end;
+};
+SumsPlace split_down_sums(const sti_dims &d, const WorkspaceLayout &wl, int m)
+{
+    const size_t ffn = (size_t)m * d.ffn_per_shard * d.d_model * 6;
+    if (ffn > wl.s_u - wl.s_ctx) return SumsPlace{align_up(wl.w32 + ffn, 256), wl.w32 + 2 * ffn};
+    return SumsPlace{wl.s_ctx, wl.s_u};
+}
+// Whether m_next shards of the layer behind can be decompressed beside the last LayerNorm: their Q, K, V and O go where FFN2 and, behind it, FFN1
+// were, not over sums that LayerNorm reads from there.
+bool clear_of_sums(const sti_dims &d, const WorkspaceLayout &wl, int T, int m_next, size_t sums, int planes)
+{
+    const size_t end = wl.w32 + (size_t)m_next * 4 * d.d_head * d.d_model * 6;
+    return planes == 0 || sums >= end || sums + (size_t)planes * T * d.d_model * 4 <= wl.w32;
+}
+
 sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer_params &prm,
                      const void *in, void *out, sti_dtype out_dtype, int B, int Lseq,
                      sti_precision prec, uint8_t *ws, const WorkspaceLayout &wl, hipStream_t stream,
@@ -702,10 +721,9 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
         STI_TRY(gemm(p, b1));
     }
     memset(&p, 0, sizeof(p));
-    if (split) {   // in front of the neurons, or where FFN1's weights were: whichever takes more
-        const size_t ffn = (size_t)m * (off_2 - off_1) * 6;
-        if (ffn > wl.s_u - wl.s_ctx) f32_sums(align_up(wl.w32 + ffn, 256), wl.w32 + 2 * ffn);
-        else f32_sums(wl.s_ctx, wl.s_u);
+    if (split) {
+        const SumsPlace place = split_down_sums(d, wl, m);
+        f32_sums(place.begin, place.end);
     } else if (f32) f32_sums(wl.qkv, wl.h);
     else pre = (float *)(ws + wl.pre_down);
     p.a_layout = inner;
@@ -715,15 +733,13 @@ sti_status run_layer(const sti_dims &d, const sti_shard *shards, const sti_layer
     if (riding > 0 && !out_carries) carry(p);
     if (no_products) pre_partials = 0;
     else STI_TRY(gemm(p, b2));
-    // the next layer's Q, K, V and O go where FFN2 and, behind it, FFN1 were: not over sums that LayerNorm reads from there
     SplitRide next_weights = {&t32, 0, dh, f, false, ws + wl.w32};
     if (split && planes_out && chain && chain->next) {
         int m_next = 0;
         memset(&t32, 0, sizeof(t32));
         for (int i = 0; i < M; ++i)
             if (chain->next[i].bitwidth != 0) t32.d[m_next++] = make_desc(chain->next[i], i);
-        const uint8_t *begin = ws + wl.w32, *end = begin + (size_t)m_next * off_1 * 6, *sums = (const uint8_t *)pre;
-        if (pre_partials == 0 || sums >= end || sums + (size_t)pre_partials * partial_stride * 4 <= begin) next_weights.n_shards = m_next;
+        if (clear_of_sums(d, wl, T, m_next, (size_t)((const uint8_t *)pre - ws), pre_partials)) next_weights.n_shards = m_next;
     }
     const bool next_rides = next_weights.n_shards > 0;
     STI_TRY(layernorm(out, out_dtype, out_layout, prm.ln2_g, prm.ln2_b, prm.b2, h, inner, split && planes_out ? ws + wl.s_in : nullptr,
@@ -753,6 +769,22 @@ sti_status check_key_lengths(const int32_t *key_lengths)
 }
 
 }  // namespace sti
+
+// Whether a layer of m shards of 64 features per head, in float32 on the bfloat16 matrix cores, has the m_next of the layer behind it decompressed
+// beside its last LayerNorm, for the tests (no device is touched); -1: it does not go that way.
+extern "C" int sti_internal_next_layer_beside_layernorm(int T, int d_model, int n_heads, int ffn_per_shard, int m, int m_next)
+{
+    using namespace sti;
+    const sti_dims d = {d_model, n_heads, 64, ffn_per_shard, 1e-12f};
+    const WorkspaceLayout wl = workspace_layout(d, T, STI_PREC_F32, false);
+    if (!wl.split || m <= 0) return -1;
+    const SumsPlace place = split_down_sums(d, wl, m);
+    const int most = (int)std::min<size_t>(kF32MaxSplits, (place.end - place.begin) / ((size_t)T * d_model * 4));
+    GemmProblem p = {};
+    p.kind = GEMM_FFN_DOWN;
+    p.T = T; p.n_blocks = m; p.block_rows = d_model; p.block_cols = ffn_per_shard;
+    return clear_of_sums(d, wl, T, m_next, most < 1 ? wl.pre_out : place.begin, gemm_split_k_splits(p, most));
+}
 
 using namespace sti;
 

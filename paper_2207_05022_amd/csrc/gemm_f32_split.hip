@@ -279,6 +279,11 @@ hipError_t launch_split_kind(const GemmProblem &p, const void *W, int64_t block_
 
 }  // namespace
 
+int gemm_split_k_splits(const GemmProblem &p, int max_splits)
+{
+    return choose_split(p, p.block_rows, p.n_blocks * p.block_cols / BK, max_splits < 1 ? 1 : max_splits).splits;
+}
+
 hipError_t launch_gemm_split(const GemmProblem &p, const GemmBlocks &blocks, int max_splits, int *splits_used, hipStream_t stream)
 {
     const bool n_split = (p.kind == GEMM_QKV || p.kind == GEMM_FFN_UP);

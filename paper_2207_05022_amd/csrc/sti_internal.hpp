@@ -225,6 +225,7 @@ hipError_t launch_gemm_f32(const GemmProblem &p, const GemmBlocks &blocks, int m
 // The same on the bfloat16 matrix cores (gemm_f32_split.hip): A and the weight blocks are planes of three bfloat16 values per
 // float32, in cells; FFN_UP leaves planes, the others as above.
 hipError_t launch_gemm_split(const GemmProblem &p, const GemmBlocks &blocks, int max_splits, int *splits_used, hipStream_t stream);
+int gemm_split_k_splits(const GemmProblem &p, int max_splits);   // those of O or FFN2
 // rows [T x d] of float32 -> planes; a layer's shards (no outlier dictionaries) -> planes, Q, K, V and O shard by shard, or (ffn) all of
 // FFN2 and then all of FFN1
 hipError_t launch_split_rows(const float *src, void *dst, int T, int d, hipStream_t stream);

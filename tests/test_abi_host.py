@@ -208,6 +208,17 @@ def test_sums_stay_in_float32_up_to_64_tiles(P, d, last):
     assert tiles.sum_planes(P, tiles.QKV, 100, 12, 192, d) == tiles.sum_planes(P, tiles.FFN1, 100, 12, 256, d) == 0
 
 
+@pytest.mark.parametrize("d,M,f,T,m,most", [(768, 12, 256, 1024, 9, 9), (768, 12, 256, 1024, 5, 12), (768, 12, 192, 512, 12, 9), (1024, 16, 128, 512, 16, 8),
+                                            (1024, 16, 256, 303, 14, 14), (320, 32, 64, 1050, 32, 32)])
+def test_next_layer_beside_a_layernorm_up_to_the_sums(P, d, M, f, T, m, most):
+    """FFN2's sums lie behind its own planes, m f d values of six bytes, or elsewhere: up to there the next layer's Q, K, V and O, 4 x 64 d
+    values per shard, are decompressed beside the LayerNorm that reads them."""
+    ask = P.lib.sti_internal_next_layer_beside_layernorm
+    assert most == M or most == m * f // (4 * 64)
+    assert [ask(T, d, M, f, m, n) for n in range(1, M + 1)] == [int(n <= most) for n in range(1, M + 1)]
+    assert ask(T, d, M, f, 0, M) == -1 and ask(20, d, M, f, m, M) == -1
+
+
 @pytest.mark.parametrize("d,M,f,last", [(768, 12, 256, 640), (1024, 16, 256, 512), (512, 8, 128, 1024), (256, 4, 64, 1024),
                                         (1024, 16, 64, 704), (1024, 16, 128, 576), (896, 14, 128, 704), (1024, 8, 256, 704),
                                         (768, 12, 192, 704), (896, 10, 192, 768), (128, 2, 64, 192), (1088, 4, 64, 128)])

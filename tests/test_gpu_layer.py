@@ -284,6 +284,22 @@ def test_f32_weights_decompressed_beside_a_layernorm(gpu, d, M, f, B, L, shift, 
     assert torch.isfinite(y).all() and torch.equal(y, cur)
 
 
+@pytest.mark.parametrize("d,M,f,B,L,present,beside", [
+    (768, 12, 256, 8, 128, (12, 12, 6, 12), (1, 1, 1)),
+    (768, 12, 256, 8, 128, (9, 10, 10, 9), (0, 1, 1)),     # FFN2's sums lie behind its weights: a shard more goes over them
+    (768, 12, 192, 4, 128, (12, 12, 8, 9), (0, 1, 0)),
+    (1024, 16, 128, 4, 128, (16, 16, 16), (0, 0)),
+    (1024, 16, 256, 3, 101, (16, 14, 15, 16), (1, 0, 0)),
+    (1088, 17, 256, 3, 101, (16, 17, 17), (0, 1)),         # a decompression of its own behind the LayerNorm
+    (512, 4, 256, 20, 100, (4, 4), (1,)),                  # room for four descriptors
+])
+def test_f32_weights_not_over_sums_that_layernorm_reads(gpu, d, M, f, B, L, present, beside):
+    """Which layers have the next one's Q, K, V and O decompressed beside their last LayerNorm: those where FFN2's sums are not in the way."""
+    ask = gpu[1].lib.sti_internal_next_layer_beside_layernorm
+    assert tuple(ask(B * L, d, M, f, a, b) for a, b in zip(present, present[1:])) == beside
+    test_f32_weights_decompressed_beside_a_layernorm(gpu, d, M, f, B, L, 0, present)
+
+
 @pytest.mark.parametrize("d,shift,joint", [(1024, 0, True), (1088, 0, False), (1024, 1, False)])
 def test_float32_decompressions_are_timed_with_layernorm_or_by_themselves(gpu, d, shift, joint):
     """48 shards of 64 and of 256 neurons: as much of Q, K, V and O to decompress, four times as much of FFN1 and FFN2, half as much and
