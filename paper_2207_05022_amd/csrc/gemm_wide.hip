@@ -635,9 +635,11 @@ hipError_t launch_variant(const GemmProblem &p, const GemmBlocks &blocks, int N,
 template <int KIND, int RA, int NW, int KS>
 hipError_t launch_shape(const GemmProblem &p, const GemmBlocks &blocks, int N, hipStream_t stream)
 {
-    constexpr bool n_split = (KIND == GEMM_QKV || KIND == GEMM_FFN_UP || KIND == GEMM_QKV_ATTN);
-    if constexpr (!n_split) {
-        if (p.k_splits > 0) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
+    // (tiles of choose() for sums: 32 x 96, 64 x 64 and, O with dictionaries beside it, 64 x 192)
+    constexpr bool sums = KS == 2 && (RA == 1 || NW == 2 || (NW == 6 && KIND == GEMM_OUT));
+    if (p.k_splits > 0) {
+        if constexpr (sums) return launch_variant<KIND, RA, NW, KS, true>(p, blocks, N, stream);
+        return hipErrorInvalidValue;
     }
     return launch_variant<KIND, RA, NW, KS, false>(p, blocks, N, stream);
 }
@@ -817,6 +819,8 @@ Choice choose(const GemmProblem &p, int N)
         const long per_cu = (tiles + kComputeUnits - 1) / kComputeUnits;   // workgroups on the busiest unit
         // (64 x 128 tiles, three and more to a unit: twelve shapes of 1300 to 6500 tokens 1 % faster to 6 % slower than the next larger shape)
         if ((sh.groups > 1 && per_cu > 1) || (c == W64x128 && per_cu > 2) || (groups && sh.groups != groups)) continue;
+        // (sums, 12 K tiles and more on at most 192 units in tiles of 64 x 64: one group of waves, or 64 x 96 tiles, are slower by this table)
+        if (sums && (sh.groups == 1 || c == G64x96)) continue;
         // (an output projection with dictionaries beside it: tiles with units to spare, or FFN2 takes them, see gemm_wide_out_carries)
         if (p.kind == GEMM_OUT && p.next_outliers > 0 && (c == W64x128 || sh.cols < 192)) continue;
         const float rounds = sh.shared ? std::max(1.f, (avg + per_cu) / 2) : (float)per_cu;

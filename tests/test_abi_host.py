@@ -208,6 +208,22 @@ def test_sums_stay_in_float32_up_to_64_tiles(P, d, last):
     assert tiles.sum_planes(P, tiles.QKV, 100, 12, 192, d) == tiles.sum_planes(P, tiles.FFN1, 100, 12, 256, d) == 0
 
 
+@pytest.mark.parametrize("d", [64, 192, 448, 768, 1024, 1088, 2048, 4096])
+def test_tiles_that_leave_sums(P, d):
+    """Float32 sums come from the tiles that are compiled for them, and up to 64 tiles of 64 x 192 each is on a unit of its own."""
+    import tiles
+    found = set()
+    for shards in (1, 3, 6, 10, 12, 13, 16, 24, 48):
+        for kind, cols in ((tiles.O, 64), (tiles.FFN2, 64), (tiles.FFN2, 192), (tiles.FFN2, 512)):
+            for n in (1, 31, 64, 97, 130, 300, 640, 641, 1000, 1344, 2048, 4096, 12000):
+                for entries in (0, 200):
+                    if tiles.sum_planes(P, kind, n, shards, d, cols, entries):
+                        rows, columns, groups, large = tiles.tile(P, kind, n, shards, d, cols, entries)
+                        assert groups == 2 and not large and -(-n // rows) * -(-d // columns) <= 256
+                        found.add((rows, columns, kind == tiles.O and entries > 0))
+    assert found and found <= {(32, 96, False), (64, 64, False), (64, 192, True)}
+
+
 @pytest.mark.parametrize("d,M,f,T,m,most", [(768, 12, 256, 1024, 9, 9), (768, 12, 256, 1024, 5, 12), (768, 12, 192, 512, 12, 9), (1024, 16, 128, 512, 16, 8),
                                             (1024, 16, 256, 303, 14, 14), (320, 32, 64, 1050, 32, 32)])
 def test_next_layer_beside_a_layernorm_up_to_the_sums(P, d, M, f, T, m, most):
