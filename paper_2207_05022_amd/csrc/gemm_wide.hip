@@ -779,11 +779,11 @@ bool gemm_wide_supported(const GemmProblem &p, const GemmBlocks &blocks)
 
 namespace {
 
-// Whether O and FFN2 leave their sums in float32, with bias and residual added by LayerNorm, instead of rows in binary16: few tokens and K of
-// 12 tiles or more, with which K can be split over workgroups (gemm_wide_sum_planes), and then whether it is or not.  What a call of
+// Whether O and FFN2 leave their sums in float32, with bias and residual added by LayerNorm, instead of rows in binary16: few tokens and
+// K tiles in fours, from 12 on, with which K can be split over workgroups (gemm_wide_sum_planes), and then whether it is or not.  What a call of
 // so many tokens keeps by it: 12 layers of BERT-base, error against float64 with these rows in binary16 and with sums, 2-norm, 707 tokens 6.9e-4 /
 // 5.5e-4, 1024 tokens 6.6e-4 / 5.2e-4; what it costs: 557 / 567, 605 / 612 us.
-inline bool leaves_sums(int64_t T, int N, int k_tiles) { return T <= gemm_wide_most_tokens(2, N) && k_tiles >= 12; }
+inline bool leaves_sums(int64_t T, int N, int k_tiles) { return T <= gemm_wide_most_tokens(2, N) && k_tiles >= 12 && k_tiles % 4 == 0; }
 
 struct Choice {
     int shape;       // index into kShapes
