@@ -305,11 +305,16 @@ __global__ __launch_bounds__(kWaves * 64, 2) void gemm_large_kernel(
                 half8 o, res;
                 if constexpr (!n_split) res = *slot;
 #pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] += bias[r][q][e >> 2][e & 3];
+                if constexpr (KIND == GEMM_FFN_UP) {
+                    const float none = zero_of(x);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = gelu_wide(x[e], none);
+                }
+#pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    float y = x[e] + bias[r][q][e >> 2][e & 3];
-                    if constexpr (KIND == GEMM_FFN_UP) y = gelu_wide(y);
-                    if constexpr (!n_split) y += (float)res[e];
-                    o[e] = (_Float16)y;
+                    if constexpr (!n_split) x[e] += (float)res[e];
+                    o[e] = (_Float16)x[e];
                 }
                 *slot = o;
             }

@@ -7,11 +7,12 @@ namespace sti {
 // GELU with the Gaussian CDF (the erf form, not the tanh form):  z Phi(z) = max(z, 0) - a Phi(-a),  a = |z|.
 // log2 Phi(-a) is close to a parabola: a polynomial of degree 4, the minimax fit of a 2^p(a) to a Phi(-a) (linear program in float64) with
 // p(0) = -1.  |error| < 9e-6, relative below 1e-4 for z > -1 and 2e-3 for z > -3; beyond a = 5.5 (a Phi(-a) = 1e-7) the clamped argument.
-// -0 z is a zero that is none where z is infinite or NaN: max(z, -0 z) is max(z, 0), but -inf gives -inf, as in the polynomial of degree 8
-// before it, and NaN gives NaN.  Nine instructions, one of them transcendental: the epilogue of FFN1 is bound by exactly these.  That
-// polynomial in z^2 took 13 (errors 4.1e-5, 2.5e-4, 5e-3): 11440 -> 10690 clocks for 128 x 384 outputs with
-// max(z, 0), which loses -inf: 24 x 384 tokens of d_model 1024, 24 layers 7000 us so, 7030 with the product.
-__device__ inline float gelu_wide(float z)
+// none (zero_of) is 0, or NaN where z or another of eight values of the same token is infinite or NaN.  max(z, none) is max(z, 0) or z, so that -inf
+// and NaN come out as such, as in the polynomial of degree 8 before it; what the others of the eight come out as then does not matter, since FFN2
+// adds all neurons of a token up.  Eight instructions, one of them transcendental, and five for eight values' `none`: the epilogue of FFN1 is bound by
+// exactly these.  That polynomial in z^2 took 13 (errors 4.1e-5, 2.5e-4, 5e-3).  Clocks for 128 x 384 outputs: 11440 so, 10960 now, 10690 with
+// max(z, 0), which makes -inf a 0, 11400 with a product -0 z for each value.
+__device__ inline float gelu_wide(float z, float none)
 {
     const float a = __builtin_fminf(__builtin_fabsf(z), 5.5f);
     float p = 4.161671270e-03f;
@@ -19,7 +20,14 @@ __device__ inline float gelu_wide(float z)
     p = fmaf(p, a, -4.649304450e-01f);
     p = fmaf(p, a, -1.149567008f);
     p = fmaf(p, a, -1.0f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(z, z * -0.f));
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(z, none));
+}
+__device__ inline float zero_of(const float (&z)[8])
+{
+    float most = __builtin_fabsf(z[0]);
+#pragma unroll
+    for (int e = 1; e < 8; ++e) most = __builtin_elementwise_maximum(most, __builtin_fabsf(z[e]));
+    return most * 0.f;
 }
 
 struct ShardIds {   // original shard id of every weight block (selects the bias slice), four to a scalar-loadable dword

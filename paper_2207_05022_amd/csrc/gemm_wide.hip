@@ -591,11 +591,16 @@ __global__ __launch_bounds__(NW * KS * 64, 3) void gemm_wide_kernel(
             half8 res = {}, o;
             if constexpr (EARLY) res = __builtin_bit_cast(half8, resv[j]);
 #pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] += bias[BIASES == 1 ? 0 : q][e >> 2][e & 3];
+            if constexpr (KIND == GEMM_FFN_UP) {
+                const float none = zero_of(x);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = gelu_wide(x[e], none);
+            }
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float y = x[e] + bias[BIASES == 1 ? 0 : q][e >> 2][e & 3];
-                if constexpr (KIND == GEMM_FFN_UP) y = gelu_wide(y);
-                if constexpr (!n_split) y += (float)res[e];
-                o[e] = (_Float16)y;
+                if constexpr (!n_split) x[e] += (float)res[e];
+                o[e] = (_Float16)x[e];
             }
             *(half8 *)(tile_out + row * LDT + wave * 32 + 16 * q + 8 * g) = o;
         }

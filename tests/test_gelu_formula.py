@@ -29,12 +29,14 @@ def test_error_of_the_many_token_gelu():
 
 
 def test_many_token_gelu_far_out_and_where_there_is_no_number():
-    """max(z, -0 z) - a 2^p(a): the bits of max(z, 0) - a 2^p(a) wherever z is a number, far beyond the range of the fit, too; infinities and NaN
-    come out as z Phi(z) has them, but for -inf, whose sign stays."""
-    text = open(SOURCE).read().split("inline float gelu_wide", 1)[1].split("}", 1)[0]
+    """max(z, none) - a 2^p(a) with none = 0 max|z| over eight values: the bits of max(z, 0) - a 2^p(a) where all of them are numbers, far beyond the
+    range of the fit, too; infinities and NaN come out as themselves."""
+    source = open(SOURCE).read()
+    text = source.split("inline float gelu_wide", 1)[1].split("}", 1)[0]
     c = [np.float32(v) for v in re.findall(r"(?:p = |p, a, )(-?[0-9.e+-]+)f", text)]
     assert "fminf(__builtin_fabsf(z), 5.5f)" in text
-    assert "return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(z, z * -0.f));" in text
+    assert "return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(z, none));" in text
+    assert "most = __builtin_elementwise_maximum(most, __builtin_fabsf(z[e]))" in source and "return most * 0.f;" in source
 
     def gelu(z, positive):
         a = np.fmin(np.abs(z), np.float32(5.5)).astype(np.float64)
@@ -45,11 +47,14 @@ def test_many_token_gelu_far_out_and_where_there_is_no_number():
 
     def part(z):
         with np.errstate(invalid="ignore"):
-            return np.fmax(z, z * np.float32(-0.0))
+            return np.fmax(z, np.maximum.reduce(np.abs(z).reshape(-1, 8), axis=1).repeat(8) * np.float32(0.0))     # (np.maximum: NaN stays)
 
-    z = np.concatenate([np.linspace(-200, 200, 400001), np.logspace(-44, 38, 4000), -np.logspace(-44, 38, 4000)]).astype(np.float32)
+    z = np.concatenate([np.linspace(-200, 200, 400000), np.logspace(-44, 38, 4000), -np.logspace(-44, 38, 4000)]).astype(np.float32)
     np.testing.assert_array_equal(gelu(z, part(z)), gelu(z, np.maximum(z, 0)))
-    far = z[np.abs(z) > 5.5]
-    np.testing.assert_allclose(gelu(far, part(far)), np.maximum(far, 0), atol=1.5e-7, rtol=6e-8)
-    odd = np.array([-np.inf, np.inf, np.nan], np.float32)
-    np.testing.assert_array_equal(gelu(odd, part(odd)), odd)
+    far = np.abs(z) > 5.5
+    np.testing.assert_allclose(gelu(z, part(z))[far], np.maximum(z, 0)[far], atol=1.5e-7, rtol=6e-8)
+    for odd in (-np.inf, np.inf, np.nan):
+        for at in range(8):
+            eight = np.linspace(-7, 7, 8, dtype=np.float32)
+            eight[at] = odd
+            np.testing.assert_array_equal(gelu(eight, part(eight))[at], np.float32(odd))
