@@ -206,14 +206,17 @@ sti_status check_decode_shard(const sti_shard &s)
 
 // Which GEMM family a matrix-core layer takes.  The few-token kernels decode every weight once per
 // 64-row block and take partial sums through LayerNorm; from some row blocks on it is cheaper to
-// decompress the layer once into the working buffer and run the wide-tile kernels.  Measured per layer (us,
-// few-token against working buffer, 6-bit mix, full shard set): BERT-base 640 tokens 48 / 57, 768 56 / 58, 896 62 / 59; d_model
-// 1024 x 16 shards 512 60 / 70, 640 68 / 71; 1024 x 16 of 64 neurons 768 54 / 58, 1024 59 / 59; 1024 x 8 of 256 896 59 / 60;
-// 640 x 9 of 192 1024 51 / 54; 512 x 8 of 128 1024 38 / 45.  What a row block costs grows with the columns of Q/K/V and FFN1, what
-// the other route costs with d_model: the line is 1 / tokens = a columns + b, a tenth below where the two meet, which is where they
-// meet for layers with outlier dictionaries (they take the working buffer on either route, here in launches of their own:
-// BERT-base 640 tokens 53 / 56, 768 58 / 56).  26 random shapes (d_model 256 .. 1024, 2 to 16 shards of 64 to 256 neurons, up to
-// half of them absent, a third with dictionaries) half a row block below the line: 0.5 % slower at most, 9 % faster on average.
+// decompress the layer once into the working buffer and run the wide-tile kernels.  What a row block costs grows with the columns of
+// Q/K/V and FFN1, what the other route costs with d_model: the line is 1 / tokens = a columns + b, drawn a tenth below where the two met for
+// the many-token kernels of before the small tiles (gemm_wide.hip): BERT-base 896 tokens 62 / 59 us per layer, few-token against working
+// buffer, 6-bit mix, full shard set.  With today's they meet a row block or two lower where all shards are present: BERT-base 512 tokens
+// 43 / 46, 640 47 / 47, 704 52 / 48, 768 53 / 48; d_model 1024 x 16 shards 384 49 / 57, 512 58 / 58, 640 64 / 57; 1024 x 16 of 64 neurons
+// 640 48 / 43, 768 51 / 47; 1024 x 8 of 256 640 45 / 46, 704 48 / 45; 640 x 9 of 192 768 41 / 40, 1024 47 / 40; 512 x 8 of 128 768
+// 36 / 36, 1024 37 / 36; BERT-base with outlier dictionaries (the working buffer on either route, here in launches of their own) 512 50 / 49,
+// 640 54 / 51.  26 random shapes half a row block below the line (d_model 256 .. 1024, 2 to 16 shards of 64 to 256 neurons, some absent, a
+// third with dictionaries): the few-token kernels 13 % faster to 22 % slower, 8 % slower on average.  The line stays all the same: a call's
+// route, and with it its bits and its workspace, depends on dimensions and tokens alone, and where shards are absent the few-token kernels
+// still win there (960 x 12 shards, 6 absent, 864 tokens 37 / 39; 384 x 2, one absent, 992 tokens 26 / 30).
 inline int64_t few_token_limit(const sti_dims &d);
 inline bool few_token_path(const sti_dims &d, int64_t T)
 {
@@ -1192,8 +1195,8 @@ sti_status model_forward(const sti_dims *dims, int n_layers, const sti_shard *st
                                                 dims->ffn_per_shard, w16_of(l), stream));
         return STI_OK;
     };
-    // ... or, for a layer decompressed beside its predecessor's Q/K/V projection, beside the predecessor's output
-    // projection: the most entries a shard has, 0 if there are none or too many.  (kRidingEntries: no more than
+    // ... or, for a layer decompressed beside its predecessor's Q/K/V projection, beside the predecessor's O or FFN2
+    // projection (gemm_wide_out_carries): the most entries a shard has, 0 if there are none or too many.  (kRidingEntries: no more than
     // 256 workgroups of 256 threads and one more per shard; larger dictionaries spread over the chip by themselves.)
     auto riding_outliers = [&](size_t a, size_t b) -> int {
         uint32_t max_outliers = 0;

@@ -5,10 +5,10 @@
 // in tiles of 64 RA rows x 256 columns (RA = 2, 3 or 4), one workgroup of eight waves per compute unit that goes from tile to tile.
 //
 // What bounds it: the matrix cores at the rate that the chip's power leaves them, and the epilogue, beside which they are idle.  9216 tokens,
-// 12 shards of d_model 1024, clocks of wave 0 (libsti_phases.so): FFN1, 256 x 256 tiles, 2350 per K tile of 64, 2048 of them products, at
-// 1.6 GHz; Q/K/V, 192 x 256, 1840 and 1536; O and FFN2 on 192 of the 256 units 2180 and 1900 and 1536, at 1.7 GHz (with a branch around every
+// 12 shards of d_model 1024, clocks of wave 0 (libsti_phases.so): FFN1, 256 x 256 tiles, 2370 per K tile of 64, 2048 of them products, at
+// 1.66 GHz; Q/K/V, 192 x 256, 1850 and 1536; O and FFN2 on 192 of the 256 units 2220 and 1930 and 1536, at 1.8 GHz (with a branch around every
 // request 2530, 2030, 2450 and 2160, at 1.8 and 2.0: the denser the products the lower the clock).  An epilogue takes
-// 9600 with GELU, 3600 for Q/K/V, 5100 to 5200 with residual rows.  160-row tiles, which put O and FFN2 on 232 units, gave 0 to 0.6 %.  What costs power or leaves the matrix cores idle:
+// 9830 with GELU, 3600 for Q/K/V, 5000 to 5200 with residual rows.  160-row tiles, which put O and FFN2 on 232 units, gave 0 to 0.6 %.  What costs power or leaves the matrix cores idle:
 //   - bytes: both operands go through LDS (an A row is read by four waves, a weight by two), so that a unit asks for 64 KiB per K tile
 //     and 256 x 256 outputs - the kernel with weights straight into registers (gemm_wide.hip) asks for 96;
 //   - requests in a burst: 64 KiB keep the unit's address path busy for 1024 clocks, and a wave whose request has to wait does not issue
@@ -17,7 +17,9 @@
 //     of a step's reads in front of them a fifth more);
 //   - start and end of a tile: a workgroup asks for the next tile's first two stages during the last two K tiles of this one.  The
 //     epilogue is each wave's own (4 KiB of LDS, no barrier), the residual rows asked for in front of the last K tile.
-// Launches, us, this kernel against gemm_wide.hip before it (which held 128 x 256 tiles of four waves): see the table of shapes there.
+// Launches, us, this kernel with those branches against gemm_wide.hip before it, which held 128 x 256 tiles of four waves: 9216 tokens, d_model
+// 1024, 12 shards Q/K/V 192 x 256 47 / 52, FFN1 256 x 256 66 / 69, O 192 x 256 21.6 / 23.5, FFN2 192 x 256 59 / 66; 5000 tokens, d_model 768
+// Q/K/V 22.5 / 27.2; 3000 tokens, 10 shards Q/K/V 128 x 256 14.5 / 17.3.
 #include <algorithm>
 #include <type_traits>
 #include "sti_internal.hpp"

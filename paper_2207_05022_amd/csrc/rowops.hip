@@ -94,6 +94,9 @@ __device__ inline float row_quotient(float sum, double inv_d) { return (float)((
 // Few rows: bound by latency (the launch, one round trip, two sums over the row).  The leading 14 dwords of the arguments arrive preloaded
 // in scalar registers: everything the requests of a row depend on, but for the distance of the second and later planes of partial sums.
 // shape: n_partials | resid_layout << 8 | y_layout << 16.
+// (A function that the kernels inline, not a kernel's own body: that was compiled with a wait for everything behind each of a tiled row's first
+// three bias requests, three round trips ahead of the sums'.  256 tokens of d_model 1024, us per launch: one plane 4.3, now 3.3, several planes
+// 4.7 / 4.0; 24 layers 988 / 948.)
 template <int DT, typename RT, bool TILED, int LPR, int MAXC, int PLANES, int ROWS>
 __device__ __forceinline__ void layernorm_rows(const float *pre, const float *bias, const RT *resid, const float *g,
                                                             const float *b, int T, int d, int shape, float eps, int64_t partial_stride,
