@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 # only while the kernel sources still hash to the value recorded with the counters.
 TRAFFIC = {
     "gemm": {"files": ("gemm_wide.hip", "gemm_tile.hpp", "attention_core.hpp", "lane_ops.hpp", "weight_loader.hpp", "sti_internal.hpp"),
-             "sha256": "507906f1d0faaec869dc38f9d6901dee28a26623df9cbe9df8904491900ba54b",
+             "sha256": "118049aa9c52b5b4463e3262319e34f70899246134395727b7d5696b200a19a7",
              "bytes_per_launch": 58943386},
     "decode": {"files": ("decode.hip", "weight_loader.hpp", "sti_internal.hpp"),
                "sha256": "1bc53fb769da749de9d0f25ee748d0303a7b85e41e3db5e072f1e735e717e7fe",

@@ -953,8 +953,7 @@ hipError_t launch_gemm_wide(const GemmProblem &p, const GemmBlocks &blocks, hipS
 }  // namespace sti
 
 // The tile that a projection takes in a launch of its own, for the tests of its kernels (no device is touched): rows, columns, groups of
-// waves that share K, whether it is one of gemm_large.hip, and planes of float32 sums (gemm_wide_sum_planes).  outliers: entries per dictionary
-// of a next layer put in beside it.
+// waves that share K, and whether it is one of gemm_large.hip.  outliers: entries per dictionary of a next layer put in beside it.
 extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int block_rows, int block_cols, int outliers, int *tile)
 {
     sti::GemmProblem p = {};
@@ -963,7 +962,16 @@ extern "C" void sti_internal_projection_tile(int kind, int T, int n_blocks, int 
     const bool n_split = kind == sti::GEMM_QKV || kind == sti::GEMM_FFN_UP;
     const sti::Choice ch = sti::choose(p, n_split ? n_blocks * block_rows : block_rows);
     const sti::Shape &sh = sti::kShapes[ch.shape];
-    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large; tile[4] = sti::gemm_wide_sum_planes(p);
+    tile[0] = sh.rows; tile[1] = sh.cols; tile[2] = sh.groups; tile[3] = sh.large;
+}
+
+// The planes of float32 sums that it leaves (gemm_wide_sum_planes); likewise.
+extern "C" int sti_internal_sum_planes(int kind, int T, int n_blocks, int block_rows, int block_cols, int outliers)
+{
+    sti::GemmProblem p = {};
+    p.kind = (sti::GemmKind)kind;
+    p.T = T; p.n_blocks = n_blocks; p.block_rows = block_rows; p.block_cols = block_cols; p.next_outliers = outliers;
+    return sti::gemm_wide_sum_planes(p);
 }
 
 // Whether O (or else FFN2) takes the next layer's dictionaries along, of at most `outliers` entries each; likewise for the tests.

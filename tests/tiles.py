@@ -4,21 +4,16 @@ import ctypes as C
 QKV, FFN1, O, FFN2 = range(4)
 
 
-def _ask(P, kind, tokens, shards, block_rows, block_cols, outliers):
-    out = (C.c_int * 5)()
-    P.lib.sti_internal_projection_tile(kind, tokens, shards, block_rows, block_cols, outliers, out)
-    return out
-
-
 def tile(P, kind, tokens, shards, block_rows, block_cols, outliers=0):
     """(rows, columns, groups of waves that share K, kernel with both operands through LDS)"""
-    out = _ask(P, kind, tokens, shards, block_rows, block_cols, outliers)
+    out = (C.c_int * 4)()
+    P.lib.sti_internal_projection_tile(kind, tokens, shards, block_rows, block_cols, outliers, out)
     return out[0], out[1], out[2], bool(out[3])
 
 
 def sum_planes(P, kind, tokens, shards, block_rows, block_cols, outliers=0):
     """Planes of float32 sums that O or FFN2 leaves, 0: finished rows in binary16"""
-    return _ask(P, kind, tokens, shards, block_rows, block_cols, outliers)[4]
+    return P.lib.sti_internal_sum_planes(kind, tokens, shards, block_rows, block_cols, outliers)
 
 
 def out_carries(P, dims, tokens, shards, entries):
